@@ -437,18 +437,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // SPLIT: one workgroup per query head of the group instead of one per K/V head (4x the workgroups and a 4x
 // shorter longest one under grouped-query attention); partial dK/dV are then summed with fp32 atomics
 // into dkv_acc [n][2][nkv * HD], which attn_dkv_store_kernel rounds into dqkv afterwards.
-template <int N> __device__ __forceinline__ void wait_vmcnt_lgkm0() {
-    // gfx9 encoding: vmcnt = bits 3:0 and 15:14, expcnt = bits 6:4 (7: no wait), lgkmcnt = bits 11:8 (0)
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
-// barrier between waves that exchange data through LDS, without the full memory fence of __syncthreads (which would
-// wait for every outstanding load): the wavefront-scope fences only keep the compiler from moving LDS accesses across
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int HD, bool CAUSAL, bool SPLIT, int NW, int NST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_mfma_kernel(
     const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o, const float2 *__restrict__ ld2,

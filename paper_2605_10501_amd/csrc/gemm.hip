@@ -2,9 +2,11 @@
 //
 // bf16: C = alpha * A(m,k) B(n,k) on the CDNA4 matrix cores, all four operand layouts.
 //   * gemm_bf16_fast_kernel: workgroup tile 256 x 256 x 64 (8 waves, wave tile 128 x 64, one workgroup per CU) or
-//     128 x 128 x 64 (4 waves, two per CU); v_mfma_f32_16x16x32_bf16 by default (v_mfma_f32_32x32x16_bf16 selectable);
-//   * every operand tile goes global -> LDS directly (buffer_load ... lds), two LDS buffers per operand, one barrier
-//     per K tile; a K-contiguous operand lands as [rows][64] with the 16-byte chunk index XOR-swizzled (applied on the
+//     128 x 128 x 64 (4 waves, two per CU) for grids that fill the chip, and 128 x 256, 128 x 128, 64 x 128 and 64 x 64
+//     tiles with a ring of three or four LDS stages for grids that do not (kTiles, choose_tile);
+//     v_mfma_f32_16x16x32_bf16 by default (v_mfma_f32_32x32x16_bf16 selectable for the first two);
+//   * every operand tile goes global -> LDS directly (buffer_load ... lds), two (or more) LDS buffers per operand, one
+//     barrier per K tile; a K-contiguous operand lands as [rows][64] with the 16-byte chunk index XOR-swizzled (applied on the
 //     global side of the load; the swizzle makes every fragment read pattern free of LDS bank conflicts), a K-major operand (weight gradients, input gradients) lands as a row tile and is read
 //     through the transposing LDS load (ds_read_b64_tr_b16), so no layout needs a transposed copy;
 //   * fragments are double-buffered in registers, LDS reads of the next k-step interleaved with the MFMAs;
@@ -300,12 +302,14 @@ __device__ __forceinline__ void sched_pairs(std::integer_sequence<int, I...>) {
     (sched_reads_then_mfma<((I + 1) * PER <= R ? PER : R - I * PER)>(), ...);
 }
 // Scheduling pattern of one k-step with 16-row fragments: per row block, its NB MFMAs and then the reads that
-// refill its A fragment (RA reads) and, behind the first NB row blocks, one B fragment (RB reads).
+// refill its A fragment (RA reads) and the next BPB of the NB B fragments (RB reads each).
 // VM = number of direct-to-LDS loads issued in this k-step (0, or one tile's worth): spread evenly over the row blocks.
 template <int NB, int RA, int RB, int VM, int... I>
 __device__ __forceinline__ void sched_mfma_then_reads(std::integer_sequence<int, I...>) {
     constexpr int MB = sizeof...(I), PB = (VM + MB - 1) / MB;      // loads per row block
-    ((__builtin_amdgcn_sched_group_barrier(0x008, NB, 0), __builtin_amdgcn_sched_group_barrier(0x100, RA + (I < NB ? RB : 0), 0),
+    constexpr int BPB = (NB + MB - 1) / MB;                        // B fragments per row block
+    ((__builtin_amdgcn_sched_group_barrier(0x008, NB, 0),
+      __builtin_amdgcn_sched_group_barrier(0x100, RA + RB * (I * BPB >= NB ? 0 : (NB - I * BPB < BPB ? NB - I * BPB : BPB)), 0),
       (I * PB < VM ? __builtin_amdgcn_sched_group_barrier(0x020, (VM - I * PB < PB ? VM - I * PB : PB), 0) : (void)0)), ...);
 }
 template <int R, int M>
@@ -363,7 +367,10 @@ struct KFragAddr16 {
 // M16 selects v_mfma_f32_16x16x32_bf16 (16-row fragments, two k-steps of 32 per K tile) instead of
 // v_mfma_f32_32x32x16_bf16 (32-row fragments, four k-steps of 16): the same LDS traffic and the same number of
 // accumulator registers, but on operands with realistic bit activity the chip sustains a higher clock on it.
-template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI = EPI_NONE, bool M16 = false>
+// NST = LDS stages: two (a K tile is requested one tile time before its first use, which is what the big tile's LDS
+// allows) or a deeper ring for grids that leave CUs with one workgroup, where a tile time is shorter than the latency
+// of a load (see kTiles).
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI = EPI_NONE, bool M16 = false, int NST = 2>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams p) {
     constexpr int NT = 64 * WM * WN;
     constexpr int FR = M16 ? 16 : 32;                         // rows of an MFMA fragment / accumulator block
@@ -375,7 +382,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
     // four separate LDS objects (not one carved array): the compiler orders LDS reads against
     // in-flight direct-to-LDS loads by alias analysis, and can only tell the buffer being filled
     // from the buffer being read when they are distinct objects
-    __shared__ __align__(16) bf16_t As0[BM * BK], As1[BM * BK], Bs0[BN * BK], Bs1[BN * BK];
+    static_assert(NST >= 2 && NST <= 4, "ring of 2..4 stages");
+    constexpr int A2 = NST > 2 ? BM * BK : 8, B2 = NST > 2 ? BN * BK : 8, A3 = NST > 3 ? BM * BK : 8, B3 = NST > 3 ? BN * BK : 8;
+    __shared__ __align__(16) bf16_t As0[BM * BK], As1[BM * BK], As2[A2], As3[A3], Bs0[BN * BK], Bs1[BN * BK], Bs2[B2], Bs3[B3];
+    bf16_t *const Ast[4] = {As0, As1, As2, As3}, *const Bst[4] = {Bs0, Bs1, Bs2, Bs3};
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it in a scalar register
@@ -445,9 +455,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
     // Operand fragments are double-buffered in registers: the LDS reads of k-step kk+1 are issued between
     // the MFMAs of k-step kk.
     bf16x8 af[2][MI], bfr[2][NI];
-    std::conditional_t<M16, TrFragAddr16, TrFragAddr> tra, trb;
+    std::conditional_t<M16, TrFragAddr16, TrFragAddr> tra, trb, trb1;
+    static_assert((WM == 2 || (WM == 4 && BM == 128 && M16)) && (WN >= 2 || M16), "K-major blocks are spread over sub-tile pairs");
     if constexpr (TA) tra.init(wm, lane);     // block i of the wave: columns i * 32 * WM + wm * 32 of the row tile
     if constexpr (TB) trb.init(wn, lane);
+    if constexpr (TB && WN == 1) trb1.init(1, lane);   // one wave column: its two 32-column blocks are the halves of a sub-tile
     KFragAddr16 ka, kb;
     if constexpr (M16 && !TA) ka.init(wm * WTM, lane);
     if constexpr (M16 && !TB) kb.init(wn * WTN, lane);
@@ -458,7 +470,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
         else af[slot][i] = *(const bf16x8 *)(as + lds_off(frow_base(i) + frow, kk * (KSTEP / 8) + fhalf));
     };
     auto load_b = [&](const bf16_t *bs, int kk, int slot, int j) {
-        if constexpr (TB && M16) bfr[slot][j] = trb.frag(bs, kk, j, (j >> 1) * (32 * WN / 64) * 4096);
+        if constexpr (TB && WN == 1) bfr[slot][j] = (j >> 1 ? trb1 : trb).frag(bs, kk, j, 0);
+        else if constexpr (TB && M16) bfr[slot][j] = trb.frag(bs, kk, j, (j >> 1) * (32 * WN / 64) * 4096);
         else if constexpr (TB) bfr[slot][j] = trb.frag(bs, kk, j * (32 * WN / 64) * 4096);
         else if constexpr (M16) bfr[slot][j] = kb.frag(bs, kk, j);
         else bfr[slot][j] = *(const bf16x8 *)(bs + lds_off(fcol_base(j) + frow, kk * (KSTEP / 8) + fhalf));
@@ -488,14 +501,15 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
         constexpr int cur = decltype(cur_c)::value;          // compile-time: the fragment arrays must stay registers
         constexpr int VM = decltype(fetch_c)::value ? (BM + BN) / 8 / (WM * WN) : 0;   // loads of a fetch issued just before
         if constexpr (M16) {
-            static_assert(NI <= MI, "B fragments are read behind the first NI row blocks");
+            constexpr int BPB = (NI + MI - 1) / MI;          // B fragments read behind each row block
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
                 load_a(la, lkk, cur ^ 1, i);
-                if (i < NI) load_b(lb, lkk, cur ^ 1, i);
+#pragma unroll
+                for (int j = i * BPB; j < NI && j < (i + 1) * BPB; ++j) load_b(lb, lkk, cur ^ 1, j);
             }
             sched_mfma_then_reads<NI, (TA ? 2 : 1), (TB ? 2 : 1), VM>(std::make_integer_sequence<int, MI>{});
         } else {
@@ -519,20 +533,34 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
             step(S1{}, S0{}, ca, cb, 2);
             step(S0{}, S0{}, ca, cb, 3);
         }
-        dma_publish_barrier();
+        if constexpr (NST == 2) {
+            dma_publish_barrier();
+        } else {
+            // own loads of the next tile have landed; the NST - 2 younger tiles' loads stay in flight
+            wait_vmcnt_lgkm0<(NST - 2) * ((BM + BN) / 8 / (WM * WN))>();
+            lds_barrier();
+        }
         fetch(kt_fetch, fa, fb);
         step(S1{}, S1{}, na, nb, 0);
     };
 
-    fetch(0, As0, Bs0);
-    dma_publish_barrier();
-    fetch(1, As1, Bs1);
+    if constexpr (NST == 2) {
+        fetch(0, As0, Bs0);
+        dma_publish_barrier();
+        fetch(1, As1, Bs1);
+    } else {
+#pragma unroll
+        for (int k = 0; k < NST; ++k) fetch(k, Ast[k], Bst[k]);
+        wait_vmcnt_lgkm0<(NST - 1) * ((BM + BN) / 8 / (WM * WN))>();
+        lds_barrier();
+    }
     load_frags(As0, Bs0, 0, 0);
-    // two K tiles per trip so that each half names its LDS buffers statically; an odd tile count is
-    // rounded up with a tile of zeros (a single loop exit keeps the accumulators in place)
-    for (int kt = 0; kt < nk; kt += 2) {
-        tile(As0, Bs0, As1, Bs1, As0, Bs0, kt + 2);
-        tile(As1, Bs1, As0, Bs0, As1, Bs1, kt + 3);
+    // NST K tiles per trip so that each part names its LDS buffers statically; the tile count is
+    // rounded up with tiles of zeros (a single loop exit keeps the accumulators in place)
+    for (int kt = 0; kt < nk; kt += NST) {
+#pragma unroll
+        for (int k = 0; k < NST; ++k)
+            tile(Ast[k], Bst[k], Ast[(k + 1) % NST], Bst[(k + 1) % NST], Ast[k], Bst[k], kt + k + NST);
     }
     dma_publish_barrier();   // the (all-zero) tiles still in flight must land before the epilogue reuses LDS
 
@@ -573,6 +601,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
         }
         wave_sync();     // every lane's values are in LDS before any lane reads
     };
+    // 8 KB of the idle tile buffers per wave; wpa waves fit into one A buffer
+    auto stage_area = [&](int wpa) __attribute__((always_inline)) {
+        const int q = wave / wpa;
+        return (float *)(q == 0 ? As0 : q == 1 ? As1 : q == 2 ? Bs0 : Bs1) + (wave % wpa) * 2048;
+    };
     // ---- epilogue.  C and the residual are addressed through buffer descriptors: rows past M are
     // dropped (stores) or read as zero by the range check, columns past N by one select.
     const int esz = p.c_fp32 ? 4 : 2;
@@ -586,7 +619,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
         // through LDS as [32 rows][gate 32 | up 32], and each lane then owns 4 consecutive output columns.
         static_assert(WTN == 64 && NI32 == 2 && !TA && !TB, "SwiGLU epilogue is built for the K-contiguous layout");
         constexpr int WPA = BM / 64;
-        float *stg = (float *)((wave / WPA) ? As1 : As0) + (wave % WPA) * 2048;
+        float *stg = stage_area(WPA);
         const int prow = lane >> 3, pcol = (lane & 7) * 4;
         const int colg = n0 / 2 + wn * 32 + pcol;
         const bool cok = colg < p.N;
@@ -631,7 +664,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
     if (EPI != EPI_NONE || p.vec_epilogue) {
         static_assert(WTN == 64, "staging assumes 64-column wave tiles");
         constexpr int WPA = BM / 64;                       // waves sharing one of the (now idle) A buffers
-        float *stg = (float *)((wave / WPA) ? As1 : As0) + (wave % WPA) * 2048;
+        float *stg = stage_area(WPA);
         const int prow = lane >> 4, pcol = (lane & 15) * 4;
         const int colg = n0 + col_base(pcol >> 5) + (pcol & 31);
         const bool cok = colg < p.N;
@@ -856,6 +889,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
 MS_INST(256, 4, false, false); MS_INST(256, 4, false, true); MS_INST(256, 4, true, false); MS_INST(256, 4, true, true);
 MS_INST(128, 2, false, false); MS_INST(128, 2, false, true); MS_INST(128, 2, true, false); MS_INST(128, 2, true, true);
 #undef MS_INST
+#define MS_INST_RING(BM, BN, WM, WN, NST, TA, TB) \
+    template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI_NONE, true, NST>(GemmParams)
+#define MS_INST_RINGS(BM, BN, WM, WN, NST)                                                             \
+    MS_INST_RING(BM, BN, WM, WN, NST, false, false); MS_INST_RING(BM, BN, WM, WN, NST, false, true);   \
+    MS_INST_RING(BM, BN, WM, WN, NST, true, false); MS_INST_RING(BM, BN, WM, WN, NST, true, true);     \
+    template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI_KD_DZ, true, NST>(GemmParams);     \
+    template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI_KD_STATS, true, NST>(GemmParams);  \
+    template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI_SWIGLU, true, NST>(GemmParams)
+MS_INST_RINGS(128, 128, 4, 2, 4); MS_INST_RINGS(128, 256, 2, 4, 3); MS_INST_RINGS(64, 128, 2, 2, 3); MS_INST_RINGS(64, 64, 2, 1, 4);
+#undef MS_INST_RINGS
+#undef MS_INST_RING
 #define MS_INST_EPI(EPI)                                                                                      \
     template __global__ void gemm_bf16_fast_kernel<256, 256, 2, 4, false, false, EPI, false>(GemmParams);    \
     template __global__ void gemm_bf16_fast_kernel<256, 256, 2, 4, false, false, EPI, true>(GemmParams);     \
@@ -882,28 +926,80 @@ bool use_mfma16() {
     return o != kUnset ? o != 0 : env;
 }
 
-template <int BM, int BN, int WM, int WN, int EPI>
-void launch_fast_epi(const GemmParams &p, dim3 grid, hipStream_t s) {
-    // (the 128 x 128 dz variant would need more than the 256 registers that let two workgroups share a CU)
-    if (use_mfma16() && !(BM == 128 && EPI == EPI_KD_DZ))
-        gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI, true><<<grid, 64 * WM * WN, 0, s>>>(p);
-    else gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI, false><<<grid, 64 * WM * WN, 0, s>>>(p);
+// The fast kernel's workgroup tiles.  256 x 256 and 128 x 128 have two LDS stages; a K tile is then requested one tile
+// time before its first use, which covers the latency of the load only when the CU is busy with a large tile (256) or
+// a second workgroup (128).  The ring tiles keep two or three tiles in flight and are for grids that do not fill the
+// chip with those: at one workgroup per CU the two-stage 128 x 128 kernel takes 0.61 us per K tile, the ring kernel of
+// the same tile 0.36, and smaller tiles spread a small output over more CUs.
+// us_per_ktile are fits to a sweep over M = 300 .. 10000, N = 1024 .. 8192, K = 1024 .. 17920 (K-contiguous and K-major
+// B) on MI355X: time per 64-deep K tile with one workgroup per CU, few and all CUs busy (the L2s and the power budget
+// are shared), then with two per CU, few and all CUs with a second one.  us_round = prologue and epilogue of a round.
+struct TileShape {
+    int code, bm, bn, per_cu;
+    double us_per_ktile[4], us_round;
+};
+enum { T256 = 0, T128 = 1, R128 = 2, R128x256 = 3, R64x128 = 4, R64 = 5, kNumTiles = 6 };
+constexpr TileShape kTiles[kNumTiles] = {
+    {256, 256, 256, 1, {1.08, 1.48, 0, 0}, 3.5},          {128, 128, 128, 2, {0.60, 0.70, 0.78, 0.97}, 1.8},
+    {128128, 128, 128, 1, {0.36, 0.47, 0, 0}, 1.5},       {128256, 128, 256, 1, {0.60, 0.80, 0, 0}, 2.5},
+    {64128, 64, 128, 2, {0.33, 0.38, 0.54, 0.68}, 1.3},   {64064, 64, 64, 2, {0.285, 0.32, 0.35, 0.41}, 1.2}};
+
+// Estimated time (us) of a grid of `wgs` workgroups with kt K tiles each: full rounds of the chip, then the rest.
+double tile_time(const TileShape &t, long wgs, int kt) {
+    const long slots = 256L * t.per_cu, full = wgs / slots, rest = wgs % slots;
+    const double *u = t.us_per_ktile;
+    double est = full * (kt * u[2 * t.per_cu - 1] + t.us_round);
+    if (rest > 256) est += kt * (u[2] + (u[3] - u[2]) * (rest - 256) / 256) + t.us_round;
+    else if (rest > 0) est += kt * (u[0] + (u[1] - u[0]) * rest / 256) + t.us_round;
+    return est;
 }
 
-template <int BM, int BN, int WM, int WN>
-ms_status launch_bf16_fast(const GemmParams &p, int ta, int tb, int splits, hipStream_t s) {
-    dim3 grid(p.tiles_m * p.tiles_n, splits);
-    ProfScope ps((ta || tb) ? 1 : 0, 2.0 * p.M * p.N * p.K, s);
-#define GO(TA, TB)                                                                                             \
-    do {                                                                                                       \
-        if (use_mfma16()) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI_NONE, true><<<grid, 64 * WM * WN, 0, s>>>(p);   \
-        else gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI_NONE, false><<<grid, 64 * WM * WN, 0, s>>>(p);  \
-    } while (0)
-    if (!ta && !tb) GO(false, false);
+// The tile with the least estimated time for an M x N output (N = rows of B) of kt K tiles.  Every tile adds up K in
+// the same order (one accumulator per element, ascending K, the same MFMA), so the choice does not change results: the
+// rows of a short micro-batch come out as they do in a long one.
+int choose_tile(int M, int N, int kt) {
+    const int forced = forced_tile();
+    const bool m16 = use_mfma16();
+    int best = T128;
+    double best_us = 1e30;
+    for (int i = 0; i < kNumTiles; ++i) {
+        if (forced > 0 ? kTiles[i].code != forced : (!m16 && i > T128)) continue;
+        const double us = tile_time(kTiles[i], (long)ms_cdiv(M, kTiles[i].bm) * ms_cdiv(N, kTiles[i].bn), kt);
+        if (us < best_us) { best_us = us; best = i; }
+    }
+    return best;
+}
+
+template <int BM, int BN, int WM, int WN, int NST, int EPI>
+void launch_fast_tile(const GemmParams &p, int ta, int tb, dim3 grid, hipStream_t s) {
+    constexpr int NT = 64 * WM * WN;
+#define GO(TA, TB)                                                                                                           do {                                                                                                                         if constexpr (NST > 2) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true, NST><<<grid, NT, 0, s>>>(p);             else if (use_mfma16() && !(BM == 128 && EPI == EPI_KD_DZ))                                                                   gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true><<<grid, NT, 0, s>>>(p);                                     else gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, false><<<grid, NT, 0, s>>>(p);                               } while (0)
+    // (the 128 x 128 dz variant on 16-row fragments would need more than the 256 registers that let two workgroups
+    // share a CU)
+    if constexpr (EPI != EPI_NONE) GO(false, false);
+    else if (!ta && !tb) GO(false, false);
     else if (!ta && tb) GO(false, true);
     else if (ta && !tb) GO(true, false);
     else GO(true, true);
 #undef GO
+}
+
+// p.tiles_m / tiles_n are set here; EPI_SWIGLU tiles cover bn / 2 output columns (gate and up rows of B)
+template <int EPI>
+ms_status launch_bf16_fast(GemmParams &p, int tile, int ta, int tb, int splits, double flops, hipStream_t s) {
+    const TileShape &t = kTiles[tile];
+    p.tiles_m = ms_cdiv(p.M, t.bm);
+    p.tiles_n = ms_cdiv(p.N, EPI == EPI_SWIGLU ? t.bn / 2 : t.bn);
+    dim3 grid(p.tiles_m * p.tiles_n, splits);
+    ProfScope ps((ta || tb) ? 1 : 0, flops, s);
+    switch (tile) {
+        case T256: launch_fast_tile<256, 256, 2, 4, 2, EPI>(p, ta, tb, grid, s); break;
+        case R128: launch_fast_tile<128, 128, 4, 2, 4, EPI>(p, ta, tb, grid, s); break;
+        case R128x256: launch_fast_tile<128, 256, 2, 4, 3, EPI>(p, ta, tb, grid, s); break;
+        case R64x128: launch_fast_tile<64, 128, 2, 2, 3, EPI>(p, ta, tb, grid, s); break;
+        case R64: launch_fast_tile<64, 64, 2, 1, 4, EPI>(p, ta, tb, grid, s); break;
+        default: launch_fast_tile<128, 128, 2, 2, 2, EPI>(p, ta, tb, grid, s); break;
+    }
     MS_LAUNCH_CHECK();
     return MS_OK;
 }
@@ -935,8 +1031,10 @@ ms_status launch_bf16(const GemmParams &p, int ta, int tb, int splits, hipStream
 }  // namespace
 
 extern "C" ms_status ms_k_gemm_config(int32_t tile, int32_t mfma16) {
-    if (!(tile == -1 || tile == 0 || tile == 128 || tile == 256) || mfma16 < -1 || mfma16 > 1)
-        return ms_fail(MS_ERR_INVALID_ARG, "gemm_config: tile must be -1, 0, 128 or 256 and mfma16 -1, 0 or 1");
+    bool known = tile == -1 || tile == 0;
+    for (const TileShape &t : kTiles) known = known || tile == t.code;
+    if (!known || mfma16 < -1 || mfma16 > 1)
+        return ms_fail(MS_ERR_INVALID_ARG, "gemm_config: tile must be -1, 0, 128, 256, 128128, 128256, 64128 or 64064 and mfma16 -1, 0 or 1");
     g_tile_override = tile == 0 ? kUnset : tile;
     g_mfma16_override = mfma16 < 0 ? kUnset : mfma16;
     return MS_OK;
@@ -972,45 +1070,40 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
     p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha;
     p.c_fp32 = c_fp32; p.accumulate = accumulate; p.res_fp32 = residual_fp32;
     // fast path (direct-to-LDS loads, descriptor-addressed epilogue) needs full K tiles for a K-contiguous
-    // operand and 32-bit byte offsets; tile 256 x 256 when that still gives every CU work, else 128 x 128
+    // operand and 32-bit byte offsets
     const int forced = forced_tile();
     const long lim = (1L << 32) - (1L << 20);
     const long rows_a = trans_a ? K : M, rows_b = trans_b ? K : N;
     const bool fast = forced >= 0 && ((trans_a && trans_b) || K % BK == 0) && (rows_a + 256) * lda * 2 < lim &&
                       (rows_b + 256) * ldb * 2 < lim && ((long)M + 256) * ldc * 4 < lim &&
                       (!residual || ((long)M + 256) * ldr * 4 < lim);
-    // 256 x 256 (8 waves, one workgroup per CU) runs ~1.25x the rate of 128 x 128 (4 waves, two per CU) when the
-    // grid fills whole rounds of CUs: pick by estimated rate x last-round occupancy
-    const long tiles256 = (long)ms_cdiv(M, 256) * ms_cdiv(N, 256), tiles128 = (long)ms_cdiv(M, 128) * ms_cdiv(N, 128);
-    const double eff256 = (double)tiles256 / (double)(ms_cdiv(tiles256, 256) * 256L);
-    const double eff128 = (double)tiles128 / (double)(ms_cdiv(tiles128, 512) * 512L);
-    bool big = fast && (forced > 0 ? forced == 256 : (tiles256 >= 192 && 1.25 * eff256 > eff128));
     const int kt_total = ms_cdiv(K, BK) < 1 ? 1 : ms_cdiv(K, BK);
+    int tile = fast ? choose_tile(M, N, kt_total) : T128;
     int splits = split_k;
     if (splits <= 0) {  // automatic: only when accumulating into fp32 (weight gradients: small M x N, long K)
         splits = 1;
         if (accumulate && c_fp32 && fast) {
-            // Cost model fitted to measurements on wgrad shapes (microseconds): rounds of resident workgroups
-            // x (K tiles per split x time per K tile + fixed part) + one pass of fp32 atomics over C per split
-            // at ~2 TB/s.  256 x 256: one workgroup per CU, 1.57 us per K tile; 128 x 128: two per CU, 1.07 us.
+            // Tile and number of K splits together, by the tiles' estimated time plus what the output costs: a read and
+            // a write of C without splits, one pass of fp32 atomics per split (1.6 TB/s) and the second round of
+            // prologues with them.  Above 256 K tiles the operands stream from HBM, where the smaller ring tiles lose
+            // 25-45 % (M = N = 1024, K = 32768: 221-285 us unsplit, 90-110 us for the tiles left in) and 128 x 256 12 %.
             double best = 1e30;
-            for (int t256 = 0; t256 <= 1; ++t256) {
-                if (forced > 0 && (forced == 256) != (t256 == 1)) continue;
-                const long tiles = t256 ? tiles256 : tiles128, slots = t256 ? 256 : 512;
-                const double tk = t256 ? 1.57 : 1.07, fix = t256 ? 12.0 : 5.0;
+            for (int i = 0; i < kNumTiles; ++i) {
+                const TileShape &t = kTiles[i];
+                if (forced > 0 ? t.code != forced : ((!use_mfma16() && i > T128) || (kt_total > 256 && i > T128 && i != R128x256))) continue;
+                const double stream = kt_total > 256 && i == R128x256 ? 1.12 : 1.0;
+                const long tiles = (long)ms_cdiv(M, t.bm) * ms_cdiv(N, t.bn);
                 for (int sp = 1; sp <= 8 && (sp == 1 || kt_total / sp >= 8); ++sp) {
-                    const double rounds = (double)ms_cdiv(tiles * sp, slots);
-                    const double est = rounds * (ms_cdiv(kt_total, sp) * tk + fix) + (sp > 1 ? 4.0e-6 * M * N * sp / 2.0 : 0.0);
-                    if (est < best) { best = est; splits = sp; big = t256 == 1; }
+                    const double est = stream * tile_time(t, tiles * sp, ms_cdiv(kt_total, sp)) +
+                                       (sp > 1 ? 2.5e-6 * M * N * sp + 4.0 : 1.6e-6 * M * N);
+                    if (est < best) { best = est; splits = sp; tile = i; }
                 }
             }
         } else if (accumulate && c_fp32) {
-            const int tiles = (int)tiles128;
+            const int tiles = ms_cdiv(M, 128) * ms_cdiv(N, 128);
             while (tiles * splits < 512 && kt_total / (splits * 2) >= 8) splits *= 2;
         }
     }
-    const int BM = big ? 256 : 128, BN = BM;
-    p.tiles_m = ms_cdiv(M, BM); p.tiles_n = ms_cdiv(N, BN);
     if (splits > 1 && !(accumulate && c_fp32)) return ms_fail(MS_ERR_INVALID_ARG, "gemm: split_k needs accumulate into fp32");
     if (splits > kt_total) splits = kt_total;
     p.k_tiles_per_split = ms_cdiv(kt_total, splits);
@@ -1019,8 +1112,8 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
     auto al16 = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
     p.vec_epilogue = !p.atomic && N % 4 == 0 && ldc % 4 == 0 && al16(C) && (!residual || (ldr % 4 == 0 && al16(residual))) &&
                      (!bias || ((uintptr_t)bias & 7) == 0);
-    if (big) return launch_bf16_fast<256, 256, 2, 4>(p, trans_a, trans_b, splits, s);
-    if (fast) return launch_bf16_fast<128, 128, 2, 2>(p, trans_a, trans_b, splits, s);
+    if (fast) return launch_bf16_fast<EPI_NONE>(p, tile, trans_a, trans_b, splits, 2.0 * M * N * K, s);
+    p.tiles_m = ms_cdiv(M, 128); p.tiles_n = ms_cdiv(N, 128);
     return launch_bf16<128, 128>(p, trans_a, trans_b, splits, s);
 }
 
@@ -1049,25 +1142,10 @@ ms_status gemm_kd_epilogue(int mode, int M, int N, int K, const void *A, long ld
     p.A = A; p.B = B; p.C = dz; p.lda = lda; p.ldb = ldb; p.ldc = lddz; p.M = M; p.N = N; p.K = K; p.alpha = 1.f;
     p.c_fp32 = dz_fp32;
     p.kd_zt = zt; p.kd_ldz = ldz; p.kd_stats = stats; p.kd_part = part; p.kd_nparts = nparts; p.kd_inv_t = inv_t; p.kd_coef = coef;
-    const int forced = forced_tile();
-    const long tiles256 = (long)ms_cdiv(M, 256) * ms_cdiv(N, 256), tiles128 = (long)ms_cdiv(M, 128) * ms_cdiv(N, 128);
-    const double eff256 = (double)tiles256 / (double)(ms_cdiv(tiles256, 256) * 256L);
-    const double eff128 = (double)tiles128 / (double)(ms_cdiv(tiles128, 512) * 512L);
-    const bool big = forced > 0 ? forced == 256 : (tiles256 >= 192 && 1.25 * eff256 > eff128);
-    const int BM = big ? 256 : 128;
-    p.tiles_m = ms_cdiv(M, BM); p.tiles_n = ms_cdiv(N, BM);
     p.k_tiles_per_split = ms_cdiv(K, BK);
-    dim3 grid(p.tiles_m * p.tiles_n, 1);
-    ProfScope ps(0, 2.0 * M * N * K, s);
-    if (big) {
-        if (mode == EPI_KD_DZ) launch_fast_epi<256, 256, 2, 4, EPI_KD_DZ>(p, grid, s);
-        else launch_fast_epi<256, 256, 2, 4, EPI_KD_STATS>(p, grid, s);
-    } else {
-        if (mode == EPI_KD_DZ) launch_fast_epi<128, 128, 2, 2, EPI_KD_DZ>(p, grid, s);
-        else launch_fast_epi<128, 128, 2, 2, EPI_KD_STATS>(p, grid, s);
-    }
-    MS_LAUNCH_CHECK();
-    return MS_OK;
+    const int tile = choose_tile(M, N, p.k_tiles_per_split);
+    if (mode == EPI_KD_DZ) return launch_bf16_fast<EPI_KD_DZ>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
+    return launch_bf16_fast<EPI_KD_STATS>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
 }
 
 // ------------------------------------------------------------------ fused gate/up GEMM + SwiGLU
@@ -1090,21 +1168,8 @@ ms_status gemm_swiglu(int M, int F, int K, const void *A, long lda, const void *
     GemmParams p = {};
     p.A = A; p.B = W; p.C = act; p.lda = lda; p.ldb = ldw; p.ldc = ldact; p.M = M; p.N = F; p.K = K; p.alpha = 1.f;
     p.sg_f = F; p.sg_gu = gate_up; p.sg_ldgu = ldgu;
-    const int forced = forced_tile();
-    // a tile covers BN/2 output columns (BN weight rows: gate and up)
-    const long tiles256 = (long)ms_cdiv(M, 256) * ms_cdiv(F, 128), tiles128 = (long)ms_cdiv(M, 128) * ms_cdiv(F, 64);
-    const double eff256 = (double)tiles256 / (double)(ms_cdiv(tiles256, 256) * 256L);
-    const double eff128 = (double)tiles128 / (double)(ms_cdiv(tiles128, 512) * 512L);
-    const bool big = forced > 0 ? forced == 256 : (tiles256 >= 192 && 1.25 * eff256 > eff128);
-    const int BM = big ? 256 : 128;
-    p.tiles_m = ms_cdiv(M, BM); p.tiles_n = ms_cdiv(F, BM / 2);
     p.k_tiles_per_split = ms_cdiv(K, BK);
-    dim3 grid(p.tiles_m * p.tiles_n, 1);
-    ProfScope ps(0, 4.0 * M * F * K, s);
-    if (big) launch_fast_epi<256, 256, 2, 4, EPI_SWIGLU>(p, grid, s);
-    else launch_fast_epi<128, 128, 2, 2, EPI_SWIGLU>(p, grid, s);
-    MS_LAUNCH_CHECK();
-    return MS_OK;
+    return launch_bf16_fast<EPI_SWIGLU>(p, choose_tile(M, 2 * F, p.k_tiles_per_split), 0, 0, 1, 4.0 * M * F * K, s);
 }
 
 extern "C" ms_status ms_k_gemm_swiglu(int32_t M, int32_t F, int32_t K, const void *A, int64_t lda, const void *W, int64_t ldw,

@@ -44,6 +44,19 @@ __device__ __forceinline__ void dma_publish_barrier() {
     __syncthreads();
 }
 
+// The pieces of such a barrier for a ring of stages: wait until at most N of this wave's loads are in flight (loads
+// complete in order, so the older ones have landed) and its LDS accesses are done ...
+template <int N> __device__ __forceinline__ void wait_vmcnt_lgkm0() {
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+}
+// ... then a barrier without the full memory fence of __syncthreads (which would wait for every outstanding load): the
+// wavefront-scope fences only keep the compiler from moving LDS accesses across
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- transposing LDS read (ds_read_b64_tr_b16) --------------------------------------------------
 // Within each group of 16 lanes, lane r supplies the address of an 8-byte row (4 bf16); lane i
 // receives element i%4 of rows i/4, 4 + i/4, 8 + i/4, 12 + i/4.  With a tile stored [k][m]
