@@ -1,6 +1,6 @@
-// Variable-length softmax attention on packed tokens: host entry points and the scalar
-// (one wave per query row) kernels used for fp32 data and for shapes the matrix-core kernels
-// do not cover.  The matrix-core kernels live in attention_mfma.hip.
+// Variable-length softmax attention on packed tokens: host entry points, the fp32 kernels (head_dim 64, 80, 128) and
+// the scalar (one wave per query row) kernels for the head sizes that no matrix-core kernel covers.  The bf16
+// matrix-core kernels live in attention_mfma.hip.
 #include "common.h"
 #include "launch.h"
 #include "attention.h"
@@ -162,6 +162,226 @@ __global__ void dkv_convert_kernel(const float *__restrict__ dkv, T *__restrict_
     dqkv[t * ld + qcols + c] = from_f32<T>(dkv[i]);
 }
 
+// ---------------------------------------------------------------- fp32 on the matrix cores
+// v_mfma_f32_16x16x4_f32 (operand lane = row lane % 16, k lane / 16; accumulator register r of lane l = row
+// 4 (l / 16) + r, column l % 16).  A workgroup of four waves owns 16 queries (forward, dQ) or 16 keys (dK / dV) of one
+// head; its waves take every fourth 16-row block of the other side, without a barrier between blocks, and meet in LDS
+// at the end.  Scores are computed as S^T = K Q^T for the query-owning kernels (as S = Q K^T for the key-owning one), so
+// a lane holds four keys (queries) of its own column and the four accumulator registers are the B operand of the next
+// product as they stand.  The fp32 sections are short (16 .. 128 tokens): the kernels are bound by latency, so every
+// operand comes straight from global memory (L2) and nothing is staged.
+constexpr int kF32Tile = 16;
+
+// Operand fragments of 16 rows with the contraction over HD: component c of fragment f is element 16 f + 4 (lane / 16) + c.
+template <int HD> struct RowFrag {
+    float v[HD / 16][4];
+    __device__ __forceinline__ void load(const float *row, int lane) {      // row: this lane's row (lane % 16)
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f) {
+            const float4 t = *(const float4 *)(row + 16 * f + 4 * (lane >> 4));
+            v[f][0] = t.x; v[f][1] = t.y; v[f][2] = t.z; v[f][3] = t.w;
+        }
+    }
+};
+template <int HD>
+__device__ __forceinline__ f32x4 mfma_rows(const RowFrag<HD> &a, const RowFrag<HD> &b) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[f][c], b.v[f][c], acc, 0, 0, 0);
+    return acc;
+}
+// out^T[d][col] += sum over the 16 rows of X[row][d] w[row][col]: w as a score accumulator holds it, X row-major;
+// rows at or past row_end count as zeros
+template <int HD>
+__device__ __forceinline__ void mfma_cols(f32x4 *acc, const float *X, long ld, int row0, int row_end, const float *w, int lane) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        int row = row0 + 4 * (lane >> 4) + r;
+        const bool ok = row < row_end;
+        const float *x = X + (long)(ok ? row : row_end - 1) * ld + (lane & 15);
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? x[16 * f] : 0.f, w[r], acc[f], 0, 0, 0);
+    }
+}
+__device__ __forceinline__ float cols_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
+__device__ __forceinline__ float cols_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
+
+// grid: (n_seqs * ceil(max_seqlen / 16), nq)
+template <int HD>
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float *__restrict__ qkv, float *__restrict__ o,
+                                                            float *__restrict__ lse, const int *__restrict__ cu, int ntile_max,
+                                                            int n, int nq, int nkv, int causal, float scale) {
+    __shared__ float po[4][HD][kF32Tile + 1], pm[4][kF32Tile], pl[4][kF32Tile];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15;
+    const int b = blockIdx.x / ntile_max, h = blockIdx.y, g = h / (nq / nkv);
+    const int s0 = cu[b], s1 = cu[b + 1], q0 = s0 + (int)(blockIdx.x % ntile_max) * kF32Tile;
+    if (q0 >= s1) return;
+    const long ld = (long)(nq + 2 * nkv) * HD;
+    const float *K = qkv + (long)(nq + g) * HD, *V = qkv + (long)(nq + nkv + g) * HD;
+    const int q = q0 + col;
+    const int kend = causal && q0 + kF32Tile < s1 ? q0 + kF32Tile : s1;
+    RowFrag<HD> qf;
+    qf.load(qkv + (long)(q < s1 ? q : s1 - 1) * ld + (long)h * HD, lane);
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc[HD / 16];
+#pragma unroll
+    for (int f = 0; f < HD / 16; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = s0 + wave * kF32Tile; k0 < kend; k0 += 4 * kF32Tile) {
+        RowFrag<HD> kf;
+        kf.load(K + (long)(k0 + col < s1 ? k0 + col : s1 - 1) * ld, lane);
+        const f32x4 s = mfma_rows<HD>(kf, qf);
+        float p[4], mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int key = k0 + 4 * (lane >> 4) + r;
+            p[r] = key < kend && (!causal || key <= q) ? s[r] * scale : -INFINITY;
+            mx = fmaxf(mx, p[r]);
+        }
+        const float mn = fmaxf(m, cols_max(mx));
+        const float mu = mn == -INFINITY ? 0.f : mn, corr = __expf(m - mu);
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = __expf(p[r] - mu);
+            sum += p[r];
+        }
+        l = l * corr + cols_sum(sum);
+        m = mn;
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[f][r] *= corr;
+        mfma_cols<HD>(acc, V, ld, k0, s1, p, lane);
+    }
+#pragma unroll
+    for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) po[wave][16 * f + 4 * (lane >> 4) + r][col] = acc[f][r];
+    if (lane < kF32Tile) {
+        pm[wave][lane] = m;
+        pl[wave][lane] = l;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kF32Tile * HD; i += 256) {
+        const int c = i / HD, d = i % HD;
+        if (q0 + c >= s1) continue;
+        const float mm = fmaxf(fmaxf(pm[0][c], pm[1][c]), fmaxf(pm[2][c], pm[3][c]));   // finite: a query sees itself
+        float ll = 0.f, oo = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float f = __expf(pm[w][c] - mm);
+            ll += pl[w][c] * f;
+            oo += po[w][d][c] * f;
+        }
+        o[(long)(q0 + c) * nq * HD + (long)h * HD + d] = oo / ll;
+        if (d == 0) lse[(long)h * n + q0 + c] = mm + __logf(ll);
+    }
+}
+
+// One launch for dQ (blockIdx.y < nq: 16 queries of a query head) and dK / dV (the rest: 16 keys of a key/value head,
+// all query heads of its group, so that nothing is summed with atomics).  delta = rowsum(dO o O) is recomputed where it
+// is needed.
+template <int HD>
+__global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ o,
+                                                            const float *__restrict__ lse, const float *__restrict__ d_o,
+                                                            float *__restrict__ dqkv, const int *__restrict__ cu, int ntile_max,
+                                                            int n, int nq, int nkv, int causal, float scale) {
+    __shared__ float part[4][HD][kF32Tile + 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15;
+    const int b = blockIdx.x / ntile_max, grp = nq / nkv;
+    const int s0 = cu[b], s1 = cu[b + 1], r0 = s0 + (int)(blockIdx.x % ntile_max) * kF32Tile;
+    if (r0 >= s1) return;
+    const long ld = (long)(nq + 2 * nkv) * HD, ldo = (long)nq * HD;
+    const int own = r0 + col, ownc = own < s1 ? own : s1 - 1;       // this lane's query (dQ) or key (dK / dV)
+    f32x4 acc[2][HD / 16];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto row_delta = [&](const RowFrag<HD> &df, const float *orow) __attribute__((always_inline)) {
+        RowFrag<HD> of;
+        of.load(orow, lane);
+        float s = 0.f;
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) s += df.v[f][c] * of.v[f][c];
+        return cols_sum(s);
+    };
+    // sums the four waves' partial outputs and writes 16 rows of HD columns
+    auto reduce = [&](const f32x4 *a, float *dst, float mul) __attribute__((always_inline)) {
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[wave][16 * f + 4 * (lane >> 4) + r][col] = a[f][r];
+        __syncthreads();
+        for (int i = threadIdx.x; i < kF32Tile * HD; i += 256) {
+            const int c = i / HD, d = i % HD;
+            if (r0 + c < s1) dst[(long)(r0 + c) * ld + d] = (part[0][d][c] + part[1][d][c] + part[2][d][c] + part[3][d][c]) * mul;
+        }
+    };
+    RowFrag<HD> f0, f1;
+    if ((int)blockIdx.y < nq) {
+        const int h = blockIdx.y, g = h / grp;
+        const float *K = qkv + (long)(nq + g) * HD, *V = qkv + (long)(nq + nkv + g) * HD;
+        f0.load(qkv + (long)ownc * ld + (long)h * HD, lane);
+        f1.load(d_o + (long)ownc * ldo + (long)h * HD, lane);
+        const float delta = row_delta(f1, o + (long)ownc * ldo + (long)h * HD), L = lse[(long)h * n + ownc];
+        const int kend = causal && r0 + kF32Tile < s1 ? r0 + kF32Tile : s1;
+        for (int k0 = s0 + wave * kF32Tile; k0 < kend; k0 += 4 * kF32Tile) {
+            RowFrag<HD> kf, vf;
+            const long kr = (long)(k0 + col < s1 ? k0 + col : s1 - 1) * ld;
+            kf.load(K + kr, lane);
+            vf.load(V + kr, lane);
+            const f32x4 s = mfma_rows<HD>(kf, f0), dp = mfma_rows<HD>(vf, f1);
+            float ds[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int key = k0 + 4 * (lane >> 4) + r;
+                ds[r] = key < kend && (!causal || key <= own) ? __expf(s[r] * scale - L) * (dp[r] - delta) : 0.f;
+            }
+            mfma_cols<HD>(acc[0], K, ld, k0, s1, ds, lane);
+        }
+        reduce(acc[0], dqkv + (long)h * HD, scale);
+        return;
+    }
+    const int g = (int)blockIdx.y - nq;
+    f0.load(qkv + (long)ownc * ld + (long)(nq + g) * HD, lane);
+    f1.load(qkv + (long)ownc * ld + (long)(nq + nkv + g) * HD, lane);
+    for (int h = g * grp; h < (g + 1) * grp; ++h) {
+        const float *Q = qkv + (long)h * HD, *dO = d_o + (long)h * HD;
+        for (int q0 = (causal ? r0 : s0) + wave * kF32Tile; q0 < s1; q0 += 4 * kF32Tile) {
+            RowFrag<HD> qf, df;
+            const int qr = q0 + col < s1 ? q0 + col : s1 - 1;
+            qf.load(Q + (long)qr * ld, lane);
+            df.load(dO + (long)qr * ldo, lane);
+            const float delta = row_delta(df, o + (long)qr * ldo + (long)h * HD), L = lse[(long)h * n + qr];
+            const f32x4 s = mfma_rows<HD>(qf, f0), dp = mfma_rows<HD>(df, f1);
+            float p[4], ds[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int qi = 4 * (lane >> 4) + r, qq = q0 + qi;
+                const float Lr = __shfl(L, qi, 64), dr = __shfl(delta, qi, 64);
+                const bool ok = qq < s1 && (!causal || own <= qq);
+                p[r] = ok ? __expf(s[r] * scale - Lr) : 0.f;
+                ds[r] = ok ? p[r] * (dp[r] - dr) : 0.f;
+            }
+            mfma_cols<HD>(acc[0], Q, ld, q0, s1, ds, lane);
+            mfma_cols<HD>(acc[1], dO, ldo, q0, s1, p, lane);
+        }
+    }
+    reduce(acc[0], dqkv + (long)(nq + g) * HD, scale);
+    reduce(acc[1], dqkv + (long)(nq + nkv + g) * HD, 1.f);
+}
+
+bool f32_tiles_supported(int hd, int n_seqs, int max_seqlen, int heads, const void *qkv, const void *o) {
+    return (hd == 64 || hd == 80 || hd == 128) && max_seqlen > 0 && heads <= 65535 &&
+           (long)n_seqs * ms_cdiv(max_seqlen, kF32Tile) <= 0x7fffffffL && (((uintptr_t)qkv | (uintptr_t)o) & 15) == 0;
+}
+
 }  // namespace
 
 static ms_status check_attn(const char *who, int dtype, int nq, int nkv, int hd, int n, int n_seqs, int max_seqlen,
@@ -185,6 +405,15 @@ extern "C" ms_status ms_k_attention_forward(int32_t dtype, int32_t causal, int32
     ProfScope ps(2, 0.0, s);  // work (flops) depends on the sequence lengths: computed by the caller
     if (dtype == MS_BF16 && attn_mfma_forward_supported(hd))
         return attn_mfma_forward(causal, nq, nkv, hd, n, n_seqs, max_seqlen, cu, qkv, o, lse, s);
+    if (dtype == MS_F32 && f32_tiles_supported(hd, n_seqs, max_seqlen, nq, qkv, o)) {
+        const int nt = ms_cdiv(max_seqlen, kF32Tile);
+        const dim3 grid((unsigned)((long)n_seqs * nt), nq);
+#define GO(HD) attn_fwd_f32_kernel<HD><<<grid, 256, 0, s>>>((const float *)qkv, (float *)o, lse, cu, nt, n, nq, nkv, causal, scale)
+        if (hd == 64) GO(64); else if (hd == 80) GO(80); else GO(128);
+#undef GO
+        MS_LAUNCH_CHECK();
+        return MS_OK;
+    }
     dim3 grid(n, ms_cdiv(nq, 4));
     if (dtype == MS_BF16)
         attn_fwd_scalar_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)qkv, (bf16_t *)o, lse, cu, n_seqs, n, nq, nkv, hd, causal, scale);
@@ -212,6 +441,15 @@ extern "C" ms_status ms_k_attention_backward(int32_t dtype, int32_t causal, int3
     ProfScope ps(3, 0.0, s);
     if (dtype == MS_BF16 && attn_mfma_backward_supported(hd))
         return attn_mfma_backward(causal, nq, nkv, hd, n, n_seqs, max_seqlen, cu, qkv, o, lse, d_o, dqkv, scratch, s);
+    if (dtype == MS_F32 && f32_tiles_supported(hd, n_seqs, max_seqlen, nq + nkv, qkv, o) && (((uintptr_t)d_o) & 15) == 0) {
+        const int nt = ms_cdiv(max_seqlen, kF32Tile);
+        const dim3 grid((unsigned)((long)n_seqs * nt), nq + nkv);
+#define GO(HD) attn_bwd_f32_kernel<HD><<<grid, 256, 0, s>>>((const float *)qkv, (const float *)o, lse, (const float *)d_o, (float *)dqkv, cu, nt, n, nq, nkv, causal, scale)
+        if (hd == 64) GO(64); else if (hd == 80) GO(80); else GO(128);
+#undef GO
+        MS_LAUNCH_CHECK();
+        return MS_OK;
+    }
     float *dkv = (float *)scratch;
     const long total = (long)n * 2 * nkv * hd;
     MS_TRY(launch_fill_f32(dkv, total, 0.f, s));

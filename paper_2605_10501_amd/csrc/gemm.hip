@@ -17,7 +17,7 @@
 //     x all N-tiles, and shares operand panels in its L2;
 //   * gemm_bf16_kernel is the register-staged, bounds-checked fallback (K not a multiple of 64 with a K-contiguous
 //     operand, matrices of 4 GB and more).
-// fp32: a plain LDS-tiled FMA kernel (correctness path of the fp32 workload).
+// fp32: v_mfma_f32_16x16x4_f32 on 32 x 32 tiles with K split over the waves of a workgroup.
 #include <stdlib.h>
 
 #include <atomic>
@@ -830,55 +830,105 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
     }
 }
 
-// ------------------------------------------------------------------ fp32 reference-speed kernel
+// ------------------------------------------------------------------ fp32
 struct GemmF32Params {
     const float *A, *B;
     float *C;
     const float *bias, *residual;
-    long sam, sak, sbn, sbk, ldc, ldr;
-    int M, N, K;
+    long lda, ldb, ldc, ldr;
+    int M, N, K, tiles_n;
     float alpha;
-    int accumulate;
+    int accumulate, vec_a, vec_b;      // vec: K-contiguous rows are 16-byte aligned and K % 4 == 0
 };
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
-    __shared__ float As[16][65], Bs[16][65];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < p.K; k0 += 16) {
-        for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-            const int r = i >> 4, k = i & 15;
-            As[k][r] = (m0 + r < p.M && k0 + k < p.K) ? p.A[(long)(m0 + r) * p.sam + (long)(k0 + k) * p.sak] : 0.f;
-            Bs[k][r] = (n0 + r < p.N && k0 + k < p.K) ? p.B[(long)(n0 + r) * p.sbn + (long)(k0 + k) * p.sbk] : 0.f;
+// One operand's fragments for v_mfma_f32_16x16x4_f32: two 16-row blocks x 16 k.  Lane = (row lane % 16, k-group
+// lane / 16); component c of a block's four values is k = k0 + 4 (lane / 16) + c, so four MFMAs (one per component)
+// contract 16 k.  TRANS: the operand is stored [K][rows].  Rows past the end repeat the last one (never stored), k past
+// the end reads as zero.
+template <bool TRANS> struct F32Frag {
+    float v[2][4];
+    __device__ __forceinline__ void load(const float *P, long ld, int row0, int rows, int k0, int K, int vec, int lane) {
+        const int k = k0 + 4 * (lane >> 4);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            int r = row0 + 16 * b + (lane & 15);
+            r = r < rows ? r : rows - 1;
+            if (!TRANS && vec) {
+                const float4 t = *(const float4 *)(P + (long)r * ld + (k < K ? k : 0));
+                v[b][0] = k < K ? t.x : 0.f; v[b][1] = k < K ? t.y : 0.f; v[b][2] = k < K ? t.z : 0.f; v[b][3] = k < K ? t.w : 0.f;
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int kc = k + c < K ? k + c : 0;
+                    const float t = TRANS ? P[(long)kc * ld + r] : P[(long)r * ld + kc];
+                    v[b][c] = k + c < K ? t : 0.f;
+                }
+            }
         }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[k][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-        }
-        __syncthreads();
     }
+};
+
+// fp32 GEMM for the small matrices of the fp32 workload (a few hundred rows): latency is what it costs, not flops.  A
+// workgroup computes a 32 x 32 tile; its four waves take every fourth 16-deep slice of K each (a quarter of the serial
+// chain) and add up through LDS.  Fragments come straight from global memory (the operands are a few hundred KB and
+// stay in L2), three slices ahead of the MFMAs that use them.  M = 293, N = 128, K = 1024: 103 us with the 64 x 64
+// FMA kernel this replaces (10 workgroups, a barrier and a load latency per 16 k); see the figures at ms_k_gemm.
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
+    __shared__ float part[4][32][33];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m0 = (int)(blockIdx.x / p.tiles_n) * 32, n0 = (int)(blockIdx.x % p.tiles_n) * 32;
+    const int slices = (p.K + 15) / 16, mine = slices > wave ? (slices - wave + 3) / 4 : 0;
+    F32Frag<TA> a[4];
+    F32Frag<TB> b[4];
+    f32x4 acc[2][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int row = m0 + ty + 16 * i, col = n0 + tx + 16 * j;
-            if (row >= p.M || col >= p.N) continue;
-            float v = acc[i][j] * p.alpha;
-            if (p.bias) v += p.bias[col];
-            if (p.residual) v += p.residual[(long)row * p.ldr + col];
-            float *c = p.C + (long)row * p.ldc + col;
-            *c = p.accumulate ? *c + v : v;
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int slot, int s) __attribute__((always_inline)) {
+        const int k0 = (wave + 4 * s) * 16;
+        a[slot].load(p.A, p.lda, m0, p.M, k0, p.K, p.vec_a, lane);
+        b[slot].load(p.B, p.ldb, n0, p.N, k0, p.K, p.vec_b, lane);
+    };
+    if (mine > 0) {          // (slices past the end read the first k of their rows and become zeros)
+        load(0, 0);
+        load(1, 1);
+        load(2, 2);
+    }
+    for (int s = 0; s < mine; s += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (s + u >= mine) break;
+            load((u + 3) & 3, s + u + 3);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].v[i][c], b[u].v[j][c], acc[i][j], 0, 0, 0);
         }
+    }
+    // accumulator (i, j) register r: row 16 i + 4 (lane / 16) + r, column 16 j + lane % 16
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[wave][16 * i + 4 * (lane >> 4) + r][16 * j + (lane & 15)] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int rr = (threadIdx.x >> 5) + 8 * e, cc = threadIdx.x & 31;
+        const int row = m0 + rr, col = n0 + cc;
+        if (row >= p.M || col >= p.N) continue;
+        float v = (part[0][rr][cc] + part[1][rr][cc] + part[2][rr][cc] + part[3][rr][cc]) * p.alpha;
+        if (p.bias) v += p.bias[col];
+        if (p.residual) v += p.residual[(long)row * p.ldr + col];
+        float *c = p.C + (long)row * p.ldc + col;
+        *c = p.accumulate ? *c + v : v;
+    }
 }
 
 // Explicit instantiations: the host pass has been seen to reference the launch stubs of some of these
@@ -1053,10 +1103,17 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
         GemmF32Params p;
         p.A = (const float *)A; p.B = (const float *)B; p.C = (float *)C;
         p.bias = (const float *)bias; p.residual = (const float *)residual;
-        p.sam = trans_a ? 1 : lda; p.sak = trans_a ? lda : 1;
-        p.sbn = trans_b ? 1 : ldb; p.sbk = trans_b ? ldb : 1;
-        p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.accumulate = accumulate;
-        gemm_f32_kernel<<<dim3(ms_cdiv(N, 64), ms_cdiv(M, 64)), 256, 0, s>>>(p);
+        p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.accumulate = accumulate;
+        p.vec_a = ((uintptr_t)A & 15) == 0 && lda % 4 == 0 && K % 4 == 0;
+        p.vec_b = ((uintptr_t)B & 15) == 0 && ldb % 4 == 0 && K % 4 == 0;
+        p.tiles_n = ms_cdiv(N, 32);
+        const long tiles = (long)ms_cdiv(M, 32) * p.tiles_n;
+        if (tiles > 0x7fffffffL) return ms_fail(MS_ERR_UNSUPPORTED, "gemm(fp32): %d x %d is too large", M, N);
+        const unsigned grid = (unsigned)tiles;
+        if (!trans_a && !trans_b) gemm_f32_kernel<false, false><<<grid, 256, 0, s>>>(p);
+        else if (!trans_a && trans_b) gemm_f32_kernel<false, true><<<grid, 256, 0, s>>>(p);
+        else if (trans_a && !trans_b) gemm_f32_kernel<true, false><<<grid, 256, 0, s>>>(p);
+        else gemm_f32_kernel<true, true><<<grid, 256, 0, s>>>(p);
         MS_LAUNCH_CHECK();
         return MS_OK;
     }

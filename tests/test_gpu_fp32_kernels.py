@@ -1,0 +1,66 @@
+"""fp32 GEMM (K split over the waves of a workgroup) and fp32 attention (16-row tiles, waves over every fourth block) at
+the edges of their tiles and splits, against fp64."""
+import math
+
+import pytest
+import torch
+
+from paper_2605_10501_amd import binding as B
+from paper_2605_10501_amd import workloads as wl
+from parity import TOL_F32, assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def f64(t):
+    return t.detach().cpu().to(torch.float64).numpy()
+
+
+def dev(name, shape, std=1.0):
+    return wl.normal(29, name, shape, std, 0.0, torch.float32, "cuda")
+
+
+# K: one element, below one 16-deep slice, one slice short of / at / past the four waves, several rounds of slices;
+# K % 4 and odd leading dimensions take the scalar loads
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 15), (32, 32, 48), (33, 70, 64), (64, 31, 65), (5, 129, 260), (97, 40, 1027)])
+def test_gemm_fp32_edges(ta, tb, M, N, K):
+    a, b = dev(f"a{M}.{K}", (K, M) if ta else (M, K)), dev(f"b{N}.{K}", (K, N) if tb else (N, K))
+    ref = (f64(a).T if ta else f64(a)) @ (f64(b) if tb else f64(b).T)
+    assert_parity(B.k_gemm(a, b, ta, tb), ref, TOL_F32)
+    c = dev("c", (M, N))
+    out = c.clone()
+    B.k_gemm(a, b, ta, tb, c=out, accumulate=True, c_fp32=True, alpha=0.5)
+    assert_parity(out, f64(c) + 0.5 * ref, TOL_F32, "accumulate")
+
+
+@pytest.mark.parametrize("hd,nq,nkv", [(64, 4, 4), (80, 2, 1), (128, 6, 2)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("lens", [[1], [15, 16, 17], [64, 0, 65, 130]])
+def test_attention_fp32_edges(hd, nq, nkv, causal, lens):
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    batch, n = B.Batch(cu), cu[-1]
+    qkv = dev(f"qkv{hd}{n}", (n, (nq + 2 * nkv) * hd))
+    d_o = dev(f"do{hd}{n}", (n, nq * hd))
+    x = qkv.cpu().double().requires_grad_()
+    heads, outs, lses = x.view(n, nq + 2 * nkv, hd), [], []
+    for a, b in zip(cu[:-1], cu[1:]):
+        if a == b:
+            continue
+        q, k, v = heads[a:b, :nq], heads[a:b, nq:nq + nkv], heads[a:b, nq + nkv:]
+        k, v = (t.repeat_interleave(nq // nkv, 1).transpose(0, 1) for t in (k, v))
+        s = q.transpose(0, 1) @ k.transpose(1, 2) / math.sqrt(hd)
+        if causal:
+            s = s.masked_fill(torch.ones(b - a, b - a, dtype=torch.bool).triu(1), -math.inf)
+        outs.append((s.softmax(-1) @ v).transpose(0, 1).reshape(b - a, nq * hd))
+        lses.append(s.logsumexp(-1))
+    ref = torch.cat(outs)
+    ref.backward(d_o.cpu().double())
+    o, lse = B.k_attention_forward(qkv, batch, nq, nkv, hd, causal)
+    assert_parity(o, ref.detach().numpy(), TOL_F32, "o")
+    assert_parity(lse, torch.cat(lses, 1).detach().numpy(), TOL_F32, "lse")
+    dqkv = B.k_attention_backward(qkv, o, lse, d_o, batch, nq, nkv, hd, causal)
+    assert_parity(dqkv, x.grad.numpy(), TOL_F32, "dqkv")
+    assert torch.equal(dqkv, B.k_attention_backward(qkv, o, lse, d_o, batch, nq, nkv, hd, causal))   # no atomics
