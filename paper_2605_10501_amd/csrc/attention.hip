@@ -4,6 +4,7 @@
 #include "common.h"
 #include "launch.h"
 #include "attention.h"
+#include "mfma_tiles.h"
 
 namespace {
 
@@ -185,25 +186,34 @@ template <int HD> struct RowFrag {
 };
 template <int HD>
 __device__ __forceinline__ f32x4 mfma_rows(const RowFrag<HD> &a, const RowFrag<HD> &b) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};      // two chains: half the dependent latency
 #pragma unroll
     for (int f = 0; f < HD / 16; ++f)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[f][c], b.v[f][c], acc, 0, 0, 0);
-    return acc;
+        for (int c = 0; c < 4; ++c) acc[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[f][c], b.v[f][c], acc[c & 1], 0, 0, 0);
+    return acc[0] + acc[1];
 }
-// out^T[d][col] += sum over the 16 rows of X[row][d] w[row][col]: w as a score accumulator holds it, X row-major;
-// rows at or past row_end count as zeros
-template <int HD>
-__device__ __forceinline__ void mfma_cols(f32x4 *acc, const float *X, long ld, int row0, int row_end, const float *w, int lane) {
+// 16 rows of X as the A operand of out^T[d][col] += sum over rows of X[row][d] w[row][col], w as a score accumulator holds
+// it (row 4 (lane / 16) + r): component r of block f is X[row0 + 4 (lane / 16) + r][16 f + lane % 16].  Rows at or past
+// row_end read as zeros (range check of the descriptor).
+template <int HD> struct ColFrag {
+    float v[HD / 16][4];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, long ld, int row0, int row_end, int col0, int lane) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        int row = row0 + 4 * (lane >> 4) + r;
-        const bool ok = row < row_end;
-        const float *x = X + (long)(ok ? row : row_end - 1) * ld + (lane & 15);
+        for (int r = 0; r < 4; ++r) {
+            const int row = row0 + 4 * (lane >> 4) + r;
+            const unsigned off = row < row_end ? (unsigned)((long)row * ld + col0 + (lane & 15)) * 4u : kOob;
 #pragma unroll
-        for (int f = 0; f < HD / 16; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? x[16 * f] : 0.f, w[r], acc[f], 0, 0, 0);
+            for (int f = 0; f < HD / 16; ++f) v[f][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, f * 64, 0));
+        }
     }
+};
+template <int HD>
+__device__ __forceinline__ void mfma_cols(f32x4 *acc, const ColFrag<HD> &x, const float *w) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[f][r], w[r], acc[f], 0, 0, 0);
 }
 __device__ __forceinline__ float cols_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
 __device__ __forceinline__ float cols_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
@@ -219,7 +229,8 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float *__restri
     const int s0 = cu[b], s1 = cu[b + 1], q0 = s0 + (int)(blockIdx.x % ntile_max) * kF32Tile;
     if (q0 >= s1) return;
     const long ld = (long)(nq + 2 * nkv) * HD;
-    const float *K = qkv + (long)(nq + g) * HD, *V = qkv + (long)(nq + nkv + g) * HD;
+    const float *K = qkv + (long)(nq + g) * HD;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(qkv, (long)n * ld * 4);
     const int q = q0 + col;
     const int kend = causal && q0 + kF32Tile < s1 ? q0 + kF32Tile : s1;
     RowFrag<HD> qf;
@@ -231,6 +242,9 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float *__restri
     for (int k0 = s0 + wave * kF32Tile; k0 < kend; k0 += 4 * kF32Tile) {
         RowFrag<HD> kf;
         kf.load(K + (long)(k0 + col < s1 ? k0 + col : s1 - 1) * ld, lane);
+        ColFrag<HD> vc;
+        vc.load(rs, ld, k0, s1, (nq + nkv + g) * HD, lane);
+        __builtin_amdgcn_sched_barrier(0);           // all requests of the block in front of its first product
         const f32x4 s = mfma_rows<HD>(kf, qf);
         float p[4], mx = -INFINITY;
 #pragma unroll
@@ -253,7 +267,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float *__restri
         for (int f = 0; f < HD / 16; ++f)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[f][r] *= corr;
-        mfma_cols<HD>(acc, V, ld, k0, s1, p, lane);
+        mfma_cols<HD>(acc, vc, p);
     }
 #pragma unroll
     for (int f = 0; f < HD / 16; ++f)
@@ -323,6 +337,7 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
             if (r0 + c < s1) dst[(long)(r0 + c) * ld + d] = (part[0][d][c] + part[1][d][c] + part[2][d][c] + part[3][d][c]) * mul;
         }
     };
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(qkv, (long)n * ld * 4), rd = make_rsrc(d_o, (long)n * ldo * 4);
     RowFrag<HD> f0, f1;
     if ((int)blockIdx.y < nq) {
         const int h = blockIdx.y, g = h / grp;
@@ -336,6 +351,9 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
             const long kr = (long)(k0 + col < s1 ? k0 + col : s1 - 1) * ld;
             kf.load(K + kr, lane);
             vf.load(V + kr, lane);
+            ColFrag<HD> kc;
+            kc.load(rs, ld, k0, s1, (nq + g) * HD, lane);
+            __builtin_amdgcn_sched_barrier(0);
             const f32x4 s = mfma_rows<HD>(kf, f0), dp = mfma_rows<HD>(vf, f1);
             float ds[4];
 #pragma unroll
@@ -343,7 +361,7 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
                 const int key = k0 + 4 * (lane >> 4) + r;
                 ds[r] = key < kend && (!causal || key <= own) ? __expf(s[r] * scale - L) * (dp[r] - delta) : 0.f;
             }
-            mfma_cols<HD>(acc[0], K, ld, k0, s1, ds, lane);
+            mfma_cols<HD>(acc[0], kc, ds);
         }
         reduce(acc[0], dqkv + (long)h * HD, scale);
         return;
@@ -358,6 +376,10 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
             const int qr = q0 + col < s1 ? q0 + col : s1 - 1;
             qf.load(Q + (long)qr * ld, lane);
             df.load(dO + (long)qr * ldo, lane);
+            ColFrag<HD> qc, dc;
+            qc.load(rs, ld, q0, s1, h * HD, lane);
+            dc.load(rd, ldo, q0, s1, h * HD, lane);
+            __builtin_amdgcn_sched_barrier(0);
             const float delta = row_delta(df, o + (long)qr * ldo + (long)h * HD), L = lse[(long)h * n + qr];
             const f32x4 s = mfma_rows<HD>(qf, f0), dp = mfma_rows<HD>(df, f1);
             float p[4], ds[4];
@@ -369,16 +391,16 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
                 p[r] = ok ? __expf(s[r] * scale - Lr) : 0.f;
                 ds[r] = ok ? p[r] * (dp[r] - dr) : 0.f;
             }
-            mfma_cols<HD>(acc[0], Q, ld, q0, s1, ds, lane);
-            mfma_cols<HD>(acc[1], dO, ldo, q0, s1, p, lane);
+            mfma_cols<HD>(acc[0], qc, ds);
+            mfma_cols<HD>(acc[1], dc, p);
         }
     }
     reduce(acc[0], dqkv + (long)(nq + g) * HD, scale);
     reduce(acc[1], dqkv + (long)(nq + nkv + g) * HD, 1.f);
 }
 
-bool f32_tiles_supported(int hd, int n_seqs, int max_seqlen, int heads, const void *qkv, const void *o) {
-    return (hd == 64 || hd == 80 || hd == 128) && max_seqlen > 0 && heads <= 65535 &&
+bool f32_tiles_supported(int hd, int n, int n_seqs, int max_seqlen, int nq, int nkv, int heads, const void *qkv, const void *o) {
+    return (long)n * (nq + 2 * nkv) * hd * 4 < (1L << 32) - (1L << 20) && (hd == 64 || hd == 80 || hd == 128) && max_seqlen > 0 && heads <= 65535 &&
            (long)n_seqs * ms_cdiv(max_seqlen, kF32Tile) <= 0x7fffffffL && (((uintptr_t)qkv | (uintptr_t)o) & 15) == 0;
 }
 
@@ -405,7 +427,7 @@ extern "C" ms_status ms_k_attention_forward(int32_t dtype, int32_t causal, int32
     ProfScope ps(2, 0.0, s);  // work (flops) depends on the sequence lengths: computed by the caller
     if (dtype == MS_BF16 && attn_mfma_forward_supported(hd))
         return attn_mfma_forward(causal, nq, nkv, hd, n, n_seqs, max_seqlen, cu, qkv, o, lse, s);
-    if (dtype == MS_F32 && f32_tiles_supported(hd, n_seqs, max_seqlen, nq, qkv, o)) {
+    if (dtype == MS_F32 && f32_tiles_supported(hd, n, n_seqs, max_seqlen, nq, nkv, nq, qkv, o)) {
         const int nt = ms_cdiv(max_seqlen, kF32Tile);
         const dim3 grid((unsigned)((long)n_seqs * nt), nq);
 #define GO(HD) attn_fwd_f32_kernel<HD><<<grid, 256, 0, s>>>((const float *)qkv, (float *)o, lse, cu, nt, n, nq, nkv, causal, scale)
@@ -441,7 +463,7 @@ extern "C" ms_status ms_k_attention_backward(int32_t dtype, int32_t causal, int3
     ProfScope ps(3, 0.0, s);
     if (dtype == MS_BF16 && attn_mfma_backward_supported(hd))
         return attn_mfma_backward(causal, nq, nkv, hd, n, n_seqs, max_seqlen, cu, qkv, o, lse, d_o, dqkv, scratch, s);
-    if (dtype == MS_F32 && f32_tiles_supported(hd, n_seqs, max_seqlen, nq + nkv, qkv, o) && (((uintptr_t)d_o) & 15) == 0) {
+    if (dtype == MS_F32 && f32_tiles_supported(hd, n, n_seqs, max_seqlen, nq, nkv, nq + nkv, qkv, o) && (((uintptr_t)d_o) & 15) == 0) {
         const int nt = ms_cdiv(max_seqlen, kF32Tile);
         const dim3 grid((unsigned)((long)n_seqs * nt), nq + nkv);
 #define GO(HD) attn_bwd_f32_kernel<HD><<<grid, 256, 0, s>>>((const float *)qkv, (const float *)o, lse, (const float *)d_o, (float *)dqkv, cu, nt, n, nq, nkv, causal, scale)

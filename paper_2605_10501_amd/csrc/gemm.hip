@@ -838,30 +838,32 @@ struct GemmF32Params {
     long lda, ldb, ldc, ldr;
     int M, N, K, tiles_n;
     float alpha;
-    int accumulate, vec_a, vec_b;      // vec: K-contiguous rows are 16-byte aligned and K % 4 == 0
+    int accumulate;
 };
 
 // One operand's fragments for v_mfma_f32_16x16x4_f32: two 16-row blocks x 16 k.  Lane = (row lane % 16, k-group
 // lane / 16); component c of a block's four values is k = k0 + 4 (lane / 16) + c, so four MFMAs (one per component)
-// contract 16 k.  TRANS: the operand is stored [K][rows].  Rows past the end repeat the last one (never stored), k past
-// the end reads as zero.
-template <bool TRANS> struct F32Frag {
+// contract 16 k.  TRANS: the operand is stored [K][rows].  Rows and k past the end read as zero.  FAST: loads through a
+// buffer descriptor whose range check returns the zeros, so that nothing but the MFMAs waits for a load.
+template <bool TRANS, bool FAST> struct F32Frag {
     float v[2][4];
-    __device__ __forceinline__ void load(const float *P, long ld, int row0, int rows, int k0, int K, int vec, int lane) {
+    __device__ __forceinline__ void load(const float *P, __amdgpu_buffer_rsrc_t rs, long ld, int row0, int rows, int k0, int K, int lane) {
         const int k = k0 + 4 * (lane >> 4);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            int r = row0 + 16 * b + (lane & 15);
-            r = r < rows ? r : rows - 1;
-            if (!TRANS && vec) {
-                const float4 t = *(const float4 *)(P + (long)r * ld + (k < K ? k : 0));
-                v[b][0] = k < K ? t.x : 0.f; v[b][1] = k < K ? t.y : 0.f; v[b][2] = k < K ? t.z : 0.f; v[b][3] = k < K ? t.w : 0.f;
+            const int r = row0 + 16 * b + (lane & 15);
+            if constexpr (FAST && !TRANS) {
+                const unsigned off = r < rows && k < K ? (unsigned)((long)r * ld + k) * 4u : kOob;
+                const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[b][c] = __uint_as_float(t[c]);
             } else {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const int kc = k + c < K ? k + c : 0;
-                    const float t = TRANS ? P[(long)kc * ld + r] : P[(long)r * ld + kc];
-                    v[b][c] = k + c < K ? t : 0.f;
+                    const bool ok = r < rows && k + c < K;
+                    const long at = TRANS ? (long)(k + c) * ld + r : (long)r * ld + k + c;
+                    if constexpr (FAST) v[b][c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, ok ? (unsigned)at * 4u : kOob, 0, 0));
+                    else v[b][c] = ok ? P[at] : 0.f;
                 }
             }
         }
@@ -871,16 +873,20 @@ template <bool TRANS> struct F32Frag {
 // fp32 GEMM for the small matrices of the fp32 workload (a few hundred rows): latency is what it costs, not flops.  A
 // workgroup computes a 32 x 32 tile; its four waves take every fourth 16-deep slice of K each (a quarter of the serial
 // chain) and add up through LDS.  Fragments come straight from global memory (the operands are a few hundred KB and
-// stay in L2), three slices ahead of the MFMAs that use them.  M = 293, N = 128, K = 1024: 103 us with the 64 x 64
-// FMA kernel this replaces (10 workgroups, a barrier and a load latency per 16 k); see the figures at ms_k_gemm.
-template <bool TA, bool TB>
+// stay in L2), three slices ahead of the MFMAs that use them; what the epilogue reads is requested before the main loop.
+// The 64 x 64 FMA kernel that this replaces took 1.3 us per 16 k (10..80 workgroups, a load latency and two barriers
+// each): 47 us per launch on average in the c1 step, against 6.9 us now.
+// FAST needs 16-byte aligned K-contiguous rows with K % 4 == 0 and operands below 4 GB; the other form covers the rest.
+template <bool TA, bool TB, bool FAST>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
     __shared__ float part[4][32][33];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m0 = (int)(blockIdx.x / p.tiles_n) * 32, n0 = (int)(blockIdx.x % p.tiles_n) * 32;
     const int slices = (p.K + 15) / 16, mine = slices > wave ? (slices - wave + 3) / 4 : 0;
-    F32Frag<TA> a[4];
-    F32Frag<TB> b[4];
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.A, FAST ? ((long)((TA ? p.K : p.M) - 1) * p.lda + (TA ? p.M : p.K)) * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.B, FAST ? ((long)((TB ? p.K : p.N) - 1) * p.ldb + (TB ? p.N : p.K)) * 4 : 0);
+    F32Frag<TA, FAST> a[4];
+    F32Frag<TB, FAST> b[4];
     f32x4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -888,19 +894,29 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto load = [&](int slot, int s) __attribute__((always_inline)) {
         const int k0 = (wave + 4 * s) * 16;
-        a[slot].load(p.A, p.lda, m0, p.M, k0, p.K, p.vec_a, lane);
-        b[slot].load(p.B, p.ldb, n0, p.N, k0, p.K, p.vec_b, lane);
+        a[slot].load(p.A, ra, p.lda, m0, p.M, k0, p.K, lane);
+        b[slot].load(p.B, rb, p.ldb, n0, p.N, k0, p.K, lane);
     };
-    if (mine > 0) {          // (slices past the end read the first k of their rows and become zeros)
-        load(0, 0);
-        load(1, 1);
-        load(2, 2);
-    }
+    load(0, 0);
+    load(1, 1);
+    load(2, 2);
+    // this thread's four output elements: rows threadIdx.x / 32 + 8 e, column threadIdx.x % 32
+    const int rr = threadIdx.x >> 5, cc = threadIdx.x & 31, col = n0 + cc;
+    float add[4] = {0.f, 0.f, 0.f, 0.f};
+    if (p.bias && col < p.N) add[0] = add[1] = add[2] = add[3] = p.bias[col];
+    float res[4] = {0.f, 0.f, 0.f, 0.f}, old[4] = {0.f, 0.f, 0.f, 0.f};
+    auto inside = [&](int e) { return m0 + rr + 8 * e < p.M && col < p.N; };
+    if (p.residual)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (inside(e)) res[e] = p.residual[(long)(m0 + rr + 8 * e) * p.ldr + col];
+    if (p.accumulate)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (inside(e)) old[e] = p.C[(long)(m0 + rr + 8 * e) * p.ldc + col];
     for (int s = 0; s < mine; s += 4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (s + u >= mine) break;
-            load((u + 3) & 3, s + u + 3);
+            load((u + 3) & 3, s + u + 3);             // (slices past the end are zeros)
+            __builtin_amdgcn_sched_barrier(0);        // the requests stay in front of the MFMAs
 #pragma unroll
             for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -920,14 +936,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const int rr = (threadIdx.x >> 5) + 8 * e, cc = threadIdx.x & 31;
-        const int row = m0 + rr, col = n0 + cc;
-        if (row >= p.M || col >= p.N) continue;
-        float v = (part[0][rr][cc] + part[1][rr][cc] + part[2][rr][cc] + part[3][rr][cc]) * p.alpha;
-        if (p.bias) v += p.bias[col];
-        if (p.residual) v += p.residual[(long)row * p.ldr + col];
-        float *c = p.C + (long)row * p.ldc + col;
-        *c = p.accumulate ? *c + v : v;
+        const int q = rr + 8 * e;
+        const float v = (part[0][q][cc] + part[1][q][cc] + part[2][q][cc] + part[3][q][cc]) * p.alpha + add[e] + res[e];
+        if (inside(e)) p.C[(long)(m0 + q) * p.ldc + col] = p.accumulate ? old[e] + v : v;
     }
 }
 
@@ -1104,16 +1115,23 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
         p.A = (const float *)A; p.B = (const float *)B; p.C = (float *)C;
         p.bias = (const float *)bias; p.residual = (const float *)residual;
         p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.accumulate = accumulate;
-        p.vec_a = ((uintptr_t)A & 15) == 0 && lda % 4 == 0 && K % 4 == 0;
-        p.vec_b = ((uintptr_t)B & 15) == 0 && ldb % 4 == 0 && K % 4 == 0;
         p.tiles_n = ms_cdiv(N, 32);
         const long tiles = (long)ms_cdiv(M, 32) * p.tiles_n;
         if (tiles > 0x7fffffffL) return ms_fail(MS_ERR_UNSUPPORTED, "gemm(fp32): %d x %d is too large", M, N);
         const unsigned grid = (unsigned)tiles;
-        if (!trans_a && !trans_b) gemm_f32_kernel<false, false><<<grid, 256, 0, s>>>(p);
-        else if (!trans_a && trans_b) gemm_f32_kernel<false, true><<<grid, 256, 0, s>>>(p);
-        else if (trans_a && !trans_b) gemm_f32_kernel<true, false><<<grid, 256, 0, s>>>(p);
-        else gemm_f32_kernel<true, true><<<grid, 256, 0, s>>>(p);
+        auto fast = [&](const void *q, long ld, bool trans, long rows) {
+            return (trans || (((uintptr_t)q & 15) == 0 && ld % 4 == 0 && K % 4 == 0)) && (trans ? K : rows) * ld * 4 < (1L << 32) - (1L << 20);
+        };
+#define GO(TA, TB)                                                                                     \
+    do {                                                                                               \
+        if (fast(A, lda, TA, M) && fast(B, ldb, TB, N)) gemm_f32_kernel<TA, TB, true><<<grid, 256, 0, s>>>(p);  \
+        else gemm_f32_kernel<TA, TB, false><<<grid, 256, 0, s>>>(p);                                   \
+    } while (0)
+        if (!trans_a && !trans_b) GO(false, false);
+        else if (!trans_a && trans_b) GO(false, true);
+        else if (trans_a && !trans_b) GO(true, false);
+        else GO(true, true);
+#undef GO
         MS_LAUNCH_CHECK();
         return MS_OK;
     }
