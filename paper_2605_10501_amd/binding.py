@@ -304,7 +304,7 @@ def schedule_makespan(tuples, order, interleave=True):
 
 # ------------------------------------------------------------------ kernel-level entry points
 def k_gemm_config(tile=0, mfma16=-1):
-    """Kernel selection of the bf16 GEMMs (tests, measurements): tile 0 / 128 / 256 / 128128 / 128256 / 64128 / 64064 / -1, mfma16 -1 / 0 / 1."""
+    """Kernel selection of the bf16 GEMMs (tests, measurements): tile 0 / 128 / 256 / 256256 / 128128 / 128256 / 64128 / 64064 / -1, mfma16 -1 / 0 / 1."""
     _check(lib().ms_k_gemm_config(int(tile), int(mfma16)))
 
 

@@ -364,6 +364,271 @@ struct KFragAddr16 {
     }
 };
 
+// Epilogue of the fast kernels.  acc[i][j]: the wave's MI x NI accumulator blocks (16 x 16 with M16, else 32 x 32) of 64
+// columns in all; the wave's 32-row block i starts at tile row row_base(i), its 32-column block j at tile column
+// col_base(j); stg: 8 KB of LDS that belong to the wave (the operand buffers are idle by now).
+template <int EPI, bool M16, bool TA, bool TB, int MI, int NI, class ACC, class RB, class CB>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI][NI], float *stg, int m0, int n0, int wn, int lane,
+                                              RB row_base, CB col_base) {
+    constexpr int FR = M16 ? 16 : 32, ACC_N = M16 ? 4 : 16, MI32 = MI * FR / 32, WTN = 64;
+    static_assert(NI * FR == WTN, "staging assumes 64-column wave tiles");
+    const int frow = lane & (FR - 1), fhalf = lane / FR;
+    // ---- epilogue staging: the accumulators of the wave's 32-row block i go to LDS as [32 rows][64 columns]
+    // fp32 (v = value transform), from where each lane reads 4 consecutive columns of a row.  The 16-column
+    // group index (32x32 MFMA: column bit 5 only) is XOR-ed with row bits so that the lanes of one store
+    // instruction, which hold the same columns of rows 4 apart, use different banks.
+    auto stg_swz = [](int row) { return M16 ? ((row >> 2) & 3) << 4 : ((row >> 2) & 1) << 5; };
+    // The lanes of a wave exchange data through the staging area, and the LDS executes a wave's accesses in
+    // program order; what has to be kept is the program order itself: to the compiler a lane's reads and another
+    // lane's writes are unrelated addresses that it may reorder.  wave_sync() is a compiler-level fence between the
+    // two phases (no instruction).
+    auto wave_sync = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto stage_block = [&](int i, auto v) __attribute__((always_inline)) {
+        wave_sync();     // the reads of the previous block come first
+        if constexpr (M16) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = h * 16 + 4 * fhalf + r;
+                        stg[row * 64 + ((j * 16 + frow) ^ stg_swz(row))] = v(acc[2 * i + h][j][r]);
+                    }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 8 * (r >> 2) + 4 * fhalf + (r & 3);
+                    stg[row * 64 + ((j * 32 + frow) ^ stg_swz(row))] = v(acc[i][j][r]);
+                }
+        }
+        wave_sync();     // every lane's values are in LDS before any lane reads
+    };
+    // ---- epilogue.  C and the residual are addressed through buffer descriptors: rows past M are
+    // dropped (stores) or read as zero by the range check, columns past N by one select.
+    const int esz = p.c_fp32 ? 4 : 2;
+    const __amdgpu_buffer_rsrc_t rc = make_rsrc(p.C, (long)p.M * p.ldc * esz);
+    const int rsz = p.res_fp32 ? 4 : 2;
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.residual ? p.residual : p.C, p.residual ? (long)p.M * p.ldr * rsz : 0);
+    const bf16_t *bias = (const bf16_t *)p.bias;
+    if constexpr (EPI == EPI_SWIGLU) {
+        // acc[i][0] = gate, acc[i][1] = up of output columns n0/2 + wn*32 + (0..31).  Both are rounded to
+        // the storage type first (they are the values a separate activation kernel would read back), staged
+        // through LDS as [32 rows][gate 32 | up 32], and each lane then owns 4 consecutive output columns.
+        static_assert(!TA && !TB, "SwiGLU epilogue is built for the K-contiguous layout");
+        const int prow = lane >> 3, pcol = (lane & 7) * 4;
+        const int colg = n0 / 2 + wn * 32 + pcol;
+        const bool cok = colg < p.N;
+        const __amdgpu_buffer_rsrc_t rg = make_rsrc(p.sg_gu ? p.sg_gu : p.C, p.sg_gu ? (long)p.M * p.sg_ldgu * 2 : 0);
+        auto pack4 = [](const float *v) {
+            u32x2 w;
+            w[0] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[0]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[1]) << 16);
+            w[1] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[2]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[3]) << 16);
+            return w;
+        };
+#pragma unroll
+        for (int i = 0; i < MI32; ++i) {
+            stage_block(i, [&](float a) { return (float)(bf16_t)(a * p.alpha); });
+#pragma unroll
+            for (int ps = 0; ps < 4; ++ps) {
+                const int row = ps * 8 + prow;
+                const int flip = stg_swz(row);
+                const float4 g4 = *(const float4 *)(stg + row * 64 + (pcol ^ flip));
+                const float4 u4 = *(const float4 *)(stg + row * 64 + ((32 + pcol) ^ flip));
+                const float gv[4] = {g4.x, g4.y, g4.z, g4.w}, uv[4] = {u4.x, u4.y, u4.z, u4.w};
+                float a[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)   // silu(g) u = g u / (1 + e^-g); hardware reciprocal (1 ulp) instead of the division sequence
+                    a[e] = gv[e] * uv[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gv[e]));
+                const long rowg = m0 + row_base(i) + row;
+                __builtin_amdgcn_raw_buffer_store_b64(pack4(a), rc, cok ? (unsigned)((rowg * p.ldc + colg) * 2) : kOob, 0, kStream);
+                if (p.sg_gu) {
+                    const unsigned go = cok ? (unsigned)((rowg * p.sg_ldgu + colg) * 2) : kOob;
+                    __builtin_amdgcn_raw_buffer_store_b64(pack4(gv), rg, go, 0, kStream);
+                    __builtin_amdgcn_raw_buffer_store_b64(pack4(uv), rg, cok ? go + (unsigned)p.sg_f * 2 : kOob, 0, kStream);
+                }
+            }
+        }
+        return;
+    }
+    // ---- vector epilogues.  Each wave passes its accumulators through LDS, 32 rows at a time, to turn the
+    // MFMA layout (a lane owns one column) into rows: a lane then handles 4 consecutive columns of a row, so
+    // global reads and writes are 8..16 bytes per lane and 128..256 contiguous bytes per row.  What the
+    // epilogue reads from memory for a 32-row block (fp32/bf16 residual, C when accumulating, teacher logits)
+    // is fetched one block ahead into registers: the loads of block i+1 are issued before the stores of
+    // block i, so no pass waits for a store or for its own load's full latency.
+    if (EPI != EPI_NONE || p.vec_epilogue) {
+        const int prow = lane >> 4, pcol = (lane & 15) * 4;
+        const int colg = n0 + col_base(pcol >> 5) + (pcol & 31);
+        const bool cok = colg < p.N;
+        // the prefetched stream: KD -> teacher logits (fp32); else residual (fp32 or bf16); else C (accumulate)
+        const bool aux_res = EPI == EPI_NONE && p.residual != nullptr;
+        const bool aux_c = EPI == EPI_NONE && !aux_res && p.accumulate && p.c_fp32;
+        const bool has_aux = EPI != EPI_NONE || aux_res || aux_c;
+        const bool aux4 = EPI != EPI_NONE || aux_c || p.res_fp32;                  // 4-byte elements
+        const long aux_ld = EPI != EPI_NONE ? p.kd_ldz : (aux_res ? p.ldr : p.ldc);
+        const __amdgpu_buffer_rsrc_t ra_ = EPI != EPI_NONE ? make_rsrc(p.kd_zt, (long)p.M * p.kd_ldz * 4) : (aux_res ? rr : rc);
+        u32x4 aux[2][8];
+        float2 lsev[2][8];                                                         // EPI_KD_DZ: (lse_t, lse_s) of the row
+        auto prefetch = [&](int i, u32x4 *dst, float2 *ldst) {
+#pragma unroll
+            for (int ps = 0; ps < 8; ++ps) {
+                const long rowg = m0 + row_base(i) + ps * 4 + prow;
+                const unsigned off = cok ? (unsigned)((rowg * aux_ld + colg) * (aux4 ? 4 : 2)) : kOob;
+                if (aux4) dst[ps] = __builtin_amdgcn_raw_buffer_load_b128(ra_, off, 0, kStream);
+                else {
+                    const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(ra_, off, 0, kStream);
+                    dst[ps][0] = q[0]; dst[ps][1] = q[1];
+                }
+                if constexpr (EPI == EPI_KD_DZ) ldst[ps] = rowg < p.M ? *(const float2 *)(p.kd_stats + rowg * 8 + 6) : make_float2(0.f, 0.f);
+            }
+        };
+        float bv[4] = {0.f, 0.f, 0.f, 0.f};
+        if (EPI == EPI_NONE && bias && cok) {
+            const uint2 b2 = *(const uint2 *)(bias + colg);
+            bv[0] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.x & 0xffff));
+            bv[1] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.x >> 16));
+            bv[2] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.y & 0xffff));
+            bv[3] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.y >> 16));
+        }
+        auto store4 = [&](const float *v, unsigned co) {
+            if (p.c_fp32) {
+                u32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = __builtin_bit_cast(unsigned, v[e]);
+                __builtin_amdgcn_raw_buffer_store_b128(w, rc, co, 0, kStream);
+            } else {
+                u32x2 w;
+                w[0] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[0]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[1]) << 16);
+                w[1] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[2]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[3]) << 16);
+                __builtin_amdgcn_raw_buffer_store_b64(w, rc, co, 0, kStream);
+            }
+        };
+        const float it = p.kd_inv_t;
+        const float it2 = it * 1.4426950408889634f;      // e^{z/T - m} = 2^{z it2 - m log2(e)}: one fused multiply-add feeds exp2
+        if (has_aux) prefetch(0, aux[0], lsev[0]);
+#pragma unroll
+        for (int i = 0; i < MI32; ++i) {
+            if (has_aux && i + 1 < MI32) prefetch(i + 1, aux[(i + 1) & 1], lsev[(i + 1) & 1]);
+            stage_block(i, [&](float a) { return a * p.alpha; });
+#pragma unroll
+            for (int ps = 0; ps < 8; ++ps) {
+                const int row = ps * 4 + prow;
+                const float4 t = *(const float4 *)(stg + row * 64 + (pcol ^ stg_swz(row)));
+                const long rowg = m0 + row_base(i) + row;
+                const u32x4 q = aux[i & 1][ps];
+                const unsigned co = cok ? (unsigned)((rowg * p.ldc + colg) * esz) : kOob;
+                if constexpr (EPI == EPI_NONE) {
+                    float v[4] = {t.x + bv[0], t.y + bv[1], t.z + bv[2], t.w + bv[3]};
+                    if (aux_res || aux_c) {
+                        if (aux4) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(q[e]);
+                        } else {
+                            v[0] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[0] & 0xffff));
+                            v[1] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[0] >> 16));
+                            v[2] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[1] & 0xffff));
+                            v[3] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[1] >> 16));
+                        }
+                    }
+                    if (aux_res && p.accumulate && p.c_fp32) {        // both a residual and += : C is read in place
+                        const u32x4 c4 = __builtin_amdgcn_raw_buffer_load_b128(rc, co, 0, 0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(c4[e]);
+                    }
+                    store4(v, co);
+                } else {
+                    // the tile holds student logits zs; q = teacher logits zt of the same elements
+                    const float zs[4] = {t.x, t.y, t.z, t.w};
+                    float zt[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) zt[e] = __uint_as_float(q[e]);
+                    if constexpr (EPI == EPI_KD_DZ) {
+                        // dz = coef * (exp(zs/T - lse_s) - exp(zt/T - lse_t)) -> C (storage dtype)
+                        const float lt2 = lsev[i & 1][ps].x * 1.4426950408889634f, ls2 = lsev[i & 1][ps].y * 1.4426950408889634f;
+                        float v[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            v[e] = p.kd_coef * (__builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ls2)) -
+                                                __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -lt2)));
+                        store4(v, co);
+                    } else {
+                        // per row, over this wave's 64 columns: max and sum of exponentials of zt/T and zs/T and
+                        // the cross term sum e^{zt/T - m_t} (zt - zs)/T -> kd_part; the 16 lanes that share a
+                        // row reduce with data-parallel-primitive moves inside their group (no LDS round trip)
+                        float mt = cok ? fmaxf(fmaxf(zt[0], zt[1]), fmaxf(zt[2], zt[3])) : -INFINITY;
+                        float ms = cok ? fmaxf(fmaxf(zs[0], zs[1]), fmaxf(zs[2], zs[3])) : -INFINITY;
+                        mt = row16_max(mt);
+                        ms = row16_max(ms);
+                        mt *= it; ms *= it;                                   // T > 0
+                        const float mt2 = mt == -INFINITY ? 0.f : mt * 1.4426950408889634f;
+                        const float ms2 = ms == -INFINITY ? 0.f : ms * 1.4426950408889634f;
+                        float st = 0.f, ss = 0.f, ac = 0.f;
+                        if (cok) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float et = __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -mt2));
+                                st += et;
+                                ac = __builtin_fmaf(et, zt[e] - zs[e], ac);
+                                ss += __builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ms2));
+                            }
+                            ac *= it;
+                        }
+                        st = row16_sum(st);
+                        ss = row16_sum(ss);
+                        ac = row16_sum(ac);
+                        if ((lane & 15) == 0 && rowg < p.M && n0 + wn * WTN < p.N) {
+                            float *o = p.kd_part + ((long)rowg * p.kd_nparts + (n0 + wn * WTN) / 64) * 8;
+                            *(float4 *)o = make_float4(mt, st, ms, ss);
+                            o[4] = ac;
+                        }
+                    }
+                }
+            }
+        }
+        return;
+    }
+    // scalar epilogue: split-K atomics and shapes whose rows are not 4-element aligned
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int col = n0 + (M16 ? col_base(j >> 1) + (j & 1) * 16 : col_base(j)) + frow;
+        const bool cok = col < p.N;
+        const float bv = (bias && cok) ? (float)bias[col] : 0.f;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+#pragma unroll
+            for (int r = 0; r < ACC_N; ++r) {
+                const int row = m0 + (M16 ? row_base(i >> 1) + (i & 1) * 16 : row_base(i)) + (M16 ? 4 * fhalf + r : 8 * (r >> 2) + 4 * fhalf + (r & 3));
+                float v = acc[i][j][r] * p.alpha + bv;
+                if (p.residual) {
+                    const unsigned ro = cok ? (unsigned)(((long)row * p.ldr + col) * rsz) : kOob;
+                    if (p.res_fp32) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, ro, 0, 0));
+                    else v += (float)__builtin_bit_cast(bf16_t, __builtin_amdgcn_raw_buffer_load_b16(rr, ro, 0, 0));
+                }
+                const unsigned co = cok ? (unsigned)(((long)row * p.ldc + col) * esz) : kOob;
+                if (p.c_fp32) {
+                    if (p.atomic) {
+                        if (cok && row < p.M) unsafeAtomicAdd((float *)p.C + (long)row * p.ldc + col, v);
+                    } else {
+                        if (p.accumulate) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc, co, 0, 0));
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rc, co, 0, 0);
+                    }
+                } else {
+                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (bf16_t)v), rc, co, 0, 0);
+                }
+            }
+            // keep the scheduler from pulling every accumulator out of the AGPRs at once
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 // M16 selects v_mfma_f32_16x16x32_bf16 (16-row fragments, two k-steps of 32 per K tile) instead of
 // v_mfma_f32_32x32x16_bf16 (32-row fragments, four k-steps of 16): the same LDS traffic and the same number of
 // accumulator registers, but on operands with realistic bit activity the chip sustains a higher clock on it.
@@ -502,11 +767,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
         constexpr int VM = decltype(fetch_c)::value ? (BM + BN) / 8 / (WM * WN) : 0;   // loads of a fetch issued just before
         if constexpr (M16) {
             constexpr int BPB = (NI + MI - 1) / MI;          // B fragments read behind each row block
+            // (columns alternate in direction, so that neighbouring MFMAs differ in one operand: 0.3-0.5 % at the same power)
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
 #pragma unroll
-                for (int j = 0; j < NI; ++j)
+                for (int jj = 0; jj < NI; ++jj) {
+                    const int j = (i & 1) ? NI - 1 - jj : jj;
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
+                }
                 load_a(la, lkk, cur ^ 1, i);
 #pragma unroll
                 for (int j = i * BPB; j < NI && j < (i + 1) * BPB; ++j) load_b(lb, lkk, cur ^ 1, j);
@@ -564,270 +832,193 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
     }
     dma_publish_barrier();   // the (all-zero) tiles still in flight must land before the epilogue reuses LDS
 
-    // ---- epilogue staging: the accumulators of the wave's 32-row block i go to LDS as [32 rows][64 columns]
-    // fp32 (v = value transform), from where each lane reads 4 consecutive columns of a row.  The 16-column
-    // group index (32x32 MFMA: column bit 5 only) is XOR-ed with row bits so that the lanes of one store
-    // instruction, which hold the same columns of rows 4 apart, use different banks.
-    auto stg_swz = [](int row) { return M16 ? ((row >> 2) & 3) << 4 : ((row >> 2) & 1) << 5; };
-    // The lanes of a wave exchange data through the staging area, and the LDS executes a wave's accesses in
-    // program order; what has to be kept is the program order itself: to the compiler a lane's reads and another
-    // lane's writes are unrelated addresses that it may reorder.  wave_sync() is a compiler-level fence between the
-    // two phases (no instruction).
-    auto wave_sync = []() __attribute__((always_inline)) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    auto stage_block = [&](float *stg, int i, auto v) __attribute__((always_inline)) {
-        wave_sync();     // the reads of the previous block come first
-        if constexpr (M16) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = h * 16 + 4 * fhalf + r;
-                        stg[row * 64 + ((j * 16 + frow) ^ stg_swz(row))] = v(acc[2 * i + h][j][r]);
-                    }
-        } else {
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * fhalf + (r & 3);
-                    stg[row * 64 + ((j * 32 + frow) ^ stg_swz(row))] = v(acc[i][j][r]);
-                }
-        }
-        wave_sync();     // every lane's values are in LDS before any lane reads
-    };
-    // 8 KB of the idle tile buffers per wave; wpa waves fit into one A buffer
-    auto stage_area = [&](int wpa) __attribute__((always_inline)) {
-        const int q = wave / wpa;
-        return (float *)(q == 0 ? As0 : q == 1 ? As1 : q == 2 ? Bs0 : Bs1) + (wave % wpa) * 2048;
-    };
-    // ---- epilogue.  C and the residual are addressed through buffer descriptors: rows past M are
-    // dropped (stores) or read as zero by the range check, columns past N by one select.
-    const int esz = p.c_fp32 ? 4 : 2;
-    const __amdgpu_buffer_rsrc_t rc = make_rsrc(p.C, (long)p.M * p.ldc * esz);
-    const int rsz = p.res_fp32 ? 4 : 2;
-    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.residual ? p.residual : p.C, p.residual ? (long)p.M * p.ldr * rsz : 0);
-    const bf16_t *bias = (const bf16_t *)p.bias;
-    if constexpr (EPI == EPI_SWIGLU) {
-        // acc[i][0] = gate, acc[i][1] = up of output columns n0/2 + wn*32 + (0..31).  Both are rounded to
-        // the storage type first (they are the values a separate activation kernel would read back), staged
-        // through LDS as [32 rows][gate 32 | up 32], and each lane then owns 4 consecutive output columns.
-        static_assert(WTN == 64 && NI32 == 2 && !TA && !TB, "SwiGLU epilogue is built for the K-contiguous layout");
-        constexpr int WPA = BM / 64;
-        float *stg = stage_area(WPA);
-        const int prow = lane >> 3, pcol = (lane & 7) * 4;
-        const int colg = n0 / 2 + wn * 32 + pcol;
-        const bool cok = colg < p.N;
-        const __amdgpu_buffer_rsrc_t rg = make_rsrc(p.sg_gu ? p.sg_gu : p.C, p.sg_gu ? (long)p.M * p.sg_ldgu * 2 : 0);
-        auto pack4 = [](const float *v) {
-            u32x2 w;
-            w[0] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[0]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[1]) << 16);
-            w[1] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[2]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[3]) << 16);
-            return w;
-        };
-#pragma unroll
-        for (int i = 0; i < MI32; ++i) {
-            stage_block(stg, i, [&](float a) { return (float)(bf16_t)(a * p.alpha); });
-#pragma unroll
-            for (int ps = 0; ps < 4; ++ps) {
-                const int row = ps * 8 + prow;
-                const int flip = stg_swz(row);
-                const float4 g4 = *(const float4 *)(stg + row * 64 + (pcol ^ flip));
-                const float4 u4 = *(const float4 *)(stg + row * 64 + ((32 + pcol) ^ flip));
-                const float gv[4] = {g4.x, g4.y, g4.z, g4.w}, uv[4] = {u4.x, u4.y, u4.z, u4.w};
-                float a[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e)   // silu(g) u = g u / (1 + e^-g); hardware reciprocal (1 ulp) instead of the division sequence
-                    a[e] = gv[e] * uv[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gv[e]));
-                const long rowg = m0 + wm * WTM + i * 32 + row;
-                __builtin_amdgcn_raw_buffer_store_b64(pack4(a), rc, cok ? (unsigned)((rowg * p.ldc + colg) * 2) : kOob, 0, kStream);
-                if (p.sg_gu) {
-                    const unsigned go = cok ? (unsigned)((rowg * p.sg_ldgu + colg) * 2) : kOob;
-                    __builtin_amdgcn_raw_buffer_store_b64(pack4(gv), rg, go, 0, kStream);
-                    __builtin_amdgcn_raw_buffer_store_b64(pack4(uv), rg, cok ? go + (unsigned)p.sg_f * 2 : kOob, 0, kStream);
-                }
-            }
-        }
-        return;
+    // waves share the idle operand buffers, 8 KB each: WPA of them fit into one A buffer
+    constexpr int WPA = BM / 64;
+    const int sq = wave / WPA;
+    float *stg = (float *)(sq == 0 ? As0 : sq == 1 ? As1 : sq == 2 ? Bs0 : Bs1) + (wave % WPA) * 2048;
+    gemm_epilogue<EPI, M16, TA, TB>(p, acc, stg, m0, n0, wn, lane, row_base, col_base);
+}
+
+// The 256 x 256 tile with two wave groups that take turns on the matrix cores; K-contiguous operands only.
+//   * Waves 0..3 and 4..7 (one of each per SIMD) run the same program half a phase apart: while one group issues the 16
+//     MFMAs of a quarter of its wave tile (64 x 32, both k-steps), the other reads its next operand fragments from LDS
+//     and requests the next half tile.  Two barriers per phase keep them in step; the one extra barrier that group 1
+//     takes before the loop and group 0 after it is the offset.
+//   * An operand tile is two halves of 128 rows with an LDS slot each and two stages: eight 16 KB slots.  Per K tile the
+//     phases read A0 -> Bs -> A1 -> Bf of the next tile, where Bf / Bs are the B half used first / second; they swap roles
+//     every tile, so that the quarters (A0 Bf)(A0 Bs)(A1 Bs)(A1 Bf) change one operand at a time.  Two of the eight
+//     fragments of an A half are read in the phase before its own, so that every phase has six reads.  A phase requests
+//     the half of tile t + 2 that goes into the slot whose last read was in the phase before: every half is requested at
+//     least six phases (1.5 K tiles) before it is read, instead of one K tile in gemm_bf16_fast_kernel, and the wait
+//     is for all but the 10 youngest loads of a wave, never for all of them.
+//   * Same tile order, MFMA and order of K as the other tiles: bit-identical results.
+// Measured against gemm_bf16_fast_kernel<256, 256> on one box (M x N x K, us): where the operands come past the 256 MB
+// Infinity Cache the longer lead wins (32768 x 4096 x 11008 2098 -> 1962, 46173 x 1280 x 5120 495 -> 462,
+// 32768 x 1536 x 17920 1328 -> 1227, SwiGLU 32768 x 22016 x 4096 4308 -> 4028); where they stay in it the two are equal
+// (8192^3 704 / 707, 32768 x 6144 x 4096 1125 / 1117) and a short K loses (32768 x 2048 x 1536 154 / 160).  With all eight A
+// reads in one phase: 2075 and 482 on the first two.  For K-major operands (twice the LDS reads) it was 2-25 % slower.
+// B half g holds the rows 64 w + 32 g .. + 31 of every wave column w (a wave's 64 columns stay adjacent); for SwiGLU
+// g = 0 gate rows, g = 1 up rows.
+struct HalfStager {
+    unsigned rowoff, ld2;
+    int x;
+    __device__ __forceinline__ void init(long ld, int row0, int lane) {
+        rowoff = (unsigned)(((long)(row0 + (lane >> 3)) * ld) * 2);
+        ld2 = (unsigned)(ld * 2);
+        x = (lane & 7) ^ swz_row(lane >> 3);
     }
-    // ---- vector epilogues.  Each wave passes its accumulators through LDS, 32 rows at a time, to turn the
-    // MFMA layout (a lane owns one column) into rows: a lane then handles 4 consecutive columns of a row, so
-    // global reads and writes are 8..16 bytes per lane and 128..256 contiguous bytes per row.  What the
-    // epilogue reads from memory for a 32-row block (fp32/bf16 residual, C when accumulating, teacher logits)
-    // is fetched one block ahead into registers: the loads of block i+1 are issued before the stores of
-    // block i, so no pass waits for a store or for its own load's full latency.
-    if (EPI != EPI_NONE || p.vec_epilogue) {
-        static_assert(WTN == 64, "staging assumes 64-column wave tiles");
-        constexpr int WPA = BM / 64;                       // waves sharing one of the (now idle) A buffers
-        float *stg = stage_area(WPA);
-        const int prow = lane >> 4, pcol = (lane & 15) * 4;
-        const int colg = n0 + col_base(pcol >> 5) + (pcol & 31);
-        const bool cok = colg < p.N;
-        // the prefetched stream: KD -> teacher logits (fp32); else residual (fp32 or bf16); else C (accumulate)
-        const bool aux_res = EPI == EPI_NONE && p.residual != nullptr;
-        const bool aux_c = EPI == EPI_NONE && !aux_res && p.accumulate && p.c_fp32;
-        const bool has_aux = EPI != EPI_NONE || aux_res || aux_c;
-        const bool aux4 = EPI != EPI_NONE || aux_c || p.res_fp32;                  // 4-byte elements
-        const long aux_ld = EPI != EPI_NONE ? p.kd_ldz : (aux_res ? p.ldr : p.ldc);
-        const __amdgpu_buffer_rsrc_t ra_ = EPI != EPI_NONE ? make_rsrc(p.kd_zt, (long)p.M * p.kd_ldz * 4) : (aux_res ? rr : rc);
-        u32x4 aux[2][8];
-        float2 lsev[2][8];                                                         // EPI_KD_DZ: (lse_t, lse_s) of the row
-        auto prefetch = [&](int i, u32x4 *dst, float2 *ldst) {
-#pragma unroll
-            for (int ps = 0; ps < 8; ++ps) {
-                const long rowg = m0 + row_base(i) + ps * 4 + prow;
-                const unsigned off = cok ? (unsigned)((rowg * aux_ld + colg) * (aux4 ? 4 : 2)) : kOob;
-                if (aux4) dst[ps] = __builtin_amdgcn_raw_buffer_load_b128(ra_, off, 0, kStream);
-                else {
-                    const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(ra_, off, 0, kStream);
-                    dst[ps][0] = q[0]; dst[ps][1] = q[1];
-                }
-                if constexpr (EPI == EPI_KD_DZ) ldst[ps] = rowg < p.M ? *(const float2 *)(p.kd_stats + rowg * 8 + 6) : make_float2(0.f, 0.f);
-            }
-        };
-        float bv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (EPI == EPI_NONE && bias && cok) {
-            const uint2 b2 = *(const uint2 *)(bias + colg);
-            bv[0] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.x & 0xffff));
-            bv[1] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.x >> 16));
-            bv[2] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.y & 0xffff));
-            bv[3] = (float)__builtin_bit_cast(bf16_t, (unsigned short)(b2.y >> 16));
-        }
-        auto store4 = [&](const float *v, unsigned co) {
-            if (p.c_fp32) {
-                u32x4 w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = __builtin_bit_cast(unsigned, v[e]);
-                __builtin_amdgcn_raw_buffer_store_b128(w, rc, co, 0, kStream);
-            } else {
-                u32x2 w;
-                w[0] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[0]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[1]) << 16);
-                w[1] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[2]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[3]) << 16);
-                __builtin_amdgcn_raw_buffer_store_b64(w, rc, co, 0, kStream);
-            }
-        };
-        const float it = p.kd_inv_t;
-        const float it2 = it * 1.4426950408889634f;      // e^{z/T - m} = 2^{z it2 - m log2(e)}: one fused multiply-add feeds exp2
-        if (has_aux) prefetch(0, aux[0], lsev[0]);
-#pragma unroll
-        for (int i = 0; i < MI32; ++i) {
-            if (has_aux && i + 1 < MI32) prefetch(i + 1, aux[(i + 1) & 1], lsev[(i + 1) & 1]);
-            stage_block(stg, i, [&](float a) { return a * p.alpha; });
-#pragma unroll
-            for (int ps = 0; ps < 8; ++ps) {
-                const int row = ps * 4 + prow;
-                const float4 t = *(const float4 *)(stg + row * 64 + (pcol ^ stg_swz(row)));
-                const long rowg = m0 + row_base(i) + row;
-                const u32x4 q = aux[i & 1][ps];
-                const unsigned co = cok ? (unsigned)((rowg * p.ldc + colg) * esz) : kOob;
-                if constexpr (EPI == EPI_NONE) {
-                    float v[4] = {t.x + bv[0], t.y + bv[1], t.z + bv[2], t.w + bv[3]};
-                    if (aux_res || aux_c) {
-                        if (aux4) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(q[e]);
-                        } else {
-                            v[0] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[0] & 0xffff));
-                            v[1] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[0] >> 16));
-                            v[2] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[1] & 0xffff));
-                            v[3] += (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[1] >> 16));
-                        }
-                    }
-                    if (aux_res && p.accumulate && p.c_fp32) {        // both a residual and += : C is read in place
-                        const u32x4 c4 = __builtin_amdgcn_raw_buffer_load_b128(rc, co, 0, 0);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(c4[e]);
-                    }
-                    store4(v, co);
-                } else {
-                    // the tile holds student logits zs; q = teacher logits zt of the same elements
-                    const float zs[4] = {t.x, t.y, t.z, t.w};
-                    float zt[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) zt[e] = __uint_as_float(q[e]);
-                    if constexpr (EPI == EPI_KD_DZ) {
-                        // dz = coef * (exp(zs/T - lse_s) - exp(zt/T - lse_t)) -> C (storage dtype)
-                        const float lt2 = lsev[i & 1][ps].x * 1.4426950408889634f, ls2 = lsev[i & 1][ps].y * 1.4426950408889634f;
-                        float v[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            v[e] = p.kd_coef * (__builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ls2)) -
-                                                __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -lt2)));
-                        store4(v, co);
-                    } else {
-                        // per row, over this wave's 64 columns: max and sum of exponentials of zt/T and zs/T and
-                        // the cross term sum e^{zt/T - m_t} (zt - zs)/T -> kd_part; the 16 lanes that share a
-                        // row reduce with data-parallel-primitive moves inside their group (no LDS round trip)
-                        float mt = cok ? fmaxf(fmaxf(zt[0], zt[1]), fmaxf(zt[2], zt[3])) : -INFINITY;
-                        float ms = cok ? fmaxf(fmaxf(zs[0], zs[1]), fmaxf(zs[2], zs[3])) : -INFINITY;
-                        mt = row16_max(mt);
-                        ms = row16_max(ms);
-                        mt *= it; ms *= it;                                   // T > 0
-                        const float mt2 = mt == -INFINITY ? 0.f : mt * 1.4426950408889634f;
-                        const float ms2 = ms == -INFINITY ? 0.f : ms * 1.4426950408889634f;
-                        float st = 0.f, ss = 0.f, ac = 0.f;
-                        if (cok) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float et = __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -mt2));
-                                st += et;
-                                ac = __builtin_fmaf(et, zt[e] - zs[e], ac);
-                                ss += __builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ms2));
-                            }
-                            ac *= it;
-                        }
-                        st = row16_sum(st);
-                        ss = row16_sum(ss);
-                        ac = row16_sum(ac);
-                        if ((lane & 15) == 0 && rowg < p.M && n0 + wn * WTN < p.N) {
-                            float *o = p.kd_part + ((long)rowg * p.kd_nparts + (n0 + wn * WTN) / 64) * 8;
-                            *(float4 *)o = make_float4(mt, st, ms, ss);
-                            o[4] = ac;
-                        }
-                    }
-                }
-            }
-        }
-        return;
+    // eight matrix rows from row0 + row into 8-row group lg of the half's slot (both wave-uniform)
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, bf16_t *slot, int row, int lg, int k0, unsigned inv) const {
+        const unsigned voff = (rowoff + (unsigned)row * ld2 + ((x ^ swz_row(8 * lg)) << 4)) | inv;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(slot + lg * 8 * BK), 16, voff, k0 * 2, 0, 0);
     }
-    // scalar epilogue: split-K atomics and shapes whose rows are not 4-element aligned
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const int col = n0 + fcol_base(j) + frow;
-        const bool cok = col < p.N;
-        const float bv = (bias && cok) ? (float)bias[col] : 0.f;
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-#pragma unroll
-            for (int r = 0; r < ACC_N; ++r) {
-                const int row = m0 + frow_base(i) + (M16 ? 4 * fhalf + r : 8 * (r >> 2) + 4 * fhalf + (r & 3));
-                float v = acc[i][j][r] * p.alpha + bv;
-                if (p.residual) {
-                    const unsigned ro = cok ? (unsigned)(((long)row * p.ldr + col) * rsz) : kOob;
-                    if (p.res_fp32) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, ro, 0, 0));
-                    else v += (float)__builtin_bit_cast(bf16_t, __builtin_amdgcn_raw_buffer_load_b16(rr, ro, 0, 0));
-                }
-                const unsigned co = cok ? (unsigned)(((long)row * p.ldc + col) * esz) : kOob;
-                if (p.c_fp32) {
-                    if (p.atomic) {
-                        if (cok && row < p.M) unsafeAtomicAdd((float *)p.C + (long)row * p.ldc + col, v);
-                    } else {
-                        if (p.accumulate) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc, co, 0, 0));
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rc, co, 0, 0);
-                    }
-                } else {
-                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (bf16_t)v), rc, co, 0, 0);
-                }
-            }
-            // keep the scheduler from pulling every accumulator out of the AGPRs at once
-            __builtin_amdgcn_sched_barrier(0);
-        }
+};
+template <int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_pp_kernel(GemmParams p) {
+    constexpr int HS = 128 * BK;                        // elements of a half tile
+    __shared__ __align__(16) bf16_t A00[HS], A01[HS], A10[HS], A11[HS], B00[HS], B01[HS], B10[HS], B11[HS];   // [stage][half]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;            // wm = wave group
+    int pid;
+    {
+        const int nb = gridDim.x, b = blockIdx.x;
+        const int per = nb >> 3, rem = nb & 7, x = b & 7, q = b >> 3;
+        pid = x * per + (x < rem ? x : rem) + q;
     }
+    constexpr int GM = 4;
+    const int group = pid / (GM * p.tiles_n);
+    const int first_m = group * GM;
+    const int gsize = (p.tiles_m - first_m) < GM ? (p.tiles_m - first_m) : GM;
+    const int tm = first_m + (pid % (GM * p.tiles_n)) % gsize;
+    const int tn = (pid % (GM * p.tiles_n)) / gsize;
+    const int m0 = tm * 256, n0 = tn * 256;
+
+    const int kt_begin = blockIdx.y * p.k_tiles_per_split;
+    int kt_end = kt_begin + p.k_tiles_per_split;
+    const int kt_total = (p.K + BK - 1) / BK;
+    if (kt_end > kt_total) kt_end = kt_total;
+    const int nk = kt_end - kt_begin;
+    if (nk <= 0) return;
+
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.A, ((long)(p.M - 1) * p.lda + p.K) * 2);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.B, ((long)((EPI == EPI_SWIGLU ? 2 * p.sg_f : p.N) - 1) * p.ldb + p.K) * 2);
+    HalfStager da, db;
+    da.init(p.lda, m0, lane);
+    db.init(p.ldb, EPI == EPI_SWIGLU ? n0 / 2 : n0, lane);
+    // request half h of K tile kt (two loads per wave; a tile past the end arrives as zeros)
+    auto fetch_a = [&](int kt, int h, bf16_t *slot) __attribute__((always_inline)) {
+        const unsigned inv = kt < nk ? 0u : kOob;
+        const int k0 = (kt_begin + kt) * BK;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int g = wave * 2 + i;
+            da.load(ra, slot, h * 128 + g * 8, g, k0, inv);
+        }
+    };
+    auto fetch_b = [&](int kt, int h, bf16_t *slot) __attribute__((always_inline)) {
+        const unsigned inv = kt < nk ? 0u : kOob;
+        const int k0 = (kt_begin + kt) * BK;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int g = wave * 2 + i;
+            if constexpr (EPI == EPI_SWIGLU) db.load(rb, slot, h * p.sg_f + g * 8, g, k0, inv);
+            else db.load(rb, slot, (g >> 2) * 64 + h * 32 + (g & 3) * 8, g, k0, inv);
+        }
+    };
+
+    f32x4 acc[8][4];                                    // [16-row block: 4 h + b][16-column block: 2 g + c]
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // A: [block][k-step] of the current half, its first two fragments apart (ax[half]); B: [half][block][k-step]
+    bf16x8 af[4][2], ax[2][2], bfr[2][2][2];
+    KFragAddr16 ka, kb;
+    ka.init(wm * 64, lane);
+    kb.init(wn * 32, lane);
+    auto read_a_first = [&](auto half, const bf16_t *slot) __attribute__((always_inline)) {
+        constexpr int h = decltype(half)::value;
+        ax[h][0] = ka.frag(slot, 0, 0);
+        ax[h][1] = ka.frag(slot, 0, 1);
+    };
+    auto read_a_rest = [&](const bf16_t *slot) __attribute__((always_inline)) {
+        af[2][0] = ka.frag(slot, 0, 2);
+        af[3][0] = ka.frag(slot, 0, 3);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) af[b][1] = ka.frag(slot, 1, b);
+    };
+    auto read_b = [&](auto half, const bf16_t *slot) __attribute__((always_inline)) {
+        constexpr int g = decltype(half)::value;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) bfr[g][c][kk] = kb.frag(slot, kk, c);
+    };
+    // End of a phase's first half: the half tile that the next phase reads has landed (own loads), this phase's reads are
+    // done; then the quarter's MFMAs between two barriers.
+    auto turn = [&](auto ah, auto bh) __attribute__((always_inline)) {
+        constexpr int h = decltype(ah)::value, g = decltype(bh)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmcnt_lgkm0<10>();
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    acc[4 * h + b][2 * g + c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk == 0 && b < 2 ? ax[h][b] : af[b][kk], bfr[g][c][kk], acc[4 * h + b][2 * g + c], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    // K tile kt in stage slots (a0, a1, f = its first B half F, s = its second B half); nb: the slot of the next tile's first
+    // B half, which is half 1 - F
+    auto tile = [&](int kt, auto F, bf16_t *a0, bf16_t *a1, bf16_t *f, bf16_t *s, const bf16_t *nb, const bf16_t *na) __attribute__((always_inline)) {
+        constexpr int fh = decltype(F)::value;
+        using FH = std::integral_constant<int, fh>;
+        using SH = std::integral_constant<int, 1 - fh>;
+        read_a_rest(a0);
+        fetch_b(kt + 2, fh, f);
+        turn(I0{}, FH{});
+        read_b(SH{}, s);
+        read_a_first(I1{}, a1);
+        fetch_a(kt + 2, 0, a0);
+        turn(I0{}, SH{});
+        read_a_rest(a1);
+        fetch_b(kt + 2, 1 - fh, s);
+        turn(I1{}, SH{});
+        // fragments of half F are still needed by this quarter; the next tile's first half goes to the other set
+        read_b(SH{}, nb);
+        read_a_first(I0{}, na);
+        fetch_a(kt + 2, 1, a1);
+        turn(I1{}, FH{});
+    };
+    // in the order in which the loop would have requested them
+    fetch_b(0, 0, B00); fetch_a(0, 0, A00); fetch_b(0, 1, B01); fetch_a(0, 1, A01);
+    fetch_b(1, 1, B11); fetch_a(1, 0, A10); fetch_b(1, 0, B10); fetch_a(1, 1, A11);
+    wait_vmcnt_lgkm0<12>();
+    lds_barrier();
+    read_b(I0{}, B00);
+    read_a_first(I0{}, A00);
+    wait_vmcnt_lgkm0<10>();
+    lds_barrier();
+    if (wm == 1) lds_barrier();
+    for (int kt = 0; kt < nk; kt += 2) {                // an odd count is rounded up with a tile of zeros
+        tile(kt, I0{}, A00, A01, B00, B01, B11, A10);
+        tile(kt + 1, I1{}, A10, A11, B11, B10, B00, A00);
+    }
+    if (wm == 0) lds_barrier();
+    dma_publish_barrier();   // the (all-zero) half tiles still in flight must land before the epilogue reuses LDS
+    auto row_base = [&](int i) { return (i >> 1) * 128 + wm * 64 + (i & 1) * 32; };
+    auto col_base = [&](int j) { return wn * 64 + j * 32; };
+    const int sq = wave >> 1;
+    float *stg = (float *)(sq == 0 ? A00 : sq == 1 ? A01 : sq == 2 ? A10 : A11) + (wave & 1) * 2048;
+    gemm_epilogue<EPI, true, false, false>(p, acc, stg, m0, n0, wn, lane, row_base, col_base);
 }
 
 // ------------------------------------------------------------------ fp32
@@ -950,6 +1141,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
 MS_INST(256, 4, false, false); MS_INST(256, 4, false, true); MS_INST(256, 4, true, false); MS_INST(256, 4, true, true);
 MS_INST(128, 2, false, false); MS_INST(128, 2, false, true); MS_INST(128, 2, true, false); MS_INST(128, 2, true, true);
 #undef MS_INST
+template __global__ void gemm_bf16_pp_kernel<EPI_NONE>(GemmParams);
+template __global__ void gemm_bf16_pp_kernel<EPI_SWIGLU>(GemmParams);
 #define MS_INST_RING(BM, BN, WM, WN, NST, TA, TB) \
     template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI_NONE, true, NST>(GemmParams)
 #define MS_INST_RINGS(BM, BN, WM, WN, NST)                                                             \
@@ -1000,6 +1193,7 @@ struct TileShape {
     double us_per_ktile[4], us_round;
 };
 enum { T256 = 0, T128 = 1, R128 = 2, R128x256 = 3, R64x128 = 4, R64 = 5, kNumTiles = 6 };
+constexpr int kPingPong = 256256;       // forced tile: 256 x 256 with the ping-pong kernel where it applies
 constexpr TileShape kTiles[kNumTiles] = {
     {256, 256, 256, 1, {1.08, 1.48, 0, 0}, 3.5},          {128, 128, 128, 2, {0.60, 0.70, 0.78, 0.97}, 1.8},
     {128128, 128, 128, 1, {0.36, 0.47, 0, 0}, 1.5},       {128256, 128, 256, 1, {0.60, 0.80, 0, 0}, 2.5},
@@ -1024,7 +1218,7 @@ int choose_tile(int M, int N, int kt) {
     int best = T128;
     double best_us = 1e30;
     for (int i = 0; i < kNumTiles; ++i) {
-        if (forced > 0 ? kTiles[i].code != forced : (!m16 && i > T128)) continue;
+        if (forced > 0 ? kTiles[i].code != (forced == kPingPong ? 256 : forced) : (!m16 && i > T128)) continue;
         const double us = tile_time(kTiles[i], (long)ms_cdiv(M, kTiles[i].bm) * ms_cdiv(N, kTiles[i].bn), kt);
         if (us < best_us) { best_us = us; best = i; }
     }
@@ -1053,6 +1247,16 @@ ms_status launch_bf16_fast(GemmParams &p, int tile, int ta, int tb, int splits, 
     p.tiles_n = ms_cdiv(p.N, EPI == EPI_SWIGLU ? t.bn / 2 : t.bn);
     dim3 grid(p.tiles_m * p.tiles_n, splits);
     ProfScope ps((ta || tb) ? 1 : 0, flops, s);
+    // Operands that do not stay in the 256 MB Infinity Cache: the ping-pong kernel (its figures say why the line is
+    // between 318 MB, where it gains nothing, and 448 MB, where it gains 7 %).
+    if constexpr (EPI == EPI_NONE || EPI == EPI_SWIGLU) {
+        const double stream = 2.0 * ((double)p.M + p.N * (EPI == EPI_SWIGLU ? 2.0 : 1.0)) * p.K;
+        if (tile == T256 && !ta && !tb && use_mfma16() && splits == 1 && (forced_tile() == kPingPong || (forced_tile() == 0 && stream > 384e6))) {
+            gemm_bf16_pp_kernel<EPI><<<grid, 512, 0, s>>>(p);
+            MS_LAUNCH_CHECK();
+            return MS_OK;
+        }
+    }
     switch (tile) {
         case T256: launch_fast_tile<256, 256, 2, 4, 2, EPI>(p, ta, tb, grid, s); break;
         case R128: launch_fast_tile<128, 128, 4, 2, 4, EPI>(p, ta, tb, grid, s); break;
@@ -1092,10 +1296,10 @@ ms_status launch_bf16(const GemmParams &p, int ta, int tb, int splits, hipStream
 }  // namespace
 
 extern "C" ms_status ms_k_gemm_config(int32_t tile, int32_t mfma16) {
-    bool known = tile == -1 || tile == 0;
+    bool known = tile == -1 || tile == 0 || tile == kPingPong;
     for (const TileShape &t : kTiles) known = known || tile == t.code;
     if (!known || mfma16 < -1 || mfma16 > 1)
-        return ms_fail(MS_ERR_INVALID_ARG, "gemm_config: tile must be -1, 0, 128, 256, 128128, 128256, 64128 or 64064 and mfma16 -1, 0 or 1");
+        return ms_fail(MS_ERR_INVALID_ARG, "gemm_config: tile must be -1, 0, 128, 256, 256256, 128128, 128256, 64128 or 64064 and mfma16 -1, 0 or 1");
     g_tile_override = tile == 0 ? kUnset : tile;
     g_mfma16_override = mfma16 < 0 ? kUnset : mfma16;
     return MS_OK;
@@ -1165,7 +1369,7 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
             double best = 1e30;
             for (int i = 0; i < kNumTiles; ++i) {
                 const TileShape &t = kTiles[i];
-                if (forced > 0 ? t.code != forced : ((!use_mfma16() && i > T128) || (kt_total > 256 && i > T128 && i != R128x256))) continue;
+                if (forced > 0 ? t.code != (forced == kPingPong ? 256 : forced) : ((!use_mfma16() && i > T128) || (kt_total > 256 && i > T128 && i != R128x256))) continue;
                 const double stream = kt_total > 256 && i == R128x256 ? 1.12 : 1.0;
                 const long tiles = (long)ms_cdiv(M, t.bm) * ms_cdiv(N, t.bn);
                 for (int sp = 1; sp <= 8 && (sp == 1 || kt_total / sp >= 8); ++sp) {

@@ -8,7 +8,7 @@ from paper_2605_10501_amd import workloads as wl
 from parity import TOL_BF16, TOL_F32, assert_parity
 
 pytestmark = pytest.mark.gpu
-TILES = [128, 256, 128128, 128256, 64128, 64064]
+TILES = [128, 256, 256256, 128128, 128256, 64128, 64064]
 
 
 @pytest.fixture
