@@ -277,14 +277,17 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t *__restric
 // accumulator tiles with one query per lane, so P = exp2(S^T c - lse[q]) and
 // dS^T = P (dP^T - delta[q]) use per-lane scalars, and dS^T is the B operand of dQ^T += K^T dS^T
 // with K^T read from the row-major K tile through the transposing LDS load.
-template <int HD, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
+// KS = 2 (grids that leave CUs without a workgroup; see launch_bwd): the workgroup owns 64 queries, waves 0 and 1 visit
+// the even key tiles, waves 2 and 3 the odd ones for the same queries, and the two partial sums meet in LDS: twice the
+// workgroups, half the serial chain.
+template <int HD, bool CAUSAL, int KS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 - KS))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
                                                                 const float2 *__restrict__ ld2,
                                                                 bf16_t *__restrict__ dqkv, const int *__restrict__ cu, int n,
                                                                 int nq, int nkv, int n_seqs, int ntile_max, float scale) {
     using D = AttnDims<HD>;
-    constexpr int BQ = 128, BKV = 64, TS = D::NKS * 4096;
-    __shared__ __align__(16) bf16_t K0[TS], K1[TS], V0[TS], V1[TS];
+    constexpr int BQ = 128 / KS, BKV = 64, TS = D::NKS * 4096;
+    __shared__ __align__(16) bf16_t K0[KS * TS], K1[KS * TS], V0[KS * TS], V1[KS * TS];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -296,7 +299,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (qt * BQ >= s1 - s0) return;
     const int g = h / (nq / nkv);
     const long ld = (long)(nq + 2 * nkv) * HD;
-    const int q0 = s0 + qt * BQ + wave * 32;
+    const int part = KS == 2 ? wave >> 1 : 0;               // which of the KS tiles of a step this wave visits
+    const int q0 = s0 + qt * BQ + (KS == 2 ? wave & 1 : wave) * 32;
     const int kv_end = CAUSAL ? (s0 + (qt + 1) * BQ < s1 ? s0 + (qt + 1) * BQ : s1) : s1;
     const int nkt = (kv_end - s0 + BKV - 1) / BKV;
     const int kcol = (nq + g) * HD, vcol = (nq + nkv + g) * HD;
@@ -323,17 +327,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const float2 row = qok ? ld2[(long)h * n + q] : make_float2(0.f, 0.f);   // (lse * log2(e), delta)
     const float lse2 = row.x, dlt = row.y;
 
-    // (waves 0 and 1 fill the K tile, waves 2 and 3 the V tile; the lane's part of the addresses is computed once)
-    constexpr int PER = 4 * D::NKS;
+    // (one half of the waves fills K tiles, the other V tiles; the lane's part of the addresses is computed once)
+    constexpr int PER = 4 * D::NKS * KS;
     RowTileLane dl;
     dl.init(lane, (unsigned)(ld * 2));
-    const bool fill_v = wave >= 2;
+    const bool fill_v = KS == 2 ? (wave & 1) != 0 : wave >= 2;
+    const int fill0 = KS == 2 ? 0 : (wave & 1) * PER;       // first of this wave's loads of its tile
     const unsigned dcol = (unsigned)(fill_v ? vcol : kcol) * 2;
     auto issue = [&](int j, bf16_t *kt, bf16_t *vt) {
         const unsigned base = (unsigned)((long)(s0 + j * BKV) * ld * 2) + dcol;
         bf16_t *t = fill_v ? vt : kt;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), (wave & 1) * PER + i, dl);
+        for (int i = 0; i < PER; ++i) rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), fill0 + i, dl, j < nkt ? 0u : kOob);
     };
     // The same loads in KST portions, placed between the MFMAs of the S product of the tile before: a direct-to-LDS
     // load occupies the wave's issue slot for tens of cycles, which the MFMAs already queued cover.  A tile past the
@@ -344,7 +349,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         bf16_t *t = fill_v ? vt : kt;
 #pragma unroll
         for (int i = ks * PER / D::KST; i < (ks + 1) * PER / D::KST; ++i)
-            rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), (wave & 1) * PER + i, dl, inv);
+            rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), fill0 + i, dl, inv);
     };
 
     f32x16 dq[D::DB];
@@ -365,7 +370,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const int off = (ks / 4) * 4096 + lds_off(kb * 32 + lrow, (ks % 4) * 2 + half);
                 st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(kt + off), qf[ks], st, 0, 0, 0);
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(vt + off), dof[ks], dp, 0, 0, 0);
-                if (kb == 0) issue_part(ks, j + 1, kn, vn);
+                if (kb == 0) issue_part(ks, j + KS, kn, vn);
             }
             // rows past the end of the sequence have zero Q, dO, lse and delta (dS = 0 there without a mask)
             const int kfirst = s0 + j * BKV + kb * 32;
@@ -391,13 +396,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
     };
 
-    issue(0, K0, V0);
+    bf16_t *const k0 = K0 + part * TS, *const k1 = K1 + part * TS, *const v0 = V0 + part * TS, *const v1 = V1 + part * TS;
+    issue(part, k0, v0);
     dma_publish_barrier();
-    for (int j = 0; j < nkt; j += 2) {
-        compute(j, K0, V0, K1, V1);
+    for (int j = 0; j < nkt; j += 2 * KS) {
+        compute(j + part, k0, v0, k1, v1);
         dma_publish_barrier();
-        if (j + 1 < nkt) compute(j + 1, K1, V1, K0, V0);
+        if (j + KS < nkt) compute(j + KS + part, k1, v1, k0, v0);
         dma_publish_barrier();
+    }
+    if constexpr (KS == 2) {
+        // waves 2 and 3 hand their sums to waves 0 and 1 (same queries, same lanes) through the idle tile buffers
+        float *x = (float *)((wave & 1) ? V0 : K0);         // KS * TS bf16 = 16 * DB or more floats per lane
+        static_assert(KS * TS / 2 >= 64 * 16 * D::DB, "a wave's sums fit into one buffer");
+        if (part == 1)
+#pragma unroll
+            for (int i = 0; i < D::DB; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 64 + lane] = dq[i][r];
+        __syncthreads();
+        if (part == 1) return;
+#pragma unroll
+        for (int i = 0; i < D::DB; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dq[i][r] += x[(i * 16 + r) * 64 + lane];
     }
     if (!qok) return;
     bf16_t *op = dqkv + (long)q * ld + (long)h * HD;
@@ -435,13 +457,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // better than one.  (NW = 4 with NST = 3 needs 80.75 KB of LDS for head_dim 128, 768 bytes too many for two per CU.)
 // !SPLIT: the sums over the query group stay in registers, no atomics.
 // SPLIT: one workgroup per query head of the group instead of one per K/V head (4x the workgroups and a 4x
-// shorter longest one under grouped-query attention); partial dK/dV are then summed with fp32 atomics
-// into dkv_acc [n][2][nkv * HD], which attn_dkv_store_kernel rounds into dqkv afterwards.
+// shorter longest one under grouped-query attention), and of that one per `chunk` query tiles where the grid would
+// leave CUs idle (see launch_bwd); partial dK/dV are then summed with fp32 atomics into dkv_acc [n][2][nkv * HD],
+// which attn_dkv_store_kernel rounds into dqkv afterwards.
 template <int HD, bool CAUSAL, bool SPLIT, int NW, int NST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_mfma_kernel(
     const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o, const float2 *__restrict__ ld2,
     bf16_t *__restrict__ dqkv, float *__restrict__ dkv_acc, const int *__restrict__ cu, int n, int nq, int nkv, int n_seqs,
-    int nblk_max, float scale) {
+    int nblk_max, float scale, int chunk, unsigned blocks) {
     using D = AttnDims<HD>;
     static_assert(NST >= 2 && NST <= 4 && (NW == 4 || NW == 8), "ring of 2..4 stages, 4 or 8 waves");
     constexpr int BK_ = 32 * NW, BQ = 32, QS = D::NKS * 2048, VS = D::NKS * 4096;
@@ -458,12 +481,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int lrow = lane & 31, half = lane >> 5;
     // level = key block: the earliest key blocks meet the most query tiles under a causal mask
     const int grp = nq / nkv;
-    const AttnSlot slot = attn_slot(blockIdx.x, SPLIT ? nq : nkv, n_seqs, nblk_max);
+    const unsigned qpart = SPLIT ? blockIdx.x / blocks : 0;  // which `chunk` query tiles of the key block's walk
+    const AttnSlot slot = attn_slot(SPLIT ? blockIdx.x % blocks : blockIdx.x, SPLIT ? nq : nkv, n_seqs, nblk_max);
     const int hsub = SPLIT ? slot.h % grp : 0, g = SPLIT ? slot.h / grp : slot.h, b = slot.b;
     if (slot.level >= nblk_max) return;
     const int s0 = cu[b], s1 = cu[b + 1];
     const int kblk = slot.level * BK_;                      // first key of the workgroup, relative to s0
     if (kblk >= s1 - s0) return;
+    // query tiles that see this key block.  They are walked from the last one down: the workgroups of a (sequence, head)
+    // that run at the same time on an XCD (neighbouring key blocks) then read the same Q / dO rows at the same time, one
+    // fetch into L2 serving all of them, whereas walks that start at each block's own first tile are staggered.
+    const int qt_first = CAUSAL ? kblk / BQ : 0;
+    const int nqt_all = (s1 - s0 + BQ - 1) / BQ - qt_first;
+    const int nqt = SPLIT ? nqt_all - (int)qpart * chunk : nqt_all;     // tiles from this part's first one down to the last
+    if (SPLIT && nqt <= 0) return;
+    const int niter = SPLIT ? (nqt < chunk ? nqt : chunk) : nqt * grp;
     const long ld = (long)(nq + 2 * nkv) * HD, ldo = (long)nq * HD;
     const int kw0 = s0 + kblk + wave * 32;                  // first key of the wave
     const int key = kw0 + lrow;                             // this lane's key (token index)
@@ -494,13 +526,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 for (int i = 0; i < 8; ++i) kf[ks][i] = (bf16_t)0.f;
         }
     }
-    // query tiles that see this key block.  They are walked from the last one down: the workgroups of a (sequence, head)
-    // that run at the same time on an XCD (neighbouring key blocks) then read the same Q / dO rows at the same time, one
-    // fetch into L2 serving all of them, whereas walks that start at each block's own first tile are staggered.
-    const int qt_first = CAUSAL ? kblk / BQ : 0;
-    const int nqt = (s1 - s0 + BQ - 1) / BQ - qt_first;
-    const int niter = SPLIT ? nqt : nqt * grp;
-
     // Requests tile `it` (out of range: zeros that nobody reads).  Per wave: NKS loads of Q / dO rows, wave 0 one more
     // for the 32 (lse, delta) pairs = 64 consecutive floats.
     // The first half of the waves fills the Q tile, the second half the dO tile; the lane's part of the addresses
@@ -681,10 +706,25 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
                      const void *o, const float *lse, const void *d_o, void *dqkv, void *scratch, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)HD);
     const int ntile_max = ms_cdiv(max_seqlen, 128);
-    const long blocks = attn_grid(nq, n_seqs, ntile_max).blocks;
     // grouped-query attention: split the group's query heads over workgroups (see the kernel)
     const bool split = nq / nkv > 1;
-    const long blocks_dkv = attn_grid(split ? nq : nkv, n_seqs, ntile_max).blocks;     // 128 keys each, like the query tiles
+    // Small batches: nq * n / 128 tiles of 128 queries or keys do not fill 256 CUs (two workgroups each), and the longest
+    // sequence's serial walk (one step per 32 queries in dK/dV, per 64 keys in dQ) is what the launch waits for.  There a
+    // key block's walk is cut into chunks of at least 8 query tiles, up to about two workgroups per CU (each adds its 128
+    // keys' sums with atomics, which cost more than a shorter walk saves beyond that), and dQ takes its two-way key
+    // split where it leaves a CU with one workgroup.  Only under grouped-query attention: its dK / dV are summed with
+    // atomics in any case, whereas without groups a sequence's gradients do not depend on what else is in the batch and
+    // stay so.  Whole backward at 8 / 2 heads of 128, us (tiles; unsplit -> here; 6 and 4 chunks): 2053 tokens (136)
+    // 171 -> 98 (120 at 6), 4096 (256) 243 -> 150 (167 at 4), 8000 (504) 391 -> 315; 12 / 2 heads, 8000 tokens (756): 786,
+    // 824 with two chunks; dQ's split at 384 tiles loses 2 %.
+    const long tiles = (long)nq * ms_cdiv(n, 128);
+    const int steps = ms_cdiv(max_seqlen, 32);
+    long parts = split ? ms_cdiv(540, tiles) : 1;
+    if (parts > steps / 8) parts = steps / 8 < 1 ? 1 : steps / 8;
+    const int chunk = ms_cdiv(steps, parts);
+    const bool dq2 = split && tiles < 320;
+    const long blocks = attn_grid(nq, n_seqs, dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max).blocks;
+    const long blocks_kv = attn_grid(split ? nq : nkv, n_seqs, ntile_max).blocks, blocks_dkv = blocks_kv * parts;   // 128 keys each
     if (blocks > 0x7fffffffL || blocks_dkv > 0x7fffffffL || !ms_attn_offsets_fit(n, nq, nkv, HD))
         return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets");
     const unsigned grid_dkv = (unsigned)blocks_dkv;
@@ -694,23 +734,25 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
     float *dkv_acc = (float *)((char *)scratch + ms_align_up((size_t)nq * n * sizeof(float2)));
     const int w = 2 * nkv * HD;
     if (split) MS_TRY(launch_fill_f32(dkv_acc, (long)n * w, 0.f, s));
+#define DQ(C, KS)                                                                                                      \
+    attn_bwd_dq_mfma_kernel<HD, C, KS><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, ld2, \
+                                                                        (bf16_t *)dqkv, cu, n, nq, nkv, n_seqs,        \
+                                                                        dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max, scale)
+#define DKV(C, SPLIT)                                                                                                  \
+    attn_bwd_dkv_mfma_kernel<HD, C, SPLIT, 4, 2><<<grid_dkv, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o,    \
+                                                                          ld2, (bf16_t *)dqkv, dkv_acc, cu, n, nq,     \
+                                                                          nkv, n_seqs, ntile_max, scale, chunk,        \
+                                                                          (unsigned)blocks_kv)
 #define GO(C)                                                                                                          \
     do {                                                                                                               \
-        attn_bwd_dq_mfma_kernel<HD, C><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, ld2, \
-                                                                        (bf16_t *)dqkv, cu, n, nq, nkv, n_seqs,        \
-                                                                        ntile_max, scale);                             \
+        if (dq2) DQ(C, 2); else DQ(C, 1);                                                                              \
         MS_LAUNCH_CHECK();                                                                                             \
-        if (split)                                                                                                     \
-            attn_bwd_dkv_mfma_kernel<HD, C, true, 4, 2><<<grid_dkv, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, \
-                                                                                 ld2, (bf16_t *)dqkv, dkv_acc, cu, n,  \
-                                                                                 nq, nkv, n_seqs, ntile_max, scale);   \
-        else                                                                                                           \
-            attn_bwd_dkv_mfma_kernel<HD, C, false, 4, 2><<<grid_dkv, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, \
-                                                                                  ld2, (bf16_t *)dqkv, dkv_acc, cu, n, \
-                                                                                  nq, nkv, n_seqs, ntile_max, scale);  \
+        if (split) DKV(C, true); else DKV(C, false);                                                                   \
     } while (0)
     if (causal) GO(true); else GO(false);
 #undef GO
+#undef DQ
+#undef DKV
     MS_LAUNCH_CHECK();
     if (split) {
         attn_dkv_store_kernel<<<ms_cdiv((long)n * w / 4, 256), 256, 0, s>>>(dkv_acc, (bf16_t *)dqkv, n, w, (long)(nq + 2 * nkv) * HD,
