@@ -3,7 +3,7 @@
 // One workgroup (4 waves) owns 128 consecutive queries of one sequence and one query head; each
 // wave owns 32 of them and keeps its Q fragments in registers.  Keys / values are visited 64 at a
 // time through two LDS buffers filled by direct global -> LDS loads (no staging registers), both
-// row-major [64 keys][head_dim] as 64-wide swizzled sub-tiles; the P V product, which contracts
+// row-major [64 keys][head_dim] as swizzled row tiles; the P V product, which contracts
 // over keys, reads V through the transposing LDS load (ds_read_b64_tr_b16).
 // Scores are computed transposed, S^T = K Q^T (v_mfma_f32_32x32x16_bf16): in the accumulator
 // layout a lane then holds 32 keys of ONE query, so the online-softmax row maximum and sum are
@@ -18,7 +18,6 @@
 namespace {
 
 template <int HD> struct AttnDims {
-    static constexpr int NKS = (HD + 63) / 64;   // 64-wide sub-tiles of a K (or Q) tile
     static constexpr int DB = (HD + 31) / 32;    // 32-row blocks of the transposed output
     static constexpr int KST = HD / 16;          // MFMA k-steps over head_dim
 };
@@ -60,11 +59,12 @@ __device__ inline AttnSlot attn_slot(unsigned bid, int heads, int n_seqs, int nl
 }
 
 template <int HD, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_mfma_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HD == 64 ? 3 : 2, HD == 64 ? 3 : 2))) void attn_fwd_mfma_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
                                                              float *__restrict__ lse, const int *__restrict__ cu, int n,
                                                              int nq, int nkv, int n_seqs, int ntile_max, float scale_log2e) {
     using D = AttnDims<HD>;
-    constexpr int BQ = 128, BKV = 64, TS = D::NKS * 4096;
+    using T = RowTile<HD, 64>;
+    constexpr int BQ = 128, BKV = 64, TS = T::ELEMS;
     // separate LDS objects per buffer: lets the compiler tell in-flight direct-to-LDS loads from reads
     __shared__ __align__(16) bf16_t K0[TS], K1[TS], V0[TS], V1[TS];
 
@@ -96,9 +96,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int i = 0; i < 8; ++i) qf[ks][i] = (bf16_t)0.f;
         }
     }
-    // each wave issues a quarter of the 2 * 8 * NKS instructions that fill one K tile and one V tile
+    // each wave issues a quarter of the instructions that fill one K tile and one V tile
     // (waves 0 and 1 fill the K tile, waves 2 and 3 the V tile; the lane's part of the addresses is computed once)
-    constexpr int PER = 4 * D::NKS;
+    constexpr int PER = T::LOADS / 2;
     RowTileLane dl;
     dl.init(lane, (unsigned)(ld * 2));
     const bool fill_v = wave >= 2;
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const unsigned base = (unsigned)((long)(s0 + j * BKV) * ld * 2) + dcol;
         bf16_t *t = fill_v ? vt : kt;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), (wave & 1) * PER + i, dl);
+        for (int i = 0; i < PER; ++i) rowtile_dma_share<HD, 2>(rs, t, base, (unsigned)(ld * 2), i, wave & 1, dl);
     };
     // The same loads in KST portions, placed between the MFMAs of the S product of the tile before: a direct-to-LDS
     // load occupies the wave's issue slot for tens of cycles, which the MFMAs already queued cover.  A tile past the
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         bf16_t *t = fill_v ? vt : kt;
 #pragma unroll
         for (int i = ks * PER / D::KST; i < (ks + 1) * PER / D::KST; ++i)
-            rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), (wave & 1) * PER + i, dl, inv);
+            rowtile_dma_share<HD, 2>(rs, t, base, (unsigned)(ld * 2), i, wave & 1, dl, inv);
     };
 
     f32x16 oacc[D::DB];
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int r = 0; r < 16; ++r) st[kb][r] = 0.f;
         auto kfrag = [&](int ks, int kb) {
-            return *(const bf16x8 *)(kt + (ks / 4) * 4096 + lds_off(kb * 32 + lrow, (ks % 4) * 2 + half));
+            return *(const bf16x8 *)(kt + T::frag_off(kb * 32 + lrow, ks, half));
         };
         bf16x8 kf[2][2];
         kf[0][0] = kfrag(0, 0);
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const bf16x8 pf = pack8(&p[kb][8 * t]);
 #pragma unroll
                 for (int db = 0; db < D::DB; ++db)
-                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rowtile_tr_frag(vt, kb * 32 + 16 * t, db * 32, lane), pf,
+                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rowtile_tr_frag<HD, 64>(vt, kb * 32 + 16 * t, db * 32, lane), pf,
                                                                          oacc[db], 0, 0, 0);
             }
     };
@@ -281,12 +281,13 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t *__restric
 // the even key tiles, waves 2 and 3 the odd ones for the same queries, and the two partial sums meet in LDS: twice the
 // workgroups, half the serial chain.
 template <int HD, bool CAUSAL, int KS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 - KS))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 1 : HD == 64 ? 3 : 2, KS == 2 ? 1 : HD == 64 ? 3 : 2))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
                                                                 const float2 *__restrict__ ld2,
                                                                 bf16_t *__restrict__ dqkv, const int *__restrict__ cu, int n,
                                                                 int nq, int nkv, int n_seqs, int ntile_max, float scale) {
     using D = AttnDims<HD>;
-    constexpr int BQ = 128 / KS, BKV = 64, TS = D::NKS * 4096;
+    using T = RowTile<HD, 64>;
+    constexpr int BQ = 128 / KS, BKV = 64, TS = T::ELEMS;
     __shared__ __align__(16) bf16_t K0[KS * TS], K1[KS * TS], V0[KS * TS], V1[KS * TS];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -328,17 +329,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 -
     const float lse2 = row.x, dlt = row.y;
 
     // (one half of the waves fills K tiles, the other V tiles; the lane's part of the addresses is computed once)
-    constexpr int PER = 4 * D::NKS * KS;
+    constexpr int PER = T::LOADS / 2 * KS;
     RowTileLane dl;
     dl.init(lane, (unsigned)(ld * 2));
     const bool fill_v = KS == 2 ? (wave & 1) != 0 : wave >= 2;
-    const int fill0 = KS == 2 ? 0 : (wave & 1) * PER;       // first of this wave's loads of its tile
+    const int which = KS == 2 ? 0 : wave & 1;               // its share of the tile (all of it with KS = 2)
     const unsigned dcol = (unsigned)(fill_v ? vcol : kcol) * 2;
     auto issue = [&](int j, bf16_t *kt, bf16_t *vt) {
         const unsigned base = (unsigned)((long)(s0 + j * BKV) * ld * 2) + dcol;
         bf16_t *t = fill_v ? vt : kt;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), fill0 + i, dl, j < nkt ? 0u : kOob);
+        for (int i = 0; i < PER; ++i) rowtile_dma_share<HD, 2 / KS>(rs, t, base, (unsigned)(ld * 2), i, which, dl, j < nkt ? 0u : kOob);
     };
     // The same loads in KST portions, placed between the MFMAs of the S product of the tile before: a direct-to-LDS
     // load occupies the wave's issue slot for tens of cycles, which the MFMAs already queued cover.  A tile past the
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 -
         bf16_t *t = fill_v ? vt : kt;
 #pragma unroll
         for (int i = ks * PER / D::KST; i < (ks + 1) * PER / D::KST; ++i)
-            rowtile_dma_lane<HD, 64>(rs, t, base, (unsigned)(ld * 2), fill0 + i, dl, inv);
+            rowtile_dma_share<HD, 2 / KS>(rs, t, base, (unsigned)(ld * 2), i, which, dl, inv);
     };
 
     f32x16 dq[D::DB];
@@ -367,7 +368,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 -
             for (int r = 0; r < 16; ++r) { st[r] = 0.f; dp[r] = 0.f; }
 #pragma unroll
             for (int ks = 0; ks < D::KST; ++ks) {
-                const int off = (ks / 4) * 4096 + lds_off(kb * 32 + lrow, (ks % 4) * 2 + half);
+                const int off = T::frag_off(kb * 32 + lrow, ks, half);
                 st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(kt + off), qf[ks], st, 0, 0, 0);
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(vt + off), dof[ks], dp, 0, 0, 0);
                 if (kb == 0) issue_part(ks, j + KS, kn, vn);
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 -
                 const bf16x8 dsf = pack8(&ds[8 * t]);
 #pragma unroll
                 for (int db = 0; db < D::DB; ++db)
-                    dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rowtile_tr_frag(kt, kb * 32 + 16 * t, db * 32, lane), dsf,
+                    dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rowtile_tr_frag<HD, 64>(kt, kb * 32 + 16 * t, db * 32, lane), dsf,
                                                                        dq[db], 0, 0, 0);
             }
         }
@@ -407,19 +408,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3 - KS, 3 -
     }
     if constexpr (KS == 2) {
         // waves 2 and 3 hand their sums to waves 0 and 1 (same queries, same lanes) through the idle tile buffers
-        float *x = (float *)((wave & 1) ? V0 : K0);         // KS * TS bf16 = 16 * DB or more floats per lane
-        static_assert(KS * TS / 2 >= 64 * 16 * D::DB, "a wave's sums fit into one buffer");
+        // (block i of a wave goes to the wave's K or V buffer)
+        auto at = [&](int i) { return (float *)(i & 1 ? ((wave & 1) ? V1 : K1) : ((wave & 1) ? V0 : K0)) + (i >> 1) * 1024; };
+        static_assert(KS * TS / 2 >= (D::DB + 1) / 2 * 1024, "half of a wave's blocks fit into one buffer");
         if (part == 1)
 #pragma unroll
             for (int i = 0; i < D::DB; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 64 + lane] = dq[i][r];
+                for (int r = 0; r < 16; ++r) at(i)[r * 64 + lane] = dq[i][r];
         __syncthreads();
         if (part == 1) return;
 #pragma unroll
         for (int i = 0; i < D::DB; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dq[i][r] += x[(i * 16 + r) * 64 + lane];
+            for (int r = 0; r < 16; ++r) dq[i][r] += at(i)[r * 64 + lane];
     }
     if (!qok) return;
     bf16_t *op = dqkv + (long)q * ld + (long)h * HD;
@@ -467,7 +469,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int nblk_max, float scale, int chunk, unsigned blocks) {
     using D = AttnDims<HD>;
     static_assert(NST >= 2 && NST <= 4 && (NW == 4 || NW == 8), "ring of 2..4 stages, 4 or 8 waves");
-    constexpr int BK_ = 32 * NW, BQ = 32, QS = D::NKS * 2048, VS = D::NKS * 4096;
+    using TQ = RowTile<HD, 32, false>;                       // (see RowTile for why not compact)
+    using TV = RowTile<HD, 64, false>;
+    constexpr int BK_ = 32 * NW, BQ = 32, QS = TQ::ELEMS, VS = TV::ELEMS;
     constexpr int Q2 = NST > 2 ? QS : 8, Q3 = NST > 3 ? QS : 8;        // stages beyond NST are not used
     // separate LDS objects per stage: lets the compiler tell the stage being filled from the stage being read
     __shared__ __align__(16) bf16_t Qa[QS], Qb[QS], Qc[Q2], Qd[Q3], Oa[QS], Ob[QS], Oc[Q2], Od[Q3];
@@ -508,12 +512,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // only ever meet p = 0.  (Each wave only reads the rows of its own 32 keys; keeping them in registers like the K
     // fragments was measured: it spills.)
     {
-        constexpr int PER = (BK_ / 64) * 8 * D::NKS / NW;
+        RowTileLane vl;
+        vl.init(lane, (unsigned)(ld * 2));
+        const int t = wave >> 1;                             // two waves per 64-key tile
+        const unsigned base = (unsigned)(((long)(s0 + kblk + t * 64) * ld + (long)(nq + nkv + g) * HD) * 2);
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int idx = wave * PER + i, t = idx / (8 * D::NKS);
-            rowtile_dma<HD>(rq, Vs + t * VS, s0 + kblk + t * 64, ld, (nq + nkv + g) * HD, idx % (8 * D::NKS), lane);
-        }
+        for (int i = 0; i < TV::LOADS / 2; ++i)
+            rowtile_dma_lane<HD, 64, false>(rq, Vs + t * VS, base, (unsigned)(ld * 2), (wave & 1) * (TV::LOADS / 2) + i, vl);
     }
     bf16x8 kf[D::KST];
     {
@@ -526,13 +531,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 for (int i = 0; i < 8; ++i) kf[ks][i] = (bf16_t)0.f;
         }
     }
-    // Requests tile `it` (out of range: zeros that nobody reads).  Per wave: NKS loads of Q / dO rows, wave 0 one more
+    // Requests tile `it` (out of range: zeros that nobody reads).  Per wave: PERQ loads of Q / dO rows, wave 0 one more
     // for the 32 (lse, delta) pairs = 64 consecutive floats.
     // The first half of the waves fills the Q tile, the second half the dO tile; the lane's part of the addresses
     // is computed once.
-    constexpr int PERQ = 8 * D::NKS / NW;
-    static_assert((4 * D::NKS) % PERQ == 0, "a wave fills rows of one tile only");
-    const bool fill_o = wave * PERQ >= 4 * D::NKS;
+    constexpr int WPT = NW / 2, PERQ = TQ::LOADS / WPT;
+    static_assert(PERQ * WPT == TQ::LOADS, "equal shares");
+    const bool fill_o = wave >= WPT;
     const unsigned ldw2 = (unsigned)((fill_o ? ldo : ld) * 2);
     const __amdgpu_buffer_rsrc_t rw = fill_o ? ro : rq;
     RowTileLane dl;
@@ -545,7 +550,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const unsigned base = (unsigned)qs * ldw2 + (unsigned)(h * HD) * 2;
         bf16_t *t = fill_o ? ot_ : qt_;
 #pragma unroll
-        for (int i = 0; i < PERQ; ++i) rowtile_dma_lane<HD, 32>(rw, t, base, ldw2, (wave * PERQ + i) % (4 * D::NKS), dl, inv);
+        for (int i = 0; i < PERQ; ++i) rowtile_dma_lane<HD, 32, false>(rw, t, base, ldw2, wave % WPT * PERQ + i, dl, inv);
         if (wave == 0)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rf, (lds_void *)f, 4, (unsigned)((((long)h * n + qs) * 2 + lane) * 4) | inv, 0, 0, 0);
     };
@@ -570,11 +575,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int r = 0; r < 16; ++r) { st[r] = 0.f; dp[r] = 0.f; }
 #pragma unroll
         for (int ks = 0; ks < D::KST; ++ks) {
-            const int off = lds_off(lrow, (ks % 4) * 2 + half);
-            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(qt_ + (ks / 4) * 2048 + off), kf[ks], st, 0, 0, 0);
+            const int off = TQ::frag_off(lrow, ks, half);
+            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(qt_ + off), kf[ks], st, 0, 0, 0);
             if constexpr (DK) {
-                const bf16x8 vfr = *(const bf16x8 *)(vrow + (ks / 4) * 4096 + lds_off(vr, (ks % 4) * 2 + half));
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(ot_ + (ks / 4) * 2048 + off), vfr, dp, 0, 0, 0);
+                const bf16x8 vfr = *(const bf16x8 *)(vrow + TV::frag_off(vr, ks, half));
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(ot_ + off), vfr, dp, 0, 0, 0);
             }
         }
         // accumulator rows are queries 8*(r/4) + 4*half + r%4, the column is this lane's key; keys and queries past
@@ -605,12 +610,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             const bf16_t *bt = DK ? qt_ : ot_;              // dK += dS^T Q, dV += P^T dO
 #pragma unroll
             for (int db = 0; db < D::DB; ++db)
-                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, rowtile_tr_frag<2048>(bt, 16 * t, db * 32, lane), acc[db], 0, 0, 0);
+                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, rowtile_tr_frag<HD, 32, false>(bt, 16 * t, db * 32, lane), acc[db], 0, 0, 0);
             if constexpr (BOTH) {
                 const bf16x8 pf = pack8(w2);
 #pragma unroll
                 for (int db = 0; db < D::DB; ++db)
-                    acc2[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, rowtile_tr_frag<2048>(ot_, 16 * t, db * 32, lane), acc2[db], 0, 0, 0);
+                    acc2[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, rowtile_tr_frag<HD, 32, false>(ot_, 16 * t, db * 32, lane), acc2[db], 0, 0, 0);
             }
         }
     };

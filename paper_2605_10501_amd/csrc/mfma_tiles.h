@@ -70,66 +70,89 @@ __device__ __forceinline__ bf16x8 tr_frag(const bf16_t *p0, const bf16_t *p1) {
     return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// ---- "row tiles": 64 rows x W columns of a row-major matrix, kept as W/64 sub-tiles [64][64] --------
-// One direct-to-LDS instruction: instruction idx fills 8-row group idx % 8 of sub-tile idx / 8 from rows
-// row0.. of a matrix with leading dimension ld (elements), starting at column col0.  Columns past W
-// arrive as zeros; rows past the end of the matrix are zeroed by the descriptor's range check.
-template <int W>
-__device__ __forceinline__ void rowtile_dma(__amdgpu_buffer_rsrc_t rs, bf16_t *tile, int row0, long ld, int col0, int idx,
-                                            int lane, unsigned inv = 0) {
-    const int sub = idx >> 3, g = idx & 7;
-    const int r = g * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ swz_row(r);
-    const int d = sub * 64 + c * 8;
-    const unsigned voff = (d < W ? (unsigned)(((long)(row0 + r) * ld + col0 + d) * 2) : kOob) | inv;   // inv = kOob: all zeros
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(tile + sub * 4096 + g * 512), 16, voff, 0, 0, 0);
-}
+// ---- "row tiles": ROWS (64 or 32) rows x W columns of a row-major matrix --------------------------
+// Kept as W / 64 sub-tiles [ROWS][64] in the swizzled layout above and, for W % 64 == 16 (head_dim 80), a tail [ROWS][16]:
+// 32-byte rows of two 16-byte chunks, chunk c of row r at position c ^ bit 3 of r, which keeps both fragment reads free
+// of bank conflicts under the rules above (rows 24 apart, the only pairs of a 16-byte read's 16 lanes that share 32
+// bytes modulo 256, differ in bit 3; the half-wave of a transposing read covers eight consecutive rows).  !COMPACT keeps the
+// tail as another 64-wide sub-tile whose columns past W arrive as zeros: 16 instead of 10 load instructions and 16 instead
+// of 10 KB per 64-row tile, but one address pattern for all fragments.  Encoder shapes (46173 tokens, 16 heads of 80), compact
+// against not: forward 966 / 1031 us (its loads sit between the MFMAs), dQ equal within 1 %; dK/dV 2163 / 2063 us, which
+// is at its register limit (249 of 256) and not bound by its loads.
+template <int W, int ROWS, bool COMPACT = true> struct RowTile {
+    static constexpr int MAIN = COMPACT ? W / 64 : (W + 63) / 64, TAIL = COMPACT ? W % 64 : 0;
+    static_assert(TAIL == 0 || TAIL == 16, "a row tile's width is a multiple of 64, or 16 more");
+    static constexpr int G = ROWS / 8;                                    // 8-row groups per sub-tile
+    static constexpr int ELEMS = ROWS * (64 * MAIN + TAIL);               // bf16 elements of a tile
+    static constexpr int LOADS = G * MAIN + (TAIL ? ROWS / 32 : 0);       // direct-to-LDS instructions that fill it
+    // element offset of the 16-byte fragment piece (row, columns 16 ks + 8 half .. + 7)
+    static __device__ __forceinline__ int frag_off(int row, int ks, int half) {
+        if (TAIL && ks >= 4 * MAIN) return MAIN * ROWS * 64 + row * 16 + ((half ^ (row >> 3) & 1) << 3);
+        return (ks / 4) * (ROWS * 64) + lds_off(row, (ks % 4) * 2 + half);
+    }
+};
 
-// The same for a tile of 32 rows (sub-tiles [32][64]): instruction idx fills 8-row group idx % 4 of sub-tile idx / 4.
-template <int W>
-__device__ __forceinline__ void rowtile32_dma(__amdgpu_buffer_rsrc_t rs, bf16_t *tile, int row0, long ld, int col0, int idx,
-                                              int lane, unsigned inv = 0) {
-    const int sub = idx >> 2, g = idx & 3;
-    const int r = g * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ swz_row(r);
-    const int d = sub * 64 + c * 8;
-    const unsigned voff = (d < W ? (unsigned)(((long)(row0 + r) * ld + col0 + d) * 2) : kOob) | inv;   // inv = kOob: all zeros
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(tile + sub * 2048 + g * 512), 16, voff, 0, 0, 0);
-}
-
-// The same loads for a loop that fetches tile after tile: everything that depends on the lane alone is computed
+// Addresses of the loads of a loop that fetches tile after tile: everything that depends on the lane alone is computed
 // once (RowTileLane), everything that depends on the instruction index or the tile is wave-uniform and stays in
 // scalar registers, so that a load costs three vector instructions (add, xor-shift, add) instead of a 64-bit
 // address computation.  base = byte offset of (row0, col0) in the matrix, ld2 = bytes per matrix row; idx must be
-// wave-uniform.  ROWS = 64 (rowtile_dma's layout) or 32 (rowtile32_dma's).
+// wave-uniform.  Instruction idx fills 8-row group idx % G of sub-tile idx / G.  Rows past the end
+// of the matrix are zeroed by the descriptor's range check.
 struct RowTileLane {
     unsigned rowpart;   // (lane / 8) * ld2: the lane's row within an 8-row group
+    unsigned tailpart;  // (lane / 2) * ld2 + its chunk of the tail row
     int x;              // (lane % 8) ^ swz_row(lane / 8): chunk position with the lane's part of the swizzle
     __device__ __forceinline__ void init(int lane, unsigned ld2) {
         rowpart = (unsigned)(lane >> 3) * ld2;
+        tailpart = (unsigned)(lane >> 1) * ld2 + (unsigned)(((lane ^ (lane >> 4)) & 1) << 4);
         x = (lane & 7) ^ swz_row(lane >> 3);
     }
 };
-template <int W, int ROWS>
+template <int W, int ROWS, bool COMPACT = true>
 __device__ __forceinline__ void rowtile_dma_lane(__amdgpu_buffer_rsrc_t rs, bf16_t *tile, unsigned base, unsigned ld2, int idx,
                                                  const RowTileLane &L, unsigned inv = 0) {
-    constexpr int G = ROWS / 8;                              // 8-row groups per sub-tile
-    const int sub = idx / G, g = idx % G;
+    using T = RowTile<W, ROWS, COMPACT>;
+    const int sub = idx / T::G, g = idx % T::G;
     const int c = L.x ^ swz_row(8 * g);                      // swz_row is linear: swz_row(8 g + l) = swz_row(8 g) ^ swz_row(l)
     unsigned voff = L.rowpart + (base + (unsigned)(8 * g) * ld2 + (unsigned)sub * 128u) + ((unsigned)c << 4);
-    if (W % 64 != 0 && sub == W / 64) voff = c * 8 < W % 64 ? voff : kOob;   // columns past W arrive as zeros
+    if (!COMPACT && W % 64 != 0 && sub == W / 64) voff = c * 8 < W % 64 ? voff : kOob;   // columns past W arrive as zeros
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(tile + sub * (ROWS * 64) + g * 512), 16, voff | inv, 0, 0, 0);
+}
+// instruction t of the tail: 32 rows
+template <int W, int ROWS>
+__device__ __forceinline__ void rowtile_dma_tail(__amdgpu_buffer_rsrc_t rs, bf16_t *tile, unsigned base, unsigned ld2, int t,
+                                                 const RowTileLane &L, unsigned inv = 0) {
+    using T = RowTile<W, ROWS>;
+    const unsigned voff = L.tailpart + (base + (unsigned)(32 * t) * ld2 + (unsigned)T::MAIN * 128u);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(tile + T::MAIN * ROWS * 64 + t * 512), 16, voff | inv, 0, 0, 0);
+}
+// load i (compile-time after unrolling) of the share that wave `which` of SHARE has in filling a tile of 64 rows: its
+// instructions of the sub-tiles, then of the tail, so that no load sits behind a branch
+template <int W, int SHARE>
+__device__ __forceinline__ void rowtile_dma_share(__amdgpu_buffer_rsrc_t rs, bf16_t *tile, unsigned base, unsigned ld2, int i, int which,
+                                                  const RowTileLane &L, unsigned inv = 0) {
+    using T = RowTile<W, 64>;
+    constexpr int NM = T::G * T::MAIN / SHARE, NT = T::TAIL ? 2 / SHARE : 0;
+    static_assert((NM + NT) * SHARE == T::LOADS, "equal shares");
+    if (i < NM) rowtile_dma_lane<W, 64>(rs, tile, base, ld2, which * NM + i, L, inv);
+    else if constexpr (T::TAIL != 0) rowtile_dma_tail<W, 64>(rs, tile, base, ld2, which * NT + i - NM, L, inv);
 }
 
 // MFMA operand fragment whose 32 "rows" are tile columns m0 .. m0+31 and whose k-slots are tile rows:
-// half h of the wave gets rows k0 + 4h + {0..3} (slots 0..3) and k0 + 8 + 4h + {0..3} (slots 4..7).
-// SUB = elements per 64-column sub-tile (64 x tile height).
-template <int SUB = 4096>
+// half h of the wave gets rows k0 + 4h + {0..3} (slots 0..3) and k0 + 8 + 4h + {0..3} (slots 4..7).  In the tail the
+// columns past W (lanes 16..31 of each half) are not there: those lanes read other tail rows (results nobody stores).
+template <int W, int ROWS, bool COMPACT = true>
 __device__ __forceinline__ bf16x8 rowtile_tr_frag(const bf16_t *tile, int k0, int m0, int lane) {
+    using T = RowTile<W, ROWS, COMPACT>;
     const int h = lane >> 5, dg = (lane >> 4) & 1, r = lane & 15;
     const int row = k0 + 4 * h + (r >> 2);
+    if (T::TAIL && m0 >= T::MAIN * 64) {
+        const int rt = row ^ (4 * dg), m = 4 * (r & 3), f = (rt >> 3) & 1;
+        const bf16_t *base = tile + T::MAIN * ROWS * 64 + rt * 16 + (m & 7);
+        return tr_frag(base + (((m >> 3) ^ f) << 3), base + 128 + (((m >> 3) ^ f ^ 1) << 3));
+    }
     const int m = m0 + 16 * dg + 4 * (r & 3);
-    const bf16_t *base = tile + (m >> 6) * SUB + (m & 7);
+    const bf16_t *base = tile + (m >> 6) * (ROWS * 64) + (m & 7);
     const int chunk = (m & 63) >> 3;
     return tr_frag(base + lds_off(row, chunk), base + lds_off(row + 8, chunk));
 }
