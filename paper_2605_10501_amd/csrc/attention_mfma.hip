@@ -448,8 +448,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 1
         }
 }
 
-// dK, dV: workgroup = NW waves with 32 keys each of one KV head (K fragments in registers; V fragments in registers
-// as well or as a tile in LDS); it walks the query heads of the group and their query tiles, 32 rows at a time.  S = Q K^T and dP = dO V^T
+// dK, dV: workgroup = NW waves with 32 keys each of one KV head (K fragments in registers, the V tile in LDS); it walks the query heads of the group and their query tiles, 32 rows at a time.  S = Q K^T and dP = dO V^T
 // are accumulator tiles with one KEY per lane and queries down the registers, which is the A-operand layout of
 // dV += P^T dO and dK += dS^T Q; their B operands (dO and Q with queries as the contraction index) come from the
 // row-major tiles through the transposing LDS load.  256 registers per wave: two waves per SIMD (two 4-wave workgroups
@@ -462,7 +461,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 1
 // NST - 2 tiles, may still be in flight; tiles past the end are requested as out-of-range loads so that the count is
 // the same in every iteration), after it all waves have finished the previous tile, whose stage is then handed to the
 // tile NST - 1 ahead.  Measured on MI355X (c5 student / c4 encoder shapes, in the step): NW = 4, NST = 2 (two
-// independent workgroups per CU, 66 KB of LDS each) 28.0 / 57.2 ms per step; NW = 8 with NST = 3 or 4 (one workgroup
+// independent workgroups per CU) 28.0 / 57.2 ms per step; NW = 8 with NST = 3 or 4 (one workgroup
 // per CU, all eight waves in lockstep) 28.8 / 58.0 and 29.1 / 67.5: deeper prefetch buys nothing, the kernel is not
 // waiting for memory but for its own MFMA -> exponentials -> MFMA chain, which two independent workgroups overlap
 // better than one.  (NW = 4 with NST = 3 needs 80.75 KB of LDS for head_dim 128, 768 bytes too many for two per CU.)
@@ -485,6 +484,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // separate LDS objects per stage: lets the compiler tell the stage being filled from the stage being read
     __shared__ __align__(16) bf16_t Qa[QS], Qb[QS], Qc[Q2], Qd[Q3], Oa[QS], Ob[QS], Oc[Q2], Od[Q3];
     __shared__ __align__(16) bf16_t Vs[(BK_ / 64) * VS];
+    // K fragments live in registers, at head_dim 128 all but KL of the eight, which stay in LDS as [keys][16] blocks laid
+    // out like a row tile's tail (12 KB, which two workgroups per CU leave free): with all in registers the kernel
+    // spilled 17, and a reload in the loop waits for every younger load, the next tile's among them (whole backward, c5
+    // student / teacher heads: 3303 -> 3117 / 8917 -> 8392 us).
+    constexpr int KL = HD == 128 ? 3 : 0, KR = D::KST - KL;
+    __shared__ __align__(16) bf16_t Ks[KL > 0 ? KL * BK_ * 16 : 8];
     __shared__ __align__(16) float Fa[64], Fb[64], Fc[64], Fd[64];     // per query row of the tile: (lse * log2(e), delta)
     bf16_t *const Qst[4] = {Qa, Qb, Qc, Qd}, *const Ost[4] = {Oa, Ob, Oc, Od};
     float *const Fst[4] = {Fa, Fb, Fc, Fd};
@@ -529,15 +534,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int i = 0; i < TV::LOADS / 2; ++i)
             rowtile_dma_lane<HD, 64, false>(rq, Vs + t * VS, base, (unsigned)(ld * 2), (wave & 1) * (TV::LOADS / 2) + i, vl);
     }
-    bf16x8 kf[D::KST];
+    bf16x8 kf[KR];
     {
         const bf16_t *kp = qkv + (long)key * ld + (long)(nq + g) * HD + half * 8;
 #pragma unroll
         for (int ks = 0; ks < D::KST; ++ks) {
-            if (kok) kf[ks] = *(const bf16x8 *)(kp + ks * 16);
+            bf16x8 v;
+            if (kok) v = *(const bf16x8 *)(kp + ks * 16);
             else
 #pragma unroll
-                for (int i = 0; i < 8; ++i) kf[ks][i] = (bf16_t)0.f;
+                for (int i = 0; i < 8; ++i) v[i] = (bf16_t)0.f;
+            // (a wave reads back what its own lanes wrote)
+            if (ks < KR) kf[ks] = v;
+            else *(bf16x8 *)(Ks + (ks - KR) * BK_ * 16 + (wave * 32 + lrow) * 16 + ((half ^ (lrow >> 3) & 1) << 3)) = v;
         }
     }
     // Requests tile `it` (out of range: zeros that nobody reads).  Per wave: PERQ loads of Q / dO rows, wave 0 one more
@@ -566,17 +575,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
     const bf16_t *vrow = Vs + (wave >> 1) * VS;             // the 64-key row tile holding this wave's keys
     const int vr = (wave & 1) * 32 + lrow;
-    // One pass over the query tiles accumulates dV (WHICH = 0: needs S only), dK (1: needs S and dP) or both
-    // (2).  Both accumulator sets are kept (one pass) for every head_dim.  At head_dim 128 that is 128 accumulator
-    // registers and the kernel spills about 22 of its 256 registers, which was measured against the alternative that
-    // fits: two passes (0 then 1) with one accumulator set, one extra S product and a second round of exponentials per
-    // tile.  One pass is 11-13 % faster at the c5 / c2 student shapes (3.62 -> 3.21 ms, 0.51 -> 0.465 ms per layer).
-    // The two-pass code path stays selectable here.
-    constexpr bool ONE_PASS = true;
-    f32x16 acc[D::DB], acc2[ONE_PASS ? D::DB : 1];          // acc2: dV when both are accumulated (acc is dK then)
-    auto compute = [&](auto which, int it, const bf16_t *qt_, const bf16_t *ot_, const float *f) __attribute__((always_inline)) {
-        constexpr int WHICH = decltype(which)::value;
-        constexpr bool DK = WHICH >= 1, BOTH = WHICH == 2;
+    auto kfl = [&](int ks) __attribute__((always_inline)) { return *(const bf16x8 *)(Ks + (ks - KR) * BK_ * 16 + (wave * 32 + lrow) * 16 + ((half ^ (lrow >> 3) & 1) << 3)); };
+    // Both accumulator sets are kept (one pass over the query tiles) for every head_dim.  The alternative for head_dim 128,
+    // two passes with one set, an extra S product and a second round of exponentials per tile, was 11-13 % slower.
+    f32x16 acc[D::DB], acc2[D::DB];                         // dK, dV
+    auto compute = [&](int it, const bf16_t *qt_, const bf16_t *ot_, const float *f) __attribute__((always_inline)) {
         const int qs = s0 + (qt_first + nqt - 1 - it % nqt) * BQ;
         if (CAUSAL && qs + BQ - 1 < kw0) return;            // every query of the tile precedes every key of the wave
         f32x16 st, dp;
@@ -585,11 +588,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
         for (int ks = 0; ks < D::KST; ++ks) {
             const int off = TQ::frag_off(lrow, ks, half);
-            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(qt_ + off), kf[ks], st, 0, 0, 0);
-            if constexpr (DK) {
-                const bf16x8 vfr = *(const bf16x8 *)(vrow + TV::frag_off(vr, ks, half));
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(ot_ + off), vfr, dp, 0, 0, 0);
-            }
+            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(qt_ + off), ks < KR ? kf[ks < KR ? ks : 0] : kfl(ks), st, 0, 0, 0);
+            const bf16x8 vfr = *(const bf16x8 *)(vrow + TV::frag_off(vr, ks, half));
+            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(ot_ + off), vfr, dp, 0, 0, 0);
         }
         // accumulator rows are queries 8*(r/4) + 4*half + r%4, the column is this lane's key; keys and queries past
         // the end of the sequence are masked (their rows hold the next sequence's data or zeros)
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         // 16 queries (one MFMA k-step of the second product) at a time, to keep few values live
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            float w[8], w2[BOTH ? 8 : 1], pe[8], dvv[8];
+            float w[8], pe[8], dvv[8];
 #pragma unroll
             for (int rg = 0; rg < 2; ++rg) {
                 const int qr = 16 * t + 8 * rg + 4 * half;
@@ -617,21 +618,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 }
             }
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                w[r] = DK ? pe[r] * (dp[8 * t + r] - dvv[r]) : pe[r];
-                if constexpr (BOTH) w2[r] = pe[r];
-            }
+            for (int r = 0; r < 8; ++r) w[r] = pe[r] * (dp[8 * t + r] - dvv[r]);
             const bf16x8 wf = pack8(w);
-            const bf16_t *bt = DK ? qt_ : ot_;              // dK += dS^T Q, dV += P^T dO
 #pragma unroll
-            for (int db = 0; db < D::DB; ++db)
-                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, rowtile_tr_frag<HD, 32, false>(bt, 16 * t, db * 32, lane), acc[db], 0, 0, 0);
-            if constexpr (BOTH) {
-                const bf16x8 pf = pack8(w2);
+            for (int db = 0; db < D::DB; ++db)              // dK += dS^T Q
+                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, rowtile_tr_frag<HD, 32, false>(qt_, 16 * t, db * 32, lane), acc[db], 0, 0, 0);
+            const bf16x8 pf = pack8(pe);
 #pragma unroll
-                for (int db = 0; db < D::DB; ++db)
-                    acc2[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, rowtile_tr_frag<HD, 32, false>(ot_, 16 * t, db * 32, lane), acc2[db], 0, 0, 0);
-            }
+            for (int db = 0; db < D::DB; ++db)              // dV += P^T dO
+                acc2[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, rowtile_tr_frag<HD, 32, false>(ot_, 16 * t, db * 32, lane), acc2[db], 0, 0, 0);
         }
     };
     // accumulators: row = key wave*32 + 8*(r/4) + 4*half + r%4, column d = db*32 + lrow
@@ -650,7 +645,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
     };
     // one tile of the ring: stage S holds tile `it`; the stage of tile it - 1 receives tile it + NST - 1
-    auto ring_step = [&](auto which, int it, const bf16_t *q_cur, const bf16_t *o_cur, const float *f_cur, bf16_t *q_nxt,
+    auto ring_step = [&](int it, const bf16_t *q_cur, const bf16_t *o_cur, const float *f_cur, bf16_t *q_nxt,
                          bf16_t *o_nxt, float *f_nxt) __attribute__((always_inline)) {
         if (it >= niter) return;                            // workgroup-uniform
         // own loads of tile `it` have landed; the younger ones (tiles it+1 .. it+NST-2) may still be in flight
@@ -658,39 +653,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         else wait_vmcnt_lgkm0<(NST - 2) * PERQ>();
         lds_barrier();
         issue(it + NST - 1, q_nxt, o_nxt, f_nxt);
-        compute(which, it, q_cur, o_cur, f_cur);
+        compute(it, q_cur, o_cur, f_cur);
     };
-    auto pass = [&](auto which) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < D::DB; ++i)
+    for (int i = 0; i < D::DB; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                acc[i][r] = 0.f;
-                if constexpr (ONE_PASS) acc2[i][r] = 0.f;
-            }
-#pragma unroll
-        for (int k = 0; k < NST - 1; ++k) issue(k, Qst[k], Ost[k], Fst[k]);
-        for (int it = 0; it < niter; it += NST) {
-#pragma unroll
-            for (int k = 0; k < NST; ++k) {
-                constexpr int P = NST - 1;                  // stage k holds tile it + k; stage k - 1 (mod NST) is free
-                ring_step(which, it + k, Qst[k], Ost[k], Fst[k], Qst[(k + P) % NST], Ost[(k + P) % NST], Fst[(k + P) % NST]);
-            }
+        for (int r = 0; r < 16; ++r) {
+            acc[i][r] = 0.f;
+            acc2[i][r] = 0.f;
         }
-        // everything still in flight (tiles past the end: zeros) lands, and every wave is done reading, before the
-        // stages are reused by the next pass or the workgroup's LDS is released
-        __syncthreads();
-    };
-    if constexpr (ONE_PASS) {
-        pass(std::integral_constant<int, 2>{});
-        store(acc2, (nq + nkv + g) * HD, 1.f);
-        store(acc, (nq + g) * HD, scale);
-    } else {
-        pass(std::integral_constant<int, 0>{});
-        store(acc, (nq + nkv + g) * HD, 1.f);
-        pass(std::integral_constant<int, 1>{});
-        store(acc, (nq + g) * HD, scale);
+#pragma unroll
+    for (int k = 0; k < NST - 1; ++k) issue(k, Qst[k], Ost[k], Fst[k]);
+    for (int it = 0; it < niter; it += NST) {
+#pragma unroll
+        for (int k = 0; k < NST; ++k) {
+            constexpr int P = NST - 1;                      // stage k holds tile it + k; stage k - 1 (mod NST) is free
+            ring_step(it + k, Qst[k], Ost[k], Fst[k], Qst[(k + P) % NST], Ost[(k + P) % NST], Fst[(k + P) % NST]);
+        }
     }
+    // everything still in flight (tiles past the end: zeros) lands before the workgroup's LDS is released
+    dma_publish_barrier();
+    store(acc2, (nq + nkv + g) * HD, 1.f);
+    store(acc, (nq + g) * HD, scale);
 }
 
 // dqkv[:, K and V columns] = bf16(dkv_acc); w = 2 * nkv * HD fp32 per token, 4 per thread
