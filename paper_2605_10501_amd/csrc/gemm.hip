@@ -852,7 +852,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams
 //     least six phases (1.5 K tiles) before it is read, instead of one K tile in gemm_bf16_fast_kernel, and the wait
 //     is for all but the 10 youngest loads of a wave, never for all of them.
 //   * Same tile order, MFMA and order of K as the other tiles: bit-identical results.
-// Measured against gemm_bf16_fast_kernel<256, 256> on one box (M x N x K, us): where the operands come past the 256 MB
+// Measured against gemm_bf16_fast_kernel<256, 256> on one MI355X (M x N x K, us): where the operands come past the 256 MB
 // Infinity Cache the longer lead wins (32768 x 4096 x 11008 2098 -> 1962, 46173 x 1280 x 5120 495 -> 462,
 // 32768 x 1536 x 17920 1328 -> 1227, SwiGLU 32768 x 22016 x 4096 4308 -> 4028); where they stay in it the two are equal
 // (8192^3 704 / 707, 32768 x 6144 x 4096 1125 / 1117) and a short K loses (32768 x 2048 x 1536 154 / 160).  With all eight A
