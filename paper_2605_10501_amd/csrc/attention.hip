@@ -215,6 +215,34 @@ __device__ __forceinline__ void mfma_cols(f32x4 *acc, const ColFrag<HD> &x, cons
 #pragma unroll
         for (int f = 0; f < HD / 16; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[f][r], w[r], acc[f], 0, 0, 0);
 }
+// The same for a block on the causal diagonal, where some weights are zeros of masked pairs.  Zero times an infinite or
+// NaN element would reach columns that never see its row, so a block that holds one adds up the visible pairs one by
+// one: rows after the column's own token (BELOW = false, keys of a query) or before it (BELOW = true, queries of a key)
+// are left out.
+template <int HD, bool BELOW>
+__device__ __forceinline__ void mfma_cols_diagonal(f32x4 *acc, const ColFrag<HD> &x, const float *w, const float *X, long ld, int row0,
+                                                   int row_end, int col_token, int lane) {
+    float z = 0.f;
+#pragma unroll
+    for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z += x.v[f][r] * 0.f;               // NaN if any element is not finite
+    if (!__any(z != z)) {
+        mfma_cols<HD>(acc, x, w);
+        return;
+    }
+    for (int kk = 0; kk < kF32Tile; ++kk) {
+        const float w0 = __shfl(w[0], (kk >> 2) * 16 + (lane & 15), 64), w1 = __shfl(w[1], (kk >> 2) * 16 + (lane & 15), 64);
+        const float w2 = __shfl(w[2], (kk >> 2) * 16 + (lane & 15), 64), w3 = __shfl(w[3], (kk >> 2) * 16 + (lane & 15), 64);
+        const float wk = (kk & 3) == 0 ? w0 : (kk & 3) == 1 ? w1 : (kk & 3) == 2 ? w2 : w3;
+        const int row = row0 + kk;
+        if (row >= row_end || (BELOW ? row < col_token : row > col_token)) continue;
+#pragma unroll
+        for (int f = 0; f < HD / 16; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[f][r] += wk * X[(long)row * ld + 16 * f + 4 * (lane >> 4) + r];
+    }
+}
 __device__ __forceinline__ float cols_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
 __device__ __forceinline__ float cols_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
 
@@ -267,7 +295,8 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float *__restri
         for (int f = 0; f < HD / 16; ++f)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[f][r] *= corr;
-        mfma_cols<HD>(acc, vc, p);
+        if (causal && k0 + kF32Tile > q0) mfma_cols_diagonal<HD, false>(acc, vc, p, qkv + (long)(nq + nkv + g) * HD, ld, k0, s1, q, lane);
+        else mfma_cols<HD>(acc, vc, p);
     }
 #pragma unroll
     for (int f = 0; f < HD / 16; ++f)
@@ -361,7 +390,8 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
                 const int key = k0 + 4 * (lane >> 4) + r;
                 ds[r] = key < kend && (!causal || key <= own) ? __expf(s[r] * scale - L) * (dp[r] - delta) : 0.f;
             }
-            mfma_cols<HD>(acc[0], kc, ds);
+            if (causal && k0 + kF32Tile > r0) mfma_cols_diagonal<HD, false>(acc[0], kc, ds, K, ld, k0, s1, own, lane);
+            else mfma_cols<HD>(acc[0], kc, ds);
         }
         reduce(acc[0], dqkv + (long)h * HD, scale);
         return;
@@ -391,8 +421,13 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
                 p[r] = ok ? __expf(s[r] * scale - Lr) : 0.f;
                 ds[r] = ok ? p[r] * (dp[r] - dr) : 0.f;
             }
-            mfma_cols<HD>(acc[0], qc, ds);
-            mfma_cols<HD>(acc[1], dc, p);
+            if (causal && q0 < r0 + kF32Tile) {
+                mfma_cols_diagonal<HD, true>(acc[0], qc, ds, Q, ld, q0, s1, own, lane);
+                mfma_cols_diagonal<HD, true>(acc[1], dc, p, dO, ldo, q0, s1, own, lane);
+            } else {
+                mfma_cols<HD>(acc[0], qc, ds);
+                mfma_cols<HD>(acc[1], dc, p);
+            }
         }
     }
     reduce(acc[0], dqkv + (long)(nq + g) * HD, scale);

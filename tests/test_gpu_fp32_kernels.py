@@ -64,3 +64,30 @@ def test_attention_fp32_edges(hd, nq, nkv, causal, lens):
     dqkv = B.k_attention_backward(qkv, o, lse, d_o, batch, nq, nkv, hd, causal)
     assert_parity(dqkv, x.grad.numpy(), TOL_F32, "dqkv")
     assert torch.equal(dqkv, B.k_attention_backward(qkv, o, lse, d_o, batch, nq, nkv, hd, causal))   # no atomics
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_causal_masked_pairs_never_meet(hd, bad):
+    """A non-finite key, value, query or output gradient only reaches the tokens that see it, tile mates or not."""
+    n, nq, t = 40, 2, 21
+    # a tile that holds such an element adds up in another order: at most 40 terms, |w x| summed below 40: 40 * 2^-24 * 40
+    same = lambda a, c: bool(torch.isfinite(a).all()) and float((a - c).abs().max()) <= 1e-4
+    batch = B.Batch([0, n])
+    qkv, d_o = dev(f"mq{hd}", (n, 3 * nq * hd)), dev(f"md{hd}", (n, nq * hd))
+    o, lse = B.k_attention_forward(qkv, batch, nq, nq, hd, True)
+    dqkv = B.k_attention_backward(qkv, o, lse, d_o, batch, nq, nq, hd, True)
+    x = qkv.clone()
+    x[t, nq * hd:] = bad                                      # key and value of token t: earlier tokens do not see them
+    o1, lse1 = B.k_attention_forward(x, batch, nq, nq, hd, True)
+    assert same(o1[:t], o[:t]) and same(lse1[:, :t], lse[:, :t]) and not torch.isfinite(o1[t:]).all()
+    d1 = B.k_attention_backward(x, o1, lse1, d_o, batch, nq, nq, hd, True)
+    assert same(d1[:t, :nq * hd], dqkv[:t, :nq * hd])
+    x = qkv.clone()
+    x[t, :nq * hd] = bad                                      # query and output gradient of token t: later keys are not seen
+    d2o = d_o.clone()
+    d2o[t] = bad
+    o2, lse2 = B.k_attention_forward(x, batch, nq, nq, hd, True)
+    d2 = B.k_attention_backward(x, o2, lse2, d2o, batch, nq, nq, hd, True)
+    assert same(o2[:t], o[:t]) and same(o2[t + 1:], o[t + 1:])
+    assert same(d2[t + 1:], dqkv[t + 1:]) and same(d2[:t, :nq * hd], dqkv[:t, :nq * hd])
