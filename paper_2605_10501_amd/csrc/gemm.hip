@@ -24,6 +24,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "launch_plan.h"
 #include "mfma_tiles.h"
 #include <type_traits>
 #include <utility>
@@ -1068,14 +1069,15 @@ template <bool TRANS, bool FAST> struct F32Frag {
 // The 64 x 64 FMA kernel that this replaces took 1.3 us per 16 k (10..80 workgroups, a load latency and two barriers
 // each): 47 us per launch on average in the c1 step, against 6.9 us now.
 // FAST needs 16-byte aligned K-contiguous rows with K % 4 == 0 and operands below 4 GB; the other form covers the rest.
+// (The first slices are requested before the loop, also where K = 0 leaves it nothing to do: the range is then empty.)
 template <bool TA, bool TB, bool FAST>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
     __shared__ float part[4][32][33];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m0 = (int)(blockIdx.x / p.tiles_n) * 32, n0 = (int)(blockIdx.x % p.tiles_n) * 32;
     const int slices = (p.K + 15) / 16, mine = slices > wave ? (slices - wave + 3) / 4 : 0;
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.A, FAST ? ((long)((TA ? p.K : p.M) - 1) * p.lda + (TA ? p.M : p.K)) * 4 : 0);
-    const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.B, FAST ? ((long)((TB ? p.K : p.N) - 1) * p.ldb + (TB ? p.N : p.K)) * 4 : 0);
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.A, FAST ? ms_matrix_extent(TA ? p.K : p.M, TA ? p.M : p.K, p.lda) * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.B, FAST ? ms_matrix_extent(TB ? p.K : p.N, TB ? p.N : p.K, p.ldb) * 4 : 0);
     F32Frag<TA, FAST> a[4];
     F32Frag<TB, FAST> b[4];
     f32x4 acc[2][2];
@@ -1324,7 +1326,8 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
         if (tiles > 0x7fffffffL) return ms_fail(MS_ERR_UNSUPPORTED, "gemm(fp32): %d x %d is too large", M, N);
         const unsigned grid = (unsigned)tiles;
         auto fast = [&](const void *q, long ld, bool trans, long rows) {
-            return (trans || (((uintptr_t)q & 15) == 0 && ld % 4 == 0 && K % 4 == 0)) && (trans ? K : rows) * ld * 4 < (1L << 32) - (1L << 20);
+            return (trans || (((uintptr_t)q & 15) == 0 && ld % 4 == 0 && K % 4 == 0)) &&
+                   ms_buffer_range_ok(trans ? K : rows, trans ? rows : K, ld, 4);
         };
 #define GO(TA, TB)                                                                                     \
     do {                                                                                               \

@@ -1,5 +1,6 @@
 """fp32 GEMM (K split over the waves of a workgroup) and fp32 attention (16-row tiles, waves over every fourth block) at
 the edges of their tiles and splits, against fp64."""
+import ctypes as C
 import math
 
 import pytest
@@ -32,6 +33,31 @@ def test_gemm_fp32_edges(ta, tb, M, N, K):
     out = c.clone()
     B.k_gemm(a, b, ta, tb, c=out, accumulate=True, c_fp32=True, alpha=0.5)
     assert_parity(out, f64(c) + 0.5 * ref, TOL_F32, "accumulate")
+
+
+# nothing to contract: bias, residual and what C holds remain; leading dimensions past the row length, as a slice has them
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,pad", [(1, 1, 0), (33, 70, 2), (64, 31, 1023)])
+def test_gemm_fp32_without_a_contraction(ta, tb, M, N, pad):
+    a = torch.ones((1, (M if ta else 0) + pad + 1), device="cuda")
+    b = torch.ones((1, (N if tb else 0) + pad + 1), device="cuda")
+    bias, res, c = dev("kb", (N,)), dev("kr", (M, N)), dev("kc", (M, N))
+    for accumulate in (0, 1):
+        out = c.clone()
+        B._check(B.lib().ms_k_gemm(B.MS_F32, ta, tb, M, N, 0, C.c_float(2.0), B._p(a), C.c_int64(a.shape[1]), B._p(b), C.c_int64(b.shape[1]),
+                                   B._p(out), C.c_int64(N), 1, accumulate, B._p(bias), B._p(res), C.c_int64(N), 0, 1, B._stream()))
+        assert torch.equal(out, c + (bias + res) if accumulate else bias + res)
+
+
+# rows of A that lie backwards in memory: not for the descriptor
+def test_gemm_fp32_negative_leading_dimension():
+    M, N, K = 37, 20, 24
+    a, b = dev("na", (M, K)), dev("nb", (N, K))
+    out = torch.empty((M, N), device="cuda")
+    last = a[M - 1:]
+    B._check(B.lib().ms_k_gemm(B.MS_F32, 0, 0, M, N, K, C.c_float(1.0), B._p(last), C.c_int64(-K), B._p(b), C.c_int64(K), B._p(out), C.c_int64(N),
+                               1, 0, None, None, C.c_int64(0), 0, 1, B._stream()))
+    assert_parity(out, f64(a)[::-1] @ f64(b).T, TOL_F32)
 
 
 @pytest.mark.parametrize("hd,nq,nkv", [(64, 4, 4), (80, 2, 1), (128, 6, 2)])
