@@ -3,6 +3,7 @@
 // matrix-core kernels live in attention_mfma.hip.
 #include "common.h"
 #include "launch.h"
+#include "launch_plan.h"
 #include "attention.h"
 #include "mfma_tiles.h"
 
@@ -171,7 +172,7 @@ __global__ void dkv_convert_kernel(const float *__restrict__ dkv, T *__restrict_
 // a lane holds four keys (queries) of its own column and the four accumulator registers are the B operand of the next
 // product as they stand.  The fp32 sections are short (16 .. 128 tokens): the kernels are bound by latency, so every
 // operand comes straight from global memory (L2) and nothing is staged.
-constexpr int kF32Tile = 16;
+constexpr int kF32Tile = kF32AttnTile;
 
 // Operand fragments of 16 rows with the contraction over HD: component c of fragment f is element 16 f + 4 (lane / 16) + c.
 template <int HD> struct RowFrag {
@@ -435,8 +436,7 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float *__restri
 }
 
 bool f32_tiles_supported(int hd, int n, int n_seqs, int max_seqlen, int nq, int nkv, int heads, const void *qkv, const void *o) {
-    return (long)n * (nq + 2 * nkv) * hd * 4 < (1L << 32) - (1L << 20) && (hd == 64 || hd == 80 || hd == 128) && max_seqlen > 0 && heads <= 65535 &&
-           (long)n_seqs * ms_cdiv(max_seqlen, kF32Tile) <= 0x7fffffffL && (((uintptr_t)qkv | (uintptr_t)o) & 15) == 0;
+    return ms_f32_attention_tiles(hd, n, n_seqs, max_seqlen, nq, nkv, heads) && (((uintptr_t)qkv | (uintptr_t)o) & 15) == 0;
 }
 
 }  // namespace

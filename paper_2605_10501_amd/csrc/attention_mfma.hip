@@ -13,6 +13,7 @@
 
 #include "attention.h"
 #include "launch.h"
+#include "launch_plan.h"
 #include "mfma_tiles.h"
 
 namespace {
@@ -696,8 +697,8 @@ ms_status launch_fwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
                      void *o, float *lse, hipStream_t s) {
     const int ntile_max = ms_cdiv(max_seqlen, 128);
     const long blocks = attn_grid(nq, n_seqs, ntile_max).blocks;
-    if (blocks > 0x7fffffffL || !ms_attn_offsets_fit(n, nq, nkv, HD))
-        return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets");
+    if (!ms_launch_fits(blocks, 256) || !ms_attn_offsets_fit(n, nq, nkv, HD))
+        return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets or for one launch");
     const float sc = 1.4426950408889634f / sqrtf((float)HD);
     if (causal) attn_fwd_mfma_kernel<HD, true><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (bf16_t *)o, lse, cu, n, nq, nkv, n_seqs, ntile_max, sc);
     else attn_fwd_mfma_kernel<HD, false><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (bf16_t *)o, lse, cu, n, nq, nkv, n_seqs, ntile_max, sc);
@@ -729,8 +730,8 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
     const bool dq2 = split && tiles < 320;
     const long blocks = attn_grid(nq, n_seqs, dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max).blocks;
     const long blocks_kv = attn_grid(split ? nq : nkv, n_seqs, ntile_max).blocks, blocks_dkv = blocks_kv * parts;   // 128 keys each
-    if (blocks > 0x7fffffffL || blocks_dkv > 0x7fffffffL || !ms_attn_offsets_fit(n, nq, nkv, HD))
-        return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets");
+    if (!ms_launch_fits(blocks, 256) || !ms_launch_fits(blocks_dkv, 256) || !ms_attn_offsets_fit(n, nq, nkv, HD))
+        return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets or for one launch");
     const unsigned grid_dkv = (unsigned)blocks_dkv;
     float2 *ld2 = (float2 *)scratch;                       // [nq][n] pairs (lse * log2(e), delta)
     attn_delta_kernel<<<ms_cdiv((long)n * nq * 8, 256), 256, 0, s>>>((const bf16_t *)o, (const bf16_t *)d_o, lse, ld2, n, nq, HD);

@@ -3,6 +3,7 @@
 // arithmetic in fp32 and touches each element once; rows are reduced with wave shuffles.
 #include "common.h"
 #include "launch.h"
+#include "launch_plan.h"
 
 namespace {
 
@@ -714,7 +715,8 @@ ms_status launch_fill_f32(float *p, long n, float v, hipStream_t s) {
 namespace {
 template <class TS, class TD>
 ms_status convert(const TS *src, TD *dst, long n, hipStream_t s) {
-    const long n8 = aligned16(src) && aligned16(dst) ? n / 8 : 0, rest = n - 8 * n8;
+    const long one_launch = kLaunchThreads / 256 * 256;   // the other form covers what is left
+    const long n8 = aligned16(src) && aligned16(dst) ? (n / 8 < one_launch ? n / 8 : one_launch) : 0, rest = n - 8 * n8;
     if (ms_cdiv(n8, 256) > 0) convert_vec_kernel<TS, TD><<<ms_cdiv(n8, 256), 256, 0, s>>>(src, dst, n8);
     if (rest > 0) {
         const int grid = ms_cdiv(rest, 256) > 16384 ? 16384 : ms_cdiv(rest, 256);

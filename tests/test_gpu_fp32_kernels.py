@@ -60,6 +60,33 @@ def test_gemm_fp32_negative_leading_dimension():
     assert_parity(out, f64(a)[::-1] @ f64(b).T, TOL_F32)
 
 
+# more than 2^24 output tiles: beyond what one row of workgroups may hold
+def test_gemm_fp32_with_very_many_tiles():
+    N = 32 * (1 << 24) + 40
+    b = torch.arange(N, device="cuda").remainder_(8191).to(torch.float32).view(1, N)
+    out = B.k_gemm(torch.full((1, 1), 3.0, device="cuda"), b, False, True)
+    assert torch.equal(out, b.mul_(3.0))
+
+
+# very many sequences under a large bound on their length: more 16-row tiles than one launch holds
+def test_attention_fp32_very_many_sequences():
+    ones, tail, hd = 100_000, 70, 64
+    batch, n = B.Batch(list(range(ones + 1)) + [ones + tail]), ones + tail
+    batch.max_seqlen = 4096
+    qkv, d_o = dev("vm", (n, 3 * hd)), dev("vmo", (n, hd))
+    o, lse = B.k_attention_forward(qkv, batch, 1, 1, hd, True)
+    q, k, v = qkv.split(hd, 1)
+    assert torch.equal(o[:ones], v[:ones])                    # a sequence of one token returns its value
+    assert_parity(lse[0, :ones], f64((q * k).sum(1)[:ones]) / 8.0, TOL_F32)
+    dqkv = B.k_attention_backward(qkv, o, lse, d_o, batch, 1, 1, hd, True)
+    assert float(dqkv[:ones, :2 * hd].abs().max()) < 1e-4 and float((dqkv[:ones, 2 * hd:] - d_o[:ones]).abs().max()) < 1e-4
+    small = B.Batch([0, tail])
+    xt, dt = qkv[ones:].contiguous(), d_o[ones:].contiguous()
+    o2, lse2 = B.k_attention_forward(xt, small, 1, 1, hd, True)
+    assert_parity(o[ones:], f64(o2), TOL_F32)
+    assert_parity(dqkv[ones:], f64(B.k_attention_backward(xt, o2, lse2, dt, small, 1, 1, hd, True)), TOL_F32)
+
+
 @pytest.mark.parametrize("hd,nq,nkv", [(64, 4, 4), (80, 2, 1), (128, 6, 2)])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("lens", [[1], [15, 16, 17], [64, 0, 65, 130]])

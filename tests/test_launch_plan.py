@@ -47,3 +47,21 @@ def test_what_a_descriptor_cannot_address(plan):
     assert ok(1, 1 << 29, 0, 4) and not ok(1, 1 << 30, 0, 4)          # one long row counts with a zero stride as well
     assert ok(4, 8, 0, 4) and not ok(4, 8, -8, 4) and ok(1, 8, -8, 4)  # rows that go backwards are outside the range
     assert ok(0, 8, 8, 4) and ok(8, 0, 8, 4)
+
+
+@pytest.mark.parametrize("wgs", [1, 255, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, 3 * (1 << 24) + 7, (1 << 31) - 1])
+def test_grids_stay_below_the_thread_limit(plan, wgs):
+    xy = (C.c_uint * 2)()
+    plan.plan_fold_grid(C.c_long(wgs), 256, xy)
+    x, y = xy
+    assert x * 256 < 1 << 32 and y <= 65535 and wgs <= x * y < wgs + (1 << 20)
+    assert (y == 1) == (wgs < 1 << 24) == bool(plan.plan_launch_fits(C.c_long(wgs), 256))
+
+
+def test_fp32_attention_tiles_only_where_the_grid_can_be_launched(plan):
+    f = lambda n, seqs, longest, hd=64, nq=4, nkv=4, heads=4: bool(
+        plan.plan_f32_attention_tiles(hd, C.c_long(n), C.c_long(seqs), C.c_long(longest), nq, nkv, heads))
+    assert f(293, 4, 128) and f(8192, 1, 8192) and f(8192, 1, 8192, 80) and f(8192, 1, 8192, 128)
+    assert not f(293, 4, 128, 96) and not f(293, 4, 0) and not f(293, 4, 128, heads=65536)
+    assert not f(104_096, 100_001, 4096) and f(104_096, 65_535, 4096) and not f(104_096, 65_536, 4096)   # 2^24 workgroups
+    assert not f(1 << 21, 1 << 11, 1024, 128, 8, 8, 8)                                                   # qkv above 4 GB
