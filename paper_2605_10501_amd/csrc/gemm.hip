@@ -636,8 +636,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
 // NST = LDS stages: two (a K tile is requested one tile time before its first use, which is what the big tile's LDS
 // allows) or a deeper ring for grids that leave CUs with one workgroup, where a tile time is shorter than the latency
 // of a load (see kTiles).
+// The attribute only adds to what the launch bounds say for the two-stage 128 x 128 kernel with the dz epilogue: left to
+// itself the compiler gives it 276 registers, which leave a CU with one workgroup, instead of 173 (dz at
+// 3629 x 4480 x 1536: 70.9 us; 74.2 on v_mfma_f32_32x32x16, which needs fewer).
+constexpr int fast_waves_per_simd(int bm, int waves, int epi, int nst) { return waves == 8 || (bm == 128 && nst == 2 && epi == EPI_KD_DZ) ? 2 : 1; }
 template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI = EPI_NONE, bool M16 = false, int NST = 2>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_fast_kernel(GemmParams p) {
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI, NST)))) void gemm_bf16_fast_kernel(GemmParams p) {
     constexpr int NT = 64 * WM * WN;
     constexpr int FR = M16 ? 16 : 32;                         // rows of an MFMA fragment / accumulator block
     constexpr int KSTEP = M16 ? 32 : 16, KS = BK / KSTEP;     // contraction depth of an MFMA, k-steps per K tile
@@ -1168,8 +1172,8 @@ MS_INST_EPI(EPI_KD_DZ); MS_INST_EPI(EPI_KD_STATS); MS_INST_EPI(EPI_SWIGLU);
 #undef MS_INST_EPI
 
 // Kernel selection switches, for measurements and tests only: the environment gives the process-wide setting
-// (MS_GEMM_TILE = 128 / 256 forces the fast kernels' tile, -1 disables them; MS_GEMM_MFMA16 = 0 selects
-// v_mfma_f32_32x32x16_bf16), ms_k_gemm_config overrides it at run time.  The overrides are atomics, so changing them
+// (MS_GEMM_TILE = a tile code of kTiles, or 256256, forces the fast kernels' tile, -1 disables them; MS_GEMM_MFMA16 = 0
+// selects v_mfma_f32_32x32x16_bf16 and the two-stage tiles), ms_k_gemm_config overrides it at run time.  The overrides are atomics, so changing them
 // from one thread while another launches is defined, but which setting a concurrent launch sees is not: production
 // callers leave them alone (automatic choice by shape).
 constexpr int kUnset = -1000;
@@ -1233,9 +1237,12 @@ int choose_tile(int M, int N, int kt) {
 template <int BM, int BN, int WM, int WN, int NST, int EPI>
 void launch_fast_tile(const GemmParams &p, int ta, int tb, dim3 grid, hipStream_t s) {
     constexpr int NT = 64 * WM * WN;
-#define GO(TA, TB)                                                                                                           do {                                                                                                                         if constexpr (NST > 2) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true, NST><<<grid, NT, 0, s>>>(p);             else if (use_mfma16() && !(BM == 128 && EPI == EPI_KD_DZ))                                                                   gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true><<<grid, NT, 0, s>>>(p);                                     else gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, false><<<grid, NT, 0, s>>>(p);                               } while (0)
-    // (the 128 x 128 dz variant on 16-row fragments would need more than the 256 registers that let two workgroups
-    // share a CU)
+#define GO(TA, TB)                                                                                                  \
+    do {                                                                                                            \
+        if constexpr (NST > 2) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true, NST><<<grid, NT, 0, s>>>(p); \
+        else if (use_mfma16()) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true><<<grid, NT, 0, s>>>(p);      \
+        else gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, false><<<grid, NT, 0, s>>>(p);                       \
+    } while (0)
     if constexpr (EPI != EPI_NONE) GO(false, false);
     else if (!ta && !tb) GO(false, false);
     else if (!ta && tb) GO(false, true);
