@@ -1189,50 +1189,8 @@ bool use_mfma16() {
     return o != kUnset ? o != 0 : env;
 }
 
-// The fast kernel's workgroup tiles.  256 x 256 and 128 x 128 have two LDS stages; a K tile is then requested one tile
-// time before its first use, which covers the latency of the load only when the CU is busy with a large tile (256) or
-// a second workgroup (128).  The ring tiles keep two or three tiles in flight and are for grids that do not fill the
-// chip with those: at one workgroup per CU the two-stage 128 x 128 kernel takes 0.61 us per K tile, the ring kernel of
-// the same tile 0.36, and smaller tiles spread a small output over more CUs.
-// us_per_ktile are fits to a sweep over M = 300 .. 10000, N = 1024 .. 8192, K = 1024 .. 17920 (K-contiguous and K-major
-// B) on MI355X: time per 64-deep K tile with one workgroup per CU, few and all CUs busy (the L2s and the power budget
-// are shared), then with two per CU, few and all CUs with a second one.  us_round = prologue and epilogue of a round.
-struct TileShape {
-    int code, bm, bn, per_cu;
-    double us_per_ktile[4], us_round;
-};
-enum { T256 = 0, T128 = 1, R128 = 2, R128x256 = 3, R64x128 = 4, R64 = 5, kNumTiles = 6 };
-constexpr int kPingPong = 256256;       // forced tile: 256 x 256 with the ping-pong kernel where it applies
-constexpr TileShape kTiles[kNumTiles] = {
-    {256, 256, 256, 1, {1.08, 1.48, 0, 0}, 3.5},          {128, 128, 128, 2, {0.60, 0.70, 0.78, 0.97}, 1.8},
-    {128128, 128, 128, 1, {0.36, 0.47, 0, 0}, 1.5},       {128256, 128, 256, 1, {0.60, 0.80, 0, 0}, 2.5},
-    {64128, 64, 128, 2, {0.33, 0.38, 0.54, 0.68}, 1.3},   {64064, 64, 64, 2, {0.285, 0.32, 0.35, 0.41}, 1.2}};
-
-// Estimated time (us) of a grid of `wgs` workgroups with kt K tiles each: full rounds of the chip, then the rest.
-double tile_time(const TileShape &t, long wgs, int kt) {
-    const long slots = 256L * t.per_cu, full = wgs / slots, rest = wgs % slots;
-    const double *u = t.us_per_ktile;
-    double est = full * (kt * u[2 * t.per_cu - 1] + t.us_round);
-    if (rest > 256) est += kt * (u[2] + (u[3] - u[2]) * (rest - 256) / 256) + t.us_round;
-    else if (rest > 0) est += kt * (u[0] + (u[1] - u[0]) * rest / 256) + t.us_round;
-    return est;
-}
-
-// The tile with the least estimated time for an M x N output (N = rows of B) of kt K tiles.  Every tile adds up K in
-// the same order (one accumulator per element, ascending K, the same MFMA), so the choice does not change results: the
-// rows of a short micro-batch come out as they do in a long one.
-int choose_tile(int M, int N, int kt) {
-    const int forced = forced_tile();
-    const bool m16 = use_mfma16();
-    int best = T128;
-    double best_us = 1e30;
-    for (int i = 0; i < kNumTiles; ++i) {
-        if (forced > 0 ? kTiles[i].code != (forced == kPingPong ? 256 : forced) : (!m16 && i > T128)) continue;
-        const double us = tile_time(kTiles[i], (long)ms_cdiv(M, kTiles[i].bm) * ms_cdiv(N, kTiles[i].bn), kt);
-        if (us < best_us) { best_us = us; best = i; }
-    }
-    return best;
-}
+// The tile for an M x N output (N = rows of B) of kt K tiles whose epilogue moves out_bytes per element (ms_choose_tile)
+int choose_tile(int M, int N, int kt, double out_bytes) { return ms_choose_tile(M, N, kt, out_bytes, forced_tile(), use_mfma16()); }
 
 template <int BM, int BN, int WM, int WN, int NST, int EPI>
 void launch_fast_tile(const GemmParams &p, int ta, int tb, dim3 grid, hipStream_t s) {
@@ -1254,7 +1212,7 @@ void launch_fast_tile(const GemmParams &p, int ta, int tb, dim3 grid, hipStream_
 // p.tiles_m / tiles_n are set here; EPI_SWIGLU tiles cover bn / 2 output columns (gate and up rows of B)
 template <int EPI>
 ms_status launch_bf16_fast(GemmParams &p, int tile, int ta, int tb, int splits, double flops, hipStream_t s) {
-    const TileShape &t = kTiles[tile];
+    const MsTile &t = kTiles[tile];
     p.tiles_m = ms_cdiv(p.M, t.bm);
     p.tiles_n = ms_cdiv(p.N, EPI == EPI_SWIGLU ? t.bn / 2 : t.bn);
     dim3 grid(p.tiles_m * p.tiles_n, splits);
@@ -1309,7 +1267,7 @@ ms_status launch_bf16(const GemmParams &p, int ta, int tb, int splits, hipStream
 
 extern "C" ms_status ms_k_gemm_config(int32_t tile, int32_t mfma16) {
     bool known = tile == -1 || tile == 0 || tile == kPingPong;
-    for (const TileShape &t : kTiles) known = known || tile == t.code;
+    for (const MsTile &t : kTiles) known = known || tile == t.code;
     if (!known || mfma16 < -1 || mfma16 > 1)
         return ms_fail(MS_ERR_INVALID_ARG, "gemm_config: tile must be -1, 0, 128, 256, 256256, 128128, 128256, 64128 or 64064 and mfma16 -1, 0 or 1");
     g_tile_override = tile == 0 ? kUnset : tile;
@@ -1372,27 +1330,15 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
                       (rows_b + 256) * ldb * 2 < lim && ((long)M + 256) * ldc * 4 < lim &&
                       (!residual || ((long)M + 256) * ldr * 4 < lim);
     const int kt_total = ms_cdiv(K, BK) < 1 ? 1 : ms_cdiv(K, BK);
-    int tile = fast ? choose_tile(M, N, kt_total) : T128;
+    const double out_bytes = (c_fp32 ? 4 : 2) + (residual ? (residual_fp32 ? 4 : 2) : 0) + (accumulate ? 4 : 0);
+    int tile = fast ? choose_tile(M, N, kt_total, out_bytes) : T128;
     int splits = split_k;
     if (splits <= 0) {  // automatic: only when accumulating into fp32 (weight gradients: small M x N, long K)
         splits = 1;
         if (accumulate && c_fp32 && fast) {
-            // Tile and number of K splits together, by the tiles' estimated time plus what the output costs: a read and
-            // a write of C without splits, one pass of fp32 atomics per split (1.6 TB/s) and the second round of
-            // prologues with them.  Above 256 K tiles the operands stream from HBM, where the smaller ring tiles lose
-            // 25-45 % (M = N = 1024, K = 32768: 221-285 us unsplit, 90-110 us for the tiles left in) and 128 x 256 12 %.
-            double best = 1e30;
-            for (int i = 0; i < kNumTiles; ++i) {
-                const TileShape &t = kTiles[i];
-                if (forced > 0 ? t.code != (forced == kPingPong ? 256 : forced) : ((!use_mfma16() && i > T128) || (kt_total > 256 && i > T128 && i != R128x256))) continue;
-                const double stream = kt_total > 256 && i == R128x256 ? 1.12 : 1.0;
-                const long tiles = (long)ms_cdiv(M, t.bm) * ms_cdiv(N, t.bn);
-                for (int sp = 1; sp <= 8 && (sp == 1 || kt_total / sp >= 8); ++sp) {
-                    const double est = stream * tile_time(t, tiles * sp, ms_cdiv(kt_total, sp)) +
-                                       (sp > 1 ? 2.5e-6 * M * N * sp + 4.0 : 1.6e-6 * M * N);
-                    if (est < best) { best = est; splits = sp; tile = i; }
-                }
-            }
+            const MsSplit c = ms_choose_split(M, N, kt_total, forced, use_mfma16());
+            tile = c.tile;
+            splits = c.splits;
         } else if (accumulate && c_fp32) {
             const int tiles = ms_cdiv(M, 128) * ms_cdiv(N, 128);
             while (tiles * splits < 512 && kt_total / (splits * 2) >= 8) splits *= 2;
@@ -1437,7 +1383,7 @@ ms_status gemm_kd_epilogue(int mode, int M, int N, int K, const void *A, long ld
     p.c_fp32 = dz_fp32;
     p.kd_zt = zt; p.kd_ldz = ldz; p.kd_stats = stats; p.kd_part = part; p.kd_nparts = nparts; p.kd_inv_t = inv_t; p.kd_coef = coef;
     p.k_tiles_per_split = ms_cdiv(K, BK);
-    const int tile = choose_tile(M, N, p.k_tiles_per_split);
+    const int tile = choose_tile(M, N, p.k_tiles_per_split, kKdEpilogueBytes);
     if (mode == EPI_KD_DZ) return launch_bf16_fast<EPI_KD_DZ>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
     return launch_bf16_fast<EPI_KD_STATS>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
 }
@@ -1463,7 +1409,7 @@ ms_status gemm_swiglu(int M, int F, int K, const void *A, long lda, const void *
     p.A = A; p.B = W; p.C = act; p.lda = lda; p.ldb = ldw; p.ldc = ldact; p.M = M; p.N = F; p.K = K; p.alpha = 1.f;
     p.sg_f = F; p.sg_gu = gate_up; p.sg_ldgu = ldgu;
     p.k_tiles_per_split = ms_cdiv(K, BK);
-    return launch_bf16_fast<EPI_SWIGLU>(p, choose_tile(M, 2 * F, p.k_tiles_per_split), 0, 0, 1, 4.0 * M * F * K, s);
+    return launch_bf16_fast<EPI_SWIGLU>(p, choose_tile(M, 2 * F, p.k_tiles_per_split, gate_up ? 3 : 1), 0, 0, 1, 4.0 * M * F * K, s);
 }
 
 extern "C" ms_status ms_k_gemm_swiglu(int32_t M, int32_t F, int32_t K, const void *A, int64_t lda, const void *W, int64_t ldw,

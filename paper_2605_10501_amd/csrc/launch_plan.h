@@ -32,3 +32,100 @@ constexpr bool ms_f32_attention_tiles(int hd, long n, long n_seqs, long max_seql
     return (hd == 64 || hd == 80 || hd == 128) && n * (nq + 2 * nkv) * hd * 4 < kBufferBytes && max_seqlen > 0 && heads <= 65535 &&
            ms_launch_fits(n_seqs * ((max_seqlen + kF32AttnTile - 1) / kF32AttnTile), 256);
 }
+
+// ------------------------------------------------------------------ workgroup tiles of the bf16 GEMMs
+// 256 x 256 and 128 x 128 have two LDS stages; a K tile is then requested one tile time before its first use, which covers
+// the latency of the load only when the CU is busy with a large tile (256) or a second workgroup (128).  The ring tiles
+// keep two or three tiles in flight and are for grids that do not fill the chip with those: at one workgroup per CU the
+// two-stage 128 x 128 kernel takes 0.61 us per K tile, the ring kernel of the same tile 0.36, and smaller tiles spread a
+// small output over more CUs.
+// Times are fits to sweeps on MI355X:
+//   us_per_ktile: per 64-deep K tile with one workgroup per CU, few and all CUs busy (the L2s and the power budget are
+//   shared), then with two per CU, few and all CUs with a second one;
+//   us_round + us_out x bytes: prologue and epilogue of a round, the latter by what it reads and writes per output
+//   element, for 256 x 256 elements;  us_call: once.
+// `lin` (K-contiguous A) is fitted to what decides, the times of a shape's better tiles relative to each other, over 1278
+// shapes (M = 128 .. 46000, N = 512 .. 22016, K = 512 .. 17920, K-contiguous and K-major B, bf16 / fp32 outputs, fp32
+// residual, SwiGLU and KD epilogues; half of them choose as well for the other half).  `wgrad` (both operands K-major, +=
+// into fp32) is a fit to such products of 300 .. 32768 tokens, in which the output has terms of its own.
+struct MsTileTimes { double us_per_ktile[4], us_round, us_out, us_call; };
+struct MsTile {
+    int code, bm, bn, per_cu;
+    MsTileTimes lin, wgrad;
+};
+enum { T256 = 0, T128 = 1, R128 = 2, R128x256 = 3, R64x128 = 4, R64 = 5, kNumTiles = 6 };
+constexpr int kPingPong = 256256;       // forced tile: 256 x 256 with the ping-pong kernel where it applies
+constexpr MsTile kTiles[kNumTiles] = {
+    {256, 256, 256, 1, {{0.852, 1.483, 0, 0}, 1.58, 2.35, 0}, {{1.08, 1.48, 0, 0}, 3.5, 0, 0}},
+    {128, 128, 128, 2, {{0.450, 0.618, 0.778, 0.949}, 0.10, 4.28, 3.03}, {{0.60, 0.70, 0.78, 0.97}, 1.8, 0, 0}},
+    {128128, 128, 128, 1, {{0.289, 0.476, 0, 0}, 1.41, 2.43, 2.48}, {{0.36, 0.47, 0, 0}, 1.5, 0, 0}},
+    {128256, 128, 256, 1, {{0.474, 0.813, 0, 0}, 2.33, 2.58, 1.74}, {{0.60, 0.80, 0, 0}, 2.5, 0, 0}},
+    {64128, 64, 128, 2, {{0.236, 0.324, 0.554, 0.593}, 0.34, 3.74, 3.92}, {{0.33, 0.38, 0.54, 0.68}, 1.3, 0, 0}},
+    {64064, 64, 64, 2, {{0.200, 0.235, 0.297, 0.365}, 0.91, 6.33, 3.47}, {{0.285, 0.32, 0.35, 0.41}, 1.2, 0, 0}}};
+// What the KD epilogues cost in the same unit: 4 bytes of teacher logits, the exponentials, 2 bytes of dz or the statistics
+constexpr double kKdEpilogueBytes = 8;
+
+inline long ms_tiles(const MsTile &t, long M, long N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
+// Estimated time (us) of a grid of `wgs` workgroups with kt K tiles each: full rounds of the chip, then the rest.
+inline double ms_tile_time(const MsTile &t, const MsTileTimes &c, long wgs, int kt, double out_bytes) {
+    const long slots = 256L * t.per_cu, full = wgs / slots, rest = wgs % slots;
+    const double *u = c.us_per_ktile, fix = c.us_round + c.us_out * out_bytes * t.bm * t.bn / 65536.0;
+    double est = c.us_call + full * (kt * u[2 * t.per_cu - 1] + fix);
+    if (rest > 256) est += kt * (u[2] + (u[3] - u[2]) * (rest - 256) / 256) + fix;
+    else if (rest > 0) est += kt * (u[0] + (u[1] - u[0]) * rest / 256) + fix;
+    return est;
+}
+
+// The two-stage tile by occupancy: 256 x 256 runs about 1.25 times the rate of 128 x 128 where the grid fills whole rounds.
+inline int ms_two_stage_tile(long M, long N) {
+    const long a = ms_tiles(kTiles[T256], M, N), b = ms_tiles(kTiles[T128], M, N);
+    const double ea = (double)a / ((a + 255) / 256 * 256), eb = (double)b / ((b + 511) / 512 * 512);
+    return a >= 192 && 1.25 * ea > eb ? T256 : T128;
+}
+inline bool ms_tile_allowed(int i, int forced, bool mfma16) {
+    return forced > 0 ? kTiles[i].code == (forced == kPingPong ? 256 : forced) : (mfma16 || i <= T128);
+}
+
+// The tile with the least estimated time, if that is clearly less than the time of the two-stage tile by occupancy.  Ties do
+// not decide: without a margin, and with times that did not know the output, 128 x 256 displaced 256 x 256 and 128 x 128 on
+// estimates 0.2-6 % apart and lost up to 18 % (2494 x 8192 x 1024 with fp32 output: 60.9 us instead of 51.3; 6500 x 8192 x
+// 4096: 386.9 instead of 358.5).  Over the sweep the choice is 1.23 times as fast as the two-stage tile in the mean, never
+// more than 4.5 % slower (3 shapes of 1278 by more than 2.5 %), and 0.4 % from the best tile.
+// Every tile adds up K in the same order (one accumulator per element, ascending K), so the choice does not change
+// results: the rows of a short micro-batch come out as they do in a long one.
+constexpr double kTileMargin = 0.03;
+inline int ms_choose_tile(long M, long N, int kt, double out_bytes, int forced, bool mfma16) {
+    int best = -1;
+    double best_us = 1e30;
+    for (int i = 0; i < kNumTiles; ++i) {
+        if (!ms_tile_allowed(i, forced, mfma16)) continue;
+        const double us = ms_tile_time(kTiles[i], kTiles[i].lin, ms_tiles(kTiles[i], M, N), kt, out_bytes);
+        if (us < best_us) { best_us = us; best = i; }
+    }
+    if (forced > 0) return best < 0 ? T128 : best;
+    const int base = ms_two_stage_tile(M, N);
+    const double base_us = ms_tile_time(kTiles[base], kTiles[base].lin, ms_tiles(kTiles[base], M, N), kt, out_bytes);
+    return best_us < (1 - kTileMargin) * base_us ? best : base;
+}
+
+// Weight gradients (small M x N, long K, += into fp32): tile and number of K splits together, by the tiles' estimated time
+// plus what the output costs: a read and a write of C without splits, one pass of fp32 atomics per split (1.6 TB/s) and the
+// second round of prologues with them.  Above 200 K tiles the operands stream from HBM, where the smaller ring tiles lose
+// 10-45 % (M = N = 1024, K = 32768: 221-285 us unsplit, 90-110 us for the tiles left in; 2048 x 1536, K = 14294: 129 us
+// against 116) and 128 x 256 12 % (5632 x 1024, K = 14810: 221 us against 198 for 256 x 256 in two splits).
+struct MsSplit { int tile, splits; };
+inline MsSplit ms_choose_split(long M, long N, int kt, int forced, bool mfma16) {
+    MsSplit c = {T128, 1};
+    double best = 1e30;
+    for (int i = 0; i < kNumTiles; ++i) {
+        if (!ms_tile_allowed(i, forced, mfma16) || (forced <= 0 && kt > 200 && i > T128 && i != R128x256)) continue;
+        const double stream = kt > 200 && i == R128x256 ? 1.12 : 1.0;
+        for (int sp = 1; sp <= 8 && (sp == 1 || kt / sp >= 8); ++sp) {
+            const double est = stream * ms_tile_time(kTiles[i], kTiles[i].wgrad, ms_tiles(kTiles[i], M, N) * sp, (kt + sp - 1) / sp, 0) +
+                               (sp > 1 ? 2.5e-6 * M * N * sp + 4.0 : 1.6e-6 * M * N);
+            if (est < best) { best = est; c.splits = sp; c.tile = i; }
+        }
+    }
+    return c;
+}

@@ -8,3 +8,11 @@ extern "C" void plan_fold_grid(long wgs, int threads, unsigned *xy) { const MsGr
 extern "C" int plan_f32_attention_tiles(int hd, long n, long n_seqs, long max_seqlen, int nq, int nkv, int heads) {
     return ms_f32_attention_tiles(hd, n, n_seqs, max_seqlen, nq, nkv, heads);
 }
+extern "C" int plan_tile(long M, long N, int kt, double out_bytes) { return kTiles[ms_choose_tile(M, N, kt, out_bytes, 0, true)].code; }
+extern "C" int plan_two_stage_tile(long M, long N) { return kTiles[ms_two_stage_tile(M, N)].code; }
+extern "C" int plan_forced_tile(long M, long N, int forced, int mfma16) { return kTiles[ms_choose_tile(M, N, 16, 2, forced, mfma16 != 0)].code; }
+extern "C" void plan_split(long M, long N, int kt, int *out) {
+    const MsSplit c = ms_choose_split(M, N, kt, 0, true);
+    out[0] = kTiles[c.tile].code;
+    out[1] = c.splits;
+}

@@ -65,3 +65,45 @@ def test_fp32_attention_tiles_only_where_the_grid_can_be_launched(plan):
     assert not f(293, 4, 128, 96) and not f(293, 4, 0) and not f(293, 4, 128, heads=65536)
     assert not f(104_096, 100_001, 4096) and f(104_096, 65_535, 4096) and not f(104_096, 65_536, 4096)   # 2^24 workgroups
     assert not f(1 << 21, 1 << 11, 1024, 128, 8, 8, 8)                                                   # qkv above 4 GB
+
+
+def tile(plan, m, n, k, out_bytes=2.0):
+    return plan.plan_tile(C.c_long(m), C.c_long(n), k // 64, C.c_double(out_bytes))
+
+
+# Sizes where 128 x 256 took over on an estimate that was no better than the fit's error and lost 3-18 %: fp32 logits, KD
+# epilogues, SwiGLU with stored pre-activations (3 bytes per accumulator column), section linears
+@pytest.mark.parametrize("m,n,k,out_bytes,code", [
+    (6176, 8192, 2048, 4, 256), (6500, 8192, 4096, 4, 256), (7168, 8192, 2048, 4, 256), (6900, 8192, 2048, 8, 256),
+    (2143, 8192, 1024, 4, 128), (2494, 8192, 1024, 4, 128), (2494, 8192, 1024, 8, 128), (2522, 8192, 2048, 4, 128),
+    (4812, 4096, 1024, 4, 128), (3528, 2 * 2816, 1024, 3, 128), (11204, 1536, 1024, 2, 128), (12503, 4096, 4096, 2, 256),
+    (22889, 5120, 5120, 2, 256), (39872, 1024, 1024, 2, 256)])
+def test_estimates_within_the_fits_error_do_not_displace_a_two_stage_tile(plan, m, n, k, out_bytes, code):
+    assert tile(plan, m, n, k, out_bytes) == code == plan.plan_two_stage_tile(C.c_long(m), C.c_long(n))
+
+
+@pytest.mark.parametrize("m,n,k", [(777, 2048, 2048), (300, 3072, 2048), (1031, 1280, 5120), (2053, 1024, 2816), (64, 64, 64)])
+def test_grids_that_leave_the_chip_idle_take_ring_tiles(plan, m, n, k):
+    assert tile(plan, m, n, k) in (128128, 128256, 64128, 64064)
+
+
+def test_operands_beyond_the_infinity_cache_keep_the_tile_that_has_the_ping_pong_kernel(plan):
+    for n, k in [(1280, 5120), (4096, 11008), (1536, 17920), (1536, 8960), (5120, 5120), (2 * 11008, 4096)]:
+        for m in range(2048, 48000, 331):
+            if 2 * (m + n) * k > 384e6 and plan.plan_two_stage_tile(C.c_long(m), C.c_long(n)) == 256:
+                assert tile(plan, m, n, k) == 256, (m, n, k)
+
+
+def test_forced_tiles(plan):
+    f = lambda forced, mfma16=1: plan.plan_forced_tile(C.c_long(777), C.c_long(2048), forced, mfma16)
+    assert [f(c) for c in (128, 256, 256256, 128128, 128256, 64128, 64064)] == [128, 256, 256, 128128, 128256, 64128, 64064]
+    assert f(0, 0) in (128, 256)                               # 32-row MFMAs: two-stage tiles only
+
+
+def test_long_weight_gradients_keep_the_large_tiles(plan):
+    out = (C.c_int * 2)()
+    for m, n, tokens in [(5632, 1024, 14810), (2048, 1536, 14294), (5120, 1280, 14647), (1024, 1024, 32768), (1536, 8960, 20000)]:
+        plan.plan_split(C.c_long(m), C.c_long(n), -(-tokens // 64), out)
+        assert out[0] in (256, 128, 128256) and 1 <= out[1] <= 8
+    plan.plan_split(C.c_long(1024), C.c_long(1024), 4, out)    # 256 tokens: nothing to split
+    assert out[1] == 1
