@@ -37,17 +37,7 @@ __device__ __forceinline__ bf16x8 pack8(const float *v) {
 // the same whatever the sequence lengths are.  Level 0 is the heaviest tile (the last query tile, the first key
 // block).  Within an XCD the order is chunks of kAttnChunk levels, heaviest chunk first, and within a chunk sequence,
 // head of the class, level: the workgroups that run at one time are neighbouring levels of a few (sequence, head)
-// pairs and read the same K/V (or Q/dO) rows, which then come from L2.
-constexpr int kAttnChunk = 8;
-struct AttnGrid { int S, hpc, M; long blocks; };
-__host__ __device__ inline AttnGrid attn_grid(int heads, int n_seqs, int nlevel_max) {
-    const int low = heads & -heads, G = low < 8 ? low : 8;          // gcd(heads, 8)
-    AttnGrid a;
-    a.S = 8 / G; a.hpc = heads / G;
-    a.M = ((nlevel_max + a.S - 1) / a.S + kAttnChunk - 1) / kAttnChunk * kAttnChunk;   // levels per stripe, whole chunks
-    a.blocks = 8L * a.M * a.hpc * n_seqs;
-    return a;
-}
+// pairs and read the same K/V (or Q/dO) rows, which then come from L2.  (The grid itself: attn_grid, launch_plan.h.)
 struct AttnSlot { int b, h, level; };
 __device__ inline AttnSlot attn_slot(unsigned bid, int heads, int n_seqs, int nlevel_max) {
     const AttnGrid a = attn_grid(heads, n_seqs, nlevel_max);
@@ -284,7 +274,7 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t *__restric
 // accumulator tiles with one query per lane, so P = exp2(S^T c - lse[q]) and
 // dS^T = P (dP^T - delta[q]) use per-lane scalars, and dS^T is the B operand of dQ^T += K^T dS^T
 // with K^T read from the row-major K tile through the transposing LDS load.
-// KS = 2 (grids that leave CUs without a workgroup; see launch_bwd): the workgroup owns 64 queries, waves 0 and 1 visit
+// KS = 2 (few workgroups with long walks; see ms_attention_split): the workgroup owns 64 queries, waves 0 and 1 visit
 // the even key tiles, waves 2 and 3 the odd ones for the same queries, and the two partial sums meet in LDS: twice the
 // workgroups, half the serial chain.
 template <int HD, bool CAUSAL, int KS>
@@ -468,8 +458,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 1
 // better than one.  (NW = 4 with NST = 3 needs 80.75 KB of LDS for head_dim 128, 768 bytes too many for two per CU.)
 // !SPLIT: the sums over the query group stay in registers, no atomics.
 // SPLIT: one workgroup per query head of the group instead of one per K/V head (4x the workgroups and a 4x
-// shorter longest one under grouped-query attention), and of that one per `chunk` query tiles where the grid would
-// leave CUs idle (see launch_bwd); partial dK/dV are then summed with fp32 atomics into dkv_acc [n][2][nkv * HD],
+// shorter longest one under grouped-query attention), and of that one per `chunk` query tiles where few long
+// walks would leave CUs idle (see ms_attention_split); partial dK/dV are then summed with fp32 atomics into dkv_acc [n][2][nkv * HD],
 // which attn_dkv_store_kernel rounds into dqkv afterwards.
 template <int HD, bool CAUSAL, bool SPLIT, int NW, int NST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_mfma_kernel(
@@ -713,23 +703,11 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
     const int ntile_max = ms_cdiv(max_seqlen, 128);
     // grouped-query attention: split the group's query heads over workgroups (see the kernel)
     const bool split = nq / nkv > 1;
-    // Small batches: nq * n / 128 tiles of 128 queries or keys do not fill 256 CUs (two workgroups each), and the longest
-    // sequence's serial walk (one step per 32 queries in dK/dV, per 64 keys in dQ) is what the launch waits for.  There a
-    // key block's walk is cut into chunks of at least 8 query tiles, up to about two workgroups per CU (each adds its 128
-    // keys' sums with atomics, which cost more than a shorter walk saves beyond that), and dQ takes its two-way key
-    // split where it leaves a CU with one workgroup.  Only under grouped-query attention: its dK / dV are summed with
-    // atomics in any case, whereas without groups a sequence's gradients do not depend on what else is in the batch and
-    // stay so.  Whole backward at 8 / 2 heads of 128, us (tiles; unsplit -> here; 6 and 4 chunks): 2053 tokens (136)
-    // 171 -> 98 (120 at 6), 4096 (256) 243 -> 150 (167 at 4), 8000 (504) 391 -> 315; 12 / 2 heads, 8000 tokens (756): 786,
-    // 824 with two chunks; dQ's split at 384 tiles loses 2 %.
-    const long tiles = (long)nq * ms_cdiv(n, 128);
-    const int steps = ms_cdiv(max_seqlen, 32);
-    long parts = split ? ms_cdiv(540, tiles) : 1;
-    if (parts > steps / 8) parts = steps / 8 < 1 ? 1 : steps / 8;
-    const int chunk = ms_cdiv(steps, parts);
-    const bool dq2 = split && tiles < 320;
+    const AttnSplit plan = ms_attention_split(causal, nq, nkv, n, n_seqs, max_seqlen);
+    const bool dq2 = plan.two_way_dq;
+    const int chunk = ms_cdiv(ms_cdiv(max_seqlen, 32), plan.parts);     // query tiles per part
     const long blocks = attn_grid(nq, n_seqs, dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max).blocks;
-    const long blocks_kv = attn_grid(split ? nq : nkv, n_seqs, ntile_max).blocks, blocks_dkv = blocks_kv * parts;   // 128 keys each
+    const long blocks_kv = attn_grid(split ? nq : nkv, n_seqs, ntile_max).blocks, blocks_dkv = blocks_kv * plan.parts;   // 128 keys each
     if (!ms_launch_fits(blocks, 256) || !ms_launch_fits(blocks_dkv, 256) || !ms_attn_offsets_fit(n, nq, nkv, HD))
         return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets or for one launch");
     const unsigned grid_dkv = (unsigned)blocks_dkv;

@@ -1,6 +1,7 @@
 // Host-side rules of the launches: operand ranges, launch limits, choice of kernels.  Plain C++ without HIP, so that the
 // rules can be compiled and checked without a GPU.
 #pragma once
+#include <math.h>
 #include <stddef.h>
 
 // Elements from the first to the last one of a matrix stored as `outer` rows of `inner` elements, ld apart: the range of
@@ -128,4 +129,53 @@ inline MsSplit ms_choose_split(long M, long N, int kt, int forced, bool mfma16) 
         }
     }
     return c;
+}
+
+// ------------------------------------------------------------------ bf16 attention
+// Workgroups of a (heads, sequences, tile levels) grid; the mapping is described at attn_slot (attention_mfma.hip).
+constexpr int kAttnChunk = 8;
+struct AttnGrid { int S, hpc, M; long blocks; };
+constexpr AttnGrid attn_grid(int heads, int n_seqs, int nlevel_max) {
+    const int low = heads & -heads, G = low < 8 ? low : 8;          // gcd(heads, 8)
+    const int S = 8 / G, hpc = heads / G;
+    const int M = ((nlevel_max + S - 1) / S + kAttnChunk - 1) / kAttnChunk * kAttnChunk;   // levels per stripe, whole chunks
+    return {S, hpc, M, 8L * M * hpc * n_seqs};
+}
+
+// Expected 128-row tiles of a batch, all heads: each sequence's last one is half full in the mean.
+inline double ms_attention_tiles(int heads, long n, long n_seqs) { return heads * (n + 64.0 * n_seqs) / 128; }
+
+// Backward pass under grouped-query attention on small batches.  A dK/dV workgroup walks the query tiles (32 rows) that see
+// its 128 keys, a dQ workgroup the key tiles (64) of its 128 queries; where there are few walks, the launch waits for the
+// longest one.  Its cost in steps of a dK/dV walk, fitted to 276 batches (head_dim 64, 80, 128, 6 .. 32 heads, equal and
+// mixed lengths, 300 .. 8192 tokens): the longest walk and what a CU has to do in the mean, and what the parts of a walk
+// cost by adding their 128 keys' sums with atomics.  Of a batch the host knows the token count, the number of sequences and
+// a bound on their length; walks are taken to be half as long as that bound and half as the mean says.
+//   parts: into how many parts of at least 8 query tiles a dK/dV walk is cut.  8 / 2 heads of 128, whole backward in us,
+//     unsplit -> cut: one sequence of 620 tokens 66.2 -> 53.4, 2053 tokens in two 139 -> 103; four equal ones of 1024
+//     stay unsplit (102.6; cut in three 125), and so do very many short ones.
+//   two_way_dq: the keys of 64 queries are split over two wave pairs.  Such a workgroup has a CU to itself (128 KB of
+//     LDS), also where it finds no tile of its own, so the grid has to be small, or small next to the walk that it halves:
+//     2053 tokens in two 103 -> 85; 32 x 64 tokens 59.6 (with the split 76), 2048 tokens next to 500 single ones 504
+//     (819).  Over the batches it loses nowhere more than 0.5 %.
+// Without groups neither is done: there a sequence's gradients do not depend on what else is in the batch.  Under
+// grouped-query attention they do: dK and dV are sums of atomics in any case, and the order in which dQ adds up its keys
+// follows from this rule, that is from the batch.
+struct AttnSplit { int parts; bool two_way_dq; };
+inline AttnSplit ms_attention_split(int causal, int nq, int nkv, long n, long n_seqs, int max_seqlen) {
+    AttnSplit a = {1, false};
+    if (nq <= nkv || n <= 0 || n_seqs <= 0 || max_seqlen <= 0) return a;
+    const double walks = ms_attention_tiles(nq, n, n_seqs);
+    const double length = n_seqs > 1 ? 0.5 * max_seqlen + 0.5 * n / n_seqs : max_seqlen;
+    const int longest = (max_seqlen + 31) / 32;
+    const double mean = walks * (length / (causal ? 64 : 32) + 0.5) / 256;
+    auto cost = [&](int p) { return hypot((longest + p - 1) / p, 1.5 * mean) + 9.0 * walks * p / 256; };
+    const long blocks_kv = attn_grid(nq, (int)n_seqs, (max_seqlen + 127) / 128).blocks;
+    double best = 0.92 * cost(1);                       // a cut has to be worth 8 %, the error of the fit
+    for (int p = 2; longest / p >= 8 && ms_launch_fits(blocks_kv * p, 256); ++p)
+        if (cost(p) < best) { best = cost(p); a.parts = p; }
+    const int levels = (max_seqlen + 63) / 64;
+    const long blocks_dq = attn_grid(nq, (int)n_seqs, levels).blocks;
+    a.two_way_dq = walks < 290 && blocks_dq <= (levels * 40L > 512 ? levels * 40L : 512);
+    return a;
 }

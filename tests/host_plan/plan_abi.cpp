@@ -16,3 +16,9 @@ extern "C" void plan_split(long M, long N, int kt, int *out) {
     out[0] = kTiles[c.tile].code;
     out[1] = c.splits;
 }
+extern "C" void plan_attention_split(int causal, int nq, int nkv, long n, long n_seqs, int max_seqlen, int *out) {
+    const AttnSplit a = ms_attention_split(causal, nq, nkv, n, n_seqs, max_seqlen);
+    out[0] = a.parts;
+    out[1] = a.two_way_dq;
+}
+extern "C" long plan_attention_blocks(int heads, int n_seqs, int levels) { return attn_grid(heads, n_seqs, levels).blocks; }

@@ -107,3 +107,36 @@ def test_long_weight_gradients_keep_the_large_tiles(plan):
         assert out[0] in (256, 128, 128256) and 1 <= out[1] <= 8
     plan.plan_split(C.c_long(1024), C.c_long(1024), 4, out)    # 256 tokens: nothing to split
     assert out[1] == 1
+
+
+def attention_split(plan, lens, nq=8, nkv=2, causal=1, bound=None):
+    out = (C.c_int * 2)()
+    plan.plan_attention_split(causal, nq, nkv, C.c_long(sum(lens)), C.c_long(len(lens)), bound or max(lens), out)
+    return out[0], bool(out[1])
+
+
+# What the splits made slower than no split: many short sequences (with or without a long one), whose workgroups without a
+# tile each took a CU; equal lengths, which need no balancing
+@pytest.mark.parametrize("nq,nkv,lens", [
+    (8, 2, [64] * 32), (12, 2, [20] * 50), (12, 2, [128] * 16), (16, 4, [70] * 30), (8, 2, [1] * 2000 + [2048]), (12, 2, [1] * 500 + [2048]),
+    (6, 2, [256] * 8), (32, 8, [1031])])
+def test_short_or_balanced_batches_are_not_split(plan, nq, nkv, lens):
+    parts, two_way = attention_split(plan, lens, nq, nkv)
+    assert not two_way and (parts == 1 or len(lens) == 1)
+
+
+def test_attention_split_helps_few_long_walks_only(plan):
+    assert attention_split(plan, [1700, 353])[0] in (3, 4, 5) and attention_split(plan, [1700, 353])[1]
+    assert attention_split(plan, [620]) == (2, True) and attention_split(plan, [300]) == (1, True)
+    assert attention_split(plan, [1024] * 4)[0] == 1                                                # equal lengths
+    assert attention_split(plan, [32768]) == (1, False) and attention_split(plan, [4096] * 8) == (1, False)
+    for lens in ([620], [2053], [64] * 4):                                                          # no groups: never
+        assert attention_split(plan, lens, 8, 8) == (1, False)
+    for nq, nkv in ((4, 2), (6, 2), (8, 2), (12, 2), (16, 4), (32, 8), (5, 1)):
+        for causal in (0, 1):
+            for lens in ([1], [31], [255], [257, 1], [0, 5, 0], [4096], [16384], [300, 1, 785], [7] * 5000):
+                for bound in (None, 65536):
+                    p, two = attention_split(plan, lens, nq, nkv, causal, bound)
+                    longest = -(-(bound or max(lens)) // 32)
+                    assert p == 1 or longest // p >= 8
+                    assert plan.plan_attention_blocks(nq, len(lens), -(-(bound or max(lens)) // 128)) * p * 256 < 1 << 32 or p == 1
