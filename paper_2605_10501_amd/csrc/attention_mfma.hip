@@ -54,8 +54,9 @@ __device__ inline AttnSlot attn_slot(unsigned bid, int heads, int n_seqs, int nl
 // instructions of the head_dim 80 forward loop, 51 of 159 in dK/dV).
 __device__ __forceinline__ void keep_branch() { asm volatile(""); }
 
-template <int HD, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HD == 64 ? 3 : 2, HD == 64 ? 3 : 2))) void attn_fwd_mfma_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
+// WPS = waves per SIMD, that is workgroups per CU (ms_attention_waves)
+template <int HD, bool CAUSAL, int WPS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void attn_fwd_mfma_kernel(const bf16_t *__restrict__ qkv, bf16_t *__restrict__ o,
                                                              float *__restrict__ lse, const int *__restrict__ cu, int n,
                                                              int nq, int nkv, int n_seqs, int ntile_max, float scale_log2e) {
     using D = AttnDims<HD>;
@@ -277,8 +278,8 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t *__restric
 // KS = 2 (few workgroups with long walks; see ms_attention_split): the workgroup owns 64 queries, waves 0 and 1 visit
 // the even key tiles, waves 2 and 3 the odd ones for the same queries, and the two partial sums meet in LDS: twice the
 // workgroups, half the serial chain.
-template <int HD, bool CAUSAL, int KS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 1 : HD == 64 ? 3 : 2, KS == 2 ? 1 : HD == 64 ? 3 : 2))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
+template <int HD, bool CAUSAL, int KS, int WPS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
                                                                 const float2 *__restrict__ ld2,
                                                                 bf16_t *__restrict__ dqkv, const int *__restrict__ cu, int n,
                                                                 int nq, int nkv, int n_seqs, int ntile_max, float scale) {
@@ -690,8 +691,16 @@ ms_status launch_fwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
     if (!ms_launch_fits(blocks, 256) || !ms_attn_offsets_fit(n, nq, nkv, HD))
         return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets or for one launch");
     const float sc = 1.4426950408889634f / sqrtf((float)HD);
-    if (causal) attn_fwd_mfma_kernel<HD, true><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (bf16_t *)o, lse, cu, n, nq, nkv, n_seqs, ntile_max, sc);
-    else attn_fwd_mfma_kernel<HD, false><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (bf16_t *)o, lse, cu, n, nq, nkv, n_seqs, ntile_max, sc);
+#define GO(C, WPS)                                                                                                            \
+    attn_fwd_mfma_kernel<HD, C, WPS><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (bf16_t *)o, lse, cu, n, nq, nkv, \
+                                                                      n_seqs, ntile_max, sc)
+    bool three = false;
+    if constexpr (HD == 64) {
+        three = ms_attention_waves(HD, nq, causal, n, n_seqs, max_seqlen) == 3;
+        if (three && causal) GO(true, 3); else if (three) GO(false, 3);
+    }
+    if (!three && causal) GO(true, 2); else if (!three) GO(false, 2);
+#undef GO
     MS_LAUNCH_CHECK();
     return MS_OK;
 }
@@ -717,10 +726,10 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
     float *dkv_acc = (float *)((char *)scratch + ms_align_up((size_t)nq * n * sizeof(float2)));
     const int w = 2 * nkv * HD;
     if (split) MS_TRY(launch_fill_f32(dkv_acc, (long)n * w, 0.f, s));
-#define DQ(C, KS)                                                                                                      \
-    attn_bwd_dq_mfma_kernel<HD, C, KS><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, ld2, \
-                                                                        (bf16_t *)dqkv, cu, n, nq, nkv, n_seqs,        \
-                                                                        dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max, scale)
+#define DQ(C, KS, WPS)                                                                                                       \
+    attn_bwd_dq_mfma_kernel<HD, C, KS, WPS><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, ld2, \
+                                                                             (bf16_t *)dqkv, cu, n, nq, nkv, n_seqs,        \
+                                                                             dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max, scale)
 #define DKV(C, SPLIT)                                                                                                  \
     attn_bwd_dkv_mfma_kernel<HD, C, SPLIT, 4, 2><<<grid_dkv, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o,    \
                                                                           ld2, (bf16_t *)dqkv, dkv_acc, cu, n, nq,     \
@@ -728,7 +737,11 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
                                                                           (unsigned)blocks_kv)
 #define GO(C)                                                                                                          \
     do {                                                                                                               \
-        if (dq2) DQ(C, 2); else DQ(C, 1);                                                                              \
+        bool three = false;                                                                                            \
+        if constexpr (HD == 64) three = !dq2 && ms_attention_waves(HD, nq, causal, n, n_seqs, max_seqlen) == 3;        \
+        if (dq2) DQ(C, 2, 1);                                                                                          \
+        else if (!three) DQ(C, 1, 2);                                                                                  \
+        if constexpr (HD == 64) if (three) DQ(C, 1, 3);                                                                \
         MS_LAUNCH_CHECK();                                                                                             \
         if (split) DKV(C, true); else DKV(C, false);                                                                   \
     } while (0)

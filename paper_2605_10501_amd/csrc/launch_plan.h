@@ -145,6 +145,16 @@ constexpr AttnGrid attn_grid(int heads, int n_seqs, int nlevel_max) {
 // Expected 128-row tiles of a batch, all heads: each sequence's last one is half full in the mean.
 inline double ms_attention_tiles(int heads, long n, long n_seqs) { return heads * (n + 64.0 * n_seqs) / 128; }
 
+// Workgroups (of four waves) per CU in the forward and dQ kernels.  At head_dim 64 they fit three times; that gains 2-8 %
+// where the grid fills the chip more than once, and 6-20 % where every sequence is a single tile.  Smaller grids of longer
+// sequences are spread unevenly, three workgroups on one CU while another has one; causal tiles, whose walks differ, suffer
+// longer from it.  Forward, us, three / two per CU: 16 heads bidirectional, 528 tiles 71.8 / 56.5, 656 tiles 70.6 / 87.6; 8
+// causal heads, 656 tiles 54.5 / 42.6; 16 / 4 causal heads, 656 tiles 47.0 / 43.7, 1040 70.1 / 69.6, 1312 68.3 / 73.0; 32
+// sequences of 64 17.2 / 20.9.
+inline int ms_attention_waves(int hd, int heads, int causal, long n, long n_seqs, int max_seqlen) {
+    return hd == 64 && (max_seqlen <= 128 || ms_attention_tiles(heads, n, n_seqs) >= (causal ? 1100 : 600)) ? 3 : 2;
+}
+
 // Backward pass under grouped-query attention on small batches.  A dK/dV workgroup walks the query tiles (32 rows) that see
 // its 128 keys, a dQ workgroup the key tiles (64) of its 128 queries; where there are few walks, the launch waits for the
 // longest one.  Its cost in steps of a dK/dV walk, fitted to 276 batches (head_dim 64, 80, 128, 6 .. 32 heads, equal and

@@ -22,3 +22,6 @@ extern "C" void plan_attention_split(int causal, int nq, int nkv, long n, long n
     out[1] = a.two_way_dq;
 }
 extern "C" long plan_attention_blocks(int heads, int n_seqs, int levels) { return attn_grid(heads, n_seqs, levels).blocks; }
+extern "C" int plan_attention_waves(int hd, int heads, int causal, long n, long n_seqs, int max_seqlen) {
+    return ms_attention_waves(hd, heads, causal, n, n_seqs, max_seqlen);
+}

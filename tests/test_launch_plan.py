@@ -140,3 +140,12 @@ def test_attention_split_helps_few_long_walks_only(plan):
                     longest = -(-(bound or max(lens)) // 32)
                     assert p == 1 or longest // p >= 8
                     assert plan.plan_attention_blocks(nq, len(lens), -(-(bound or max(lens)) // 128)) * p * 256 < 1 << 32 or p == 1
+
+
+# Three workgroups per CU only where they fill the chip: grids of 400 .. 1040 tiles were up to 27 % slower with them
+@pytest.mark.parametrize("hd,heads,causal,lens,waves", [
+    (64, 16, 0, [2048] * 2, 2), (64, 8, 1, [1400] * 7, 2), (64, 16, 1, [256] * 8, 2), (64, 16, 1, [2000] * 4, 2), (64, 16, 0, [1000] * 3, 2),
+    (64, 16, 0, [1700] * 3, 3), (64, 16, 1, [1700] * 6, 3), (64, 16, 0, [2000] * 16, 3), (64, 8, 1, [64] * 32, 3),
+    (80, 16, 0, [2300] * 20, 2), (128, 32, 1, [4096] * 8, 2), (128, 8, 1, [64] * 32, 2)])
+def test_waves_per_simd_of_the_attention_kernels(plan, hd, heads, causal, lens, waves):
+    assert plan.plan_attention_waves(hd, heads, causal, C.c_long(sum(lens)), C.c_long(len(lens)), max(lens)) == waves
