@@ -52,6 +52,7 @@ __device__ inline AttnSlot attn_slot(unsigned bid, int heads, int n_seqs, int nl
 // Keeps the mask of the tiles that touch the diagonal or the end of a sequence behind its wave-uniform branch: without it
 // the compiler turns the bidirectional mask into compares and selects that every tile executes (65 of 261 vector
 // instructions of the head_dim 80 forward loop, 51 of 159 in dK/dV).
+// (The causal forward mask at head_dim 64 and 128 stays behind its branch by itself, and the barrier costs 0.5 % there.)
 __device__ __forceinline__ void keep_branch() { asm volatile(""); }
 
 // WPS = waves per SIMD, that is workgroups per CU (ms_attention_waves)
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS)))
         const int key0 = s0 + j * BKV + 4 * half;
         const bool need_mask = s0 + j * BKV + BKV > kv_end || (CAUSAL && s0 + j * BKV + BKV - 1 > q0);
         if (need_mask) {
-            keep_branch();
+            if constexpr (!CAUSAL || HD == 80) keep_branch();
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
