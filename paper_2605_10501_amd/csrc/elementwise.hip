@@ -738,26 +738,31 @@ ms_status launch_convert_from_f32(int dtype, const float *src, void *dst, long n
 }
 
 // ------------------------------------------------------------------ AdamW (the student's parameter update)
-// Five streams (four in, three or four out, all fp32, plus the weights): HBM-bound.  A thread handles 4 elements at a
-// time, two groups in flight (eight 16-byte loads before the first use); the fp32 state streams through once per step
-// and is accessed non-temporally, the weights are what the next forward pass reads and keep the default policy.
+// Five streams (four in, three or four out, all fp32, plus the weights): HBM-bound.  A state that cannot stay in the caches
+// from one step to the next (ms_adamw_streams) is accessed non-temporally, two groups of 4 elements per thread in flight
+// (eight 16-byte loads before the first use); a smaller one by the default policy, one group per thread.  The weights are
+// what the next forward pass reads and keep the default policy.
 namespace {
-template <class T>
+template <class T, int U, bool STREAM>
 __global__ __launch_bounds__(256) void adamw_kernel(long n4, float *__restrict__ grad, float *__restrict__ master,
                                                      float *__restrict__ m, float *__restrict__ v, T *__restrict__ w,
                                                      float lr, float b1, float b2, float eps, float decay, float gscale,
                                                      float inv_c1, float inv_c2, int zero_grad) {
-    constexpr int U = 2;
     f32x4 g[U], ww[U], mm[U], vv[U];
+    auto get = [](const float *p, long i) { return STREAM ? __builtin_nontemporal_load((const f32x4 *)p + i) : ((const f32x4 *)p)[i]; };
+    auto put = [](const f32x4 &x, float *p, long i) {
+        if constexpr (STREAM) __builtin_nontemporal_store(x, (f32x4 *)p + i);
+        else ((f32x4 *)p)[i] = x;
+    };
     const long i0 = (long)blockIdx.x * (256 * U) + threadIdx.x;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const long i = i0 + u * 256;
         if (i >= n4) break;
-        g[u] = __builtin_nontemporal_load((const f32x4 *)grad + i);
-        ww[u] = __builtin_nontemporal_load((const f32x4 *)master + i);
-        mm[u] = __builtin_nontemporal_load((const f32x4 *)m + i);
-        vv[u] = __builtin_nontemporal_load((const f32x4 *)v + i);
+        g[u] = get(grad, i);
+        ww[u] = get(master, i);
+        mm[u] = get(m, i);
+        vv[u] = get(v, i);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -770,10 +775,10 @@ __global__ __launch_bounds__(256) void adamw_kernel(long n4, float *__restrict__
             vv[u][e] = b2 * vv[u][e] + (1.f - b2) * ge * ge;
             ww[u][e] = ww[u][e] * decay - lr * (mm[u][e] * inv_c1) / (sqrtf(vv[u][e] * inv_c2) + eps);
         }
-        __builtin_nontemporal_store(ww[u], (f32x4 *)master + i);
-        __builtin_nontemporal_store(mm[u], (f32x4 *)m + i);
-        __builtin_nontemporal_store(vv[u], (f32x4 *)v + i);
-        if (zero_grad) __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, (f32x4 *)grad + i);
+        put(ww[u], master, i);
+        put(mm[u], m, i);
+        put(vv[u], v, i);
+        if (zero_grad) put(f32x4{0.f, 0.f, 0.f, 0.f}, grad, i);
         if (w) {
             union { T h[4]; uint2 u2; uint4 u4; } o;
 #pragma unroll
@@ -804,11 +809,16 @@ extern "C" ms_status ms_adamw_step(const ms_adamw_config *cfg, int32_t dtype, in
     const float inv_c2 = (float)(1.0 / (1.0 - pow((double)cfg->beta2, (double)cfg->step)));
     const float decay = 1.f - cfg->lr * cfg->weight_decay;
     const long n4 = n / 4;
-    const unsigned grid = (unsigned)((n4 + 511) / 512);
+    const bool stream_state = ms_adamw_streams(n);
+    const unsigned grid = (unsigned)((n4 + (stream_state ? 511 : 255)) / (stream_state ? 512 : 256));
     hipStream_t s = (hipStream_t)stream;
     ProfScope ps(11, (double)n * (4 * 7 + (weight ? (dtype == MS_BF16 ? 2 : 4) : 0) + (cfg->zero_grad ? 4 : 0)), s);
-    if (dtype == MS_BF16) adamw_kernel<bf16_t><<<grid, 256, 0, s>>>(n4, grad, master, m, v, (bf16_t *)weight, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, decay, cfg->grad_scale, inv_c1, inv_c2, cfg->zero_grad);
-    else adamw_kernel<float><<<grid, 256, 0, s>>>(n4, grad, master, m, v, (float *)weight, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, decay, cfg->grad_scale, inv_c1, inv_c2, cfg->zero_grad);
+#define GO(T, U, STREAM)                                                                                                      \
+    adamw_kernel<T, U, STREAM><<<grid, 256, 0, s>>>(n4, grad, master, m, v, (T *)weight, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, \
+                                                    decay, cfg->grad_scale, inv_c1, inv_c2, cfg->zero_grad)
+    if (dtype == MS_BF16) { if (stream_state) GO(bf16_t, 2, true); else GO(bf16_t, 1, false); }
+    else { if (stream_state) GO(float, 2, true); else GO(float, 1, false); }
+#undef GO
     MS_LAUNCH_CHECK();
     return MS_OK;
 }

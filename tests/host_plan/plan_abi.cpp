@@ -25,3 +25,4 @@ extern "C" long plan_attention_blocks(int heads, int n_seqs, int levels) { retur
 extern "C" int plan_attention_waves(int hd, int heads, int causal, long n, long n_seqs, int max_seqlen) {
     return ms_attention_waves(hd, heads, causal, n, n_seqs, max_seqlen);
 }
+extern "C" int plan_adamw_streams(long n) { return ms_adamw_streams(n); }

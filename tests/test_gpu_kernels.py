@@ -276,3 +276,21 @@ def test_adamw_step_matches_oracle(wdtype):
         assert (float(g.abs().max()) == 0.0) == (step == 3)   # cleared only when asked
     with pytest.raises(RuntimeError):
         B.adamw_step(g, master, m, v, weight, 0, lr=1e-3)     # steps count from 1
+
+
+# both access policies at their border and at the ends of their workgroups (1024 and 2048 elements)
+@pytest.mark.parametrize("n", [4, 1024, 1028, 5_000_000, 5_000_004, 2048 * 2500 + 4])
+@pytest.mark.parametrize("wdtype", [torch.bfloat16, torch.float32])
+def test_adamw_step_on_both_sides_of_the_cached_size(n, wdtype):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    g, master, m, v = (torch.randn(n, device="cuda", generator=gen) for _ in range(4))
+    v.square_()
+    weight = torch.empty(n, dtype=wdtype, device="cuda")
+    hp = dict(lr=1e-2, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.1, grad_scale=0.5)
+    gd = 0.5 * g.double()
+    rm, rv = 0.9 * m.double() + 0.1 * gd, 0.95 * v.double() + 0.05 * gd * gd
+    rw = master.double() * (1 - 1e-3) - 1e-2 * (rm / (1 - 0.9 ** 7)) / ((rv / (1 - 0.95 ** 7)).sqrt() + 1e-8)
+    B.adamw_step(g, master, m, v, weight, 7, zero_grad=True, **hp)
+    for got, want in ((master, rw), (m, rm), (v, rv)):                      # a handful of fp32 roundings of values of order 1
+        assert float(((got.double() - want).abs() / (want.abs() + 1)).max()) < 2e-6
+    assert torch.equal(weight, master.to(wdtype)) and not g.any()

@@ -149,3 +149,7 @@ def test_attention_split_helps_few_long_walks_only(plan):
     (80, 16, 0, [2300] * 20, 2), (128, 32, 1, [4096] * 8, 2), (128, 8, 1, [64] * 32, 2)])
 def test_waves_per_simd_of_the_attention_kernels(plan, hd, heads, causal, lens, waves):
     assert plan.plan_attention_waves(hd, heads, causal, C.c_long(sum(lens)), C.c_long(len(lens)), max(lens)) == waves
+
+
+def test_adamw_state_is_streamed_only_where_it_cannot_stay_cached(plan):
+    assert not plan.plan_adamw_streams(C.c_long(4_000_000)) and plan.plan_adamw_streams(C.c_long(8_000_000))
