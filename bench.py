@@ -76,7 +76,7 @@ def nt_gemm_shapes(work):
 
 def measured_traffic(name):
     """HBM-side bytes per NT-GEMM launch from the committed counter summary (two rocprofv3 --pmc runs), or None."""
-    path = os.path.join(ROOT, "profiles", f"gemm_bf16_fast_kernel_{name}_hbm_traffic.txt")
+    path = os.path.join(ROOT, "profiles", f"gemm_nt_hbm_traffic_{name}.txt")
     try:
         for line in open(path):
             if line.startswith("gemm_nt_traffic_bytes_per_launch:"):
@@ -218,7 +218,7 @@ def bench_kd_step(name, args, torch, B, wl, dev, side):
         "mfma_frac_kd_loss": fl["kd"] / sec_kd / 1e12 / PEAK_BF16_TFLOPS if sec_kd else None,
         "student_section_tflops": (fl["student"] + fl["kd"]) / sec_student / 1e12,
         "loss": loss, "logits_to_hidden_ratio": kd.vocab / kd.h_teacher,
-        "roofline": {"kernel": "gemm_bf16_fast_kernel (A[M,K] B[N,K]^T: all forward linears and lm_head chunk GEMMs)",
+        "roofline": {"kernel": "gemm_bf16_fast_kernel, gemm_bf16_pp_kernel (A[M,K] B[N,K]^T: all forward linears and lm_head chunk GEMMs)",
                      "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
                      "traffic_source": (traffic_src + " (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; bytes per launch)") if traffic else None,
