@@ -1033,7 +1033,6 @@ struct GemmF32Params {
     const float *bias, *residual;
     long lda, ldb, ldc, ldr;
     int M, N, K, tiles_n;
-    unsigned tiles;
     float alpha;
     int accumulate;
 };
@@ -1079,9 +1078,7 @@ template <bool TA, bool TB, bool FAST>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
     __shared__ float part[4][32][33];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned t = blockIdx.y * gridDim.x + blockIdx.x;
-    if (t >= p.tiles) return;
-    const int m0 = (int)(t / (unsigned)p.tiles_n) * 32, n0 = (int)(t % (unsigned)p.tiles_n) * 32;
+    const int m0 = (int)(blockIdx.x / p.tiles_n) * 32, n0 = (int)(blockIdx.x % p.tiles_n) * 32;
     const int slices = (p.K + 15) / 16, mine = slices > wave ? (slices - wave + 3) / 4 : 0;
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.A, FAST ? ms_matrix_extent(TA ? p.K : p.M, TA ? p.M : p.K, p.lda) * 4 : 0);
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.B, FAST ? ms_matrix_extent(TB ? p.K : p.N, TB ? p.N : p.K, p.ldb) * 4 : 0);
@@ -1291,10 +1288,18 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
         p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.accumulate = accumulate;
         p.tiles_n = ms_cdiv(N, 32);
         const long tiles = (long)ms_cdiv(M, 32) * p.tiles_n;
-        if (tiles > 0x7fffffffL) return ms_fail(MS_ERR_UNSUPPORTED, "gemm(fp32): %d x %d is too large", M, N);
-        p.tiles = (unsigned)tiles;
-        const MsGrid folded = ms_fold_grid(tiles, 256);
-        const dim3 grid(folded.x, folded.y);
+        if (!ms_launch_fits(tiles, 256)) {   // more tiles than one launch takes: the two halves of C along its longer side
+            const bool rows = ms_cdiv(M, 32) >= p.tiles_n;
+            const int cut = (int)(((rows ? M : N) / 2L + 31) / 32 * 32);
+            const long a = rows ? (trans_a ? cut : cut * lda) : 0, b = rows ? 0 : (trans_b ? cut : cut * ldb), c = rows ? cut * ldc : cut;
+            const long r = rows ? cut * ldr : cut;
+            MS_TRY(ms_k_gemm(dtype, trans_a, trans_b, rows ? cut : M, rows ? N : cut, K, alpha, A, lda, B, ldb, C, ldc, c_fp32, accumulate, bias,
+                             residual, ldr, residual_fp32, split_k, stream));
+            return ms_k_gemm(dtype, trans_a, trans_b, rows ? M - cut : M, rows ? N : N - cut, K, alpha, p.A + a, lda, p.B + b, ldb, p.C + c,
+                             ldc, c_fp32, accumulate, bias && !rows ? p.bias + cut : bias, residual ? p.residual + r : nullptr, ldr,
+                             residual_fp32, split_k, stream);
+        }
+        const unsigned grid = (unsigned)tiles;
         auto fast = [&](const void *q, long ld, bool trans, long rows) {
             return (trans || (((uintptr_t)q & 15) == 0 && ld % 4 == 0 && K % 4 == 0)) &&
                    ms_buffer_range_ok(trans ? K : rows, trans ? rows : K, ld, 4);

@@ -19,11 +19,6 @@ constexpr bool ms_buffer_range_ok(long outer, long inner, long ld, int es) {
 // HIP refuses a launch of 2^32 threads or more along one dimension
 constexpr long kLaunchThreads = 0xffffffffL;
 constexpr bool ms_launch_fits(long workgroups, int threads) { return workgroups <= kLaunchThreads / threads; }
-// The same number of workgroups (or a few more) in one row where that may be launched, else in rows of 2^20
-struct MsGrid { unsigned x, y; };
-constexpr MsGrid ms_fold_grid(long workgroups, int threads) {
-    return ms_launch_fits(workgroups, threads) ? MsGrid{(unsigned)workgroups, 1u} : MsGrid{1u << 20, (unsigned)((workgroups + (1L << 20) - 1) >> 20)};
-}
 
 // fp32 attention on 16-row tiles: whether the batch can be addressed and launched (max_seqlen is an upper bound; heads =
 // workgroups along y).  The scalar kernels, one workgroup per token, take the rest: a batch of very many short sequences

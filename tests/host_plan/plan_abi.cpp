@@ -4,7 +4,6 @@
 extern "C" long plan_matrix_extent(long outer, long inner, long ld) { return ms_matrix_extent(outer, inner, ld); }
 extern "C" int plan_buffer_range_ok(long outer, long inner, long ld, int es) { return ms_buffer_range_ok(outer, inner, ld, es); }
 extern "C" int plan_launch_fits(long wgs, int threads) { return ms_launch_fits(wgs, threads); }
-extern "C" void plan_fold_grid(long wgs, int threads, unsigned *xy) { const MsGrid g = ms_fold_grid(wgs, threads); xy[0] = g.x; xy[1] = g.y; }
 extern "C" int plan_f32_attention_tiles(int hd, long n, long n_seqs, long max_seqlen, int nq, int nkv, int heads) {
     return ms_f32_attention_tiles(hd, n, n_seqs, max_seqlen, nq, nkv, heads);
 }

@@ -60,12 +60,14 @@ def test_gemm_fp32_negative_leading_dimension():
     assert_parity(out, f64(a)[::-1] @ f64(b).T, TOL_F32)
 
 
-# more than 2^24 output tiles: beyond what one row of workgroups may hold
-def test_gemm_fp32_with_very_many_tiles():
-    N = 32 * (1 << 24) + 40
-    b = torch.arange(N, device="cuda").remainder_(8191).to(torch.float32).view(1, N)
-    out = B.k_gemm(torch.full((1, 1), 3.0, device="cuda"), b, False, True)
-    assert torch.equal(out, b.mul_(3.0))
+# more than 2^24 output tiles, along either side: beyond what one launch takes
+@pytest.mark.parametrize("along_n", [True, False])
+def test_gemm_fp32_with_very_many_tiles(along_n):
+    n = 32 * (1 << 24) + 40
+    long = torch.arange(n, device="cuda").remainder_(8191).to(torch.float32).view(1, n)
+    three, bias = torch.full((1, 1), 3.0, device="cuda"), long.add(1.0).view(n) if along_n else torch.ones(1, device="cuda")
+    out = B.k_gemm(three, long, False, True, bias=bias) if along_n else B.k_gemm(long, three, True, True, bias=bias)
+    assert torch.equal(out.view(1, n), long.mul_(3.0).add_(bias.view(1, -1)))
 
 
 # very many sequences under a large bound on their length: more 16-row tiles than one launch holds

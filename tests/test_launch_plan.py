@@ -49,13 +49,9 @@ def test_what_a_descriptor_cannot_address(plan):
     assert ok(0, 8, 8, 4) and ok(8, 0, 8, 4)
 
 
-@pytest.mark.parametrize("wgs", [1, 255, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, 3 * (1 << 24) + 7, (1 << 31) - 1])
-def test_grids_stay_below_the_thread_limit(plan, wgs):
-    xy = (C.c_uint * 2)()
-    plan.plan_fold_grid(C.c_long(wgs), 256, xy)
-    x, y = xy
-    assert x * 256 < 1 << 32 and y <= 65535 and wgs <= x * y < wgs + (1 << 20)
-    assert (y == 1) == (wgs < 1 << 24) == bool(plan.plan_launch_fits(C.c_long(wgs), 256))
+def test_one_launch_ends_below_the_thread_limit(plan):
+    fits = lambda wgs, threads=256: bool(plan.plan_launch_fits(C.c_long(wgs), threads))
+    assert fits(1) and fits((1 << 24) - 1) and not fits(1 << 24) and not fits((1 << 31) - 1) and fits((1 << 23) - 1, 512) and not fits(1 << 23, 512)
 
 
 def test_fp32_attention_tiles_only_where_the_grid_can_be_launched(plan):
