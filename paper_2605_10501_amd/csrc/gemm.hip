@@ -3,7 +3,7 @@
 // bf16: C = alpha * A(m,k) B(n,k) on the CDNA4 matrix cores, all four operand layouts.
 //   * gemm_bf16_fast_kernel: workgroup tile 256 x 256 x 64 (8 waves, wave tile 128 x 64, one workgroup per CU) or
 //     128 x 128 x 64 (4 waves, two per CU) for grids that fill the chip, and 128 x 256, 128 x 128, 64 x 128 and 64 x 64
-//     tiles with a ring of three or four LDS stages for grids that do not (kTiles, choose_tile);
+//     tiles with a ring of three or four LDS stages for grids that do not (launch_plan.h);
 //     v_mfma_f32_16x16x32_bf16 by default (v_mfma_f32_32x32x16_bf16 selectable for the first two);
 //   * every operand tile goes global -> LDS directly (buffer_load ... lds), two (or more) LDS buffers per operand, one
 //     barrier per K tile; a K-contiguous operand lands as [rows][64] with the 16-byte chunk index XOR-swizzled (applied on the
@@ -1214,8 +1214,9 @@ ms_status launch_bf16_fast(GemmParams &p, int tile, int ta, int tb, int splits, 
     p.tiles_n = ms_cdiv(p.N, EPI == EPI_SWIGLU ? t.bn / 2 : t.bn);
     dim3 grid(p.tiles_m * p.tiles_n, splits);
     ProfScope ps((ta || tb) ? 1 : 0, flops, s);
-    // Operands that do not stay in the 256 MB Infinity Cache: the ping-pong kernel (its figures say why the line is
-    // between 318 MB, where it gains nothing, and 448 MB, where it gains 7 %).
+    // Operands that do not stay in the 256 MB Infinity Cache: the ping-pong kernel.  The line is between 319 MB, where it
+    // gains nothing on operands that a repeated call finds there, and 448 MB, where it gains 7 %; on operands that have
+    // left the cache it would pay lower as well (3 % at 281 and 319 MB, 12 % at 218 MB with a short N).
     if constexpr (EPI == EPI_NONE || EPI == EPI_SWIGLU) {
         const double stream = 2.0 * ((double)p.M + p.N * (EPI == EPI_SWIGLU ? 2.0 : 1.0)) * p.K;
         if (tile == T256 && !ta && !tb && use_mfma16() && splits == 1 && (forced_tile() == kPingPong || (forced_tile() == 0 && stream > 384e6))) {
