@@ -22,7 +22,7 @@ extern "C" {
 /* Kernel selection of the bf16 GEMMs, for measurements and tests (host-side switch, affects later launches
  * from any thread; not meant to be changed while launches are being issued).  tile: 0 = automatic (by shape),
  * 128 or 256 = force that workgroup tile for the direct-to-LDS kernels, 128128, 128256, 64128 or 64064 = force that tile
- * (rows, columns) with the ring of LDS stages, 256256 = 256 with the ping-pong kernel where it applies, -1 = use only the generic kernel.
+ * (rows, columns) with the ring of LDS stages, 256256 = 256, -1 = use only the generic kernel.
  * mfma16: 1 = v_mfma_f32_16x16x32_bf16, 0 = v_mfma_f32_32x32x16_bf16, -1 = default.  The process-wide defaults
  * come from the environment (MS_GEMM_TILE, MS_GEMM_MFMA16). */
 ms_status ms_k_gemm_config(int32_t tile, int32_t mfma16);

@@ -1,6 +1,7 @@
 // GEMM kernels of the section path.
 //
 // bf16: C = alpha * A(m,k) B(n,k) on the CDNA4 matrix cores, all four operand layouts.
+//   * gemm_bf16_pp_kernel: workgroup tile 256 x 256 x 64, K-contiguous operands, two wave groups that take turns;
 //   * gemm_bf16_fast_kernel: workgroup tile 256 x 256 x 64 (8 waves, wave tile 128 x 64, one workgroup per CU) or
 //     128 x 128 x 64 (4 waves, two per CU) for grids that fill the chip, and 128 x 256, 128 x 128, 64 x 128 and 64 x 64
 //     tiles with a ring of three or four LDS stages for grids that do not (launch_plan.h);
@@ -857,11 +858,14 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fa
 //     least six phases (1.5 K tiles) before it is read, instead of one K tile in gemm_bf16_fast_kernel, and the wait
 //     is for all but the 10 youngest loads of a wave, never for all of them.
 //   * Same tile order, MFMA and order of K as the other tiles: bit-identical results.
-// Measured against gemm_bf16_fast_kernel<256, 256> on one MI355X (M x N x K, us): where the operands come past the 256 MB
-// Infinity Cache the longer lead wins (32768 x 4096 x 11008 2098 -> 1962, 46173 x 1280 x 5120 495 -> 462,
-// 32768 x 1536 x 17920 1328 -> 1227, SwiGLU 32768 x 22016 x 4096 4308 -> 4028); where they stay in it the two are equal
-// (8192^3 704 / 707, 32768 x 6144 x 4096 1125 / 1117) and a short K loses (32768 x 2048 x 1536 154 / 160).  With all eight A
-// reads in one phase: 2075 and 482 on the first two.  For K-major operands (twice the LDS reads) it was 2-25 % slower.
+// It is the 256 x 256 tile of K-contiguous operands for every shape and epilogue.  Against gemm_bf16_fast_kernel<256, 256> with
+// operands that have left the caches, as they have when a step comes round to them again, it was faster on 108 of 110 shapes
+// (M = 1500 .. 32768, 22 outputs; the other two within 0.6 %), us: 8192 x 8192 x 4096 with fp32 output 437 -> 391,
+// 8192 x 1280 x 5120 135 -> 114, 4096 x 3072 x 2048 51.5 -> 44.5, 32768 x 4096 x 11008 2199 -> 2010, 32768 x 1536 x 1536
+// 174 -> 170; the distillation head at 8192 tokens, V = 151936, H = 4096 / 2048 35.4 -> 32.8 ms.  On operands that stay in
+// the 256 MB Infinity Cache the two are equal (8192^3 704 / 707) up to 4 % on a short K (32768 x 2048 x 1536 154 / 160).
+// For K-major operands (twice the LDS reads) it was built too: 6-12 % slower warm, 2-8 % slower cold wherever the grid fills
+// the chip (32768 x 8960 x 1536 736 -> 788), and in smaller grids behind the other tiles.
 // B half g holds the rows 64 w + 32 g .. + 31 of every wave column w (a wave's 64 columns stay adjacent); for SwiGLU
 // g = 0 gate rows, g = 1 up rows.
 struct HalfStager {
@@ -1144,11 +1148,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
 #define MS_INST(BM, WN, TA, TB)                                                                          \
     template __global__ void gemm_bf16_fast_kernel<BM, BM, 2, WN, TA, TB, EPI_NONE, false>(GemmParams); \
     template __global__ void gemm_bf16_fast_kernel<BM, BM, 2, WN, TA, TB, EPI_NONE, true>(GemmParams)
-MS_INST(256, 4, false, false); MS_INST(256, 4, false, true); MS_INST(256, 4, true, false); MS_INST(256, 4, true, true);
+template __global__ void gemm_bf16_fast_kernel<256, 256, 2, 4, false, false, EPI_NONE, false>(GemmParams);
+MS_INST(256, 4, false, true); MS_INST(256, 4, true, false); MS_INST(256, 4, true, true);
 MS_INST(128, 2, false, false); MS_INST(128, 2, false, true); MS_INST(128, 2, true, false); MS_INST(128, 2, true, true);
 #undef MS_INST
 template __global__ void gemm_bf16_pp_kernel<EPI_NONE>(GemmParams);
 template __global__ void gemm_bf16_pp_kernel<EPI_SWIGLU>(GemmParams);
+template __global__ void gemm_bf16_pp_kernel<EPI_KD_DZ>(GemmParams);
+template __global__ void gemm_bf16_pp_kernel<EPI_KD_STATS>(GemmParams);
 #define MS_INST_RING(BM, BN, WM, WN, NST, TA, TB) \
     template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI_NONE, true, NST>(GemmParams)
 #define MS_INST_RINGS(BM, BN, WM, WN, NST)                                                             \
@@ -1162,7 +1169,6 @@ MS_INST_RINGS(128, 128, 4, 2, 4); MS_INST_RINGS(128, 256, 2, 4, 3); MS_INST_RING
 #undef MS_INST_RING
 #define MS_INST_EPI(EPI)                                                                                      \
     template __global__ void gemm_bf16_fast_kernel<256, 256, 2, 4, false, false, EPI, false>(GemmParams);    \
-    template __global__ void gemm_bf16_fast_kernel<256, 256, 2, 4, false, false, EPI, true>(GemmParams);     \
     template __global__ void gemm_bf16_fast_kernel<128, 128, 2, 2, false, false, EPI, false>(GemmParams);    \
     template __global__ void gemm_bf16_fast_kernel<128, 128, 2, 2, false, false, EPI, true>(GemmParams)
 MS_INST_EPI(EPI_KD_DZ); MS_INST_EPI(EPI_KD_STATS); MS_INST_EPI(EPI_SWIGLU);
@@ -1195,8 +1201,9 @@ void launch_fast_tile(const GemmParams &p, int ta, int tb, dim3 grid, hipStream_
 #define GO(TA, TB)                                                                                                  \
     do {                                                                                                            \
         if constexpr (NST > 2) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true, NST><<<grid, NT, 0, s>>>(p); \
-        else if (use_mfma16()) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true><<<grid, NT, 0, s>>>(p);      \
-        else gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, false><<<grid, NT, 0, s>>>(p);                       \
+        else if (!use_mfma16()) gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, false><<<grid, NT, 0, s>>>(p);    \
+        else if constexpr (BM == 256 && !TA && !TB) gemm_bf16_pp_kernel<EPI><<<grid, NT, 0, s>>>(p);                \
+        else gemm_bf16_fast_kernel<BM, BN, WM, WN, TA, TB, EPI, true><<<grid, NT, 0, s>>>(p);                        \
     } while (0)
     if constexpr (EPI != EPI_NONE) GO(false, false);
     else if (!ta && !tb) GO(false, false);
@@ -1214,17 +1221,6 @@ ms_status launch_bf16_fast(GemmParams &p, int tile, int ta, int tb, int splits, 
     p.tiles_n = ms_cdiv(p.N, EPI == EPI_SWIGLU ? t.bn / 2 : t.bn);
     dim3 grid(p.tiles_m * p.tiles_n, splits);
     ProfScope ps((ta || tb) ? 1 : 0, flops, s);
-    // Operands that do not stay in the 256 MB Infinity Cache: the ping-pong kernel.  The line is between 319 MB, where it
-    // gains nothing on operands that a repeated call finds there, and 448 MB, where it gains 7 %; on operands that have
-    // left the cache it would pay lower as well (3 % at 281 and 319 MB, 12 % at 218 MB with a short N).
-    if constexpr (EPI == EPI_NONE || EPI == EPI_SWIGLU) {
-        const double stream = 2.0 * ((double)p.M + p.N * (EPI == EPI_SWIGLU ? 2.0 : 1.0)) * p.K;
-        if (tile == T256 && !ta && !tb && use_mfma16() && splits == 1 && (forced_tile() == kPingPong || (forced_tile() == 0 && stream > 384e6))) {
-            gemm_bf16_pp_kernel<EPI><<<grid, 512, 0, s>>>(p);
-            MS_LAUNCH_CHECK();
-            return MS_OK;
-        }
-    }
     switch (tile) {
         case T256: launch_fast_tile<256, 256, 2, 4, 2, EPI>(p, ta, tb, grid, s); break;
         case R128: launch_fast_tile<128, 128, 4, 2, 4, EPI>(p, ta, tb, grid, s); break;

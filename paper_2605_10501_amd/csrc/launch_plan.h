@@ -50,7 +50,7 @@ struct MsTile {
     MsTileTimes lin, wgrad;
 };
 enum { T256 = 0, T128 = 1, R128 = 2, R128x256 = 3, R64x128 = 4, R64 = 5, kNumTiles = 6 };
-constexpr int kPingPong = 256256;       // forced tile: 256 x 256 with the ping-pong kernel where it applies
+constexpr int kPingPong = 256256;       // another code of the 256 x 256 tile (whose K-contiguous form is the ping-pong kernel)
 constexpr MsTile kTiles[kNumTiles] = {
     {256, 256, 256, 1, {{0.852, 1.483, 0, 0}, 1.58, 2.35, 0}, {{1.08, 1.48, 0, 0}, 3.5, 0, 0}},
     {128, 128, 128, 2, {{0.450, 0.618, 0.778, 0.949}, 0.10, 4.28, 3.03}, {{0.60, 0.70, 0.78, 0.97}, 1.8, 0, 0}},
