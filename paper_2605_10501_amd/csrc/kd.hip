@@ -5,7 +5,11 @@
 // five running numbers per token: max and sum-of-exponentials of both models and the cross
 // term sum_v e^{zt/T - m_t} (zt - zs)/T.  From those, KL_tok = A/s_t - lse_t + lse_s.
 // Pass 2 recomputes each chunk's logits, forms dz = (scale/T)(q - p) in the storage dtype and
-// feeds it to the two gradient GEMMs (dHs accumulated in fp32 over chunks, dWs chunk rows +=).
+// feeds it to the two gradient GEMMs (dHs accumulated in fp32 over chunks, dWs chunk rows +=).  It walks the chunks from
+// the last one down, because the logits that pass 1 left in the two [N, chunk] tiles are still there: the teacher logits of
+// the last two chunks on the bf16 fast path (whose student logits are never stored, so both tiles are free for them), the
+// last chunk's logits of both models otherwise.  They are not computed again (MI355X: 1024 tokens, V = 32000 in four
+// chunks, H = 2048 / 1024 849 -> 771 us; 8192 tokens, V = 151936 in 19 chunks, H = 4096 / 2048 32.8 -> 32.1 ms).
 // On the bf16 fast path the student logits are never stored: the epilogue of their GEMM reads the
 // teacher logits of the same tile and emits per-strip partial statistics (pass 1, merged per token
 // by a small kernel) or dz itself (pass 2).
@@ -188,38 +192,45 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
     const char *wt = (const char *)kd->w_teacher_dev, *wsd = (const char *)kd->w_student_dev;
     const int passes = (d_h_s || d_w_s) ? 2 : 1;
     const bool keep = p.keep && passes == 2;
-    if (d_h_s) MS_TRY(launch_fill_f32(p.dhs, (long)n * Hs, 0.f, s));
+    const int chunks = ms_cdiv(V, Cv);
     for (int t0 = 0; t0 < n; t0 += p.tb) {
         const int nb = n - t0 < p.tb ? n - t0 : p.tb;
         const char *ht_b = (const char *)h_t + (size_t)t0 * Ht * es, *hs_b = (const char *)h_s + (size_t)t0 * Hs * es;
         float *stats_b = p.stats + (size_t)t0 * kStat, *dhs_b = p.dhs + (size_t)t0 * Hs;
         // bf16 fast path: the student-logits GEMM consumes its own output (statistics in pass 1, dz in pass 2)
-        // together with the stored teacher logits; the zs buffer then only holds the per-strip partials
+        // together with the stored teacher logits
         bool fused = dt == MS_BF16;
         for (int v0 = 0; v0 < V && fused; v0 += Cv) {
             const int cw = V - v0 < Cv ? V - v0 : Cv;
             fused = gemm_kd_epilogue_supported(nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, p.zt, Cv, p.dz, Cv, 0);
         }
+        // Teacher logits of how many chunks, the last ones, outlive pass 1.  With two tiles for them, chunks alternate between
+        // the two, and the partial statistics (32 bytes per 64 columns) move to the dz buffer, which is not in use before pass 2.
+        const bool two = fused && passes == 2 && !keep && ms_cdiv(Cv, 64) * 32 <= Cv * 2;
+        const int kept = keep ? chunks : two ? 2 : 1;
+        float *part = two ? (float *)p.dz : p.zs;
         for (int pass = 0; pass < passes; ++pass) {
-            for (int v0 = 0, ci = 0; v0 < V; v0 += Cv, ++ci) {
-                const int cw = V - v0 < Cv ? V - v0 : Cv;
-                float *zt = keep ? p.zt + (size_t)ci * p.tb * Cv : p.zt;
-                if (pass == 0 || !keep)
+            for (int i = 0; i < chunks; ++i) {
+                const int ci = pass == 0 ? i : chunks - 1 - i;
+                const int v0 = ci * Cv, cw = V - v0 < Cv ? V - v0 : Cv;
+                float *zt = keep ? p.zt + (size_t)ci * p.tb * Cv : two && (ci & 1) ? p.zs : p.zt;
+                if (pass == 0 || i >= kept)
                     MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Ht, 1.f, ht_b, Ht, wt + (size_t)v0 * Ht * es, Ht, zt, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
                 if (fused) {
                     const int nparts = ms_cdiv(cw, 64);
                     if (pass == 0) {
-                        MS_TRY(gemm_kd_epilogue(2, nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, zt, Cv, nullptr, p.zs, nparts,
+                        MS_TRY(gemm_kd_epilogue(2, nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, zt, Cv, nullptr, part, nparts,
                                                 inv_t, 0.f, nullptr, 0, 0, s));
                         ProfScope ps(9, 32.0 * nb * nparts, s);
-                        kd_combine_kernel<<<ms_cdiv(nb, 4), 256, 0, s>>>(p.zs, nparts, nb, v0 == 0, stats_b);
+                        kd_combine_kernel<<<ms_cdiv(nb, 4), 256, 0, s>>>(part, nparts, nb, v0 == 0, stats_b);
                         MS_LAUNCH_CHECK();
                         continue;
                     }
                     MS_TRY(gemm_kd_epilogue(1, nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, zt, Cv, stats_b, nullptr, 0, inv_t,
                                             kd->loss_scale * inv_t, p.dz, Cv, 0, s));
                 } else {
-                    MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Hs, 1.f, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, p.zs, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
+                    if (pass == 0 || i > 0)
+                        MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Hs, 1.f, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, p.zs, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
                     if (pass == 0) {
                         ProfScope ps(9, 8.0 * nb * cw, s);
                         kd_stats_kernel<<<nb, 256, 0, s>>>(zt, p.zs, Cv, cw, inv_t, v0 == 0, stats_b);
@@ -235,8 +246,8 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
                     }
                     MS_LAUNCH_CHECK();
                 }
-                if (d_h_s)  // dHs[N, Hs] += dz[N, cw] Ws_c[cw, Hs]
-                    MS_TRY(ms_k_gemm(dt, 0, 1, nb, Hs, cw, 1.f, p.dz, Cv, wsd + (size_t)v0 * Hs * es, Hs, dhs_b, Hs, 1, 1, nullptr, nullptr, 0, 0, 1, s));
+                if (d_h_s)  // dHs[N, Hs] (+)= dz[N, cw] Ws_c[cw, Hs]
+                    MS_TRY(ms_k_gemm(dt, 0, 1, nb, Hs, cw, 1.f, p.dz, Cv, wsd + (size_t)v0 * Hs * es, Hs, dhs_b, Hs, 1, i > 0, nullptr, nullptr, 0, 0, 1, s));
                 if (d_w_s)  // dWs_c[cw, Hs] += dz^T[cw, N] Hs[N, Hs]
                     MS_TRY(ms_k_gemm(dt, 1, 1, cw, Hs, nb, 1.f, p.dz, Cv, hs_b, Hs, (float *)d_w_s + (size_t)v0 * Hs, Hs, 1, 1, nullptr, nullptr, 0, 0, 0, s));
             }
