@@ -4,7 +4,9 @@
 // Tensors that live between kernels are stored in the section dtype, except the forward residual
 // stream (layer inputs, post-attention sums, last layer output), which is the running sum of all
 // branch outputs and is kept in fp32; norm statistics, log-sum-exps, weight gradients and the loss
-// are fp32 too.  In forward+backward mode every layer keeps its
+// are fp32 too.  The first layer's input of a bf16 section is bf16 already (x_in, or rows of the embedding table) and is
+// read as it is: the same numbers, without a conversion pass and with half the bytes for the norm, the residual and the
+// norm backward that read it.  In forward+backward mode every layer keeps its
 // input, both normed activations, the (rotated) qkv, the attention output and log-sum-exp, the
 // post-attention residual, the FFN pre-activation and activation: nothing is recomputed.
 #include <vector>
@@ -153,13 +155,15 @@ struct Exec {
     Plan *p;
     hipStream_t s;
     int dt, kind;
+    const void *x0;               // first layer's input in the storage type, null if it is in the fp32 stream like the others'
 
+    bool fp32_stream(const void *x) const { return x != x0; }
     ms_status gemm(int ta, int tb, int M, int N, int K, const void *A, long lda, const void *B, long ldb, void *C,
                    long ldc, bool c_fp32, bool acc, const void *bias, const void *res, long ldr) {
-        return ms_k_gemm(dt, ta, tb, M, N, K, 1.f, A, lda, B, ldb, C, ldc, c_fp32, acc, bias, res, ldr, res != nullptr,
+        return ms_k_gemm(dt, ta, tb, M, N, K, 1.f, A, lda, B, ldb, C, ldc, c_fp32, acc, bias, res, ldr, res && fp32_stream(res),
                          acc ? 0 : 1, s);
     }
-    // y[n, out] = x[n, in] W[out, in]^T (+ bias) (+ res); with a residual, res and y are the fp32 stream
+    // y[n, out] = x[n, in] W[out, in]^T (+ bias) (+ res); with a residual, y is the fp32 stream
     ms_status linear(const void *x, int in, const void *W, const void *bias, int out, void *y, const void *res) {
         return gemm(0, 0, m.n, out, in, x, in, W, in, y, out, res != nullptr, false, bias, res, out);
     }
@@ -182,8 +186,28 @@ struct Exec {
         return MS_OK;
     }
 
+    // The first layer's input: x_in itself, rows of the embedding table in `buf`, or, where x_in cannot be read in place (its
+    // rows are not 16-byte aligned, or the call writes h_out or d_x_in over it before the backward pass is done with it), a
+    // copy in the fp32 stream.
+    ms_status first_input(const void *x_in, const ms_section_ptrs *weights, void *buf, const void *h_out, const void *d_x_in, const void **x) {
+        const size_t bytes = (size_t)m.n * m.d * m.es;
+        auto overlaps = [&](const void *q) { return q && (const char *)q < (const char *)x_in + bytes && (const char *)x_in < (const char *)q + bytes; };
+        if (c->vocab > 0) {
+            MS_TRY(ms_k_embedding_forward(dt, 0, m.n, m.d, c->vocab, (const int32_t *)x_in, weights->embedding, buf, s));
+            x0 = *x = buf;
+        } else if (dt == MS_F32) {
+            x0 = *x = x_in;
+        } else if (((uintptr_t)x_in & 15) == 0 && !overlaps(h_out) && !overlaps(d_x_in)) {
+            x0 = *x = x_in;
+        } else {
+            MS_TRY(launch_convert_bf16_to_f32(x_in, (float *)buf, (long)m.n * m.d, s));
+            *x = buf;
+        }
+        return MS_OK;
+    }
+
     ms_status layer_forward(const ms_layer_ptrs &w, const void *x, LayerBuf &l, void *y) {
-        MS_TRY(ms_k_norm_forward(kind, dt, 1, m.n, m.d, c->norm_eps, x, w.norm1_g, w.norm1_b, l.h1, l.mean1, l.rstd1, s));
+        MS_TRY(ms_k_norm_forward(kind, dt, fp32_stream(x), m.n, m.d, c->norm_eps, x, w.norm1_g, w.norm1_b, l.h1, l.mean1, l.rstd1, s));
         MS_TRY(linear(l.h1, m.d, w.w_qkv, m.dec ? nullptr : w.b_qkv, m.dqkv, l.qkv, nullptr));
         if (m.dec) MS_TRY(ms_k_rope(dt, m.n, m.nq + m.nkv, m.hd, m.dqkv, l.qkv, p->pos, p->rope, 0, s));
         MS_TRY(ms_k_attention_forward(dt, m.dec, m.nq, m.nkv, m.hd, m.n, b->n_seqs, m.max_seqlen, b->cu_seqlens_dev,
@@ -219,7 +243,7 @@ struct Exec {
         if (m.dec) MS_TRY(ms_k_rope(dt, m.n, m.nq + m.nkv, m.hd, m.dqkv, p->dqkv, p->pos, p->rope, 1, s));
         MS_TRY(dgrad(p->dqkv, m.dqkv, w.w_qkv, m.d, p->dh));
         MS_TRY(wgrad(p->dqkv, m.dqkv, l.h1, m.d, g.w_qkv, g.b_qkv));
-        MS_TRY(ms_k_norm_backward(kind, dt, 1, m.n, m.d, p->dh, l.x, w.norm1_g, l.mean1, l.rstd1, p->dx2, dx,
+        MS_TRY(ms_k_norm_backward(kind, dt, fp32_stream(l.x), m.n, m.d, p->dh, l.x, w.norm1_g, l.mean1, l.rstd1, p->dx2, dx,
                                   (float *)g.norm1_g, (float *)g.norm1_b, p->norm_scratch, s));
         return MS_OK;
     }
@@ -247,19 +271,14 @@ extern "C" ms_status ms_section_forward(const ms_section_config *cfg, const ms_s
     if (workspace_bytes < p.bytes)
         return ms_fail(MS_ERR_WORKSPACE, "section_forward: workspace %zu < %zu bytes", workspace_bytes, p.bytes);
     Exec e{cfg, dims_of(cfg, batch->n_tokens, max_seqlen), batch, &p, (hipStream_t)stream, cfg->dtype,
-           cfg->arch == MS_ENCODER ? 1 : 0};
+           cfg->arch == MS_ENCODER ? 1 : 0, nullptr};
     MS_TRY(e.prologue());
-    const void *x = x_in;
-    if (cfg->vocab > 0) {
-        MS_TRY(ms_k_embedding_forward(e.dt, 1, e.m.n, e.m.d, cfg->vocab, (const int32_t *)x_in, weights->embedding, p.xa, e.s));
-        x = p.xa;
-    } else if (e.dt == MS_BF16) {
-        MS_TRY(launch_convert_bf16_to_f32(x_in, (float *)p.xa, (long)e.m.n * e.m.d, e.s));
-        x = p.xa;
-    }
+    const void *x = nullptr;
+    MS_TRY(e.first_input(x_in, weights, p.xa, nullptr, nullptr, &x));
     for (int li = 0; li < cfg->n_layers; ++li) {
         void *y = li + 1 == cfg->n_layers ? p.y_last : (x == p.xa ? p.xb : p.xa);
         MS_TRY(e.layer_forward(weights->layers[li], x, p.layers[0], y));
+        e.x0 = nullptr;                       // (its buffer takes a later layer's fp32 stream)
         x = y;
     }
     return ms_k_norm_forward(e.kind, e.dt, 1, e.m.n, e.m.d, cfg->norm_eps, x, weights->final_norm_g, weights->final_norm_b,
@@ -294,17 +313,11 @@ extern "C" ms_status ms_section_forward_backward(const ms_section_config *cfg, c
     const size_t kd_bytes = kd ? ms_kd_workspace_bytes(kd, batch->n_tokens) : 0;
     if (workspace_bytes < p.bytes + kd_bytes)
         return ms_fail(MS_ERR_WORKSPACE, "section_forward_backward: workspace %zu < %zu bytes", workspace_bytes, p.bytes + kd_bytes);
-    Exec e{cfg, dims_of(cfg, batch->n_tokens, max_seqlen), batch, &p, s, cfg->dtype, cfg->arch == MS_ENCODER ? 1 : 0};
+    Exec e{cfg, dims_of(cfg, batch->n_tokens, max_seqlen), batch, &p, s, cfg->dtype, cfg->arch == MS_ENCODER ? 1 : 0, nullptr};
     MS_TRY(e.prologue());
     const int L = cfg->n_layers;
-    const void *x = x_in;
-    if (cfg->vocab > 0) {
-        MS_TRY(ms_k_embedding_forward(e.dt, 1, e.m.n, e.m.d, cfg->vocab, (const int32_t *)x_in, weights->embedding, p.layers[0].x, s));
-        x = p.layers[0].x;
-    } else if (e.dt == MS_BF16) {
-        MS_TRY(launch_convert_bf16_to_f32(x_in, (float *)p.layers[0].x, (long)e.m.n * e.m.d, s));
-        x = p.layers[0].x;
-    }
+    const void *x = nullptr;
+    MS_TRY(e.first_input(x_in, weights, p.layers[0].x, h_out, d_x_in, &x));
     for (int li = 0; li < L; ++li) {
         void *y = li + 1 == L ? p.y_last : p.layers[li + 1].x;
         p.layers[li].x = const_cast<void *>(x);
