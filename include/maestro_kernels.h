@@ -41,6 +41,12 @@ ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, 
                     int64_t ldc, int32_t c_fp32, int32_t accumulate, const void *bias,
                     const void *residual, int64_t ldr, int32_t residual_fp32, int32_t split_k, void *stream);
 
+/* Backward pass of a linear layer y[n,out] = x[n,in] W[out,in]^T: dx[n,in] (+)= dy W and dW[out,in] += dy^T x (fp32), in one launch
+ * where that is faster than one each.  dy has rows ldy apart; dx is fp32 if dx_fp32 and is added to if dx_accumulate
+ * (which for bf16 products needs an fp32 dx).  dx and dW must not overlap an input. */
+ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy, const void *W,
+                               const void *x, void *dx, int32_t dx_fp32, int32_t dx_accumulate, void *dW, void *stream);
+
 /* Gate/up projection of a SwiGLU FFN with the activation fused into the GEMM (bf16 only):
  *   gate_up[M, 2F] = round(A[M,K] W[2F,K]^T)  (W rows: F gate rows, then F up rows; written if gate_up != NULL)
  *   act[M, F]      = silu(gate) * up, evaluated on the rounded pre-activations (what a separate kernel would read).

@@ -641,29 +641,35 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
 // itself the compiler gives it 276 registers, which leave a CU with one workgroup, instead of 173 (dz at
 // 3629 x 4480 x 1536: 70.9 us; 74.2 on v_mfma_f32_32x32x16, which needs fewer).
 constexpr int fast_waves_per_simd(int bm, int waves, int epi, int nst) { return waves == 8 || (bm == 128 && nst == 2 && epi == EPI_KD_DZ) ? 2 : 1; }
-template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI = EPI_NONE, bool M16 = false, int NST = 2>
-__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI, NST)))) void gemm_bf16_fast_kernel(GemmParams p) {
-    constexpr int NT = 64 * WM * WN;
+template <int BM, int BN, int NST> struct FastLds {
+    bf16_t *a[4], *b[4];
+};
+// The kernel's LDS: separate objects (not one carved array), because the compiler orders LDS reads against in-flight
+// direct-to-LDS loads by alias analysis, and can only tell the buffer being filled from the buffer being read when
+// they are distinct objects
+#define MS_FAST_LDS(BM, BN, NST)                                                                                       \
+    static_assert(NST >= 2 && NST <= 4, "ring of 2..4 stages");                                                        \
+    __shared__ __align__(16) bf16_t As0[BM * BK], As1[BM * BK], As2[NST > 2 ? BM * BK : 8], As3[NST > 3 ? BM * BK : 8]; \
+    __shared__ __align__(16) bf16_t Bs0[BN * BK], Bs1[BN * BK], Bs2[NST > 2 ? BN * BK : 8], Bs3[NST > 3 ? BN * BK : 8]; \
+    const FastLds<BM, BN, NST> lds = {{As0, As1, As2, As3}, {Bs0, Bs1, Bs2, Bs3}}
+
+// Workgroup b of the nb that compute one product (of one K split)
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI, bool M16, int NST>
+__device__ __forceinline__ void gemm_fast_body(const GemmParams &p, const FastLds<BM, BN, NST> &lds, int b, int nb, int split) {
     constexpr int FR = M16 ? 16 : 32;                         // rows of an MFMA fragment / accumulator block
     constexpr int KSTEP = M16 ? 32 : 16, KS = BK / KSTEP;     // contraction depth of an MFMA, k-steps per K tile
     constexpr int WTM = BM / WM, WTN = BN / WN, MI = WTM / FR, NI = WTN / FR;
     constexpr int MI32 = WTM / 32, NI32 = WTN / 32;           // the epilogues work on 32-row blocks
     using acc_t = std::conditional_t<M16, f32x4, f32x16>;
     constexpr int ACC_N = M16 ? 4 : 16;
-    // four separate LDS objects (not one carved array): the compiler orders LDS reads against
-    // in-flight direct-to-LDS loads by alias analysis, and can only tell the buffer being filled
-    // from the buffer being read when they are distinct objects
-    static_assert(NST >= 2 && NST <= 4, "ring of 2..4 stages");
-    constexpr int A2 = NST > 2 ? BM * BK : 8, B2 = NST > 2 ? BN * BK : 8, A3 = NST > 3 ? BM * BK : 8, B3 = NST > 3 ? BN * BK : 8;
-    __shared__ __align__(16) bf16_t As0[BM * BK], As1[BM * BK], As2[A2], As3[A3], Bs0[BN * BK], Bs1[BN * BK], Bs2[B2], Bs3[B3];
-    bf16_t *const Ast[4] = {As0, As1, As2, As3}, *const Bst[4] = {Bs0, Bs1, Bs2, Bs3};
+    bf16_t *const As0 = lds.a[0], *const As1 = lds.a[1], *const Bs0 = lds.b[0], *const Bs1 = lds.b[1];
+    bf16_t *const Ast[4] = {lds.a[0], lds.a[1], lds.a[2], lds.a[3]}, *const Bst[4] = {lds.b[0], lds.b[1], lds.b[2], lds.b[3]};
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it in a scalar register
     const int wm = wave / WN, wn = wave % WN;
     int pid;
     {
-        const int nb = gridDim.x, b = blockIdx.x;
         const int per = nb >> 3, rem = nb & 7, x = b & 7, q = b >> 3;
         pid = x * per + (x < rem ? x : rem) + q;
     }
@@ -675,7 +681,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fa
     const int tn = (pid % (GM * p.tiles_n)) / gsize;
     const int m0 = tm * BM, n0 = tn * BN;
 
-    const int kt_begin = blockIdx.y * p.k_tiles_per_split;
+    const int kt_begin = split * p.k_tiles_per_split;
     int kt_end = kt_begin + p.k_tiles_per_split;
     const int kt_total = (p.K + BK - 1) / BK;
     if (kt_end > kt_total) kt_end = kt_total;
@@ -843,6 +849,30 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fa
     const int sq = wave / WPA;
     float *stg = (float *)(sq == 0 ? As0 : sq == 1 ? As1 : sq == 2 ? Bs0 : Bs1) + (wave % WPA) * 2048;
     gemm_epilogue<EPI, M16, TA, TB>(p, acc, stg, m0, n0, wn, lane, row_base, col_base);
+}
+
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI = EPI_NONE, bool M16 = false, int NST = 2>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI, NST)))) void gemm_bf16_fast_kernel(GemmParams p) {
+    MS_FAST_LDS(BM, BN, NST);
+    gemm_fast_body<BM, BN, WM, WN, TA, TB, EPI, M16, NST>(p, lds, blockIdx.x, gridDim.x, blockIdx.y);
+}
+
+// Both products of a linear layer's backward pass, which share dy and nothing else, in one grid: the input gradient's
+// workgroups (pd: dx = dy W, K-major B) and the weight gradient's (pw: dW += dy^T x, both K-major, `splits` parts of K).
+// One product of a small micro-batch leaves CUs idle (100-250 workgroups) and any product has a last round; together they
+// leave one.  The product with the longer workgroups comes first (see ms_choose_pair).  One MI355X, us, backward GEMMs of a
+// layer apart -> together: c2 student at 2053 tokens 176 -> 146, encoder at 1031 tokens 175 -> 130; the fp32 form (five pairs in
+// the c1 step) takes the step from 271 to 242.
+template <int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI_NONE, NST)))) void gemm_bf16_pair_kernel(GemmParams pd, GemmParams pw, int nd, int nw, int wgrad_first) {
+    MS_FAST_LDS(BM, BN, NST);
+    const int b = blockIdx.x, total_w = gridDim.x - nd;
+    if (wgrad_first ? b < total_w : b >= nd) {
+        const int bw = wgrad_first ? b : b - nd;
+        gemm_fast_body<BM, BN, WM, WN, true, true, EPI_NONE, true, NST>(pw, lds, bw % nw, nw, bw / nw);
+    } else {
+        gemm_fast_body<BM, BN, WM, WN, false, true, EPI_NONE, true, NST>(pd, lds, wgrad_first ? b - total_w : b, nd, 0);
+    }
 }
 
 // The 256 x 256 tile with two wave groups that take turns on the matrix cores; K-contiguous operands only.
@@ -1079,10 +1109,9 @@ template <bool TRANS, bool FAST> struct F32Frag {
 // FAST needs 16-byte aligned K-contiguous rows with K % 4 == 0 and operands below 4 GB; the other form covers the rest.
 // (The first slices are requested before the loop, also where K = 0 leaves it nothing to do: the range is then empty.)
 template <bool TA, bool TB, bool FAST>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
-    __shared__ float part[4][32][33];
+__device__ __forceinline__ void gemm_f32_body(const GemmF32Params &p, float (&part)[4][32][33], int b_) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int m0 = (int)(blockIdx.x / p.tiles_n) * 32, n0 = (int)(blockIdx.x % p.tiles_n) * 32;
+    const int m0 = b_ / p.tiles_n * 32, n0 = b_ % p.tiles_n * 32;
     const int slices = (p.K + 15) / 16, mine = slices > wave ? (slices - wave + 3) / 4 : 0;
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.A, FAST ? ms_matrix_extent(TA ? p.K : p.M, TA ? p.M : p.K, p.lda) * 4 : 0);
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.B, FAST ? ms_matrix_extent(TB ? p.K : p.N, TB ? p.N : p.K, p.ldb) * 4 : 0);
@@ -1142,6 +1171,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
         if (inside(e)) p.C[(long)(m0 + q) * p.ldc + col] = p.accumulate ? old[e] + v : v;
     }
 }
+template <bool TA, bool TB, bool FAST>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
+    __shared__ float part[4][32][33];
+    gemm_f32_body<TA, TB, FAST>(p, part, (int)blockIdx.x);
+}
+// Both products of a linear layer's backward pass in one grid (see gemm_bf16_pair_kernel); the first nd workgroups are the
+// input gradient's
+template <bool FAST>
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(GemmF32Params pd, GemmF32Params pw, int nd) {
+    __shared__ float part[4][32][33];
+    const int b = (int)blockIdx.x;
+    if (b < nd) gemm_f32_body<false, true, FAST>(pd, part, b);
+    else gemm_f32_body<true, true, FAST>(pw, part, b - nd);
+}
 
 // Explicit instantiations: the host pass has been seen to reference the launch stubs of some of these
 // without defining them when they are only instantiated implicitly from the launcher below.
@@ -1166,6 +1209,10 @@ template __global__ void gemm_bf16_pp_kernel<EPI_KD_STATS>(GemmParams);
     template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI_SWIGLU, true, NST>(GemmParams)
 MS_INST_RINGS(128, 128, 4, 2, 4); MS_INST_RINGS(128, 256, 2, 4, 3); MS_INST_RINGS(64, 128, 2, 2, 3); MS_INST_RINGS(64, 64, 2, 1, 4);
 #undef MS_INST_RINGS
+#define MS_INST_PAIR(BM, BN, WM, WN, NST) template __global__ void gemm_bf16_pair_kernel<BM, BN, WM, WN, NST>(GemmParams, GemmParams, int, int, int)
+MS_INST_PAIR(256, 256, 2, 4, 2); MS_INST_PAIR(128, 128, 2, 2, 2); MS_INST_PAIR(128, 128, 4, 2, 4); MS_INST_PAIR(128, 256, 2, 4, 3);
+MS_INST_PAIR(64, 128, 2, 2, 3); MS_INST_PAIR(64, 64, 2, 1, 4);
+#undef MS_INST_PAIR
 #undef MS_INST_RING
 #define MS_INST_EPI(EPI)                                                                                      \
     template __global__ void gemm_bf16_fast_kernel<256, 256, 2, 4, false, false, EPI, false>(GemmParams);    \
@@ -1257,6 +1304,56 @@ ms_status launch_bf16(const GemmParams &p, int ta, int tb, int splits, hipStream
     return MS_OK;
 }
 
+// fp32: whether an operand (rows x K as the product sees it) can be read through a descriptor, 16 bytes at a time where it is
+// K-contiguous
+bool f32_fast(const void *q, long ld, bool trans, long rows, long K) {
+    return (trans || (((uintptr_t)q & 15) == 0 && ld % 4 == 0 && K % 4 == 0)) && ms_buffer_range_ok(trans ? K : rows, trans ? rows : K, ld, 4);
+}
+
+// Checked arguments of a bf16 product, all but the split of K
+struct Bf16Gemm {
+    GemmParams p;
+    bool fast;          // the direct-to-LDS kernels take it
+    int kt;             // K tiles
+    double out_bytes;   // what the epilogue moves per output element
+};
+ms_status prepare_bf16(int trans_a, int trans_b, int M, int N, int K, float alpha, const void *A, long lda, const void *B, long ldb,
+                       void *C, long ldc, int c_fp32, int accumulate, const void *bias, const void *residual, long ldr,
+                       int residual_fp32, Bf16Gemm *g) {
+    auto al = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
+    if (!al(A) || !al(B) || lda % 8 || ldb % 8 || (trans_a ? M % 8 : K % 8) || (trans_b ? N % 8 : K % 8))
+        return ms_fail(MS_ERR_UNSUPPORTED,
+                       "gemm(bf16): contiguous dimension of each operand must be a multiple of 8 and 16-byte aligned "
+                       "(M=%d N=%d K=%d ta=%d tb=%d lda=%ld ldb=%ld)", M, N, K, trans_a, trans_b, (long)lda, (long)ldb);
+    GemmParams &p = g->p;
+    p = {};
+    p.A = A; p.B = B; p.C = C; p.bias = bias; p.residual = residual;
+    p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha;
+    p.c_fp32 = c_fp32; p.accumulate = accumulate; p.res_fp32 = residual_fp32;
+    // fast path (direct-to-LDS loads, descriptor-addressed epilogue) needs full K tiles for a K-contiguous
+    // operand and 32-bit byte offsets
+    const long lim = (1L << 32) - (1L << 20);
+    const long rows_a = trans_a ? K : M, rows_b = trans_b ? K : N;
+    g->fast = forced_tile() >= 0 && ((trans_a && trans_b) || K % BK == 0) && (rows_a + 256) * lda * 2 < lim &&
+              (rows_b + 256) * ldb * 2 < lim && ((long)M + 256) * ldc * 4 < lim &&
+              (!residual || ((long)M + 256) * ldr * 4 < lim);
+    g->kt = ms_cdiv(K, BK) < 1 ? 1 : ms_cdiv(K, BK);
+    g->out_bytes = (c_fp32 ? 4 : 2) + (residual ? (residual_fp32 ? 4 : 2) : 0) + (accumulate ? 4 : 0);
+    return MS_OK;
+}
+// The last arguments, which depend on the number of K splits; returns how many there really are
+int set_splits(Bf16Gemm &g, int splits) {
+    GemmParams &p = g.p;
+    auto al = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
+    if (splits > g.kt) splits = g.kt;
+    p.k_tiles_per_split = ms_cdiv(g.kt, splits);
+    splits = ms_cdiv(g.kt, p.k_tiles_per_split);
+    p.atomic = splits > 1;
+    p.vec_epilogue = !p.atomic && p.N % 4 == 0 && p.ldc % 4 == 0 && al(p.C) && (!p.residual || (p.ldr % 4 == 0 && al(p.residual))) &&
+                     (!p.bias || ((uintptr_t)p.bias & 7) == 0);
+    return splits;
+}
+
 }  // namespace
 
 extern "C" ms_status ms_k_gemm_config(int32_t tile, int32_t mfma16) {
@@ -1297,13 +1394,9 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
                              residual_fp32, split_k, stream);
         }
         const unsigned grid = (unsigned)tiles;
-        auto fast = [&](const void *q, long ld, bool trans, long rows) {
-            return (trans || (((uintptr_t)q & 15) == 0 && ld % 4 == 0 && K % 4 == 0)) &&
-                   ms_buffer_range_ok(trans ? K : rows, trans ? rows : K, ld, 4);
-        };
 #define GO(TA, TB)                                                                                     \
     do {                                                                                               \
-        if (fast(A, lda, TA, M) && fast(B, ldb, TB, N)) gemm_f32_kernel<TA, TB, true><<<grid, 256, 0, s>>>(p);  \
+        if (f32_fast(A, lda, TA, M, K) && f32_fast(B, ldb, TB, N, K)) gemm_f32_kernel<TA, TB, true><<<grid, 256, 0, s>>>(p);  \
         else gemm_f32_kernel<TA, TB, false><<<grid, 256, 0, s>>>(p);                                   \
     } while (0)
         if (!trans_a && !trans_b) GO(false, false);
@@ -1314,49 +1407,80 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
         MS_LAUNCH_CHECK();
         return MS_OK;
     }
-    auto al = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
-    if (!al(A) || !al(B) || lda % 8 || ldb % 8 || (trans_a ? M % 8 : K % 8) || (trans_b ? N % 8 : K % 8))
-        return ms_fail(MS_ERR_UNSUPPORTED,
-                       "gemm(bf16): contiguous dimension of each operand must be a multiple of 8 and 16-byte aligned "
-                       "(M=%d N=%d K=%d ta=%d tb=%d lda=%ld ldb=%ld)", M, N, K, trans_a, trans_b, (long)lda, (long)ldb);
-    GemmParams p = {};
-    p.A = A; p.B = B; p.C = C; p.bias = bias; p.residual = residual;
-    p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha;
-    p.c_fp32 = c_fp32; p.accumulate = accumulate; p.res_fp32 = residual_fp32;
-    // fast path (direct-to-LDS loads, descriptor-addressed epilogue) needs full K tiles for a K-contiguous
-    // operand and 32-bit byte offsets
-    const int forced = forced_tile();
-    const long lim = (1L << 32) - (1L << 20);
-    const long rows_a = trans_a ? K : M, rows_b = trans_b ? K : N;
-    const bool fast = forced >= 0 && ((trans_a && trans_b) || K % BK == 0) && (rows_a + 256) * lda * 2 < lim &&
-                      (rows_b + 256) * ldb * 2 < lim && ((long)M + 256) * ldc * 4 < lim &&
-                      (!residual || ((long)M + 256) * ldr * 4 < lim);
-    const int kt_total = ms_cdiv(K, BK) < 1 ? 1 : ms_cdiv(K, BK);
-    const double out_bytes = (c_fp32 ? 4 : 2) + (residual ? (residual_fp32 ? 4 : 2) : 0) + (accumulate ? 4 : 0);
-    int tile = fast ? choose_tile(M, N, kt_total, out_bytes) : T128;
+    Bf16Gemm g;
+    MS_TRY(prepare_bf16(trans_a, trans_b, M, N, K, alpha, A, lda, B, ldb, C, ldc, c_fp32, accumulate, bias, residual, ldr, residual_fp32, &g));
+    int tile = g.fast ? choose_tile(M, N, g.kt, g.out_bytes) : T128;
     int splits = split_k;
     if (splits <= 0) {  // automatic: only when accumulating into fp32 (weight gradients: small M x N, long K)
         splits = 1;
-        if (accumulate && c_fp32 && fast) {
-            const MsSplit c = ms_choose_split(M, N, kt_total, forced, use_mfma16());
+        if (accumulate && c_fp32 && g.fast) {
+            const MsSplit c = ms_choose_split(M, N, g.kt, forced_tile(), use_mfma16());
             tile = c.tile;
             splits = c.splits;
         } else if (accumulate && c_fp32) {
             const int tiles = ms_cdiv(M, 128) * ms_cdiv(N, 128);
-            while (tiles * splits < 512 && kt_total / (splits * 2) >= 8) splits *= 2;
+            while (tiles * splits < 512 && g.kt / (splits * 2) >= 8) splits *= 2;
         }
     }
     if (splits > 1 && !(accumulate && c_fp32)) return ms_fail(MS_ERR_INVALID_ARG, "gemm: split_k needs accumulate into fp32");
-    if (splits > kt_total) splits = kt_total;
-    p.k_tiles_per_split = ms_cdiv(kt_total, splits);
-    splits = ms_cdiv(kt_total, p.k_tiles_per_split);
-    p.atomic = splits > 1;
-    auto al16 = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
-    p.vec_epilogue = !p.atomic && N % 4 == 0 && ldc % 4 == 0 && al16(C) && (!residual || (ldr % 4 == 0 && al16(residual))) &&
-                     (!bias || ((uintptr_t)bias & 7) == 0);
-    if (fast) return launch_bf16_fast<EPI_NONE>(p, tile, trans_a, trans_b, splits, 2.0 * M * N * K, s);
-    p.tiles_m = ms_cdiv(M, 128); p.tiles_n = ms_cdiv(N, 128);
-    return launch_bf16<128, 128>(p, trans_a, trans_b, splits, s);
+    splits = set_splits(g, splits);
+    if (g.fast) return launch_bf16_fast<EPI_NONE>(g.p, tile, trans_a, trans_b, splits, 2.0 * M * N * K, s);
+    g.p.tiles_m = ms_cdiv(M, 128); g.p.tiles_n = ms_cdiv(N, 128);
+    return launch_bf16<128, 128>(g.p, trans_a, trans_b, splits, s);
+}
+
+// ------------------------------------------------------------------ backward pass of a linear layer
+extern "C" ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy, const void *W,
+                                          const void *x, void *dx, int32_t dx_fp32, int32_t dx_accumulate, void *dW, void *stream) {
+    auto one_by_one = [&]() {
+        MS_TRY(ms_k_gemm(dtype, 0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, 1, stream));
+        return ms_k_gemm(dtype, 1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, 0, stream);
+    };
+    if (n <= 0 || out <= 0 || in <= 0 || !dy || !W || !x || !dx || !dW) return one_by_one();      // (which has the checks)
+    hipStream_t s = (hipStream_t)stream;
+    if (dtype == MS_F32) {
+        const long nd = (long)ms_cdiv(n, 32) * ms_cdiv(in, 32), nw = (long)ms_cdiv(out, 32) * ms_cdiv(in, 32);
+        if (!ms_launch_fits(nd + nw, 256)) return one_by_one();
+        GemmF32Params pd = {}, pw = {};
+        pd.A = pw.A = (const float *)dy; pd.lda = pw.lda = ldy;
+        pd.B = (const float *)W; pw.B = (const float *)x; pd.ldb = pw.ldb = in;
+        pd.C = (float *)dx; pw.C = (float *)dW; pd.ldc = pw.ldc = in;
+        pd.M = n; pd.N = in; pd.K = out; pw.M = out; pw.N = in; pw.K = n;
+        pd.tiles_n = pw.tiles_n = ms_cdiv(in, 32);
+        pd.alpha = pw.alpha = 1.f; pd.accumulate = dx_accumulate; pw.accumulate = 1;
+        const bool fast = f32_fast(dy, ldy, false, n, out) && f32_fast(W, in, true, in, out) && f32_fast(dy, ldy, true, out, n) &&
+                          f32_fast(x, in, true, in, n);
+        if (fast) gemm_f32_pair_kernel<true><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
+        else gemm_f32_pair_kernel<false><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
+        MS_LAUNCH_CHECK();
+        return MS_OK;
+    }
+    if (dx_accumulate && !dx_fp32) return one_by_one();
+    Bf16Gemm d, w;
+    MS_TRY(prepare_bf16(0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, &d));
+    MS_TRY(prepare_bf16(1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, &w));
+    if (!d.fast || !w.fast || !use_mfma16()) return one_by_one();
+    const MsPair c = ms_choose_pair(n, out, in, d.out_bytes, forced_tile());
+    if (c.tile < 0) return one_by_one();
+    set_splits(d, 1);
+    const int splits = set_splits(w, c.splits);
+    const MsTile &t = kTiles[c.tile];
+    d.p.tiles_m = ms_cdiv(n, t.bm); w.p.tiles_m = ms_cdiv(out, t.bm);
+    d.p.tiles_n = w.p.tiles_n = ms_cdiv(in, t.bn);
+    const long nd = (long)d.p.tiles_m * d.p.tiles_n, nw = (long)w.p.tiles_m * w.p.tiles_n;
+    if (!ms_launch_fits(nd + nw * splits, 512)) return one_by_one();
+    ProfScope ps(1, 4.0 * n * out * in, s);
+    const unsigned grid = (unsigned)(nd + nw * splits);
+    switch (c.tile) {
+        case T256: gemm_bf16_pair_kernel<256, 256, 2, 4, 2><<<grid, 512, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+        case R128: gemm_bf16_pair_kernel<128, 128, 4, 2, 4><<<grid, 512, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+        case R128x256: gemm_bf16_pair_kernel<128, 256, 2, 4, 3><<<grid, 512, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+        case R64x128: gemm_bf16_pair_kernel<64, 128, 2, 2, 3><<<grid, 256, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+        case R64: gemm_bf16_pair_kernel<64, 64, 2, 1, 4><<<grid, 128, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+        default: gemm_bf16_pair_kernel<128, 128, 2, 2, 2><<<grid, 256, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+    }
+    MS_LAUNCH_CHECK();
+    return MS_OK;
 }
 
 // ------------------------------------------------------------------ student-logits GEMM with KD epilogues

@@ -246,10 +246,15 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
                     }
                     MS_LAUNCH_CHECK();
                 }
-                if (d_h_s)  // dHs[N, Hs] (+)= dz[N, cw] Ws_c[cw, Hs]
-                    MS_TRY(ms_k_gemm(dt, 0, 1, nb, Hs, cw, 1.f, p.dz, Cv, wsd + (size_t)v0 * Hs * es, Hs, dhs_b, Hs, 1, i > 0, nullptr, nullptr, 0, 0, 1, s));
-                if (d_w_s)  // dWs_c[cw, Hs] += dz^T[cw, N] Hs[N, Hs]
-                    MS_TRY(ms_k_gemm(dt, 1, 1, cw, Hs, nb, 1.f, p.dz, Cv, hs_b, Hs, (float *)d_w_s + (size_t)v0 * Hs, Hs, 1, 1, nullptr, nullptr, 0, 0, 0, s));
+                // dHs[N, Hs] (+)= dz[N, cw] Ws_c[cw, Hs] and dWs_c[cw, Hs] += dz^T[cw, N] Hs[N, Hs]
+                const char *ws_c = wsd + (size_t)v0 * Hs * es;
+                float *dws_c = d_w_s ? (float *)d_w_s + (size_t)v0 * Hs : nullptr;
+                if (d_h_s && d_w_s)
+                    MS_TRY(ms_k_linear_backward(dt, nb, cw, Hs, p.dz, Cv, ws_c, hs_b, dhs_b, 1, i > 0, dws_c, s));
+                else if (d_h_s)
+                    MS_TRY(ms_k_gemm(dt, 0, 1, nb, Hs, cw, 1.f, p.dz, Cv, ws_c, Hs, dhs_b, Hs, 1, i > 0, nullptr, nullptr, 0, 0, 1, s));
+                else
+                    MS_TRY(ms_k_gemm(dt, 1, 1, cw, Hs, nb, 1.f, p.dz, Cv, hs_b, Hs, dws_c, Hs, 1, 1, nullptr, nullptr, 0, 0, 0, s));
             }
             if (pass == 0) {
                 kd_token_kernel<<<ms_cdiv(nb, 256), 256, 0, s>>>(stats_b, nb, kl_tok_dev ? kl_tok_dev + t0 : nullptr);

@@ -110,20 +110,86 @@ inline int ms_choose_tile(long M, long N, int kt, double out_bytes, int forced, 
 // second round of prologues with them.  Above 200 K tiles the operands stream from HBM, where the smaller ring tiles lose
 // 10-45 % (M = N = 1024, K = 32768: 221-285 us unsplit, 90-110 us for the tiles left in; 2048 x 1536, K = 14294: 129 us
 // against 116) and 128 x 256 12 % (5632 x 1024, K = 14810: 221 us against 198 for 256 x 256 in two splits).
-struct MsSplit { int tile, splits; };
+struct MsSplit { int tile, splits; double us; };
 inline MsSplit ms_choose_split(long M, long N, int kt, int forced, bool mfma16) {
-    MsSplit c = {T128, 1};
-    double best = 1e30;
+    MsSplit c = {T128, 1, 1e30};
     for (int i = 0; i < kNumTiles; ++i) {
         if (!ms_tile_allowed(i, forced, mfma16) || (forced <= 0 && kt > 200 && i > T128 && i != R128x256)) continue;
         const double stream = kt > 200 && i == R128x256 ? 1.12 : 1.0;
         for (int sp = 1; sp <= 8 && (sp == 1 || kt / sp >= 8); ++sp) {
             const double est = stream * ms_tile_time(kTiles[i], kTiles[i].wgrad, ms_tiles(kTiles[i], M, N) * sp, (kt + sp - 1) / sp, 0) +
                                (sp > 1 ? 2.5e-6 * M * N * sp + 4.0 : 1.6e-6 * M * N);
-            if (est < best) { best = est; c.splits = sp; c.tile = i; }
+            if (est < c.us) c = {i, sp, est};
         }
     }
     return c;
+}
+
+// Both products of a linear layer's backward pass (dx [n, in] = dy W, dW [out, in] += dy^T x) as one grid of one tile: which
+// tile, how many K splits of the weight gradient and which product comes first (the one with the longer workgroups); tile
+// -1: one launch each.
+// The times are a fit like kTiles' to such grids: 18 layers (out = 1024 .. 17920, in = 1024 .. 8960, KD chunks with an fp32 dx) x
+// 18 token counts from 256 to 46173, operands out of the caches.  d, w: us per K tile of the input / weight gradient (as
+// us_per_ktile), each with a part per round, us_out as in MsTileTimes; us_c: the weight gradient's read and write of C, in
+// 1e-6 us per element (with splits atomics, as in ms_choose_split).  The best tile of a pair is 1.17 times as fast as two
+// launches in the mean, the chosen one 1.15 times (two tiles' estimates may be close); pairs that are not estimated 3 % faster
+// than two launches stay apart.  One of the 324 loses more than 1 % then (777 tokens, 1536 x 8960: 66 us apart, 72 together).
+// E.g. us, apart -> together: 2053 tokens, 5632 x 1024 87 -> 64; 1031 tokens, 1280 x 5120 50 -> 43; 32768 tokens, 1536 x 1536
+// 285 -> 274; a KD chunk of 1024 tokens, 8192 x 1024 84 -> 67; 4096 tokens, 5632 x 1024 111, together 114: stays apart.
+struct MsPairTimes { double d[4], us_round, us_out, us_call, w[4], us_round_w, us_c; };
+constexpr MsPairTimes kPairTimes[kNumTiles] = {
+    {{0.927, 1.331, 0, 0}, 5.80, 0.71, 0, {1.197, 1.532, 0, 0}, 1.56, 1.02},
+    {{0.556, 0.560, 0.641, 0.840}, 3.70, 2.30, 0, {0.694, 0.695, 0.695, 0.949}, 5.36, 0.77},
+    {{0.376, 0.428, 0, 0}, 2.76, 0.74, 0, {0.468, 0.572, 0, 0}, 3.26, 0.96},
+    {{0.365, 0.717, 0, 0}, 5.44, 0.82, 0, {0.780, 0.888, 0, 0}, 2.53, 1.20},
+    {{0.301, 0.301, 0.364, 0.365}, 3.13, 1.87, 0, {0.422, 0.604, 0.604, 0.709}, 2.10, 1.37},
+    {{0.140, 0.182, 0.222, 0.222}, 3.28, 2.62, 1.27, {0.289, 0.371, 0.438, 0.438}, 3.00, 1.30}};
+constexpr double kPairMargin = 0.03;
+struct MsPair { int tile, splits, wgrad_first; double us; };
+// us of a K tile while `wgs` workgroups are there
+inline double ms_ktile_us(const double *u, int per_cu, long wgs) {
+    if (per_cu == 1 || wgs <= 256) return u[0] + (u[1] - u[0]) * (wgs < 256 ? wgs : 256) / 256;
+    return u[2] + (u[3] - u[2]) * ((wgs < 512 ? wgs : 512) - 256) / 256;
+}
+// When `slots` places are done with na workgroups of da us followed by nb of db us
+inline double ms_two_kinds(long slots, long na, double da, long nb, double db) {
+    const long full = na / slots, more = na % slots;          // `more` places have one more than `full` of the first kind
+    const double late = (full + (more > 0)) * da, early = full * da;
+    double best = 1e30;
+    for (int g = 0; g < 2; ++g) {                             // the last one of the second kind runs in an early or a late place
+        const double start = g ? late : early;
+        for (long lo = 1, hi = nb; lo <= hi;) {               // the fewest rounds k there with room for nb in all
+            const long k = (lo + hi) / 2;
+            const double end = start + k * db + 1e-9;
+            const long room = (end > early ? (long)((end - early) / db) : 0) * (slots - more) + (end > late ? (long)((end - late) / db) : 0) * more;
+            if (room >= nb) { if (end < best) best = end; hi = k - 1; } else lo = k + 1;
+        }
+    }
+    return best > late ? best : late;
+}
+inline MsPair ms_choose_pair(long n, long out, long in, double dx_bytes, int forced) {
+    const int ktd = (int)((out + 63) / 64), ktw = (int)((n + 63) / 64);
+    MsPair best = {-1, 1, 0, 1e30};
+    for (int i = 0; i < kNumTiles; ++i) {
+        if (!ms_tile_allowed(i, forced, true)) continue;
+        const MsTile &t = kTiles[i];
+        const MsPairTimes &c = kPairTimes[i];
+        const long nd = ms_tiles(t, n, in), nw = ms_tiles(t, out, in), slots = 256L * t.per_cu;
+        for (int sp = 1; sp <= 8 && (sp == 1 || ktw / sp >= 8); ++sp) {
+            const long wgs = nd + nw * sp;
+            const double dd = ktd * ms_ktile_us(c.d, t.per_cu, wgs) + c.us_round + c.us_out * dx_bytes * t.bm * t.bn / 65536.0;
+            const double dw = (ktw + sp - 1) / sp * ms_ktile_us(c.w, t.per_cu, wgs) + c.us_round_w;
+            const bool wf = dw > dd;
+            const double us = c.us_call + (wf ? ms_two_kinds(slots, nw * sp, dw, nd, dd) : ms_two_kinds(slots, nd, dd, nw * sp, dw)) +
+                              (sp > 1 ? 2.5e-6 * out * in * sp + 4.0 : c.us_c * 1e-6 * out * in);
+            if (us < best.us) best = {i, sp, wf, us};
+        }
+    }
+    if (forced > 0) return best;
+    const MsTile &t = kTiles[ms_choose_tile(n, in, ktd, dx_bytes, 0, true)];
+    const double apart = ms_tile_time(t, t.lin, ms_tiles(t, n, in), ktd, dx_bytes) + ms_choose_split(out, in, ktw, 0, true).us;
+    if (best.us > (1 - kPairMargin) * apart) best.tile = -1;
+    return best;
 }
 
 // ------------------------------------------------------------------ bf16 attention

@@ -102,13 +102,11 @@ extern "C" ms_status ms_merger_backward(const ms_merger_config *cfg, const ms_me
                                                                                   n_groups, vpr, n_llm_tokens);
     MS_LAUNCH_CHECK();
     // second linear: d_act = d_out W2;  dW2 += d_out^T act;  db2 += colsum(d_out)
-    MS_TRY(ms_k_gemm(dt, 0, 1, n_groups, dh, dl, 1.f, p.d_out, dl, w->w2, dh, p.d_act, dh, 0, 0, nullptr, nullptr, 0, 0, 1, s));
-    MS_TRY(ms_k_gemm(dt, 1, 1, dl, dh, n_groups, 1.f, p.d_out, dl, p.act, dh, (void *)grads->w2, dh, 1, 1, nullptr, nullptr, 0, 0, 0, s));
+    MS_TRY(ms_k_linear_backward(dt, n_groups, dl, dh, p.d_out, dl, w->w2, p.act, p.d_act, 0, 0, (void *)grads->w2, s));
     MS_TRY(ms_k_colsum(dt, n_groups, dl, p.d_out, (float *)grads->b2, p.colsum, s));
     MS_TRY(ms_k_act_backward(1, dt, n_groups, dh, p.d_act, p.a1, p.d_a1, s));
     // first linear: d_cat = d_a1 W1, written as the encoder's output gradient [merge * G, d_vit]
-    MS_TRY(ms_k_gemm(dt, 0, 1, n_groups, din, dh, 1.f, p.d_a1, dh, w->w1, din, d_h_vit, din, 0, 0, nullptr, nullptr, 0, 0, 1, s));
-    MS_TRY(ms_k_gemm(dt, 1, 1, dh, din, n_groups, 1.f, p.d_a1, dh, h_vit, din, (void *)grads->w1, din, 1, 1, nullptr, nullptr, 0, 0, 0, s));
+    MS_TRY(ms_k_linear_backward(dt, n_groups, dh, din, p.d_a1, dh, w->w1, h_vit, d_h_vit, 0, 0, (void *)grads->w1, s));
     MS_TRY(ms_k_colsum(dt, n_groups, dh, p.d_a1, (float *)grads->b1, p.colsum, s));
     return MS_OK;
 }

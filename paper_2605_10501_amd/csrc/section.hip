@@ -14,6 +14,15 @@
 #include "common.h"
 #include "launch.h"
 
+// The executor also builds for the host alone (sanitizer runs, where stand-ins take the place of the kernels).  There the two
+// products go one after the other through ms_k_gemm; in the library this definition gives way to the one in gemm.hip.
+extern "C" __attribute__((weak)) ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy,
+                                                                const void *W, const void *x, void *dx, int32_t dx_fp32,
+                                                                int32_t dx_accumulate, void *dW, void *stream) {
+    MS_TRY(ms_k_gemm(dtype, 0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, 1, stream));
+    return ms_k_gemm(dtype, 1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, 0, stream);
+}
+
 namespace {
 
 struct LayerBuf {
@@ -167,13 +176,9 @@ struct Exec {
     ms_status linear(const void *x, int in, const void *W, const void *bias, int out, void *y, const void *res) {
         return gemm(0, 0, m.n, out, in, x, in, W, in, y, out, res != nullptr, false, bias, res, out);
     }
-    // dx[n, in] = dy[n, out] W[out, in]
-    ms_status dgrad(const void *dy, int out, const void *W, int in, void *dx) {
-        return gemm(0, 1, m.n, in, out, dy, out, W, in, dx, in, false, false, nullptr, nullptr, 0);
-    }
-    // dW[out, in] += dy[n, out]^T x[n, in];  db[out] += colsum(dy)
-    ms_status wgrad(const void *dy, int out, const void *x, int in, void *dW, void *db) {
-        MS_TRY(gemm(1, 1, out, in, m.n, dy, out, x, in, dW, in, true, true, nullptr, nullptr, 0));
+    // dx[n, in] = dy[n, out] W[out, in];  dW[out, in] += dy[n, out]^T x[n, in];  db[out] += colsum(dy)
+    ms_status linear_backward(const void *dy, int out, const void *W, int in, const void *x, void *dx, void *dW, void *db) {
+        MS_TRY(ms_k_linear_backward(dt, m.n, out, in, dy, out, W, x, dx, 0, 0, dW, s));
         if (db && !m.dec) MS_TRY(ms_k_colsum(dt, m.n, out, dy, (float *)db, p->norm_scratch, s));
         return MS_OK;
     }
@@ -229,20 +234,16 @@ struct Exec {
 
     // dy: gradient of the layer output; dx: gradient of the layer input (distinct buffers)
     ms_status layer_backward(const ms_layer_ptrs &w, const ms_layer_ptrs &g, const LayerBuf &l, const void *dy, void *dx) {
-        MS_TRY(dgrad(dy, m.d, w.w_down, m.f, p->da));
-        MS_TRY(wgrad(dy, m.d, l.act, m.f, g.w_down, g.b_down));
+        MS_TRY(linear_backward(dy, m.d, w.w_down, m.f, l.act, p->da, g.w_down, g.b_down));
         MS_TRY(ms_k_act_backward(m.dec ? 0 : 1, dt, m.n, m.f, p->da, l.up, p->dup, s));
-        MS_TRY(dgrad(p->dup, m.dup, w.w_up, m.d, p->dh));
-        MS_TRY(wgrad(p->dup, m.dup, l.h2, m.d, g.w_up, g.b_up));
+        MS_TRY(linear_backward(p->dup, m.dup, w.w_up, m.d, l.h2, p->dh, g.w_up, g.b_up));
         MS_TRY(ms_k_norm_backward(kind, dt, 1, m.n, m.d, p->dh, l.x2, w.norm2_g, l.mean2, l.rstd2, dy, p->dx2,
                                   (float *)g.norm2_g, (float *)g.norm2_b, p->norm_scratch, s));
-        MS_TRY(dgrad(p->dx2, m.d, w.w_o, m.dattn, p->d_o));
-        MS_TRY(wgrad(p->dx2, m.d, l.o, m.dattn, g.w_o, g.b_o));
+        MS_TRY(linear_backward(p->dx2, m.d, w.w_o, m.dattn, l.o, p->d_o, g.w_o, g.b_o));
         MS_TRY(ms_k_attention_backward(dt, m.dec, m.nq, m.nkv, m.hd, m.n, b->n_seqs, m.max_seqlen, b->cu_seqlens_dev,
                                        l.qkv, l.o, l.lse, p->d_o, p->dqkv, p->attn_scratch, s));
         if (m.dec) MS_TRY(ms_k_rope(dt, m.n, m.nq + m.nkv, m.hd, m.dqkv, p->dqkv, p->pos, p->rope, 1, s));
-        MS_TRY(dgrad(p->dqkv, m.dqkv, w.w_qkv, m.d, p->dh));
-        MS_TRY(wgrad(p->dqkv, m.dqkv, l.h1, m.d, g.w_qkv, g.b_qkv));
+        MS_TRY(linear_backward(p->dqkv, m.dqkv, w.w_qkv, m.d, l.h1, p->dh, g.w_qkv, g.b_qkv));
         MS_TRY(ms_k_norm_backward(kind, dt, fp32_stream(l.x), m.n, m.d, p->dh, l.x, w.norm1_g, l.mean1, l.rstd1, p->dx2, dx,
                                   (float *)g.norm1_g, (float *)g.norm1_b, p->norm_scratch, s));
         return MS_OK;

@@ -1,0 +1,53 @@
+"""Backward pass of a linear layer in one grid (ms_k_linear_backward) against fp64 and against the two products one by one."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2605_10501_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(dy, W, x, dx, acc, dW):
+    n, (out, inn) = dy.shape[0], W.shape
+    B._check(B.lib().ms_k_linear_backward(int(dy.dtype == torch.bfloat16), n, out, inn, B._p(dy), C.c_int64(dy.stride(0)), B._p(W), B._p(x), B._p(dx),
+                                          int(dx.dtype == torch.float32), int(acc), B._p(dW), B._stream()))
+
+
+# tile 0: chosen by size (-1 would be the generic kernel); out = 72: no full K tile, so the products stay apart
+@pytest.mark.parametrize("tile", [0, 256, 128, 128128, 128256, 64128, 64064])
+@pytest.mark.parametrize("n,out,inn,pad,f32", [(1, 64, 8, 0, 0), (70, 64, 64, 0, 1), (257, 128, 264, 64, 1), (513, 320, 256, 0, 0),
+                                               (1100, 192, 520, 8, 0), (130, 72, 40, 0, 0)])
+def test_bf16(tile, n, out, inn, pad, f32):
+    g = torch.Generator(device="cuda").manual_seed(n + out)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=g).bfloat16()
+    dy, W, x = rand(n, out + pad)[:, :out], rand(out, inn), rand(n, inn)
+    old, dw0 = torch.empty(n, inn, device="cuda").normal_(generator=g), torch.empty(out, inn, device="cuda").normal_(generator=g)
+    dx = old.clone() if f32 else torch.full((n, inn), float("nan"), device="cuda", dtype=torch.bfloat16)
+    dW = dw0.clone()
+    try:
+        B.k_gemm_config(tile, -1)
+        _run(dy, W, x, dx, f32, dW)
+    finally:
+        B.k_gemm_config(0, -1)
+    one = old.clone() if f32 else torch.empty_like(dx)
+    B.k_gemm(dy, W, trans_b=True, c=one, c_fp32=bool(f32), accumulate=bool(f32))
+    assert torch.equal(dx, one)                                     # the same K order whatever the grid
+    # fp32 sums of K products of bf16 numbers: sqrt(K) roundings of 2^-24 on a sum of size sqrt(K), with a margin of 8
+    ref = dw0.double() + dy.double().T @ x.double()
+    assert ((dW.double() - ref).norm() / ref.norm()).item() < 8 * n ** 0.5 * 2 ** -24 + 2 ** -23
+    ref = (old.double() if f32 else 0.0) + dy.double() @ W.double()
+    assert ((dx.double() - ref).norm() / ref.norm()).item() < (8 * out ** 0.5 * 2 ** -24 + 2 ** -23 if f32 else 2 ** -8)
+
+
+@pytest.mark.parametrize("n,out,inn", [(1, 4, 4), (293, 688, 128), (33, 31, 65), (64, 32, 32)])    # 31, 65: rows not 16-byte aligned
+def test_fp32(n, out, inn):
+    g = torch.Generator(device="cuda").manual_seed(n + out)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=g)
+    dy, W, x, dw0, old = rand(n, out), rand(out, inn), rand(n, inn), rand(out, inn), rand(n, inn)
+    for acc in (False, True):
+        dx, dW = old.clone(), dw0.clone()
+        _run(dy, W, x, dx, acc, dW)
+        for got, ref, k in ((dx, (old.double() if acc else 0.0) + dy.double() @ W.double(), out), (dW, dw0.double() + dy.double().T @ x.double(), n)):
+            assert ((got.double() - ref).norm() / ref.norm()).item() < 8 * k ** 0.5 * 2 ** -24 + 2 ** -23

@@ -1,0 +1,58 @@
+"""Rules for the two products of a linear layer's backward pass in one grid (host code, no GPU)."""
+import ctypes as C
+import heapq
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if not cxx:
+        pytest.skip("needs a host C++ compiler")
+    so = str(tmp_path_factory.mktemp("plan") / "libpair.so")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2605_10501_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host_plan", "pair_abi.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+    lib.pair_two_kinds.restype = C.c_double
+    return lib
+
+
+def choose(plan, n, out, inn, dx_bytes=2.0, forced=0):
+    r = (C.c_int * 3)()
+    plan.pair_choose(C.c_long(n), C.c_long(out), C.c_long(inn), C.c_double(dx_bytes), forced, r)
+    return list(r)
+
+
+def test_two_kinds_is_the_time_of_greedy_dispatch(plan):
+    rng = random.Random(1)
+    for _ in range(300):
+        slots, na, nb = rng.randint(1, 40), rng.randint(1, 150), rng.randint(1, 150)
+        da = rng.uniform(1, 30)
+        db = rng.uniform(0.2, 1.0) * da                             # the longer ones first
+        free = [0.0] * slots
+        for d in [da] * na + [db] * nb:
+            heapq.heapreplace(free, free[0] + d)
+        got = plan.pair_two_kinds(C.c_long(slots), C.c_long(na), C.c_double(da), C.c_long(nb), C.c_double(db))
+        assert abs(got - max(free)) <= 1e-6 * max(free), (slots, na, da, nb, db)
+
+
+def test_small_micro_batches_share_a_grid(plan):
+    for n, out, inn in [(256, 1024, 1024), (1031, 1280, 1280), (1031, 3840, 1280), (2053, 5632, 1024), (600, 1536, 1536)]:
+        assert choose(plan, n, out, inn)[0] > 0
+
+
+def test_splits_leave_at_least_eight_k_tiles_and_forced_tiles_are_taken(plan):
+    rng = random.Random(2)
+    for _ in range(300):
+        n, out, inn = (64 * rng.randint(1, 12) * 2 ** rng.randint(0, 5) + rng.randint(0, 63), 64 * rng.randint(1, 280), 8 * rng.randint(1, 1100))
+        tile, splits, _ = choose(plan, n, out, inn)
+        assert 1 <= splits <= 8 and (splits == 1 or (n + 63) // 64 // splits >= 8)
+        for code in (256, 128, 128128, 128256, 64128, 64064):
+            assert choose(plan, n, out, inn, forced=code)[0] == code
