@@ -21,6 +21,24 @@ bool gemm_swiglu_supported(int M, int F, int K, const void *A, long lda, const v
 ms_status gemm_swiglu(int M, int F, int K, const void *A, long lda, const void *W, long ldw, void *act, long ldact,
                       void *gate_up, long ldgu, hipStream_t s);
 
+// Column reductions of a backward pass that nobody waits for (norm gains and shifts, biases): the kernels that produce their
+// partial rows run when the data is there, one launch adds up what has gathered (elementwise.hip).  scratch holds the
+// partial rows of everything pending; what does not fit, or adds to a row that is already pending, is preceded by a
+// column_work_finish.
+struct ColReduce { const float *part; float *out; int np, c; };        // out[c] += sum of np partial rows
+struct ColumnWork {
+    static constexpr int kJobs = 12;
+    char *scratch;
+    size_t bytes, used;
+    int count;
+    ColReduce job[kJobs];
+};
+struct ColSum { const void *x; float *out; int c; };                    // out[c] += column sums of x [n, c]
+ms_status norm_backward_pending(int kind, int dtype, int x_fp32, int n, int d, const void *dy, const void *x, const void *g, const float *mean,
+                                const float *rstd, const void *add, void *dx, float *dg, float *db, ColumnWork *w, hipStream_t s);
+ms_status column_sums_pending(int dtype, int n, const ColSum *sums, int count, ColumnWork *w, hipStream_t s);
+ms_status column_work_finish(ColumnWork *w, hipStream_t s);
+
 // KD-loss pieces (kd.hip)
 ms_status kd_forward_backward(const ms_kd_config *kd, int n_tokens, const void *h_teacher, const void *h_student,
                               float *loss_dev, float *kl_tok_dev, void *d_h_student, void *d_w_student,

@@ -29,6 +29,7 @@ __global__ __launch_bounds__(256) void rows_indexed_kernel(const uint4 *__restri
 
 struct MergerPlan {
     void *a1, *act, *out, *d_out, *d_act, *d_a1, *colsum;
+    size_t colsum_bytes;
     size_t bytes;
 };
 
@@ -43,7 +44,8 @@ MergerPlan merger_plan(const ms_merger_config *c, int groups, void *ws) {
     p.d_act = a.take<void>(g * c->d_hidden * es);
     p.d_a1 = a.take<void>(g * c->d_hidden * es);
     const int widest = c->d_hidden > c->d_llm ? c->d_hidden : c->d_llm;
-    p.colsum = a.take<void>(ms_k_norm_backward_scratch_bytes(widest));
+    p.colsum_bytes = ms_k_norm_backward_scratch_bytes(widest);
+    p.colsum = a.take<void>(p.colsum_bytes);
     p.bytes = a.off;
     return p;
 }
@@ -103,10 +105,12 @@ extern "C" ms_status ms_merger_backward(const ms_merger_config *cfg, const ms_me
     MS_LAUNCH_CHECK();
     // second linear: d_act = d_out W2;  dW2 += d_out^T act;  db2 += colsum(d_out)
     MS_TRY(ms_k_linear_backward(dt, n_groups, dl, dh, p.d_out, dl, w->w2, p.act, p.d_act, 0, 0, (void *)grads->w2, s));
-    MS_TRY(ms_k_colsum(dt, n_groups, dl, p.d_out, (float *)grads->b2, p.colsum, s));
     MS_TRY(ms_k_act_backward(1, dt, n_groups, dh, p.d_act, p.a1, p.d_a1, s));
     // first linear: d_cat = d_a1 W1, written as the encoder's output gradient [merge * G, d_vit]
     MS_TRY(ms_k_linear_backward(dt, n_groups, dh, din, p.d_a1, dh, w->w1, h_vit, d_h_vit, 0, 0, (void *)grads->w1, s));
-    MS_TRY(ms_k_colsum(dt, n_groups, dh, p.d_a1, (float *)grads->b1, p.colsum, s));
-    return MS_OK;
+    // db2 += colsum(d_out), db1 += colsum(d_a1)
+    ColumnWork cols = {(char *)p.colsum, p.colsum_bytes, 0, 0, {}};
+    const ColSum sums[2] = {{p.d_out, (float *)grads->b2, dl}, {p.d_a1, (float *)grads->b1, dh}};
+    MS_TRY(column_sums_pending(dt, n_groups, sums, 2, &cols, s));
+    return column_work_finish(&cols, s);
 }
