@@ -241,47 +241,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS)))
 }
 
 // ===================================================================== backward
-// Row terms of the softmax backward, one pair per (head, token): ld[h, t] = (lse[h, t] * log2(e), delta[h, t]) with
-// delta = sum_d dO[t, h, d] O[t, h, d] (the row term of the softmax Jacobian).  Interleaved so that the 32 pairs of a
-// 32-query tile are 256 contiguous bytes (one direct-to-LDS load in the dK/dV kernel).
-__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16_t *__restrict__ o, const bf16_t *__restrict__ d_o,
-                                                          const float *__restrict__ lse, float2 *__restrict__ ld, int n, int nq,
-                                                          int hd) {
-    // 8 lanes per (token, head): consecutive lanes read consecutive 16-byte pieces, so a wave's load is one
-    // contiguous run; the 8 partial sums meet through xor-shuffles
-    const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long idx = gid >> 3;
-    const int sub = (int)(gid & 7);
-    const bool live = idx < (long)n * nq;
-    float acc = 0.f;
-    if (live) {
-        const bf16_t *a = o + idx * hd, *b = d_o + idx * hd;
-        for (int d = sub * 8; d < hd; d += 64) {
-            const Vec16<bf16_t> x = ldv(a + d), y = ldv(b + d);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc += (float)x.v[e] * (float)y.v[e];
-        }
-    }
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    acc += __shfl_xor(acc, 4, 64);
-    if (live && sub == 0) {
-        const long at = (long)(idx % nq) * n + idx / nq;
-        ld[at] = make_float2(lse[at] * 1.4426950408889634f, acc);
-    }
-}
-
 // dQ: same decomposition as the forward kernel (workgroup = 128 queries of one head, keys visited
 // 64 at a time, K and V tiles loaded directly into LDS).  S^T = K Q^T and dP^T = V dO^T are
 // accumulator tiles with one query per lane, so P = exp2(S^T c - lse[q]) and
 // dS^T = P (dP^T - delta[q]) use per-lane scalars, and dS^T is the B operand of dQ^T += K^T dS^T
 // with K^T read from the row-major K tile through the transposing LDS load.
+// The kernel also prepares what the dK/dV kernel reads and adds to, in place of two launches (c2 student layer at 2053 tokens 420
+// -> 415 us, large batches 0.1-0.2 %): the row terms of the softmax backward, ld2[h, t] =
+// (lse[h, t] * log2(e), delta[h, t]) with delta = sum_d dO[t, h, d] O[t, h, d] (a wave has its dO rows in registers;
+// interleaved so that the 32 pairs of a 32-query tile are 256 contiguous bytes, one direct-to-LDS load), and zeros in the
+// accumulator of dK and dV (acc, acc_n float4; none without grouped-query attention).
 // KS = 2 (few workgroups with long walks; see ms_attention_split): the workgroup owns 64 queries, waves 0 and 1 visit
 // the even key tiles, waves 2 and 3 the odd ones for the same queries, and the two partial sums meet in LDS: twice the
 // workgroups, half the serial chain.
 template <int HD, bool CAUSAL, int KS, int WPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void attn_bwd_dq_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ d_o,
-                                                                const float2 *__restrict__ ld2,
+                                                                const bf16_t *__restrict__ o, const float *__restrict__ lse,
+                                                                float2 *__restrict__ ld2, float4 *__restrict__ acc, long acc_n,
                                                                 bf16_t *__restrict__ dqkv, const int *__restrict__ cu, int n,
                                                                 int nq, int nkv, int n_seqs, int ntile_max, float scale) {
     using D = AttnDims<HD>;
@@ -290,6 +266,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS)))
     __shared__ __align__(16) bf16_t K0[KS * TS], K1[KS * TS], V0[KS * TS], V1[KS * TS];
 
     const int tid = threadIdx.x, lane = tid & 63;
+    for (long i = (long)blockIdx.x * 256 + tid; i < acc_n; i += (long)gridDim.x * 256) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lrow = lane & 31, half = lane >> 5;
     const AttnSlot slot = attn_slot(blockIdx.x, nq, n_seqs, ntile_max);
@@ -310,22 +287,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS)))
     const int q = q0 + lrow;
     const bool qok = q < s1;
     bf16x8 qf[D::KST], dof[D::KST];
+    const float lse2 = qok ? lse[(long)h * n + q] * 1.4426950408889634f : 0.f;
+    float dlt = 0.f;
     {
         const bf16_t *qp = qkv + (long)q * ld + (long)h * HD + half * 8;
-        const bf16_t *dp = d_o + (long)q * nq * HD + (long)h * HD + half * 8;
+        const bf16_t *dp = d_o + (long)q * nq * HD + (long)h * HD + half * 8, *op = o + (long)q * nq * HD + (long)h * HD + half * 8;
+        bf16x8 of[D::KST];
 #pragma unroll
         for (int ks = 0; ks < D::KST; ++ks) {
             if (qok) {
                 qf[ks] = *(const bf16x8 *)(qp + ks * 16);
                 dof[ks] = *(const bf16x8 *)(dp + ks * 16);
+                of[ks] = *(const bf16x8 *)(op + ks * 16);
             } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) { qf[ks][i] = (bf16_t)0.f; dof[ks][i] = (bf16_t)0.f; }
+                for (int i = 0; i < 8; ++i) { qf[ks][i] = (bf16_t)0.f; dof[ks][i] = (bf16_t)0.f; of[ks][i] = (bf16_t)0.f; }
             }
         }
+#pragma unroll
+        for (int ks = 0; ks < D::KST; ++ks)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) dlt += (float)of[ks][i] * (float)dof[ks][i];
+        dlt += __shfl_xor(dlt, 32, 64);
+        if (qok && half == 0 && part == 0) ld2[(long)h * n + q] = make_float2(lse2, dlt);
     }
-    const float2 row = qok ? ld2[(long)h * n + q] : make_float2(0.f, 0.f);   // (lse * log2(e), delta)
-    const float lse2 = row.x, dlt = row.y;
 
     // (one half of the waves fills K tiles, the other V tiles; the lane's part of the addresses is computed once)
     constexpr int PER = T::LOADS / 2 * KS;
@@ -722,15 +707,12 @@ ms_status launch_bwd(int causal, int nq, int nkv, int n, int n_seqs, int max_seq
         return ms_fail(MS_ERR_UNSUPPORTED, "attention: batch too large for 32-bit tile offsets or for one launch");
     const unsigned grid_dkv = (unsigned)blocks_dkv;
     float2 *ld2 = (float2 *)scratch;                       // [nq][n] pairs (lse * log2(e), delta)
-    attn_delta_kernel<<<ms_cdiv((long)n * nq * 8, 256), 256, 0, s>>>((const bf16_t *)o, (const bf16_t *)d_o, lse, ld2, n, nq, HD);
-    MS_LAUNCH_CHECK();
     float *dkv_acc = (float *)((char *)scratch + ms_align_up((size_t)nq * n * sizeof(float2)));
     const int w = 2 * nkv * HD;
-    if (split) MS_TRY(launch_fill_f32(dkv_acc, (long)n * w, 0.f, s));
 #define DQ(C, KS, WPS)                                                                                                       \
-    attn_bwd_dq_mfma_kernel<HD, C, KS, WPS><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o, ld2, \
-                                                                             (bf16_t *)dqkv, cu, n, nq, nkv, n_seqs,        \
-                                                                             dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max, scale)
+    attn_bwd_dq_mfma_kernel<HD, C, KS, WPS><<<(unsigned)blocks, 256, 0, s>>>(                                          \
+        (const bf16_t *)qkv, (const bf16_t *)d_o, (const bf16_t *)o, lse, ld2, (float4 *)dkv_acc, split ? (long)n * w / 4 : 0, \
+        (bf16_t *)dqkv, cu, n, nq, nkv, n_seqs, dq2 ? ms_cdiv(max_seqlen, 64) : ntile_max, scale)
 #define DKV(C, SPLIT)                                                                                                  \
     attn_bwd_dkv_mfma_kernel<HD, C, SPLIT, 4, 2><<<grid_dkv, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)d_o,    \
                                                                           ld2, (bf16_t *)dqkv, dkv_acc, cu, n, nq,     \
