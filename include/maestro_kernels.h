@@ -47,6 +47,12 @@ ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, 
 ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy, const void *W,
                                const void *x, void *dx, int32_t dx_fp32, int32_t dx_accumulate, void *dW, void *stream);
 
+/* The same for the layer behind a SwiGLU, x = act = silu(gate) * up: dW[out,f] += dy^T act, and the gradient of the pre-activations,
+ * d_gate_up[n, 2 f] = [dgate | dup], from da = dy W.  da[n,f] is scratch, written only where the derivative is not taken in the
+ * product's epilogue. */
+ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t f, const void *dy, const void *W, const void *act,
+                                      const void *gate_up, void *da, void *d_gate_up, void *dW, void *stream);
+
 /* Gate/up projection of a SwiGLU FFN with the activation fused into the GEMM (bf16 only):
  *   gate_up[M, 2F] = round(A[M,K] W[2F,K]^T)  (W rows: F gate rows, then F up rows; written if gate_up != NULL)
  *   act[M, F]      = silu(gate) * up, evaluated on the rounded pre-activations (what a separate kernel would read).

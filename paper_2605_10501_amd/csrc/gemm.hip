@@ -60,7 +60,8 @@ struct GemmParams {
     long sg_ldgu;
 };
 
-enum { EPI_NONE = 0, EPI_KD_DZ = 1, EPI_KD_STATS = 2, EPI_SWIGLU = 3 };
+// EPI_SWIGLU_BWD: the tile holds da = dL/d(silu(gate) * up); sg_gu = the pre-activations [M, sg_ldgu], read; C = [dgate | dup] [M, ldc]
+enum { EPI_NONE = 0, EPI_KD_DZ = 1, EPI_KD_STATS = 2, EPI_SWIGLU = 3, EPI_SWIGLU_BWD = 4 };
 
 // All-reduce over each aligned group of 16 lanes with DPP moves (one vector-ALU instruction per step, no LDS
 // crossbar): swap within pairs, swap pairs within quads, mirror within 8 lanes (reaches the other quad), mirror within
@@ -470,18 +471,27 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
         const int colg = n0 + col_base(pcol >> 5) + (pcol & 31);
         const bool cok = colg < p.N;
         // the prefetched stream: KD -> teacher logits (fp32); else residual (fp32 or bf16); else C (accumulate)
+        // (SwiGLU backward -> gate and up, 4 bf16 each)
         const bool aux_res = EPI == EPI_NONE && p.residual != nullptr;
         const bool aux_c = EPI == EPI_NONE && !aux_res && p.accumulate && p.c_fp32;
         const bool has_aux = EPI != EPI_NONE || aux_res || aux_c;
         const bool aux4 = EPI != EPI_NONE || aux_c || p.res_fp32;                  // 4-byte elements
         const long aux_ld = EPI != EPI_NONE ? p.kd_ldz : (aux_res ? p.ldr : p.ldc);
-        const __amdgpu_buffer_rsrc_t ra_ = EPI != EPI_NONE ? make_rsrc(p.kd_zt, (long)p.M * p.kd_ldz * 4) : (aux_res ? rr : rc);
+        const __amdgpu_buffer_rsrc_t ra_ = EPI == EPI_SWIGLU_BWD ? make_rsrc(p.sg_gu, (long)p.M * p.sg_ldgu * 2)
+                                           : EPI != EPI_NONE     ? make_rsrc(p.kd_zt, (long)p.M * p.kd_ldz * 4) : (aux_res ? rr : rc);
         u32x4 aux[2][8];
         float2 lsev[2][8];                                                         // EPI_KD_DZ: (lse_t, lse_s) of the row
         auto prefetch = [&](int i, u32x4 *dst, float2 *ldst) {
 #pragma unroll
             for (int ps = 0; ps < 8; ++ps) {
                 const long rowg = m0 + row_base(i) + ps * 4 + prow;
+                if constexpr (EPI == EPI_SWIGLU_BWD) {
+                    const unsigned go = cok ? (unsigned)((rowg * p.sg_ldgu + colg) * 2) : kOob;
+                    const u32x2 g = __builtin_amdgcn_raw_buffer_load_b64(ra_, go, 0, kStream);
+                    const u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(ra_, cok ? go + (unsigned)p.sg_f * 2 : kOob, 0, kStream);
+                    dst[ps][0] = g[0]; dst[ps][1] = g[1]; dst[ps][2] = u[0]; dst[ps][3] = u[1];
+                    continue;
+                }
                 const unsigned off = cok ? (unsigned)((rowg * aux_ld + colg) * (aux4 ? 4 : 2)) : kOob;
                 if (aux4) dst[ps] = __builtin_amdgcn_raw_buffer_load_b128(ra_, off, 0, kStream);
                 else {
@@ -545,6 +555,20 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
                         for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(c4[e]);
                     }
                     store4(v, co);
+                } else if constexpr (EPI == EPI_SWIGLU_BWD) {
+                    // da is rounded to the storage type first (it is what a separate activation kernel would read back)
+                    const float da[4] = {(float)(bf16_t)t.x, (float)(bf16_t)t.y, (float)(bf16_t)t.z, (float)(bf16_t)t.w};
+                    float dg[4], du[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float gg = (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[e >> 1] >> (16 * (e & 1))));
+                        const float uu = (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[2 + (e >> 1)] >> (16 * (e & 1))));
+                        const float sg = 1.f / (1.f + __expf(-gg));
+                        dg[e] = da[e] * uu * sg * (1.f + gg * (1.f - sg));
+                        du[e] = da[e] * gg * sg;
+                    }
+                    store4(dg, co);
+                    store4(du, cok ? co + (unsigned)p.sg_f * 2 : kOob);
                 } else {
                     // the tile holds student logits zs; q = teacher logits zt of the same elements
                     const float zs[4] = {t.x, t.y, t.z, t.w};
@@ -863,7 +887,11 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fa
 // leave one.  The product with the longer workgroups comes first (see ms_choose_pair).  One MI355X, us, backward GEMMs of a
 // layer apart -> together: c2 student at 2053 tokens 176 -> 146, encoder at 1031 tokens 175 -> 130; the fp32 form (five pairs in
 // the c1 step) takes the step from 271 to 242.
-template <int BM, int BN, int WM, int WN, int NST>
+// EPI = EPI_SWIGLU_BWD: x is the output of a SwiGLU; the input gradient goes through its derivative in the epilogue and leaves as
+// [dgate | dup].  A kernel of its own read the 2 f pre-activations too, but also da, which the product had written (c5 student
+// layer at 32768 tokens 532 us, 5.5 TB/s): 13.16 -> 13.09 ms, c2 student layer at 2053 tokens 438 -> 434 us; the epilogue's
+// bursts are not behind MFMAs, which eats most of the bytes saved.
+template <int BM, int BN, int WM, int WN, int NST, int EPI = EPI_NONE>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI_NONE, NST)))) void gemm_bf16_pair_kernel(GemmParams pd, GemmParams pw, int nd, int nw, int wgrad_first) {
     MS_FAST_LDS(BM, BN, NST);
     const int b = blockIdx.x, total_w = gridDim.x - nd;
@@ -871,7 +899,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fa
         const int bw = wgrad_first ? b : b - nd;
         gemm_fast_body<BM, BN, WM, WN, true, true, EPI_NONE, true, NST>(pw, lds, bw % nw, nw, bw / nw);
     } else {
-        gemm_fast_body<BM, BN, WM, WN, false, true, EPI_NONE, true, NST>(pd, lds, wgrad_first ? b - total_w : b, nd, 0);
+        gemm_fast_body<BM, BN, WM, WN, false, true, EPI, true, NST>(pd, lds, wgrad_first ? b - total_w : b, nd, 0);
     }
 }
 
@@ -1209,7 +1237,9 @@ template __global__ void gemm_bf16_pp_kernel<EPI_KD_STATS>(GemmParams);
     template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI_SWIGLU, true, NST>(GemmParams)
 MS_INST_RINGS(128, 128, 4, 2, 4); MS_INST_RINGS(128, 256, 2, 4, 3); MS_INST_RINGS(64, 128, 2, 2, 3); MS_INST_RINGS(64, 64, 2, 1, 4);
 #undef MS_INST_RINGS
-#define MS_INST_PAIR(BM, BN, WM, WN, NST) template __global__ void gemm_bf16_pair_kernel<BM, BN, WM, WN, NST>(GemmParams, GemmParams, int, int, int)
+#define MS_INST_PAIR(BM, BN, WM, WN, NST)                                                                                    \
+    template __global__ void gemm_bf16_pair_kernel<BM, BN, WM, WN, NST, EPI_NONE>(GemmParams, GemmParams, int, int, int);   \
+    template __global__ void gemm_bf16_pair_kernel<BM, BN, WM, WN, NST, EPI_SWIGLU_BWD>(GemmParams, GemmParams, int, int, int)
 MS_INST_PAIR(256, 256, 2, 4, 2); MS_INST_PAIR(128, 128, 2, 2, 2); MS_INST_PAIR(128, 128, 4, 2, 4); MS_INST_PAIR(128, 256, 2, 4, 3);
 MS_INST_PAIR(64, 128, 2, 2, 3); MS_INST_PAIR(64, 64, 2, 1, 4);
 #undef MS_INST_PAIR
@@ -1430,6 +1460,39 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
 }
 
 // ------------------------------------------------------------------ backward pass of a linear layer
+namespace {
+// Input gradient d and weight gradient w of one layer in one grid, if that is estimated faster (done = false: it is not)
+template <int EPI>
+ms_status launch_pair(Bf16Gemm &d, Bf16Gemm &w, bool *done, hipStream_t s) {
+    const int n = d.p.M, in = d.p.N, out = d.p.K;
+    if (!d.fast || !w.fast || !use_mfma16()) return MS_OK;
+    const MsPair c = ms_choose_pair(n, out, in, d.out_bytes, forced_tile());
+    if (c.tile < 0) return MS_OK;
+    set_splits(d, 1);
+    const int splits = set_splits(w, c.splits);
+    const MsTile &t = kTiles[c.tile];
+    d.p.tiles_m = ms_cdiv(n, t.bm); w.p.tiles_m = ms_cdiv(out, t.bm);
+    d.p.tiles_n = w.p.tiles_n = ms_cdiv(in, t.bn);
+    const long nd = (long)d.p.tiles_m * d.p.tiles_n, nw = (long)w.p.tiles_m * w.p.tiles_n;
+    if (!ms_launch_fits(nd + nw * splits, 512)) return MS_OK;
+    *done = true;
+    ProfScope ps(1, 4.0 * n * out * in, s);
+    const unsigned grid = (unsigned)(nd + nw * splits);
+#define GO(BM, BN, WM, WN, NST) gemm_bf16_pair_kernel<BM, BN, WM, WN, NST, EPI><<<grid, 64 * WM * WN, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first)
+    switch (c.tile) {
+        case T256: GO(256, 256, 2, 4, 2); break;
+        case R128: GO(128, 128, 4, 2, 4); break;
+        case R128x256: GO(128, 256, 2, 4, 3); break;
+        case R64x128: GO(64, 128, 2, 2, 3); break;
+        case R64: GO(64, 64, 2, 1, 4); break;
+        default: GO(128, 128, 2, 2, 2); break;
+    }
+#undef GO
+    MS_LAUNCH_CHECK();
+    return MS_OK;
+}
+}  // namespace
+
 extern "C" ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy, const void *W,
                                           const void *x, void *dx, int32_t dx_fp32, int32_t dx_accumulate, void *dW, void *stream) {
     auto one_by_one = [&]() {
@@ -1459,28 +1522,31 @@ extern "C" ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out,
     Bf16Gemm d, w;
     MS_TRY(prepare_bf16(0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, &d));
     MS_TRY(prepare_bf16(1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, &w));
-    if (!d.fast || !w.fast || !use_mfma16()) return one_by_one();
-    const MsPair c = ms_choose_pair(n, out, in, d.out_bytes, forced_tile());
-    if (c.tile < 0) return one_by_one();
-    set_splits(d, 1);
-    const int splits = set_splits(w, c.splits);
-    const MsTile &t = kTiles[c.tile];
-    d.p.tiles_m = ms_cdiv(n, t.bm); w.p.tiles_m = ms_cdiv(out, t.bm);
-    d.p.tiles_n = w.p.tiles_n = ms_cdiv(in, t.bn);
-    const long nd = (long)d.p.tiles_m * d.p.tiles_n, nw = (long)w.p.tiles_m * w.p.tiles_n;
-    if (!ms_launch_fits(nd + nw * splits, 512)) return one_by_one();
-    ProfScope ps(1, 4.0 * n * out * in, s);
-    const unsigned grid = (unsigned)(nd + nw * splits);
-    switch (c.tile) {
-        case T256: gemm_bf16_pair_kernel<256, 256, 2, 4, 2><<<grid, 512, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
-        case R128: gemm_bf16_pair_kernel<128, 128, 4, 2, 4><<<grid, 512, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
-        case R128x256: gemm_bf16_pair_kernel<128, 256, 2, 4, 3><<<grid, 512, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
-        case R64x128: gemm_bf16_pair_kernel<64, 128, 2, 2, 3><<<grid, 256, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
-        case R64: gemm_bf16_pair_kernel<64, 64, 2, 1, 4><<<grid, 128, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
-        default: gemm_bf16_pair_kernel<128, 128, 2, 2, 2><<<grid, 256, 0, s>>>(d.p, w.p, (int)nd, (int)nw, c.wgrad_first); break;
+    bool done = false;
+    MS_TRY(launch_pair<EPI_NONE>(d, w, &done, s));
+    return done ? MS_OK : one_by_one();
+}
+
+// The down projection of a SwiGLU block backwards: dW += dy^T act and [dgate | dup] from da = dy W, which is not stored where the
+// two products share a grid.
+extern "C" ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t f, const void *dy, const void *W, const void *act,
+                                                 const void *gate_up, void *da, void *d_gate_up, void *dW, void *stream) {
+    hipStream_t s = (hipStream_t)stream;
+    auto al = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
+    if (dtype == MS_BF16 && n > 0 && out > 0 && f > 0 && f % 4 == 0 && dy && W && act && gate_up && d_gate_up && dW && al(gate_up) && al(d_gate_up) && ((long)n + 256) * 2 * f * 2 < (1L << 32) - (1L << 20)) {
+        Bf16Gemm d, w;
+        MS_TRY(prepare_bf16(0, 1, n, f, out, 1.f, dy, out, W, f, d_gate_up, 2L * f, 0, 0, nullptr, nullptr, 0, 0, &d));
+        MS_TRY(prepare_bf16(1, 1, out, f, n, 1.f, dy, out, act, f, dW, f, 1, 1, nullptr, nullptr, 0, 0, &w));
+        d.p.sg_f = f;
+        d.p.sg_gu = const_cast<void *>(gate_up);
+        d.p.sg_ldgu = 2L * f;
+        d.out_bytes = 8;
+        bool done = false;
+        MS_TRY(launch_pair<EPI_SWIGLU_BWD>(d, w, &done, s));
+        if (done) return MS_OK;
     }
-    MS_LAUNCH_CHECK();
-    return MS_OK;
+    MS_TRY(ms_k_linear_backward(dtype, n, out, f, dy, out, W, act, da, 0, 0, dW, s));
+    return ms_k_act_backward(0, dtype, n, f, da, gate_up, d_gate_up, s);
 }
 
 // ------------------------------------------------------------------ student-logits GEMM with KD epilogues

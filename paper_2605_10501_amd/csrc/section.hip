@@ -23,6 +23,12 @@ extern "C" __attribute__((weak)) ms_status ms_k_linear_backward(int32_t dtype, i
     MS_TRY(ms_k_gemm(dtype, 0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, 1, stream));
     return ms_k_gemm(dtype, 1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, 0, stream);
 }
+extern "C" __attribute__((weak)) ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t f, const void *dy, const void *W,
+                                                                       const void *act, const void *gate_up, void *da, void *d_gate_up,
+                                                                       void *dW, void *stream) {
+    MS_TRY(ms_k_linear_backward(dtype, n, out, f, dy, out, W, act, da, 0, 0, dW, stream));
+    return ms_k_act_backward(0, dtype, n, f, da, gate_up, d_gate_up, stream);
+}
 __attribute__((weak)) ms_status norm_backward_pending(int kind, int dtype, int x_fp32, int n, int d, const void *dy, const void *x, const void *g,
                                                       const float *mean, const float *rstd, const void *add, void *dx, float *dg,
                                                       float *db, ColumnWork *w, hipStream_t s) {
@@ -251,8 +257,12 @@ struct Exec {
 
     // dy: gradient of the layer output; dx: gradient of the layer input (distinct buffers)
     ms_status layer_backward(const ms_layer_ptrs &w, const ms_layer_ptrs &g, const LayerBuf &l, const void *dy, void *dx) {
-        MS_TRY(linear_backward(dy, m.d, w.w_down, m.f, l.act, p->da, g.w_down, g.b_down));
-        MS_TRY(ms_k_act_backward(m.dec ? 0 : 1, dt, m.n, m.f, p->da, l.up, p->dup, s));
+        if (m.dec) {
+            MS_TRY(ms_k_swiglu_linear_backward(dt, m.n, m.d, m.f, dy, w.w_down, l.act, l.up, p->da, p->dup, g.w_down, s));
+        } else {
+            MS_TRY(linear_backward(dy, m.d, w.w_down, m.f, l.act, p->da, g.w_down, g.b_down));
+            MS_TRY(ms_k_act_backward(1, dt, m.n, m.f, p->da, l.up, p->dup, s));
+        }
         MS_TRY(linear_backward(p->dup, m.dup, w.w_up, m.d, l.h2, p->dh, g.w_up, g.b_up));
         MS_TRY(norm_backward_pending(kind, dt, 1, m.n, m.d, p->dh, l.x2, w.norm2_g, l.mean2, l.rstd2, dy, p->dx2,
                                      (float *)g.norm2_g, (float *)g.norm2_b, &cols, s));

@@ -51,3 +51,26 @@ def test_fp32(n, out, inn):
         _run(dy, W, x, dx, acc, dW)
         for got, ref, k in ((dx, (old.double() if acc else 0.0) + dy.double() @ W.double(), out), (dW, dw0.double() + dy.double().T @ x.double(), n)):
             assert ((got.double() - ref).norm() / ref.norm()).item() < 8 * k ** 0.5 * 2 ** -24 + 2 ** -23
+
+
+@pytest.mark.parametrize("tile", [0, 256, 128, 128128, 128256, 64128, 64064])
+@pytest.mark.parametrize("n,out,f", [(1, 64, 8), (70, 64, 64), (257, 128, 264), (513, 320, 256), (130, 72, 40)])   # 72: the products stay apart
+def test_swiglu_derivative_in_the_epilogue(tile, n, out, f):
+    g = torch.Generator(device="cuda").manual_seed(n + out + f)
+    rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=g).bfloat16()
+    dy, W, act, up, dw0 = rand(n, out), rand(out, f), rand(n, f), 3 * rand(n, 2 * f), rand(out, f).float()
+    one = {k: torch.full((n, c), float("nan"), device="cuda", dtype=torch.bfloat16) for k, c in (("da", f), ("dup", 2 * f))}
+    dW, dW1 = dw0.clone(), dw0.clone()
+    try:
+        B.k_gemm_config(tile, -1)
+        B._check(B.lib().ms_k_swiglu_linear_backward(1, n, out, f, B._p(dy), B._p(W), B._p(act), B._p(up), B._p(one["da"]), B._p(one["dup"]), B._p(dW), B._stream()))
+        da = torch.empty(n, f, device="cuda", dtype=torch.bfloat16)
+        _run(dy, W, act, da, False, dW1)
+    finally:
+        B.k_gemm_config(0, -1)
+    two = torch.empty(n, 2 * f, device="cuda", dtype=torch.bfloat16)
+    B._check(B.lib().ms_k_act_backward(0, 1, n, f, B._p(da), B._p(up), B._p(two), B._stream()))
+    # the same formula on the same rounded da; one bf16 ulp for a compiler's choice of fused multiply-adds
+    assert ((one["dup"].float() - two.float()).abs() <= 2 ** -7 * two.float().abs() + 1e-30).all()
+    assert (one["dup"] == two).float().mean() > 0.99
+    assert ((dW - dW1).norm() / dW1.norm()).item() < 8 * n ** 0.5 * 2 ** -24 + 2 ** -23
