@@ -311,23 +311,36 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSums m, int n) {
 }
 
 // ------------------------------------------------------------------ rotary embedding
-__global__ void positions_kernel(int n, int n_seqs, const int *__restrict__ cu, int *__restrict__ pos) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
+__device__ __forceinline__ int position_of(int t, int n_seqs, const int *cu) {
     int lo = 0, hi = n_seqs;  // largest b with cu[b] <= t
     while (hi - lo > 1) {
         int mid = (lo + hi) >> 1;
         if (cu[mid] <= t) lo = mid; else hi = mid;
     }
-    pos[t] = t - cu[lo];
+    return t - cu[lo];
 }
-
+__device__ __forceinline__ float2 rope_entry(int p, int i, int hd, double base) {
+    double ang = (double)p * pow(base, -2.0 * (double)i / (double)hd);
+    return make_float2((float)cos(ang), (float)sin(ang));
+}
+__global__ void positions_kernel(int n, int n_seqs, const int *__restrict__ cu, int *__restrict__ pos) {
+    int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) pos[t] = position_of(t, n_seqs, cu);
+}
 __global__ void rope_table_kernel(int max_pos, int half, int hd, double base, float2 *__restrict__ table) {
     int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= max_pos * half) return;
-    int p = idx / half, i = idx % half;
-    double ang = (double)p * pow(base, -2.0 * (double)i / (double)hd);
-    table[idx] = make_float2((float)cos(ang), (float)sin(ang));
+    if (idx < max_pos * half) table[idx] = rope_entry(idx / half, idx % half, hd, base);
+}
+// both: the first pos_blocks workgroups do the positions
+__global__ void rope_setup_kernel(int n, int n_seqs, const int *__restrict__ cu, int *__restrict__ pos, int pos_blocks, int max_pos, int half,
+                                  int hd, double base, float2 *__restrict__ table) {
+    if ((int)blockIdx.x < pos_blocks) {
+        const int t = blockIdx.x * blockDim.x + threadIdx.x;
+        if (t < n) pos[t] = position_of(t, n_seqs, cu);
+    } else {
+        const int idx = (blockIdx.x - pos_blocks) * blockDim.x + threadIdx.x;
+        if (idx < max_pos * half) table[idx] = rope_entry(idx / half, idx % half, hd, base);
+    }
 }
 
 template <class T>
@@ -697,6 +710,17 @@ extern "C" ms_status ms_k_rope_table(int32_t max_pos, int32_t head_dim, float ba
     if (!table || max_pos < 0 || head_dim <= 0 || head_dim % 2) return ms_fail(MS_ERR_INVALID_ARG, "rope_table: bad argument");
     const int half = head_dim / 2;
     rope_table_kernel<<<ms_cdiv((long)max_pos * half, 256), 256, 0, (hipStream_t)stream>>>(max_pos, half, head_dim, (double)base, (float2 *)table);
+    MS_LAUNCH_CHECK();
+    return MS_OK;
+}
+
+ms_status launch_rope_setup(int n, int n_seqs, const int32_t *cu, int32_t *pos, int max_pos, int hd, float base, float *table, hipStream_t s) {
+    if (n <= 0 || max_pos <= 0 || hd <= 0 || hd % 2 || !cu || !pos || !table || n_seqs <= 0) {      // (which have the checks)
+        MS_TRY(ms_k_positions(n, n_seqs, cu, pos, s));
+        return ms_k_rope_table(max_pos, hd, base, table, s);
+    }
+    const int pos_blocks = ms_cdiv(n, 256), table_blocks = ms_cdiv((long)max_pos * (hd / 2), 256);
+    rope_setup_kernel<<<pos_blocks + table_blocks, 256, 0, s>>>(n, n_seqs, cu, pos, pos_blocks, max_pos, hd / 2, hd, (double)base, (float2 *)table);
     MS_LAUNCH_CHECK();
     return MS_OK;
 }

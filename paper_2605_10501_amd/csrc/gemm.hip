@@ -1097,6 +1097,7 @@ struct GemmF32Params {
     int M, N, K, tiles_n;
     float alpha;
     int accumulate;
+    const float *sw_up;      // SwiGLU backward: pre-activations [M, 2 N]; the product is da and C = [dgate | dup]
 };
 
 // One operand's fragments for v_mfma_f32_16x16x4_f32: two 16-row blocks x 16 k.  Lane = (row lane % 16, k-group
@@ -1170,6 +1171,13 @@ __device__ __forceinline__ void gemm_f32_body(const GemmF32Params &p, float (&pa
     if (p.accumulate)
 #pragma unroll
         for (int e = 0; e < 4; ++e) if (inside(e)) old[e] = p.C[(long)(m0 + rr + 8 * e) * p.ldc + col];
+    if (p.sw_up)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (inside(e)) {
+                res[e] = p.sw_up[(long)(m0 + rr + 8 * e) * 2 * p.N + col];            // gate
+                old[e] = p.sw_up[(long)(m0 + rr + 8 * e) * 2 * p.N + p.N + col];      // up
+            }
     for (int s = 0; s < mine; s += 4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1195,6 +1203,15 @@ __device__ __forceinline__ void gemm_f32_body(const GemmF32Params &p, float (&pa
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int q = rr + 8 * e;
+        if (p.sw_up) {
+            const float da = (part[0][q][cc] + part[1][q][cc] + part[2][q][cc] + part[3][q][cc]) * p.alpha, gg = res[e], uu = old[e];
+            const float sg = 1.f / (1.f + __expf(-gg));
+            if (inside(e)) {
+                p.C[(long)(m0 + q) * p.ldc + col] = da * uu * sg * (1.f + gg * (1.f - sg));
+                p.C[(long)(m0 + q) * p.ldc + p.N + col] = da * gg * sg;
+            }
+            continue;
+        }
         const float v = (part[0][q][cc] + part[1][q][cc] + part[2][q][cc] + part[3][q][cc]) * p.alpha + add[e] + res[e];
         if (inside(e)) p.C[(long)(m0 + q) * p.ldc + col] = p.accumulate ? old[e] + v : v;
     }
@@ -1212,6 +1229,15 @@ __global__ __launch_bounds__(256) void gemm_f32_pair_kernel(GemmF32Params pd, Ge
     const int b = (int)blockIdx.x;
     if (b < nd) gemm_f32_body<false, true, FAST>(pd, part, b);
     else gemm_f32_body<true, true, FAST>(pw, part, b - nd);
+}
+
+// Two products with K-contiguous operands in one grid; the first n0 workgroups are the first one's
+template <bool FAST>
+__global__ __launch_bounds__(256) void gemm_f32_two_kernel(GemmF32Params p0, GemmF32Params p1, int n0) {
+    __shared__ float part[4][32][33];
+    const int b = (int)blockIdx.x;
+    if (b < n0) gemm_f32_body<false, false, FAST>(p0, part, b);
+    else gemm_f32_body<false, false, FAST>(p1, part, b - n0);
 }
 
 // Explicit instantiations: the host pass has been seen to reference the launch stubs of some of these
@@ -1406,7 +1432,7 @@ extern "C" ms_status ms_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, 
     if (accumulate && !c_fp32 && dtype == MS_BF16) return ms_fail(MS_ERR_INVALID_ARG, "gemm: accumulate needs an fp32 C");
     hipStream_t s = (hipStream_t)stream;
     if (dtype == MS_F32) {
-        GemmF32Params p;
+        GemmF32Params p = {};
         p.A = (const float *)A; p.B = (const float *)B; p.C = (float *)C;
         p.bias = (const float *)bias; p.residual = (const float *)residual;
         p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldr = ldr; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.accumulate = accumulate;
@@ -1491,6 +1517,25 @@ ms_status launch_pair(Bf16Gemm &d, Bf16Gemm &w, bool *done, hipStream_t s) {
     MS_LAUNCH_CHECK();
     return MS_OK;
 }
+ms_status launch_pair_f32(int n, int out, int in, const float *dy, long ldy, const float *W, const float *x, float *dx, long ldx, int accumulate,
+                          float *dW, const float *sw_up, bool *done, hipStream_t s) {
+    const long nd = (long)ms_cdiv(n, 32) * ms_cdiv(in, 32), nw = (long)ms_cdiv(out, 32) * ms_cdiv(in, 32);
+    if (!ms_launch_fits(nd + nw, 256)) return MS_OK;
+    *done = true;
+    GemmF32Params pd = {}, pw = {};
+    pd.A = pw.A = dy; pd.lda = pw.lda = ldy;
+    pd.B = W; pw.B = x; pd.ldb = pw.ldb = in;
+    pd.C = dx; pd.ldc = ldx; pw.C = dW; pw.ldc = in;
+    pd.M = n; pd.N = in; pd.K = out; pw.M = out; pw.N = in; pw.K = n;
+    pd.tiles_n = pw.tiles_n = ms_cdiv(in, 32);
+    pd.alpha = pw.alpha = 1.f; pd.accumulate = accumulate; pw.accumulate = 1;
+    pd.sw_up = sw_up;
+    const bool fast = f32_fast(dy, ldy, false, n, out) && f32_fast(W, in, true, in, out) && f32_fast(dy, ldy, true, out, n) && f32_fast(x, in, true, in, n);
+    if (fast) gemm_f32_pair_kernel<true><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
+    else gemm_f32_pair_kernel<false><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
+    MS_LAUNCH_CHECK();
+    return MS_OK;
+}
 }  // namespace
 
 extern "C" ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy, const void *W,
@@ -1502,21 +1547,10 @@ extern "C" ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out,
     if (n <= 0 || out <= 0 || in <= 0 || !dy || !W || !x || !dx || !dW) return one_by_one();      // (which has the checks)
     hipStream_t s = (hipStream_t)stream;
     if (dtype == MS_F32) {
-        const long nd = (long)ms_cdiv(n, 32) * ms_cdiv(in, 32), nw = (long)ms_cdiv(out, 32) * ms_cdiv(in, 32);
-        if (!ms_launch_fits(nd + nw, 256)) return one_by_one();
-        GemmF32Params pd = {}, pw = {};
-        pd.A = pw.A = (const float *)dy; pd.lda = pw.lda = ldy;
-        pd.B = (const float *)W; pw.B = (const float *)x; pd.ldb = pw.ldb = in;
-        pd.C = (float *)dx; pw.C = (float *)dW; pd.ldc = pw.ldc = in;
-        pd.M = n; pd.N = in; pd.K = out; pw.M = out; pw.N = in; pw.K = n;
-        pd.tiles_n = pw.tiles_n = ms_cdiv(in, 32);
-        pd.alpha = pw.alpha = 1.f; pd.accumulate = dx_accumulate; pw.accumulate = 1;
-        const bool fast = f32_fast(dy, ldy, false, n, out) && f32_fast(W, in, true, in, out) && f32_fast(dy, ldy, true, out, n) &&
-                          f32_fast(x, in, true, in, n);
-        if (fast) gemm_f32_pair_kernel<true><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
-        else gemm_f32_pair_kernel<false><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
-        MS_LAUNCH_CHECK();
-        return MS_OK;
+        bool done = false;
+        MS_TRY(launch_pair_f32(n, out, in, (const float *)dy, ldy, (const float *)W, (const float *)x, (float *)dx, in, dx_accumulate, (float *)dW,
+                               nullptr, &done, s));
+        return done ? MS_OK : one_by_one();
     }
     if (dx_accumulate && !dx_fp32) return one_by_one();
     Bf16Gemm d, w;
@@ -1545,8 +1579,32 @@ extern "C" ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32
         MS_TRY(launch_pair<EPI_SWIGLU_BWD>(d, w, &done, s));
         if (done) return MS_OK;
     }
+    if (dtype == MS_F32 && n > 0 && out > 0 && f > 0 && dy && W && act && gate_up && d_gate_up && dW) {
+        bool done = false;
+        MS_TRY(launch_pair_f32(n, out, f, (const float *)dy, out, (const float *)W, (const float *)act, (float *)d_gate_up, 2L * f, 0, (float *)dW,
+                               (const float *)gate_up, &done, s));
+        if (done) return MS_OK;
+    }
     MS_TRY(ms_k_linear_backward(dtype, n, out, f, dy, out, W, act, da, 0, 0, dW, s));
     return ms_k_act_backward(0, dtype, n, f, da, gate_up, d_gate_up, s);
+}
+
+ms_status gemm_f32_two(int M, int N, const float *A0, const float *B0, float *C0, int K0, const float *A1, const float *B1, float *C1, int K1,
+                       long ldc, hipStream_t s) {
+    const long tiles = (long)ms_cdiv(M, 32) * ms_cdiv(N, 32);
+    if (!ms_launch_fits(2 * tiles, 256)) {
+        MS_TRY(ms_k_gemm(MS_F32, 0, 0, M, N, K0, 1.f, A0, K0, B0, K0, C0, ldc, 1, 0, nullptr, nullptr, 0, 0, 1, s));
+        return ms_k_gemm(MS_F32, 0, 0, M, N, K1, 1.f, A1, K1, B1, K1, C1, ldc, 1, 0, nullptr, nullptr, 0, 0, 1, s);
+    }
+    GemmF32Params p0 = {}, p1 = {};
+    p0.A = A0; p0.B = B0; p0.C = C0; p0.lda = p0.ldb = p0.K = K0;
+    p1.A = A1; p1.B = B1; p1.C = C1; p1.lda = p1.ldb = p1.K = K1;
+    p0.ldc = p1.ldc = ldc; p0.M = p1.M = M; p0.N = p1.N = N; p0.tiles_n = p1.tiles_n = ms_cdiv(N, 32); p0.alpha = p1.alpha = 1.f;
+    if (f32_fast(A0, K0, false, M, K0) && f32_fast(B0, K0, false, N, K0) && f32_fast(A1, K1, false, M, K1) && f32_fast(B1, K1, false, N, K1))
+        gemm_f32_two_kernel<true><<<(unsigned)(2 * tiles), 256, 0, s>>>(p0, p1, (int)tiles);
+    else gemm_f32_two_kernel<false><<<(unsigned)(2 * tiles), 256, 0, s>>>(p0, p1, (int)tiles);
+    MS_LAUNCH_CHECK();
+    return MS_OK;
 }
 
 // ------------------------------------------------------------------ student-logits GEMM with KD epilogues

@@ -46,10 +46,21 @@ __device__ __forceinline__ float block_sum(float v, float *sm) {
     return r;
 }
 
+// Behind the last chunk, once per token: log-sum-exps for pass 2 (slots 6, 7 of its statistics) and its KL term (slot 5)
+__device__ __forceinline__ void finish_token(float *st, float m_t, float s_t, float m_s, float s_s, float a, float *kl_tok) {
+    const float lse_t = m_t + __logf(s_t);
+    const float lse_s = m_s + __logf(s_s);
+    const float kl = a / s_t - lse_t + lse_s;
+    st[5] = kl;
+    st[6] = lse_t;
+    st[7] = lse_s;
+    if (kl_tok) *kl_tok = kl;
+}
+
 // one workgroup per token; zt / zs rows have leading dimension ld, cw valid columns (cw % 4 == 0)
 __global__ __launch_bounds__(256) void kd_stats_kernel(const float *__restrict__ zt, const float *__restrict__ zs,
-                                                        long ld, int cw, float inv_t, int first,
-                                                        float *__restrict__ stats) {
+                                                        long ld, int cw, float inv_t, int first, int last,
+                                                        float *__restrict__ stats, float *__restrict__ kl_tok) {
     __shared__ float sm[4];
     const long t = blockIdx.x;
     const float4 *rt = (const float4 *)(zt + t * ld), *rs = (const float4 *)(zs + t * ld);
@@ -88,26 +99,16 @@ __global__ __launch_bounds__(256) void kd_stats_kernel(const float *__restrict__
     s_s = block_sum(s_s, sm);
     a_c = block_sum(a_c, sm);
     if (threadIdx.x == 0) {
+        s_t += o_st * f_t;
+        s_s += o_ss * f_s;
+        a_c += o_a * f_t;
         st[0] = m_t;
-        st[1] = o_st * f_t + s_t;
+        st[1] = s_t;
         st[2] = m_s;
-        st[3] = o_ss * f_s + s_s;
-        st[4] = o_a * f_t + a_c;
+        st[3] = s_s;
+        st[4] = a_c;
+        if (last) finish_token(st, m_t, s_t, m_s, s_s, a_c, kl_tok ? kl_tok + t : nullptr);
     }
-}
-
-// per token: log-sum-exps for pass 2 (slots 6, 7 of its statistics) and its KL term (slot 5)
-__global__ __launch_bounds__(256) void kd_token_kernel(float *__restrict__ stats, int n, float *__restrict__ kl_tok) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= n) return;
-    float *st = stats + (long)t * kStat;
-    const float lse_t = st[0] + __logf(st[1]);
-    const float lse_s = st[2] + __logf(st[3]);
-    const float kl = st[4] / st[1] - lse_t + lse_s;
-    st[5] = kl;
-    st[6] = lse_t;
-    st[7] = lse_s;
-    if (kl_tok) kl_tok[t] = kl;
 }
 
 // single workgroup: the scalar loss from the per-token KL terms (fixed summation order)
@@ -138,8 +139,8 @@ __global__ __launch_bounds__(256) void kd_dz_kernel(const float *__restrict__ zt
 
 // Fused path: merges the per-strip partial statistics that the student-logits GEMM epilogue wrote for one
 // chunk ([n][nparts][8]: m_t, s_t, m_s, s_s, A) into the running per-token statistics.  One wave per token.
-__global__ __launch_bounds__(256) void kd_combine_kernel(const float *__restrict__ part, int nparts, int n, int first,
-                                                          float *__restrict__ stats) {
+__global__ __launch_bounds__(256) void kd_combine_kernel(const float *__restrict__ part, int nparts, int n, int first, int last,
+                                                          float *__restrict__ stats, float *__restrict__ kl_tok) {
     const int lane = threadIdx.x & 63;
     const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= n) return;
@@ -172,6 +173,7 @@ __global__ __launch_bounds__(256) void kd_combine_kernel(const float *__restrict
         float *st = stats + t * kStat;
         if (!first) merge(st[0], st[1], st[2], st[3], st[4]);
         st[0] = m_t; st[1] = s_t; st[2] = m_s; st[3] = s_s; st[4] = a;
+        if (last) finish_token(st, m_t, s_t, m_s, s_s, a, kl_tok ? kl_tok + t : nullptr);
     }
 }
 
@@ -193,10 +195,14 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
     const int passes = (d_h_s || d_w_s) ? 2 : 1;
     const bool keep = p.keep && passes == 2;
     const int chunks = ms_cdiv(V, Cv);
+    // fp32: dHs is accumulated in the result itself, unless that lies over an input (which would be overwritten too early)
+    auto apart = [&](const void *q, size_t bytes) { return (const char *)q + bytes <= (const char *)d_h_s || (const char *)d_h_s + (size_t)n * Hs * 4 <= (const char *)q; };
+    const bool in_place = dt == MS_F32 && d_h_s && apart(h_t, (size_t)n * Ht * 4) && apart(h_s, (size_t)n * Hs * 4);
+    float *const dhs = in_place ? (float *)d_h_s : p.dhs;
     for (int t0 = 0; t0 < n; t0 += p.tb) {
         const int nb = n - t0 < p.tb ? n - t0 : p.tb;
         const char *ht_b = (const char *)h_t + (size_t)t0 * Ht * es, *hs_b = (const char *)h_s + (size_t)t0 * Hs * es;
-        float *stats_b = p.stats + (size_t)t0 * kStat, *dhs_b = p.dhs + (size_t)t0 * Hs;
+        float *stats_b = p.stats + (size_t)t0 * kStat, *dhs_b = dhs + (size_t)t0 * Hs, *kl_b = kl_tok_dev ? kl_tok_dev + t0 : nullptr;
         // bf16 fast path: the student-logits GEMM consumes its own output (statistics in pass 1, dz in pass 2)
         // together with the stored teacher logits
         bool fused = dt == MS_BF16;
@@ -214,26 +220,31 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
                 const int ci = pass == 0 ? i : chunks - 1 - i;
                 const int v0 = ci * Cv, cw = V - v0 < Cv ? V - v0 : Cv;
                 float *zt = keep ? p.zt + (size_t)ci * p.tb * Cv : two && (ci & 1) ? p.zs : p.zt;
-                if (pass == 0 || i >= kept)
+                const bool teacher = pass == 0 || i >= kept, student = !fused && (pass == 0 || i > 0);
+                const char *ws_c = wsd + (size_t)v0 * Hs * es;
+                if (teacher && student && dt == MS_F32)
+                    MS_TRY(gemm_f32_two(nb, cw, (const float *)ht_b, (const float *)(wt + (size_t)v0 * Ht * es), zt, Ht, (const float *)hs_b,
+                                        (const float *)ws_c, p.zs, Hs, Cv, s));
+                else if (teacher)
                     MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Ht, 1.f, ht_b, Ht, wt + (size_t)v0 * Ht * es, Ht, zt, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
                 if (fused) {
                     const int nparts = ms_cdiv(cw, 64);
                     if (pass == 0) {
-                        MS_TRY(gemm_kd_epilogue(2, nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, zt, Cv, nullptr, part, nparts,
+                        MS_TRY(gemm_kd_epilogue(2, nb, cw, Hs, hs_b, Hs, ws_c, Hs, zt, Cv, nullptr, part, nparts,
                                                 inv_t, 0.f, nullptr, 0, 0, s));
                         ProfScope ps(9, 32.0 * nb * nparts, s);
-                        kd_combine_kernel<<<ms_cdiv(nb, 4), 256, 0, s>>>(part, nparts, nb, v0 == 0, stats_b);
+                        kd_combine_kernel<<<ms_cdiv(nb, 4), 256, 0, s>>>(part, nparts, nb, ci == 0, ci == chunks - 1, stats_b, kl_b);
                         MS_LAUNCH_CHECK();
                         continue;
                     }
-                    MS_TRY(gemm_kd_epilogue(1, nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, zt, Cv, stats_b, nullptr, 0, inv_t,
+                    MS_TRY(gemm_kd_epilogue(1, nb, cw, Hs, hs_b, Hs, ws_c, Hs, zt, Cv, stats_b, nullptr, 0, inv_t,
                                             kd->loss_scale * inv_t, p.dz, Cv, 0, s));
                 } else {
-                    if (pass == 0 || i > 0)
-                        MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Hs, 1.f, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, p.zs, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
+                    if (student && !(teacher && dt == MS_F32))
+                        MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Hs, 1.f, hs_b, Hs, ws_c, Hs, p.zs, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
                     if (pass == 0) {
                         ProfScope ps(9, 8.0 * nb * cw, s);
-                        kd_stats_kernel<<<nb, 256, 0, s>>>(zt, p.zs, Cv, cw, inv_t, v0 == 0, stats_b);
+                        kd_stats_kernel<<<nb, 256, 0, s>>>(zt, p.zs, Cv, cw, inv_t, ci == 0, ci == chunks - 1, stats_b, kl_b);
                         MS_LAUNCH_CHECK();
                         continue;
                     }
@@ -247,7 +258,6 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
                     MS_LAUNCH_CHECK();
                 }
                 // dHs[N, Hs] (+)= dz[N, cw] Ws_c[cw, Hs] and dWs_c[cw, Hs] += dz^T[cw, N] Hs[N, Hs]
-                const char *ws_c = wsd + (size_t)v0 * Hs * es;
                 float *dws_c = d_w_s ? (float *)d_w_s + (size_t)v0 * Hs : nullptr;
                 if (d_h_s && d_w_s)
                     MS_TRY(ms_k_linear_backward(dt, nb, cw, Hs, p.dz, Cv, ws_c, hs_b, dhs_b, 1, i > 0, dws_c, s));
@@ -256,15 +266,11 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
                 else
                     MS_TRY(ms_k_gemm(dt, 1, 1, cw, Hs, nb, 1.f, p.dz, Cv, hs_b, Hs, dws_c, Hs, 1, 1, nullptr, nullptr, 0, 0, 0, s));
             }
-            if (pass == 0) {
-                kd_token_kernel<<<ms_cdiv(nb, 256), 256, 0, s>>>(stats_b, nb, kl_tok_dev ? kl_tok_dev + t0 : nullptr);
-                MS_LAUNCH_CHECK();
-            }
         }
     }
     kd_loss_kernel<<<1, 1024, 0, s>>>(p.stats, n, kd->loss_scale, loss_dev);
     MS_LAUNCH_CHECK();
-    if (d_h_s) MS_TRY(launch_convert_from_f32(dt, p.dhs, d_h_s, (long)n * Hs, s));
+    if (d_h_s && !in_place) MS_TRY(launch_convert_from_f32(dt, p.dhs, d_h_s, (long)n * Hs, s));
     return MS_OK;
 }
 

@@ -21,6 +21,19 @@ bool gemm_swiglu_supported(int M, int F, int K, const void *A, long lda, const v
 ms_status gemm_swiglu(int M, int F, int K, const void *A, long lda, const void *W, long ldw, void *act, long ldact,
                       void *gate_up, long ldgu, hipStream_t s);
 
+// fp32 decoder sections: RMSNorm + QKV + rotary embedding and RMSNorm + gate / up + SwiGLU in one launch each (linear_f32.hip; done =
+// false: not for these sizes or pointers, nothing was launched).  h and rstd (normed rows and row factors) and up (pre-activations)
+// are for a backward pass and may be null.
+ms_status norm_qkv_rope_f32(int n, int d, int heads, int rotated_heads, int hd, float eps, const float *x, const float *g, const float *W,
+                            const int *pos, const float *table, float *qkv, float *h, float *rstd, bool *done, hipStream_t s);
+ms_status norm_swiglu_f32(int n, int d, int f, float eps, const float *x, const float *g, const float *W, float *act, float *up, float *h,
+                          float *rstd, bool *done, hipStream_t s);
+// Position of every token in its sequence and the (cos, sin) table of max_pos positions, one launch (elementwise.hip)
+ms_status launch_rope_setup(int n, int n_seqs, const int32_t *cu, int32_t *pos, int max_pos, int hd, float base, float *table, hipStream_t s);
+// Teacher and student logits of an fp32 chunk in one launch (gemm.hip): C_i [M, N] = A_i [M, K_i] B_i [N, K_i]^T, rows of C ldc apart
+ms_status gemm_f32_two(int M, int N, const float *A0, const float *B0, float *C0, int K0, const float *A1, const float *B1, float *C1, int K1,
+                       long ldc, hipStream_t s);
+
 // Column reductions of a backward pass that nobody waits for (norm gains and shifts, biases): the kernels that produce their
 // partial rows run when the data is there, one launch adds up what has gathered (elementwise.hip).  scratch holds the
 // partial rows of everything pending; what does not fit, or adds to a row that is already pending, is preceded by a

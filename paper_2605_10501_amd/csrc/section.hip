@@ -39,6 +39,21 @@ __attribute__((weak)) ms_status column_sums_pending(int dtype, int n, const ColS
     return MS_OK;
 }
 __attribute__((weak)) ms_status column_work_finish(ColumnWork *, hipStream_t) { return MS_OK; }
+__attribute__((weak)) ms_status launch_rope_setup(int n, int n_seqs, const int32_t *cu, int32_t *pos, int max_pos, int hd, float base, float *table,
+                                                  hipStream_t s) {
+    MS_TRY(ms_k_positions(n, n_seqs, cu, pos, s));
+    return ms_k_rope_table(max_pos, hd, base, table, s);
+}
+__attribute__((weak)) ms_status norm_qkv_rope_f32(int, int, int, int, int, float, const float *, const float *, const float *, const int *,
+                                                  const float *, float *, float *, float *, bool *done, hipStream_t) {
+    *done = false;
+    return MS_OK;
+}
+__attribute__((weak)) ms_status norm_swiglu_f32(int, int, int, float, const float *, const float *, const float *, float *, float *, float *,
+                                                float *, bool *done, hipStream_t) {
+    *done = false;
+    return MS_OK;
+}
 
 namespace {
 
@@ -207,11 +222,8 @@ struct Exec {
     }
 
     ms_status prologue() {
-        if (m.dec) {
-            MS_TRY(ms_k_positions(m.n, b->n_seqs, b->cu_seqlens_dev, p->pos, s));
-            MS_TRY(ms_k_rope_table(m.max_seqlen, m.hd, c->rope_base, p->rope, s));
-        }
-        return MS_OK;
+        if (!m.dec) return MS_OK;
+        return launch_rope_setup(m.n, b->n_seqs, b->cu_seqlens_dev, p->pos, m.max_seqlen, m.hd, c->rope_base, p->rope, s);
     }
 
     // The first layer's input: x_in itself, rows of the embedding table in `buf`, or, where x_in cannot be read in place (its
@@ -235,21 +247,33 @@ struct Exec {
     }
 
     ms_status layer_forward(const ms_layer_ptrs &w, const void *x, LayerBuf &l, void *y) {
-        MS_TRY(ms_k_norm_forward(kind, dt, fp32_stream(x), m.n, m.d, c->norm_eps, x, w.norm1_g, w.norm1_b, l.h1, l.mean1, l.rstd1, s));
-        MS_TRY(linear(l.h1, m.d, w.w_qkv, m.dec ? nullptr : w.b_qkv, m.dqkv, l.qkv, nullptr));
-        if (m.dec) MS_TRY(ms_k_rope(dt, m.n, m.nq + m.nkv, m.hd, m.dqkv, l.qkv, p->pos, p->rope, 0, s));
+        bool done = false;
+        if (m.dec && dt == MS_F32)
+            MS_TRY(norm_qkv_rope_f32(m.n, m.d, m.nq + 2 * m.nkv, m.nq + m.nkv, m.hd, c->norm_eps, (const float *)x, (const float *)w.norm1_g,
+                                     (const float *)w.w_qkv, p->pos, p->rope, (float *)l.qkv, p->bwd ? (float *)l.h1 : nullptr, l.rstd1, &done, s));
+        if (!done) {
+            MS_TRY(ms_k_norm_forward(kind, dt, fp32_stream(x), m.n, m.d, c->norm_eps, x, w.norm1_g, w.norm1_b, l.h1, l.mean1, l.rstd1, s));
+            MS_TRY(linear(l.h1, m.d, w.w_qkv, m.dec ? nullptr : w.b_qkv, m.dqkv, l.qkv, nullptr));
+            if (m.dec) MS_TRY(ms_k_rope(dt, m.n, m.nq + m.nkv, m.hd, m.dqkv, l.qkv, p->pos, p->rope, 0, s));
+        }
         MS_TRY(ms_k_attention_forward(dt, m.dec, m.nq, m.nkv, m.hd, m.n, b->n_seqs, m.max_seqlen, b->cu_seqlens_dev,
                                       l.qkv, l.o, l.lse, s));
         MS_TRY(linear(l.o, m.dattn, w.w_o, m.dec ? nullptr : w.b_o, m.d, l.x2, x));
-        MS_TRY(ms_k_norm_forward(kind, dt, 1, m.n, m.d, c->norm_eps, l.x2, w.norm2_g, w.norm2_b, l.h2, l.mean2, l.rstd2, s));
-        // decoder, bf16: SwiGLU runs in the epilogue of the gate/up GEMM (the pre-activations are only written
-        // when a backward pass will read them)
+        // decoder, fp32: norm, gate/up and SwiGLU are one launch.  bf16: SwiGLU runs in the epilogue of the gate/up GEMM.  (The
+        // pre-activations are only written when a backward pass will read them.)
         void *gu = p->bwd ? l.up : nullptr;
-        if (m.dec && dt == MS_BF16 && gemm_swiglu_supported(m.n, m.f, m.d, l.h2, m.d, w.w_up, m.d, l.act, m.f, gu, m.dup)) {
-            MS_TRY(gemm_swiglu(m.n, m.f, m.d, l.h2, m.d, w.w_up, m.d, l.act, m.f, gu, m.dup, s));
-        } else {
-            MS_TRY(linear(l.h2, m.d, w.w_up, m.dec ? nullptr : w.b_up, m.dup, l.up, nullptr));
-            MS_TRY(ms_k_act_forward(m.dec ? 0 : 1, dt, m.n, m.f, l.up, l.act, s));
+        done = false;
+        if (m.dec && dt == MS_F32)
+            MS_TRY(norm_swiglu_f32(m.n, m.d, m.f, c->norm_eps, (const float *)l.x2, (const float *)w.norm2_g, (const float *)w.w_up, (float *)l.act,
+                                   (float *)gu, p->bwd ? (float *)l.h2 : nullptr, l.rstd2, &done, s));
+        if (!done) {
+            MS_TRY(ms_k_norm_forward(kind, dt, 1, m.n, m.d, c->norm_eps, l.x2, w.norm2_g, w.norm2_b, l.h2, l.mean2, l.rstd2, s));
+            if (m.dec && dt == MS_BF16 && gemm_swiglu_supported(m.n, m.f, m.d, l.h2, m.d, w.w_up, m.d, l.act, m.f, gu, m.dup)) {
+                MS_TRY(gemm_swiglu(m.n, m.f, m.d, l.h2, m.d, w.w_up, m.d, l.act, m.f, gu, m.dup, s));
+            } else {
+                MS_TRY(linear(l.h2, m.d, w.w_up, m.dec ? nullptr : w.b_up, m.dup, l.up, nullptr));
+                MS_TRY(ms_k_act_forward(m.dec ? 0 : 1, dt, m.n, m.f, l.up, l.act, s));
+            }
         }
         MS_TRY(linear(l.act, m.f, w.w_down, m.dec ? nullptr : w.b_down, m.d, y, l.x2));
         return MS_OK;
