@@ -940,16 +940,23 @@ struct HalfStager {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(slot + lg * 8 * BK), 16, voff, k0 * 2, 0, 0);
     }
 };
+struct PpLds {
+    bf16_t *a[2][2], *b[2][2];                          // [stage][half]
+};
+#define MS_PP_LDS                                                                                                     \
+    constexpr int HS = 128 * BK; /* elements of a half tile */                                                        \
+    __shared__ __align__(16) bf16_t A00[HS], A01[HS], A10[HS], A11[HS], B00[HS], B01[HS], B10[HS], B11[HS];           \
+    const PpLds lds = {{{A00, A01}, {A10, A11}}, {{B00, B01}, {B10, B11}}}
+// Workgroup b of the nb that compute one product (of one K split)
 template <int EPI>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_pp_kernel(GemmParams p) {
-    constexpr int HS = 128 * BK;                        // elements of a half tile
-    __shared__ __align__(16) bf16_t A00[HS], A01[HS], A10[HS], A11[HS], B00[HS], B01[HS], B10[HS], B11[HS];   // [stage][half]
+__device__ __forceinline__ void gemm_pp_body(const GemmParams &p, const PpLds &lds, int b, int nb, int split) {
+    bf16_t *const A00 = lds.a[0][0], *const A01 = lds.a[0][1], *const A10 = lds.a[1][0], *const A11 = lds.a[1][1];
+    bf16_t *const B00 = lds.b[0][0], *const B01 = lds.b[0][1], *const B10 = lds.b[1][0], *const B11 = lds.b[1][1];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;            // wm = wave group
     int pid;
     {
-        const int nb = gridDim.x, b = blockIdx.x;
         const int per = nb >> 3, rem = nb & 7, x = b & 7, q = b >> 3;
         pid = x * per + (x < rem ? x : rem) + q;
     }
@@ -961,7 +968,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int tn = (pid % (GM * p.tiles_n)) / gsize;
     const int m0 = tm * 256, n0 = tn * 256;
 
-    const int kt_begin = blockIdx.y * p.k_tiles_per_split;
+    const int kt_begin = split * p.k_tiles_per_split;
     int kt_end = kt_begin + p.k_tiles_per_split;
     const int kt_total = (p.K + BK - 1) / BK;
     if (kt_end > kt_total) kt_end = kt_total;
@@ -1086,6 +1093,39 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int sq = wave >> 1;
     float *stg = (float *)(sq == 0 ? A00 : sq == 1 ? A01 : sq == 2 ? A10 : A11) + (wave & 1) * 2048;
     gemm_epilogue<EPI, true, false, false>(p, acc, stg, m0, n0, wn, lane, row_base, col_base);
+}
+template <int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_pp_kernel(GemmParams p) {
+    MS_PP_LDS;
+    gemm_pp_body<EPI>(p, lds, blockIdx.x, gridDim.x, blockIdx.y);
+}
+
+// A chunk's student logits with a KD epilogue (ps, EPI) and another chunk's teacher logits (pt) in one grid.  The student's
+// epilogue reads the stored teacher logits, 256 KB per 256 x 256 tile; in a launch of its own all CUs come to it together
+// and wait for HBM with idle matrix cores.  Here the two kinds of tiles take turns, a round of the chip each (kTwoRun): their
+// times differ, so that one kind's epilogues come to run beside the other's main loops, and one last round is left instead of
+// two (see ms_choose_two for what it gains).
+struct TwoSlot { int student, index; };
+__device__ __forceinline__ TwoSlot two_slot(int b, int nt, int ns) {
+    constexpr int run = kTwoRun;
+    const int both = (nt < ns ? nt : ns) / run * run;
+    if (b < 2 * both) return {(b / run) & 1, b / (2 * run) * run + b % run};
+    const int r = b - 2 * both;
+    return r < nt - both ? TwoSlot{0, both + r} : TwoSlot{1, both + r - (nt - both)};
+}
+template <int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_pp_two_kernel(GemmParams pt, GemmParams ps, int nt, int ns) {
+    MS_PP_LDS;
+    const TwoSlot t = two_slot(blockIdx.x, nt, ns);
+    if (t.student) gemm_pp_body<EPI>(ps, lds, t.index, ns, 0);
+    else gemm_pp_body<EPI_NONE>(pt, lds, t.index, nt, 0);
+}
+template <int BM, int BN, int WM, int WN, int NST, int EPI>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI, NST)))) void gemm_bf16_two_kernel(GemmParams pt, GemmParams ps, int nt, int ns) {
+    MS_FAST_LDS(BM, BN, NST);
+    const TwoSlot t = two_slot(blockIdx.x, nt, ns);
+    if (t.student) gemm_fast_body<BM, BN, WM, WN, false, false, EPI, true, NST>(ps, lds, t.index, ns, 0);
+    else gemm_fast_body<BM, BN, WM, WN, false, false, EPI_NONE, true, NST>(pt, lds, t.index, nt, 0);
 }
 
 // ------------------------------------------------------------------ fp32
@@ -1263,6 +1303,15 @@ template __global__ void gemm_bf16_pp_kernel<EPI_KD_STATS>(GemmParams);
     template __global__ void gemm_bf16_fast_kernel<BM, BN, WM, WN, false, false, EPI_SWIGLU, true, NST>(GemmParams)
 MS_INST_RINGS(128, 128, 4, 2, 4); MS_INST_RINGS(128, 256, 2, 4, 3); MS_INST_RINGS(64, 128, 2, 2, 3); MS_INST_RINGS(64, 64, 2, 1, 4);
 #undef MS_INST_RINGS
+#define MS_INST_TWO(EPI)                                                                                              \
+    template __global__ void gemm_bf16_pp_two_kernel<EPI>(GemmParams, GemmParams, int, int);                          \
+    template __global__ void gemm_bf16_two_kernel<128, 128, 2, 2, 2, EPI>(GemmParams, GemmParams, int, int);          \
+    template __global__ void gemm_bf16_two_kernel<128, 128, 4, 2, 4, EPI>(GemmParams, GemmParams, int, int);          \
+    template __global__ void gemm_bf16_two_kernel<128, 256, 2, 4, 3, EPI>(GemmParams, GemmParams, int, int);          \
+    template __global__ void gemm_bf16_two_kernel<64, 128, 2, 2, 3, EPI>(GemmParams, GemmParams, int, int);           \
+    template __global__ void gemm_bf16_two_kernel<64, 64, 2, 1, 4, EPI>(GemmParams, GemmParams, int, int)
+MS_INST_TWO(EPI_KD_DZ); MS_INST_TWO(EPI_KD_STATS);
+#undef MS_INST_TWO
 #define MS_INST_PAIR(BM, BN, WM, WN, NST)                                                                                    \
     template __global__ void gemm_bf16_pair_kernel<BM, BN, WM, WN, NST, EPI_NONE>(GemmParams, GemmParams, int, int, int);   \
     template __global__ void gemm_bf16_pair_kernel<BM, BN, WM, WN, NST, EPI_SWIGLU_BWD>(GemmParams, GemmParams, int, int, int)
@@ -1620,22 +1669,71 @@ bool gemm_kd_epilogue_supported(int M, int N, int K, const void *A, long lda, co
            ((long)M + 256) * ldz * 4 < lim && (!dz || (al(dz) && lddz % 4 == 0 && ((long)M + 256) * lddz * (dz_fp32 ? 4 : 2) < lim));
 }
 
-ms_status gemm_kd_epilogue(int mode, int M, int N, int K, const void *A, long lda, const void *B, long ldb, const float *zt,
-                           long ldz, float *stats, float *part, int nparts, float inv_t, float coef, void *dz, long lddz,
-                           int dz_fp32, hipStream_t s) {
+static ms_status prepare_kd(int mode, int M, int N, int K, const void *A, long lda, const void *B, long ldb, const float *zt,
+                            long ldz, float *stats, float *part, int nparts, float inv_t, float coef, void *dz, long lddz,
+                            int dz_fp32, GemmParams *out) {
     if (!gemm_kd_epilogue_supported(M, N, K, A, lda, B, ldb, zt, ldz, mode == EPI_KD_DZ ? dz : nullptr, lddz, dz_fp32))
         return ms_fail(MS_ERR_UNSUPPORTED, "gemm_kd_epilogue: shape or alignment outside the fast path");
     if ((mode == EPI_KD_DZ && (!dz || !stats)) || (mode == EPI_KD_STATS && (!part || nparts < ms_cdiv(N, 64))) ||
         (mode != EPI_KD_DZ && mode != EPI_KD_STATS))
         return ms_fail(MS_ERR_INVALID_ARG, "gemm_kd_epilogue: bad mode or null buffer");
-    GemmParams p = {};
+    GemmParams &p = *out;
+    p = {};
     p.A = A; p.B = B; p.C = dz; p.lda = lda; p.ldb = ldb; p.ldc = lddz; p.M = M; p.N = N; p.K = K; p.alpha = 1.f;
     p.c_fp32 = dz_fp32;
     p.kd_zt = zt; p.kd_ldz = ldz; p.kd_stats = stats; p.kd_part = part; p.kd_nparts = nparts; p.kd_inv_t = inv_t; p.kd_coef = coef;
     p.k_tiles_per_split = ms_cdiv(K, BK);
+    return MS_OK;
+}
+
+ms_status gemm_kd_epilogue(int mode, int M, int N, int K, const void *A, long lda, const void *B, long ldb, const float *zt,
+                           long ldz, float *stats, float *part, int nparts, float inv_t, float coef, void *dz, long lddz,
+                           int dz_fp32, hipStream_t s) {
+    GemmParams p;
+    MS_TRY(prepare_kd(mode, M, N, K, A, lda, B, ldb, zt, ldz, stats, part, nparts, inv_t, coef, dz, lddz, dz_fp32, &p));
     const int tile = choose_tile(M, N, p.k_tiles_per_split, kKdEpilogueBytes);
     if (mode == EPI_KD_DZ) return launch_bf16_fast<EPI_KD_DZ>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
     return launch_bf16_fast<EPI_KD_STATS>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
+}
+
+template <int EPI> static void launch_two(int tile, GemmParams &pt, GemmParams &ps, hipStream_t s) {
+    const MsTile &t = kTiles[tile];
+    pt.tiles_m = ps.tiles_m = ms_cdiv(ps.M, t.bm);
+    pt.tiles_n = ms_cdiv(pt.N, t.bn);
+    ps.tiles_n = ms_cdiv(ps.N, t.bn);
+    const int nt = pt.tiles_m * pt.tiles_n, ns = ps.tiles_m * ps.tiles_n;
+    if (tile == T256) {
+        gemm_bf16_pp_two_kernel<EPI><<<nt + ns, 512, 0, s>>>(pt, ps, nt, ns);
+        return;
+    }
+#define GO(BM, BN, WM, WN, NST) gemm_bf16_two_kernel<BM, BN, WM, WN, NST, EPI><<<nt + ns, 64 * WM * WN, 0, s>>>(pt, ps, nt, ns)
+    switch (tile) {
+        case R128: GO(128, 128, 4, 2, 4); break;
+        case R128x256: GO(128, 256, 2, 4, 3); break;
+        case R64x128: GO(64, 128, 2, 2, 3); break;
+        case R64: GO(64, 64, 2, 1, 4); break;
+        default: GO(128, 128, 2, 2, 2); break;
+    }
+#undef GO
+}
+
+ms_status gemm_kd_and_teacher(int mode, int M, int N, int K, const void *A, const void *B, const float *zt, float *stats, float *part, int nparts,
+                              float inv_t, float coef, void *dz, long ld, int Nt, int Kt, const void *At, const void *Bt, float *next_zt, hipStream_t s) {
+    GemmParams ps;
+    MS_TRY(prepare_kd(mode, M, N, K, A, K, B, K, zt, ld, stats, part, nparts, inv_t, coef, dz, ld, 0, &ps));
+    Bf16Gemm t;
+    MS_TRY(prepare_bf16(0, 0, M, Nt, Kt, 1.f, At, Kt, Bt, Kt, next_zt, ld, 1, 0, nullptr, nullptr, 0, 0, &t));
+    const int tile = t.fast && use_mfma16() ? ms_choose_two(M, N, ps.k_tiles_per_split, Nt, t.kt, forced_tile()) : -1;
+    if (tile >= 0 && ms_launch_fits(ms_tiles(kTiles[tile], M, N) + ms_tiles(kTiles[tile], M, Nt), 512)) {
+        set_splits(t, 1);
+        ProfScope prof(0, 2.0 * M * ((double)N * K + (double)Nt * Kt), s);
+        if (mode == EPI_KD_DZ) launch_two<EPI_KD_DZ>(tile, t.p, ps, s);
+        else launch_two<EPI_KD_STATS>(tile, t.p, ps, s);
+        MS_LAUNCH_CHECK();
+        return MS_OK;
+    }
+    MS_TRY(gemm_kd_epilogue(mode, M, N, K, A, K, B, K, zt, ld, stats, part, nparts, inv_t, coef, dz, ld, 0, s));
+    return ms_k_gemm(MS_BF16, 0, 0, M, Nt, Kt, 1.f, At, Kt, Bt, Kt, next_zt, ld, 1, 0, nullptr, nullptr, 0, 0, 1, s);
 }
 
 // ------------------------------------------------------------------ fused gate/up GEMM + SwiGLU

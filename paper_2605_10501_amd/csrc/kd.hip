@@ -210,35 +210,46 @@ ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, co
             const int cw = V - v0 < Cv ? V - v0 : Cv;
             fused = gemm_kd_epilogue_supported(nb, cw, Hs, hs_b, Hs, wsd + (size_t)v0 * Hs * es, Hs, p.zt, Cv, p.dz, Cv, 0);
         }
-        // Teacher logits of how many chunks, the last ones, outlive pass 1.  With two tiles for them, chunks alternate between
-        // the two, and the partial statistics (32 bytes per 64 columns) move to the dz buffer, which is not in use before pass 2.
-        const bool two = fused && passes == 2 && !keep && ms_cdiv(Cv, 64) * 32 <= Cv * 2;
+        // Two tiles for teacher logits, which chunks use in turn; the partial statistics (32 bytes per 64 columns) move to the dz
+        // buffer, which is not in use before pass 2.  So the logits of the last two chunks outlive pass 1, and the teacher's
+        // product for the next chunk can share a launch with the student's for this one.
+        const bool two = fused && !keep && ms_cdiv(Cv, 64) * 32 <= Cv * 2;
         const int kept = keep ? chunks : two ? 2 : 1;
         float *part = two ? (float *)p.dz : p.zs;
+        auto width = [&](int ci) { return V - ci * Cv < Cv ? V - ci * Cv : Cv; };
+        auto teacher_tile = [&](int ci) { return keep ? p.zt + (size_t)ci * p.tb * Cv : two && (ci & 1) ? p.zs : p.zt; };
+        auto teacher_rows = [&](int ci) { return wt + (size_t)ci * Cv * Ht * es; };
         for (int pass = 0; pass < passes; ++pass) {
+            bool ahead = false;                               // this chunk's teacher logits came with the last chunk's launch
             for (int i = 0; i < chunks; ++i) {
-                const int ci = pass == 0 ? i : chunks - 1 - i;
-                const int v0 = ci * Cv, cw = V - v0 < Cv ? V - v0 : Cv;
-                float *zt = keep ? p.zt + (size_t)ci * p.tb * Cv : two && (ci & 1) ? p.zs : p.zt;
-                const bool teacher = pass == 0 || i >= kept, student = !fused && (pass == 0 || i > 0);
+                const int ci = pass == 0 ? i : chunks - 1 - i, next = pass == 0 ? ci + 1 : ci - 1;
+                const int v0 = ci * Cv, cw = width(ci);
+                float *zt = teacher_tile(ci);
+                const bool teacher = (pass == 0 || i >= kept) && !ahead, student = !fused && (pass == 0 || i > 0);
                 const char *ws_c = wsd + (size_t)v0 * Hs * es;
                 if (teacher && student && dt == MS_F32)
-                    MS_TRY(gemm_f32_two(nb, cw, (const float *)ht_b, (const float *)(wt + (size_t)v0 * Ht * es), zt, Ht, (const float *)hs_b,
+                    MS_TRY(gemm_f32_two(nb, cw, (const float *)ht_b, (const float *)teacher_rows(ci), zt, Ht, (const float *)hs_b,
                                         (const float *)ws_c, p.zs, Hs, Cv, s));
                 else if (teacher)
-                    MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Ht, 1.f, ht_b, Ht, wt + (size_t)v0 * Ht * es, Ht, zt, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
+                    MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Ht, 1.f, ht_b, Ht, teacher_rows(ci), Ht, zt, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));
+                ahead = fused && (two || keep) && i + 1 < chunks && (pass == 0 || i + 1 >= kept);
+                // student logits of this chunk with their epilogue, and with them the next chunk's teacher logits
+                auto student_logits = [&](int mode, float *st, float *pt, int nparts, float coef, void *dz) {
+                    if (ahead)
+                        return gemm_kd_and_teacher(mode, nb, cw, Hs, hs_b, ws_c, zt, st, pt, nparts, inv_t, coef, dz, Cv, width(next), Ht, ht_b,
+                                                   teacher_rows(next), teacher_tile(next), s);
+                    return gemm_kd_epilogue(mode, nb, cw, Hs, hs_b, Hs, ws_c, Hs, zt, Cv, st, pt, nparts, inv_t, coef, dz, Cv, 0, s);
+                };
                 if (fused) {
                     const int nparts = ms_cdiv(cw, 64);
                     if (pass == 0) {
-                        MS_TRY(gemm_kd_epilogue(2, nb, cw, Hs, hs_b, Hs, ws_c, Hs, zt, Cv, nullptr, part, nparts,
-                                                inv_t, 0.f, nullptr, 0, 0, s));
+                        MS_TRY(student_logits(2, nullptr, part, nparts, 0.f, nullptr));
                         ProfScope ps(9, 32.0 * nb * nparts, s);
                         kd_combine_kernel<<<ms_cdiv(nb, 4), 256, 0, s>>>(part, nparts, nb, ci == 0, ci == chunks - 1, stats_b, kl_b);
                         MS_LAUNCH_CHECK();
                         continue;
                     }
-                    MS_TRY(gemm_kd_epilogue(1, nb, cw, Hs, hs_b, Hs, ws_c, Hs, zt, Cv, stats_b, nullptr, 0, inv_t,
-                                            kd->loss_scale * inv_t, p.dz, Cv, 0, s));
+                    MS_TRY(student_logits(1, stats_b, nullptr, 0, kd->loss_scale * inv_t, p.dz));
                 } else {
                     if (student && !(teacher && dt == MS_F32))
                         MS_TRY(ms_k_gemm(dt, 0, 0, nb, cw, Hs, 1.f, hs_b, Hs, ws_c, Hs, p.zs, Cv, 1, 0, nullptr, nullptr, 0, 0, 1, s));

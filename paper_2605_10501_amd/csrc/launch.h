@@ -14,6 +14,11 @@ ms_status gemm_kd_epilogue(int mode, int M, int N, int K, const void *A, long ld
                            long ldz, float *stats, float *part, int nparts, float inv_t, float coef, void *dz, long lddz,
                            int dz_fp32, hipStream_t s);
 
+// The same (bf16 dz, rows of all [M, .] results ld apart, operands without padding) together with another chunk's teacher logits
+// next_zt[M, Nt] = At[M, Kt] Bt[Nt, Kt]^T, which nothing here reads; in one launch where that is faster.
+ms_status gemm_kd_and_teacher(int mode, int M, int N, int K, const void *A, const void *B, const float *zt, float *stats, float *part, int nparts,
+                              float inv_t, float coef, void *dz, long ld, int Nt, int Kt, const void *At, const void *Bt, float *next_zt, hipStream_t s);
+
 // Fused gate/up GEMM + SwiGLU (gemm.hip): act[M,F] = silu(A Wg^T) * (A Wu^T), W = [Wg | Wu] rows; gate_up (may be
 // null) receives the rounded pre-activations [M, 2F].
 bool gemm_swiglu_supported(int M, int F, int K, const void *A, long lda, const void *W, long ldw, const void *act, long ldact,

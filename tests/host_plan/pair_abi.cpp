@@ -10,3 +10,7 @@ void pair_choose(long n, long out, long in, double dx_bytes, int forced, int *ti
     tile_splits_first[2] = p.wgrad_first;
 }
 }
+extern "C" int two_choose(long m, long n, int kt, long nt, int ktt, int forced) {
+    const int i = ms_choose_two(m, n, kt, nt, ktt, forced);
+    return i < 0 ? -1 : kTiles[i].code;
+}

@@ -56,3 +56,10 @@ def test_splits_leave_at_least_eight_k_tiles_and_forced_tiles_are_taken(plan):
         assert 1 <= splits <= 8 and (splits == 1 or (n + 63) // 64 // splits >= 8)
         for code in (256, 128, 128128, 128256, 64128, 64064):
             assert choose(plan, n, out, inn, forced=code)[0] == code
+
+
+def test_student_and_teacher_logits_share_small_grids(plan):
+    f = lambda m, n, kt, nt, ktt, forced=0: plan.two_choose(C.c_long(m), C.c_long(n), kt, C.c_long(nt), ktt, forced)
+    assert all(f(m, 8192, 16, 8192, 32) > 0 for m in (1, 64, 300, 1024))
+    assert f(1500, 8192, 32, 8192, 64) == -1                       # 192 tiles of 256 x 256 each: two launches were faster
+    assert all(f(300, 4096, 16, 1000, 32, code) == code for code in (256, 128, 128128, 128256, 64128, 64064))
