@@ -54,7 +54,7 @@ def describe(c):
 
 def nt_gemm_shapes(work):
     """(M, N, K, bytes written per output element, bytes read per output element besides A and B) of every
-    A[M,K]*B[N,K]^T launch of one KD step (decoder sections, bf16 fast path with its fused epilogues)."""
+    A[M,K]*B[N,K]^T product of one KD step (decoder sections, bf16 fast path with its fused epilogues)."""
     n = work.n_tokens
     out = []
     for cfg, bwd in ((work.teacher, False), (work.student, True)):
@@ -68,9 +68,12 @@ def nt_gemm_shapes(work):
     kd = work.kd
     for v0 in range(0, kd.vocab, kd.chunk):
         cw = min(kd.chunk, kd.vocab - v0)
-        # teacher logits stored fp32 in both passes; student logits consumed by their epilogue together with the
-        # teacher's (statistics: nothing but 0.5 B of partials per column; dz: 2 B)
-        out += [(n, cw, kd.h_teacher, 4, 0), (n, cw, kd.h_student, 0.5, 4), (n, cw, kd.h_teacher, 4, 0), (n, cw, kd.h_student, 2, 4)]
+        # teacher logits stored fp32 (the last two chunks' outlive the first pass, the others' are computed again in the
+        # second); student logits consumed by their epilogue together with the teacher's (statistics: nothing but 0.5 B of
+        # partials per column; dz: 2 B)
+        out += [(n, cw, kd.h_teacher, 4, 0), (n, cw, kd.h_student, 0.5, 4), (n, cw, kd.h_student, 2, 4)]
+        if v0 + 2 * kd.chunk < kd.vocab:
+            out += [(n, cw, kd.h_teacher, 4, 0)]
     return out
 
 
@@ -201,8 +204,9 @@ def bench_kd_step(name, args, torch, B, wl, dev, side):
     achieved = g_work / (g_ms * 1e-3) / 1e12 if g_ms > 0 else 0.0
     alg_bytes = None
     shapes = nt_gemm_shapes(work)
-    if len(shapes) == g_n / prof_steps and abs(sum(2.0 * m * nn * k for m, nn, k, _, _ in shapes) * prof_steps / g_work - 1) < 1e-3:
-        alg_bytes = sum(2.0 * (m * k + nn * k) + (ob + rb) * m * nn for m, nn, k, ob, rb in shapes) / len(shapes)
+    # (a launch may hold two of the products: student logits and the next chunk's teacher logits)
+    if g_n and abs(sum(2.0 * m * nn * k for m, nn, k, _, _ in shapes) * prof_steps / g_work - 1) < 1e-3:
+        alg_bytes = sum(2.0 * (m * k + nn * k) + (ob + rb) * m * nn for m, nn, k, ob, rb in shapes) * prof_steps / g_n
     traffic, traffic_src = measured_traffic(name)
     total_flops = fl["teacher"] + fl["student"] + fl["kd"]
     res = {
@@ -218,7 +222,7 @@ def bench_kd_step(name, args, torch, B, wl, dev, side):
         "mfma_frac_kd_loss": fl["kd"] / sec_kd / 1e12 / PEAK_BF16_TFLOPS if sec_kd else None,
         "student_section_tflops": (fl["student"] + fl["kd"]) / sec_student / 1e12,
         "loss": loss, "logits_to_hidden_ratio": kd.vocab / kd.h_teacher,
-        "roofline": {"kernel": "gemm_bf16_fast_kernel, gemm_bf16_pp_kernel (A[M,K] B[N,K]^T: all forward linears and lm_head chunk GEMMs)",
+        "roofline": {"kernel": "gemm_bf16_pp_kernel, gemm_bf16_fast_kernel, and their _two_kernel forms (A[M,K] B[N,K]^T: all forward linears and lm_head chunk GEMMs)",
                      "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
                      "traffic_source": (traffic_src + " (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; bytes per launch)") if traffic else None,
