@@ -63,24 +63,21 @@ struct GemmParams {
 // EPI_SWIGLU_BWD: the tile holds da = dL/d(silu(gate) * up); sg_gu = the pre-activations [M, sg_ldgu], read; C = [dgate | dup] [M, ldc]
 enum { EPI_NONE = 0, EPI_KD_DZ = 1, EPI_KD_STATS = 2, EPI_SWIGLU = 3, EPI_SWIGLU_BWD = 4 };
 
-// All-reduce over each aligned group of 16 lanes with DPP moves (one vector-ALU instruction per step, no LDS
-// crossbar): swap within pairs, swap pairs within quads, mirror within 8 lanes (reaches the other quad), mirror within
-// 16 lanes (reaches the other half).  After the four steps all 16 lanes hold the group's result.
-template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+// Reductions over the four 16-lane groups of a wave, on the vector ALU (no LDS crossbar): lane l gets the result over lanes
+// l % 16, l % 16 + 16, + 32 and + 48.  v_permlane16_swap of a register with itself leaves the even groups' values in one
+// result and the odd groups' in the other, v_permlane32_swap the lower and the upper half's.
+template <class F> __device__ __forceinline__ float across_groups(float v, F f) {
+    const unsigned a = __builtin_bit_cast(unsigned, v);
+    const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const unsigned b = __builtin_bit_cast(unsigned, f(__builtin_bit_cast(float, (unsigned)q[0]), __builtin_bit_cast(float, (unsigned)q[1])));
+    const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return f(__builtin_bit_cast(float, (unsigned)h[0]), __builtin_bit_cast(float, (unsigned)h[1]));
 }
-constexpr int kDppQuadXor1 = 0xB1, kDppQuadXor2 = 0x4E, kDppRowHalfMirror = 0x141, kDppRowMirror = 0x140;
-__device__ __forceinline__ float row16_max(float v) {
-    v = fmaxf(v, dpp_move<kDppQuadXor1>(v));
-    v = fmaxf(v, dpp_move<kDppQuadXor2>(v));
-    v = fmaxf(v, dpp_move<kDppRowHalfMirror>(v));
-    return fmaxf(v, dpp_move<kDppRowMirror>(v));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-    v += dpp_move<kDppQuadXor1>(v);
-    v += dpp_move<kDppQuadXor2>(v);
-    v += dpp_move<kDppRowHalfMirror>(v);
-    return v + dpp_move<kDppRowMirror>(v);
+// fmaxf of three values that no instruction has produced yet (loads) costs three more to quiet signalling NaNs; v_max3 does so itself
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
 // Cache policy of the vector epilogues' global accesses (auxiliary operand of the buffer instructions): non-temporal.
@@ -479,6 +476,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
         const long aux_ld = EPI != EPI_NONE ? p.kd_ldz : (aux_res ? p.ldr : p.ldc);
         const __amdgpu_buffer_rsrc_t ra_ = EPI == EPI_SWIGLU_BWD ? make_rsrc(p.sg_gu, (long)p.M * p.sg_ldgu * 2)
                                            : EPI != EPI_NONE     ? make_rsrc(p.kd_zt, (long)p.M * p.kd_ldz * 4) : (aux_res ? rr : rc);
+        const __amdgpu_buffer_rsrc_t rl = make_rsrc(EPI == EPI_KD_DZ ? (const void *)p.kd_stats : p.C, EPI == EPI_KD_DZ ? (long)p.M * 32 : 0);
         u32x4 aux[2][8];
         float2 lsev[2][8];                                                         // EPI_KD_DZ: (lse_t, lse_s) of the row
         auto prefetch = [&](int i, u32x4 *dst, float2 *ldst) {
@@ -498,7 +496,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
                     const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(ra_, off, 0, kStream);
                     dst[ps][0] = q[0]; dst[ps][1] = q[1];
                 }
-                if constexpr (EPI == EPI_KD_DZ) ldst[ps] = rowg < p.M ? *(const float2 *)(p.kd_stats + rowg * 8 + 6) : make_float2(0.f, 0.f);
+                if constexpr (EPI == EPI_KD_DZ) ldst[ps] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rl, (unsigned)rowg * 32 + 24, 0, 0));
             }
         };
         float bv[4] = {0.f, 0.f, 0.f, 0.f};
@@ -524,11 +522,102 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
         };
         const float it = p.kd_inv_t;
         const float it2 = it * 1.4426950408889634f;      // e^{z/T - m} = 2^{z it2 - m log2(e)}: one fused multiply-add feeds exp2
+        // Statistics of the wave's 32-row block i: per row, over the wave's 64 columns, max and sum of exponentials of zt/T and
+        // zs/T and the cross term sum e^{zt/T - m_t} (zt - zs)/T -> kd_part.  16 rows at a time both tiles go through LDS ([16][64]
+        // fp32 each, 16-byte chunk c of row r at c ^ r: no bank conflicts on either side), from where lane l takes chunks l / 16 +
+        // 4 k of row l % 16: a row is then 16 values in a lane and four lanes, and each of the five reductions costs two steps per
+        // 16 rows.  With a row's four columns per lane as in the other epilogues it is four steps for every four rows, and their
+        // moves, address arithmetic and branches were two thirds of this epilogue, which the vector ALU bounds.
+        auto kd_statistics = [&](int i, const u32x4 *q) __attribute__((always_inline)) {
+            const int r16 = lane & 15, grp = lane >> 4;
+            const bool full = n0 + wn * WTN + WTN <= p.N;                          // wave-uniform
+            float *stz = stg + 1024;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                wave_sync();
+                if constexpr (M16) {
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int row = 4 * fhalf + r;
+                            stg[row * 64 + ((j * 16 + frow) ^ (row << 2))] = acc[2 * i + h][j][r];
+                        }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) {
+                            const int row = 8 * (r >> 2) + 4 * fhalf + (r & 3);
+                            stg[row * 64 + ((j * 32 + frow) ^ (row << 2))] = acc[i][j][8 * h + r];
+                        }
+                }
+#pragma unroll
+                for (int ps = 0; ps < 4; ++ps) {
+                    const int row = ps * 4 + prow;
+                    *(u32x4 *)(stz + row * 64 + (pcol ^ (row << 2))) = q[h * 4 + ps];
+                }
+                wave_sync();
+                float zs[16], zt[16], d[16];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int at = r16 * 64 + (((4 * k + grp) ^ r16) << 2);
+                    const float4 a = *(const float4 *)(stg + at), b = *(const float4 *)(stz + at);
+                    zs[4 * k] = a.x; zs[4 * k + 1] = a.y; zs[4 * k + 2] = a.z; zs[4 * k + 3] = a.w;
+                    zt[4 * k] = b.x; zt[4 * k + 1] = b.y; zt[4 * k + 2] = b.z; zt[4 * k + 3] = b.w;
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) d[e] = zt[e] - zs[e];
+                if (!full) {                                                       // columns past N take no part
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int c = (e & ~3) + grp;
+                        const bool ok = n0 + col_base(c >> 3) + (c & 7) * 4 < p.N;
+                        zs[e] = ok ? zs[e] : -INFINITY;
+                        zt[e] = ok ? zt[e] : -INFINITY;
+                        d[e] = ok ? d[e] : 0.f;
+                    }
+                }
+                float mt = max3(zt[0], zt[1], zt[2]), ms = max3(zs[0], zs[1], zs[2]);
+#pragma unroll
+                for (int e = 3; e < 15; e += 2) {
+                    mt = max3(mt, zt[e], zt[e + 1]);
+                    ms = max3(ms, zs[e], zs[e + 1]);
+                }
+                auto larger = [](float a, float b) { return max3(a, b, b); };
+                mt = across_groups(larger(mt, zt[15]), larger) * it;               // T > 0
+                ms = across_groups(larger(ms, zs[15]), larger) * it;
+                const float mt2 = mt == -INFINITY ? 0.f : mt * 1.4426950408889634f;
+                const float ms2 = ms == -INFINITY ? 0.f : ms * 1.4426950408889634f;
+                float st = 0.f, ss = 0.f, ac = 0.f;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float et = __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -mt2));
+                    st += et;
+                    ac = __builtin_fmaf(et, d[e], ac);
+                    ss += __builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ms2));
+                }
+                auto sum = [](float a, float b) { return a + b; };
+                st = across_groups(st, sum);
+                ss = across_groups(ss, sum);
+                ac = across_groups(ac * it, sum);
+                const long rowg = m0 + row_base(i) + h * 16 + r16;
+                if (grp == 0 && rowg < p.M && n0 + wn * WTN < p.N) {
+                    float *o = p.kd_part + (rowg * p.kd_nparts + (n0 + wn * WTN) / 64) * 8;
+                    *(float4 *)o = make_float4(mt, st, ms, ss);
+                    o[4] = ac;
+                }
+            }
+        };
         if (has_aux) prefetch(0, aux[0], lsev[0]);
 #pragma unroll
         for (int i = 0; i < MI32; ++i) {
             if (has_aux && i + 1 < MI32) prefetch(i + 1, aux[(i + 1) & 1], lsev[(i + 1) & 1]);
-            stage_block(i, [&](float a) { return a * p.alpha; });
+            if constexpr (EPI == EPI_KD_STATS) {
+                kd_statistics(i, aux[i & 1]);
+                continue;
+            }
+            stage_block(i, [&](float a) { return EPI == EPI_KD_DZ ? a : a * p.alpha; });     // (the KD epilogues have alpha = 1)
 #pragma unroll
             for (int ps = 0; ps < 8; ++ps) {
                 const int row = ps * 4 + prow;
@@ -575,46 +664,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
                     float zt[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) zt[e] = __uint_as_float(q[e]);
-                    if constexpr (EPI == EPI_KD_DZ) {
-                        // dz = coef * (exp(zs/T - lse_s) - exp(zt/T - lse_t)) -> C (storage dtype)
-                        const float lt2 = lsev[i & 1][ps].x * 1.4426950408889634f, ls2 = lsev[i & 1][ps].y * 1.4426950408889634f;
-                        float v[4];
+                    // dz = coef * (exp(zs/T - lse_s) - exp(zt/T - lse_t)) -> C (storage dtype)
+                    const float lt2 = lsev[i & 1][ps].x * 1.4426950408889634f, ls2 = lsev[i & 1][ps].y * 1.4426950408889634f;
+                    float v[4];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            v[e] = p.kd_coef * (__builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ls2)) -
-                                                __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -lt2)));
-                        store4(v, co);
-                    } else {
-                        // per row, over this wave's 64 columns: max and sum of exponentials of zt/T and zs/T and
-                        // the cross term sum e^{zt/T - m_t} (zt - zs)/T -> kd_part; the 16 lanes that share a
-                        // row reduce with data-parallel-primitive moves inside their group (no LDS round trip)
-                        float mt = cok ? fmaxf(fmaxf(zt[0], zt[1]), fmaxf(zt[2], zt[3])) : -INFINITY;
-                        float ms = cok ? fmaxf(fmaxf(zs[0], zs[1]), fmaxf(zs[2], zs[3])) : -INFINITY;
-                        mt = row16_max(mt);
-                        ms = row16_max(ms);
-                        mt *= it; ms *= it;                                   // T > 0
-                        const float mt2 = mt == -INFINITY ? 0.f : mt * 1.4426950408889634f;
-                        const float ms2 = ms == -INFINITY ? 0.f : ms * 1.4426950408889634f;
-                        float st = 0.f, ss = 0.f, ac = 0.f;
-                        if (cok) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float et = __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -mt2));
-                                st += et;
-                                ac = __builtin_fmaf(et, zt[e] - zs[e], ac);
-                                ss += __builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ms2));
-                            }
-                            ac *= it;
-                        }
-                        st = row16_sum(st);
-                        ss = row16_sum(ss);
-                        ac = row16_sum(ac);
-                        if ((lane & 15) == 0 && rowg < p.M && n0 + wn * WTN < p.N) {
-                            float *o = p.kd_part + ((long)rowg * p.kd_nparts + (n0 + wn * WTN) / 64) * 8;
-                            *(float4 *)o = make_float4(mt, st, ms, ss);
-                            o[4] = ac;
-                        }
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        v[e] = p.kd_coef * (__builtin_amdgcn_exp2f(__builtin_fmaf(zs[e], it2, -ls2)) -
+                                            __builtin_amdgcn_exp2f(__builtin_fmaf(zt[e], it2, -lt2)));
+                    store4(v, co);
                 }
             }
         }
