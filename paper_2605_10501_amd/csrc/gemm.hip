@@ -412,6 +412,19 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
     };
     // ---- epilogue.  C and the residual are addressed through buffer descriptors: rows past M are
     // dropped (stores) or read as zero by the range check, columns past N by one select.
+    // Byte offset of row r of the wave's block i: the lane's part (its row within the pass and its column) once, the rest, which is
+    // the same in all lanes, on the scalar unit.  A product per row and lane on the vector ALU is a quarter-rate instruction; with the
+    // packed conversions below it was 46 instead of 35 vector instructions for four rows of the dz epilogue, 42 instead of 32 for
+    // SwiGLU's (distillation head of 8192 tokens, V = 151936 31.01 -> 30.84 ms, 1024 tokens, V = 32000 638 -> 635 us, others even).
+    auto row_bytes = [&](int i, int r, long ld, int es) { return (unsigned)(m0 + row_base(i) + r) * (unsigned)ld * (unsigned)es; };
+    // four values in the storage type, two conversions of two
+    auto pack4 = [](const float *v) {
+        typedef bf16_t pair_t __attribute__((ext_vector_type(2)));
+        u32x2 w;
+        w[0] = __builtin_bit_cast(unsigned, pair_t{(bf16_t)v[0], (bf16_t)v[1]});
+        w[1] = __builtin_bit_cast(unsigned, pair_t{(bf16_t)v[2], (bf16_t)v[3]});
+        return w;
+    };
     const int esz = p.c_fp32 ? 4 : 2;
     const __amdgpu_buffer_rsrc_t rc = make_rsrc(p.C, (long)p.M * p.ldc * esz);
     const int rsz = p.res_fp32 ? 4 : 2;
@@ -425,13 +438,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
         const int prow = lane >> 3, pcol = (lane & 7) * 4;
         const int colg = n0 / 2 + wn * 32 + pcol;
         const bool cok = colg < p.N;
+        const unsigned lane_c = (unsigned)((prow * p.ldc + colg) * 2), lane_g = (unsigned)((prow * p.sg_ldgu + colg) * 2);
         const __amdgpu_buffer_rsrc_t rg = make_rsrc(p.sg_gu ? p.sg_gu : p.C, p.sg_gu ? (long)p.M * p.sg_ldgu * 2 : 0);
-        auto pack4 = [](const float *v) {
-            u32x2 w;
-            w[0] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[0]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[1]) << 16);
-            w[1] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[2]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[3]) << 16);
-            return w;
-        };
 #pragma unroll
         for (int i = 0; i < MI32; ++i) {
             stage_block(i, [&](float a) { return (float)(bf16_t)(a * p.alpha); });
@@ -446,10 +454,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
 #pragma unroll
                 for (int e = 0; e < 4; ++e)   // silu(g) u = g u / (1 + e^-g); hardware reciprocal (1 ulp) instead of the division sequence
                     a[e] = gv[e] * uv[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gv[e]));
-                const long rowg = m0 + row_base(i) + row;
-                __builtin_amdgcn_raw_buffer_store_b64(pack4(a), rc, cok ? (unsigned)((rowg * p.ldc + colg) * 2) : kOob, 0, kStream);
+                __builtin_amdgcn_raw_buffer_store_b64(pack4(a), rc, cok ? lane_c + row_bytes(i, ps * 8, p.ldc, 2) : kOob, 0, kStream);
                 if (p.sg_gu) {
-                    const unsigned go = cok ? (unsigned)((rowg * p.sg_ldgu + colg) * 2) : kOob;
+                    const unsigned go = cok ? lane_g + row_bytes(i, ps * 8, p.sg_ldgu, 2) : kOob;
                     __builtin_amdgcn_raw_buffer_store_b64(pack4(gv), rg, go, 0, kStream);
                     __builtin_amdgcn_raw_buffer_store_b64(pack4(uv), rg, cok ? go + (unsigned)p.sg_f * 2 : kOob, 0, kStream);
                 }
@@ -479,24 +486,25 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
         const __amdgpu_buffer_rsrc_t rl = make_rsrc(EPI == EPI_KD_DZ ? (const void *)p.kd_stats : p.C, EPI == EPI_KD_DZ ? (long)p.M * 32 : 0);
         u32x4 aux[2][8];
         float2 lsev[2][8];                                                         // EPI_KD_DZ: (lse_t, lse_s) of the row
+        const unsigned lane_c = (unsigned)((prow * p.ldc + colg) * esz), lane_aux = (unsigned)((prow * aux_ld + colg) * (aux4 ? 4 : 2));
+        const unsigned lane_g = (unsigned)((prow * p.sg_ldgu + colg) * 2);
         auto prefetch = [&](int i, u32x4 *dst, float2 *ldst) {
 #pragma unroll
             for (int ps = 0; ps < 8; ++ps) {
-                const long rowg = m0 + row_base(i) + ps * 4 + prow;
                 if constexpr (EPI == EPI_SWIGLU_BWD) {
-                    const unsigned go = cok ? (unsigned)((rowg * p.sg_ldgu + colg) * 2) : kOob;
+                    const unsigned go = cok ? lane_g + row_bytes(i, ps * 4, p.sg_ldgu, 2) : kOob;
                     const u32x2 g = __builtin_amdgcn_raw_buffer_load_b64(ra_, go, 0, kStream);
                     const u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(ra_, cok ? go + (unsigned)p.sg_f * 2 : kOob, 0, kStream);
                     dst[ps][0] = g[0]; dst[ps][1] = g[1]; dst[ps][2] = u[0]; dst[ps][3] = u[1];
                     continue;
                 }
-                const unsigned off = cok ? (unsigned)((rowg * aux_ld + colg) * (aux4 ? 4 : 2)) : kOob;
+                const unsigned off = cok ? lane_aux + row_bytes(i, ps * 4, aux_ld, aux4 ? 4 : 2) : kOob;
                 if (aux4) dst[ps] = __builtin_amdgcn_raw_buffer_load_b128(ra_, off, 0, kStream);
                 else {
                     const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(ra_, off, 0, kStream);
                     dst[ps][0] = q[0]; dst[ps][1] = q[1];
                 }
-                if constexpr (EPI == EPI_KD_DZ) ldst[ps] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rl, (unsigned)rowg * 32 + 24, 0, 0));
+                if constexpr (EPI == EPI_KD_DZ) ldst[ps] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rl, prow * 32 + 24 + row_bytes(i, ps * 4, 8, 4), 0, 0));
             }
         };
         float bv[4] = {0.f, 0.f, 0.f, 0.f};
@@ -514,10 +522,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
                 for (int e = 0; e < 4; ++e) w[e] = __builtin_bit_cast(unsigned, v[e]);
                 __builtin_amdgcn_raw_buffer_store_b128(w, rc, co, 0, kStream);
             } else {
-                u32x2 w;
-                w[0] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[0]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[1]) << 16);
-                w[1] = (unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[2]) | ((unsigned)__builtin_bit_cast(unsigned short, (bf16_t)v[3]) << 16);
-                __builtin_amdgcn_raw_buffer_store_b64(w, rc, co, 0, kStream);
+                __builtin_amdgcn_raw_buffer_store_b64(pack4(v), rc, co, 0, kStream);
             }
         };
         const float it = p.kd_inv_t;
@@ -622,9 +627,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
             for (int ps = 0; ps < 8; ++ps) {
                 const int row = ps * 4 + prow;
                 const float4 t = *(const float4 *)(stg + row * 64 + (pcol ^ stg_swz(row)));
-                const long rowg = m0 + row_base(i) + row;
                 const u32x4 q = aux[i & 1][ps];
-                const unsigned co = cok ? (unsigned)((rowg * p.ldc + colg) * esz) : kOob;
+                const unsigned co = cok ? lane_c + row_bytes(i, ps * 4, p.ldc, esz) : kOob;
                 if constexpr (EPI == EPI_NONE) {
                     float v[4] = {t.x + bv[0], t.y + bv[1], t.z + bv[2], t.w + bv[3]};
                     if (aux_res || aux_c) {
