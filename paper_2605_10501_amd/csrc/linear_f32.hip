@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void norm_linear_f32_kernel(NormLinear p) {
     // this thread's outputs: rows tid / 16 and 16 more, element tid % 16 of both column blocks
     const int q0 = tid >> 4, pc = tid & 15;
     const bool rotate = !SWIGLU && c0 < p.rotated;
-    float2 cs[2] = {{1.f, 0.f}, {1.f, 0.f}};
+    float2 cs[2] = {};
     if (rotate)
 #pragma unroll
         for (int e = 0; e < 2; ++e)
@@ -121,8 +121,9 @@ __global__ __launch_bounds__(256) void norm_linear_f32_kernel(NormLinear p) {
                 p.up[row * p.N + c1 + pc] = hi;
             }
         } else {
-            p.y[row * p.N + c0 + pc] = lo * cs[e].x - hi * cs[e].y;
-            p.y[row * p.N + c1 + pc] = hi * cs[e].x + lo * cs[e].y;
+            // (values are stored as they are: by (1, 0) an infinite one would turn its partner, half a head away, into NaN)
+            p.y[row * p.N + c0 + pc] = rotate ? lo * cs[e].x - hi * cs[e].y : lo;
+            p.y[row * p.N + c1 + pc] = rotate ? hi * cs[e].x + lo * cs[e].y : hi;
         }
     }
     if (tn == 0 && p.h) {

@@ -44,3 +44,22 @@ def test_unaligned_weights_take_the_separate_kernels():
         shifted["layers"][0][k] = buf.copy_(t)
     out = B.section_forward(cfg, shifted, batch, x)
     assert ((out - ref).norm() / ref.norm()).item() < 8 * 64 ** 0.5 * 2 ** -24       # sums of 64 .. in another order
+
+
+def test_an_infinite_value_column_stays_alone():
+    """Values are not rotated: an infinite column of V leaves the column half a head away as it is."""
+    cfg = wl.SectionConfig("decoder", "fp32", 1, 64, 2, 1, 64, 48, 0)
+    w = wl.section_weights(cfg, 5, "s", "cuda")
+    x, batch, n = wl.normal(5, "x", (50, 64), 1.0, 0.0, torch.float32, "cuda"), B.Batch([0, 20, 50]), 50
+    ws = torch.zeros(B.section_workspace_bytes(cfg, n, 30, False), dtype=torch.uint8, device="cuda")
+    qkv = ws[(n * 64 * 4 + 255) // 256 * 256:][:n * cfg.d_qkv * 4].view(torch.float32).view(n, cfg.d_qkv)    # behind the normed rows
+    B.section_forward(cfg, w, batch, x, ws=ws)
+    ref = qkv.clone()
+    for col in (3 * 64 + 5, 3 * 64 + 32 + 20):                     # one in each half of the value head
+        bad = dict(w, layers=[dict(w["layers"][0])])
+        bad["layers"][0]["w_qkv"] = w["layers"][0]["w_qkv"].clone()
+        bad["layers"][0]["w_qkv"][col, 7] = float("inf")
+        B.section_forward(cfg, bad, batch, x, ws=ws)
+        assert not torch.isfinite(qkv[:, col]).any()
+        keep = [c for c in range(cfg.d_qkv) if c != col]
+        assert torch.equal(qkv[:, keep], ref[:, keep])
