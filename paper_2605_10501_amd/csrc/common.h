@@ -77,6 +77,16 @@ template <class T> __device__ __forceinline__ void stv(T *p, const Vec16<T> &r) 
     *(uint4 *)p = *(const uint4 *)&r;
 }
 
+// Derivative of a = silu(g) u: (dL/dg, dL/du) from da.  One function with its roundings spelled out, because which kernel takes it (an
+// epilogue of the down projection's input gradient or a pass of its own) depends on the number of tokens, and a token's
+// gradient must not.
+__device__ __forceinline__ void swiglu_derivative(float da, float g, float u, float *dg, float *du) {
+#pragma clang fp contract(off)
+    const float s = 1.f / (1.f + __expf(-g));
+    *dg = da * u * s * __builtin_fmaf(g, 1.f - s, 1.f);
+    *du = da * g * s;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -414,10 +414,10 @@ __global__ __launch_bounds__(256) void act_bwd_kernel(const T *__restrict__ da, 
         Vec16<T> gv = ldv(base), uv = ldv(base + f), dg, du;
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-            float gg = to_f32(gv.v[e]), uu = to_f32(uv.v[e]), d = to_f32(dav.v[e]);
-            float s = 1.f / (1.f + __expf(-gg));
-            dg.v[e] = from_f32<T>(d * uu * s * (1.f + gg * (1.f - s)));
-            du.v[e] = from_f32<T>(d * gg * s);
+            float dgf, duf;
+            swiglu_derivative(to_f32(dav.v[e]), to_f32(gv.v[e]), to_f32(uv.v[e]), &dgf, &duf);
+            dg.v[e] = from_f32<T>(dgf);
+            du.v[e] = from_f32<T>(duf);
         }
         T *ob = dup + row * 2 * f + (long)cv * V;
         stv(ob, dg);

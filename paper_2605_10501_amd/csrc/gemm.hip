@@ -656,9 +656,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams &p, ACC (&acc)[MI
                     for (int e = 0; e < 4; ++e) {
                         const float gg = (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[e >> 1] >> (16 * (e & 1))));
                         const float uu = (float)__builtin_bit_cast(bf16_t, (unsigned short)(q[2 + (e >> 1)] >> (16 * (e & 1))));
-                        const float sg = 1.f / (1.f + __expf(-gg));
-                        dg[e] = da[e] * uu * sg * (1.f + gg * (1.f - sg));
-                        du[e] = da[e] * gg * sg;
+                        swiglu_derivative(da[e], gg, uu, &dg[e], &du[e]);
                     }
                     store4(dg, co);
                     store4(du, cok ? co + (unsigned)p.sg_f * 2 : kOob);
@@ -1305,11 +1303,11 @@ __device__ __forceinline__ void gemm_f32_body(const GemmF32Params &p, float (&pa
     for (int e = 0; e < 4; ++e) {
         const int q = rr + 8 * e;
         if (p.sw_up) {
-            const float da = (part[0][q][cc] + part[1][q][cc] + part[2][q][cc] + part[3][q][cc]) * p.alpha, gg = res[e], uu = old[e];
-            const float sg = 1.f / (1.f + __expf(-gg));
+            float dg, du;
+            swiglu_derivative((part[0][q][cc] + part[1][q][cc] + part[2][q][cc] + part[3][q][cc]) * p.alpha, res[e], old[e], &dg, &du);
             if (inside(e)) {
-                p.C[(long)(m0 + q) * p.ldc + col] = da * uu * sg * (1.f + gg * (1.f - sg));
-                p.C[(long)(m0 + q) * p.ldc + p.N + col] = da * gg * sg;
+                p.C[(long)(m0 + q) * p.ldc + col] = dg;
+                p.C[(long)(m0 + q) * p.ldc + p.N + col] = du;
             }
             continue;
         }
