@@ -1320,14 +1320,16 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
     __shared__ float part[4][32][33];
     gemm_f32_body<TA, TB, FAST>(p, part, (int)blockIdx.x);
 }
-// Both products of a linear layer's backward pass in one grid (see gemm_bf16_pair_kernel); the first nd workgroups are the
-// input gradient's
-template <bool FAST>
-__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(GemmF32Params pd, GemmF32Params pw, int nd) {
+// Both products of a linear layer's backward pass in one grid (see gemm_bf16_pair_kernel), the one with the longer workgroups, whose K is
+// the token count or the layer's outputs, first.  With the weight gradient always behind, a few long workgroups were
+// left over at large token counts (us, two launches / weight gradient last / this order: 688 x 256 at 4000 tokens 53.8 / 62.1 / 43.7,
+// at 12000 139 / 179 / 114; 512 x 512 at 12000 159 / 203 / 137; over 11 layers x 64 .. 12000 tokens never slower than two).
+template <bool FAST, bool WGRAD_FIRST>
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(GemmF32Params pd, GemmF32Params pw, int first) {
     __shared__ float part[4][32][33];
     const int b = (int)blockIdx.x;
-    if (b < nd) gemm_f32_body<false, true, FAST>(pd, part, b);
-    else gemm_f32_body<true, true, FAST>(pw, part, b - nd);
+    if ((b < first) != WGRAD_FIRST) gemm_f32_body<false, true, FAST>(pd, part, WGRAD_FIRST ? b - first : b);
+    else gemm_f32_body<true, true, FAST>(pw, part, WGRAD_FIRST ? b : b - first);
 }
 
 // Two products with K-contiguous operands in one grid; the first n0 workgroups are the first one's
@@ -1639,8 +1641,15 @@ ms_status launch_pair_f32(int n, int out, int in, const float *dy, long ldy, con
     pd.alpha = pw.alpha = 1.f; pd.accumulate = accumulate; pw.accumulate = 1;
     pd.sw_up = sw_up;
     const bool fast = f32_fast(dy, ldy, false, n, out) && f32_fast(W, in, true, in, out) && f32_fast(dy, ldy, true, out, n) && f32_fast(x, in, true, in, n);
-    if (fast) gemm_f32_pair_kernel<true><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
-    else gemm_f32_pair_kernel<false><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
+    const unsigned grid = (unsigned)(nd + nw);
+#define GO(FAST)                                                                                            \
+    do {                                                                                                    \
+        if (n > out) gemm_f32_pair_kernel<FAST, true><<<grid, 256, 0, s>>>(pd, pw, (int)nw);                \
+        else gemm_f32_pair_kernel<FAST, false><<<grid, 256, 0, s>>>(pd, pw, (int)nd);                       \
+    } while (0)
+    if (fast) GO(true);
+    else GO(false);
+#undef GO
     MS_LAUNCH_CHECK();
     return MS_OK;
 }

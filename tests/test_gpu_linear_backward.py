@@ -41,7 +41,8 @@ def test_bf16(tile, n, out, inn, pad, f32):
     assert ((dx.double() - ref).norm() / ref.norm()).item() < (8 * out ** 0.5 * 2 ** -24 + 2 ** -23 if f32 else 2 ** -8)
 
 
-@pytest.mark.parametrize("n,out,inn", [(1, 4, 4), (293, 688, 128), (33, 31, 65), (64, 32, 32)])    # 31, 65: rows not 16-byte aligned
+# 31, 65: rows not 16-byte aligned; n > out: the weight gradient's workgroups come first
+@pytest.mark.parametrize("n,out,inn", [(1, 4, 4), (293, 688, 128), (33, 31, 65), (64, 32, 32), (65, 64, 40), (4000, 688, 256)])
 def test_fp32(n, out, inn):
     g = torch.Generator(device="cuda").manual_seed(n + out)
     rand = lambda *s: torch.empty(s, device="cuda").normal_(generator=g)
