@@ -1324,15 +1324,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
 // the token count or the layer's outputs, first.  With the weight gradient always behind, a few long workgroups were
 // left over at large token counts (us, two launches / weight gradient last / this order: 688 x 256 at 4000 tokens 53.8 / 62.1 / 43.7,
 // at 12000 139 / 179 / 114; 512 x 512 at 12000 159 / 203 / 137; over 11 layers x 64 .. 12000 tokens never slower than two).
-template <bool FAST, bool WGRAD_FIRST>
+template <bool WGRAD_FIRST>
 __global__ __launch_bounds__(256) void gemm_f32_pair_kernel(GemmF32Params pd, GemmF32Params pw, int first) {
     __shared__ float part[4][32][33];
     const int b = (int)blockIdx.x;
-    if ((b < first) != WGRAD_FIRST) gemm_f32_body<false, true, FAST>(pd, part, WGRAD_FIRST ? b - first : b);
-    else gemm_f32_body<true, true, FAST>(pw, part, WGRAD_FIRST ? b : b - first);
+    if ((b < first) != WGRAD_FIRST) gemm_f32_body<false, true, true>(pd, part, WGRAD_FIRST ? b - first : b);
+    else gemm_f32_body<true, true, true>(pw, part, WGRAD_FIRST ? b : b - first);
 }
 
-// Two products with K-contiguous operands in one grid; the first n0 workgroups are the first one's
+// Two products with K-contiguous operands in one grid; the first n0 workgroups are the first one's.  Both load in the same way: where
+// only one of them can be read 16 bytes at a time, it has a launch of its own (teacher and student logits of 2000 tokens, V = 8192, H = 1024
+// / 512, student states 4 bytes off: head 4.36 ms together, 3.2 apart).
 template <bool FAST>
 __global__ __launch_bounds__(256) void gemm_f32_two_kernel(GemmF32Params p0, GemmF32Params p1, int n0) {
     __shared__ float part[4][32][33];
@@ -1630,7 +1632,10 @@ ms_status launch_pair(Bf16Gemm &d, Bf16Gemm &w, bool *done, hipStream_t s) {
 ms_status launch_pair_f32(int n, int out, int in, const float *dy, long ldy, const float *W, const float *x, float *dx, long ldx, int accumulate,
                           float *dW, const float *sw_up, bool *done, hipStream_t s) {
     const long nd = (long)ms_cdiv(n, 32) * ms_cdiv(in, 32), nw = (long)ms_cdiv(out, 32) * ms_cdiv(in, 32);
-    if (!ms_launch_fits(nd + nw, 256)) return MS_OK;
+    // (dy rows that cannot be read 16 bytes at a time slow dx = dy W down, but not the weight gradient, which keeps its own launch then)
+    if (!ms_launch_fits(nd + nw, 256) || !f32_fast(dy, ldy, false, n, out) || !f32_fast(W, in, true, in, out) || !f32_fast(dy, ldy, true, out, n) ||
+        !f32_fast(x, in, true, in, n))
+        return MS_OK;
     *done = true;
     GemmF32Params pd = {}, pw = {};
     pd.A = pw.A = dy; pd.lda = pw.lda = ldy;
@@ -1640,16 +1645,8 @@ ms_status launch_pair_f32(int n, int out, int in, const float *dy, long ldy, con
     pd.tiles_n = pw.tiles_n = ms_cdiv(in, 32);
     pd.alpha = pw.alpha = 1.f; pd.accumulate = accumulate; pw.accumulate = 1;
     pd.sw_up = sw_up;
-    const bool fast = f32_fast(dy, ldy, false, n, out) && f32_fast(W, in, true, in, out) && f32_fast(dy, ldy, true, out, n) && f32_fast(x, in, true, in, n);
-    const unsigned grid = (unsigned)(nd + nw);
-#define GO(FAST)                                                                                            \
-    do {                                                                                                    \
-        if (n > out) gemm_f32_pair_kernel<FAST, true><<<grid, 256, 0, s>>>(pd, pw, (int)nw);                \
-        else gemm_f32_pair_kernel<FAST, false><<<grid, 256, 0, s>>>(pd, pw, (int)nd);                       \
-    } while (0)
-    if (fast) GO(true);
-    else GO(false);
-#undef GO
+    if (n > out) gemm_f32_pair_kernel<true><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nw);
+    else gemm_f32_pair_kernel<false><<<(unsigned)(nd + nw), 256, 0, s>>>(pd, pw, (int)nd);
     MS_LAUNCH_CHECK();
     return MS_OK;
 }
@@ -1709,7 +1706,8 @@ extern "C" ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32
 ms_status gemm_f32_two(int M, int N, const float *A0, const float *B0, float *C0, int K0, const float *A1, const float *B1, float *C1, int K1,
                        long ldc, hipStream_t s) {
     const long tiles = (long)ms_cdiv(M, 32) * ms_cdiv(N, 32);
-    if (!ms_launch_fits(2 * tiles, 256)) {
+    const bool fast = f32_fast(A0, K0, false, M, K0) && f32_fast(B0, K0, false, N, K0);
+    if (!ms_launch_fits(2 * tiles, 256) || fast != (f32_fast(A1, K1, false, M, K1) && f32_fast(B1, K1, false, N, K1))) {
         MS_TRY(ms_k_gemm(MS_F32, 0, 0, M, N, K0, 1.f, A0, K0, B0, K0, C0, ldc, 1, 0, nullptr, nullptr, 0, 0, 1, s));
         return ms_k_gemm(MS_F32, 0, 0, M, N, K1, 1.f, A1, K1, B1, K1, C1, ldc, 1, 0, nullptr, nullptr, 0, 0, 1, s);
     }
@@ -1717,8 +1715,7 @@ ms_status gemm_f32_two(int M, int N, const float *A0, const float *B0, float *C0
     p0.A = A0; p0.B = B0; p0.C = C0; p0.lda = p0.ldb = p0.K = K0;
     p1.A = A1; p1.B = B1; p1.C = C1; p1.lda = p1.ldb = p1.K = K1;
     p0.ldc = p1.ldc = ldc; p0.M = p1.M = M; p0.N = p1.N = N; p0.tiles_n = p1.tiles_n = ms_cdiv(N, 32); p0.alpha = p1.alpha = 1.f;
-    if (f32_fast(A0, K0, false, M, K0) && f32_fast(B0, K0, false, N, K0) && f32_fast(A1, K1, false, M, K1) && f32_fast(B1, K1, false, N, K1))
-        gemm_f32_two_kernel<true><<<(unsigned)(2 * tiles), 256, 0, s>>>(p0, p1, (int)tiles);
+    if (fast) gemm_f32_two_kernel<true><<<(unsigned)(2 * tiles), 256, 0, s>>>(p0, p1, (int)tiles);
     else gemm_f32_two_kernel<false><<<(unsigned)(2 * tiles), 256, 0, s>>>(p0, p1, (int)tiles);
     MS_LAUNCH_CHECK();
     return MS_OK;
