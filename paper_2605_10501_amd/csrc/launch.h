@@ -40,7 +40,7 @@ ms_status gemm_f32_two(int M, int N, const float *A0, const float *B0, float *C0
                        long ldc, hipStream_t s);
 
 // Column reductions of a backward pass that nobody waits for (norm gains and shifts, biases): the kernels that produce their
-// partial rows run when the data is there, one launch adds up what has gathered (elementwise.hip).  scratch holds the
+// partial rows run when the data is there, one launch adds up what has gathered (column_work.cpp).  scratch holds the
 // partial rows of everything pending; what does not fit, or adds to a row that is already pending, is preceded by a
 // column_work_finish.
 struct ColReduce { const float *part; float *out; int np, c; };        // out[c] += sum of np partial rows
@@ -56,6 +56,22 @@ ms_status norm_backward_pending(int kind, int dtype, int x_fp32, int n, int d, c
                                 const float *rstd, const void *add, void *dx, float *dg, float *db, ColumnWork *w, hipStream_t s);
 ms_status column_sums_pending(int dtype, int n, const ColSum *sums, int count, ColumnWork *w, hipStream_t s);
 ms_status column_work_finish(ColumnWork *w, hipStream_t s);
+// Their launches (elementwise.hip).  The norm backward writes one partial row for each of its `grid` workgroups (pg, pb), a column sum
+// `rows` of them for each of up to four matrices of n rows (`blocks` blocks of columns in all).
+struct ReduceJobs {
+    int count, first[ColumnWork::kJobs + 1];      // first block of each job
+    ColReduce job[ColumnWork::kJobs];
+};
+struct ColSums {
+    int count, first[5];                          // first column block (64 vectors) of each matrix
+    const void *x[4];
+    float *part[4];
+    int c[4];
+};
+ms_status launch_reduce_partials(const ReduceJobs &jobs, int blocks, hipStream_t s);
+ms_status launch_norm_backward(int kind, int dtype, int x_fp32, int n, int d, const void *dy, const void *x, const void *g, const float *mean,
+                               const float *rstd, const void *add, void *dx, float *pg, float *pb, int grid, hipStream_t s);
+ms_status launch_column_sums(int dtype, const ColSums &m, int n, int blocks, int rows, hipStream_t s);
 
 // KD-loss pieces (kd.hip)
 ms_status kd_forward_backward(const ms_kd_config *kd, int n_tokens, const void *h_teacher, const void *h_student,

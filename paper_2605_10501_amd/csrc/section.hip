@@ -14,47 +14,6 @@
 #include "common.h"
 #include "launch.h"
 
-// The executor also builds for the host alone (sanitizer runs, where stand-ins take the place of the kernels).  There these
-// definitions do each piece of work by itself, through the kernel-level entry points; in the library they give way to those in
-// gemm.hip and elementwise.hip.
-extern "C" __attribute__((weak)) ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy,
-                                                                const void *W, const void *x, void *dx, int32_t dx_fp32,
-                                                                int32_t dx_accumulate, void *dW, void *stream) {
-    MS_TRY(ms_k_gemm(dtype, 0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, 1, stream));
-    return ms_k_gemm(dtype, 1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, 0, stream);
-}
-extern "C" __attribute__((weak)) ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t f, const void *dy, const void *W,
-                                                                       const void *act, const void *gate_up, void *da, void *d_gate_up,
-                                                                       void *dW, void *stream) {
-    MS_TRY(ms_k_linear_backward(dtype, n, out, f, dy, out, W, act, da, 0, 0, dW, stream));
-    return ms_k_act_backward(0, dtype, n, f, da, gate_up, d_gate_up, stream);
-}
-__attribute__((weak)) ms_status norm_backward_pending(int kind, int dtype, int x_fp32, int n, int d, const void *dy, const void *x, const void *g,
-                                                      const float *mean, const float *rstd, const void *add, void *dx, float *dg,
-                                                      float *db, ColumnWork *w, hipStream_t s) {
-    return ms_k_norm_backward(kind, dtype, x_fp32, n, d, dy, x, g, mean, rstd, add, dx, dg, db, w->scratch, s);
-}
-__attribute__((weak)) ms_status column_sums_pending(int dtype, int n, const ColSum *sums, int count, ColumnWork *w, hipStream_t s) {
-    for (int k = 0; k < count; ++k) MS_TRY(ms_k_colsum(dtype, n, sums[k].c, sums[k].x, sums[k].out, w->scratch, s));
-    return MS_OK;
-}
-__attribute__((weak)) ms_status column_work_finish(ColumnWork *, hipStream_t) { return MS_OK; }
-__attribute__((weak)) ms_status launch_rope_setup(int n, int n_seqs, const int32_t *cu, int32_t *pos, int max_pos, int hd, float base, float *table,
-                                                  hipStream_t s) {
-    MS_TRY(ms_k_positions(n, n_seqs, cu, pos, s));
-    return ms_k_rope_table(max_pos, hd, base, table, s);
-}
-__attribute__((weak)) ms_status norm_qkv_rope_f32(int, int, int, int, int, float, const float *, const float *, const float *, const int *,
-                                                  const float *, float *, float *, float *, bool *done, hipStream_t) {
-    *done = false;
-    return MS_OK;
-}
-__attribute__((weak)) ms_status norm_swiglu_f32(int, int, int, float, const float *, const float *, const float *, float *, float *, float *,
-                                                float *, bool *done, hipStream_t) {
-    *done = false;
-    return MS_OK;
-}
-
 namespace {
 
 struct LayerBuf {

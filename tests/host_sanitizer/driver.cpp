@@ -1,5 +1,6 @@
 // Host-only exercise of the C ABI under AddressSanitizer / UndefinedBehaviorSanitizer: the packing step, the
-// wavefront scheduler, every argument / shape / workspace error path that is reported before a launch, and the
+// wavefront scheduler, every argument / shape / workspace error path that is reported before a launch, the column
+// reductions' use of their scratch, and the
 // section executor's plan and sequencing with the kernels replaced by the stand-ins of fake_backend.cpp.  Every
 // buffer is allocated at exactly its documented size, so any out-of-bounds carve-out or mis-sized argument is a
 // sanitizer report (the process then exits non-zero).
@@ -14,10 +15,11 @@
 #include <string>
 #include <vector>
 
-#include "maestro_kernels.h"
-#include "maestro_section.h"
+#include "launch.h"
 
 extern std::map<std::string, long> g_calls;
+struct PartialRows { const float *p; int np, c; };
+extern std::vector<PartialRows> g_pending;
 static int g_checks = 0;
 constexpr int kKdStatFloats = 8;   // per-token statistics the KD step keeps (documented workspace layout)
 #define CHECK(cond)                                                                              \
@@ -144,6 +146,7 @@ static void run_section(const SectionCase &sc, bool with_kd) {
                                           d_x.p, ws.p, ws.n, nullptr) == MS_OK);
         // per layer 4 forward linears, 4 input-gradient and 4 weight-gradient products
         CHECK(g_calls["gemm"] + g_calls["gemm_swiglu"] - gemms == 12L * c.n_layers);
+        CHECK(g_pending.empty());                           // every partial row of a column reduction was added up
         CHECK(ms_section_forward_backward(&c, &w, &g, &b, x_in.p, h_out.p, d_h.p, nullptr, nullptr, nullptr, nullptr, nullptr,
                                           d_x.p, ws.p, ws.n - 1, nullptr) == MS_ERR_WORKSPACE);
         CHECK(ms_section_forward_backward(&c, &w, &g, &b, x_in.p, h_out.p, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -187,6 +190,7 @@ static void test_sections() {
     run_section({dec_f32, {0, 3, 11}}, true);
     run_section({enc_bf16, {0, 9, 40}}, false);
     CHECK(g_calls["gemm_swiglu"] > 0 && g_calls["act_forward"] > 0 && g_calls["colsum"] > 0 && g_calls["kd"] == 3);
+    CHECK(g_calls["norm_linear_f32"] > 0 && g_calls["rope_setup"] > 0);
 
     // ---- configuration and batch errors, all before any launch (the pointers below are never dereferenced)
     ms_layer_ptrs lp = {};
@@ -256,10 +260,64 @@ static void test_kd() {
           (size_t)64 * 49 * (kKdStatFloats * 4 + 128 * 4));                      // only statistics and the dHs accumulator grow
 }
 
+// Column reductions by themselves, on a scratch of exactly its size: whatever is asked for in whatever order, partial rows stay inside
+// the scratch, none is written over before it is added up, and every output gets each of its contributions once.
+static void test_column_work(std::mt19937 &rng) {
+    for (int trial = 0; trial < 300; ++trial) {
+        const int dtype = rng() % 2 ? MS_BF16 : MS_F32, kind = rng() % 2, widest = 8 * (1 + rng() % 40), n = 1 + rng() % (trial % 20 ? 300 : 20000);
+        const size_t es = dtype == MS_BF16 ? 2 : 4;
+        Buf scratch(ms_k_norm_backward_scratch_bytes(widest));
+        ColumnWork w = {(char *)scratch.p, scratch.n, 0, 0, {}};
+        std::vector<std::vector<float>> out;                                         // some are asked for more than once
+        std::vector<int> want;
+        auto output = [&](int c) {
+            for (size_t i = 0; i < out.size(); ++i)
+                if ((int)out[i].size() == c && rng() % 3 == 0) { ++want[i]; return (int)i; }
+            out.emplace_back(c, 0.f);
+            want.push_back(1);
+            return (int)out.size() - 1;
+        };
+        out.reserve(64);
+        for (int step = 0; step < 6; ++step) {
+            if (rng() % 2) {
+                const int d = 8 * (1 + rng() % (widest / 8));
+                Buf x((size_t)n * d * es), gain(d * es), stat((size_t)n * 4);
+                const int g = output(d);
+                const int b = kind ? (int)out.size() : g;                            // the shift's output is never the gain's
+                if (kind) { out.emplace_back(d, 0.f); want.push_back(1); }
+                CHECK(norm_backward_pending(kind, dtype, 0, n, d, x.p, x.p, gain.p, (float *)stat.p, (float *)stat.p, nullptr, x.p, out[g].data(),
+                                            kind ? out[b].data() : nullptr, &w, nullptr) == MS_OK);
+            } else {
+                const int count = 1 + rng() % 4;
+                std::vector<std::unique_ptr<Buf>> x;
+                ColSum sums[4];
+                for (int k = 0; k < count; ++k) {
+                    const int c = 8 * (1 + rng() % (widest / 8));
+                    x.emplace_back(new Buf((size_t)n * c * es));
+                    sums[k] = {x[k]->p, out[output(c)].data(), c};
+                }
+                CHECK(column_sums_pending(dtype, n, sums, count, &w, nullptr) == MS_OK);
+            }
+            if (rng() % 8 == 0) CHECK(column_work_finish(&w, nullptr) == MS_OK && g_pending.empty());
+        }
+        CHECK(column_work_finish(&w, nullptr) == MS_OK && g_pending.empty());
+        for (size_t i = 0; i < out.size(); ++i)
+            for (float v : out[i]) CHECK(v == (float)want[i]);
+        const long launches = g_calls["reduce_partials"];
+        CHECK(column_work_finish(&w, nullptr) == MS_OK && g_calls["reduce_partials"] == launches);       // nothing left to add up
+    }
+    // a scratch that cannot hold one call's rows is an error, not a write past its end
+    Buf x(64 * 64 * 4), small(255), out(64 * 4);
+    ColumnWork w = {(char *)small.p, small.n, 0, 0, {}};
+    const ColSum one = {x.p, (float *)out.p, 64};
+    CHECK(column_sums_pending(MS_F32, 64, &one, 1, &w, nullptr) == MS_ERR_WORKSPACE);
+}
+
 int main() {
     std::mt19937 rng(12345);
     test_pack(rng);
     test_schedule(rng);
+    test_column_work(rng);
     test_sections();
     test_kd();
     printf("host sanitizer driver: OK (%d checks)\n", g_checks);

@@ -4,20 +4,20 @@
 // its buffers over the full extent the real kernel reads or writes (host memory here): inputs are read byte by byte,
 // outputs are filled.  With every buffer allocated at exactly its documented size, AddressSanitizer then reports any
 // call whose pointers or sizes do not fit -- an arena carve-out beyond ms_*_workspace_bytes, a mis-sized temporary, a
-// wrong leading dimension.  Nothing here computes anything.
+// wrong leading dimension.  Nothing here computes anything, except that the stand-ins of the column reductions keep account of their
+// partial rows: a launch must not write over rows that nobody has added up yet, and an addition must find the rows that it
+// expects.  Each contribution is one row of ones above rows of zeros, so an output grows by exactly one for each.
 #include <stdint.h>
 #include <string.h>
 
 #include <map>
 #include <string>
 
-#include "maestro_kernels.h"
-#include "maestro_section.h"
+#include <stdio.h>
+#include <stdlib.h>
+#include <vector>
 
-struct ihipStream_t;
-typedef ihipStream_t *hipStream_t;
-ms_status ms_fail(ms_status code, const char *fmt, ...);
-struct KdPlanView { float *zt, *zs, *stats, *dhs; void *dz; size_t bytes; int tb; bool keep; };
+#include "launch.h"
 
 std::map<std::string, long> g_calls;          // how often each stand-in ran (read by the driver)
 volatile unsigned g_sink;
@@ -38,8 +38,6 @@ static size_t mat(long rows, long cols, long ld, size_t es) { return rows > 0 ? 
 
 extern "C" {
 
-size_t ms_k_norm_backward_scratch_bytes(int32_t d) { return d > 0 ? 2 * up256((size_t)1024 * d * 4) : 0; }
-
 ms_status ms_k_norm_forward(int32_t kind, int32_t dtype, int32_t x_fp32, int32_t n, int32_t d, float, const void *x, const void *g,
                             const void *b, void *y, float *mean, float *rstd, void *) {
     ++g_calls["norm_forward"];
@@ -47,19 +45,6 @@ ms_status ms_k_norm_forward(int32_t kind, int32_t dtype, int32_t x_fp32, int32_t
     rd(x, (size_t)n * d * (x_fp32 ? 4 : es)); rd(g, d * es);
     if (kind == 1) { rd(b, d * es); wr(mean, (size_t)n * 4); }
     wr(y, (size_t)n * d * es); wr(rstd, (size_t)n * 4);
-    return MS_OK;
-}
-
-ms_status ms_k_norm_backward(int32_t kind, int32_t dtype, int32_t x_fp32, int32_t n, int32_t d, const void *dy, const void *x,
-                             const void *g, const float *mean, const float *rstd, const void *add, void *dx, float *dg, float *db,
-                             void *scratch, void *) {
-    ++g_calls["norm_backward"];
-    const size_t es = es_of(dtype);
-    rd(dy, (size_t)n * d * es); rd(x, (size_t)n * d * (x_fp32 ? 4 : es)); rd(g, d * es); rd(rstd, (size_t)n * 4);
-    rd(add, (size_t)n * d * es);
-    if (kind == 1) { rd(mean, (size_t)n * 4); rd(db, (size_t)d * 4); wr(db, (size_t)d * 4); }
-    wr(scratch, ms_k_norm_backward_scratch_bytes(d));
-    wr(dx, (size_t)n * d * es); rd(dg, (size_t)d * 4); wr(dg, (size_t)d * 4);
     return MS_OK;
 }
 
@@ -78,15 +63,18 @@ ms_status ms_k_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N,
     return MS_OK;
 }
 
-ms_status ms_k_positions(int32_t n, int32_t n_seqs, const int32_t *cu, int32_t *pos, void *) {
-    ++g_calls["positions"];
-    rd(cu, (size_t)(n_seqs + 1) * 4); wr(pos, (size_t)n * 4);
-    return MS_OK;
+// both products of a linear layer's backward pass, then the same with the SwiGLU derivative taken in the first one
+ms_status ms_k_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t in, const void *dy, int64_t ldy, const void *W,
+                               const void *x, void *dx, int32_t dx_fp32, int32_t dx_accumulate, void *dW, void *stream) {
+    ms_k_gemm(dtype, 0, 1, n, in, out, 1.f, dy, ldy, W, in, dx, in, dx_fp32, dx_accumulate, nullptr, nullptr, 0, 0, 1, stream);
+    return ms_k_gemm(dtype, 1, 1, out, in, n, 1.f, dy, ldy, x, in, dW, in, 1, 1, nullptr, nullptr, 0, 0, 0, stream);
 }
 
-ms_status ms_k_rope_table(int32_t max_pos, int32_t hd, float, float *table, void *) {
-    ++g_calls["rope_table"];
-    wr(table, (size_t)max_pos * hd * 4);
+ms_status ms_k_swiglu_linear_backward(int32_t dtype, int32_t n, int32_t out, int32_t f, const void *dy, const void *W, const void *act,
+                                      const void *gate_up, void *da, void *d_gate_up, void *dW, void *stream) {
+    const size_t w = (size_t)n * 2 * f * es_of(dtype);
+    ms_k_linear_backward(dtype, n, out, f, dy, out, W, act, da, 0, 0, dW, stream);      // (da: where the derivative is a pass of its own)
+    rd(gate_up, w); wr(d_gate_up, w);
     return MS_OK;
 }
 
@@ -126,14 +114,8 @@ ms_status ms_k_embedding_backward(int32_t dtype, int32_t n, int32_t d, int32_t v
     return MS_OK;
 }
 
-ms_status ms_k_colsum(int32_t dtype, int32_t n, int32_t c, const void *x, float *out, void *scratch, void *) {
-    ++g_calls["colsum"];
-    rd(x, (size_t)n * c * es_of(dtype)); rd(out, (size_t)c * 4); wr(out, (size_t)c * 4); wr(scratch, ms_k_norm_backward_scratch_bytes(c));
-    return MS_OK;
-}
-
 size_t ms_k_attention_backward_scratch_bytes(int32_t, int32_t nq, int32_t nkv, int32_t hd, int32_t n) {
-    return up256((size_t)nq * n * 4) + up256((size_t)n * 2 * nkv * hd * 4);
+    return up256((size_t)nq * n * 8) + up256((size_t)n * 2 * nkv * hd * 4);
 }
 
 ms_status ms_k_attention_forward(int32_t dtype, int32_t, int32_t nq, int32_t nkv, int32_t hd, int32_t n, int32_t n_seqs, int32_t,
@@ -171,6 +153,87 @@ ms_status gemm_swiglu(int M, int F, int K, const void *A, long lda, const void *
     return MS_OK;
 }
 
+ms_status launch_rope_setup(int n, int n_seqs, const int32_t *cu, int32_t *pos, int max_pos, int hd, float, float *table, hipStream_t) {
+    ++g_calls["rope_setup"];
+    rd(cu, (size_t)(n_seqs + 1) * 4); wr(pos, (size_t)n * 4); wr(table, (size_t)max_pos * hd * 4);
+    return MS_OK;
+}
+
+// fp32 decoder layers: both launches, for every second call (the executor's separate kernels run for the others)
+static bool every_second() { static int k; return ++k % 2; }
+static void norm_linear(int n, int d, int out, const float *x, const float *g, const float *W, float *h, float *rstd) {
+    ++g_calls["gemm"]; ++g_calls["norm_linear_f32"];
+    rd(x, (size_t)n * d * 4); rd(g, d * 4); rd(W, (size_t)out * d * 4);
+    if (h) { wr(h, (size_t)n * d * 4); wr(rstd, (size_t)n * 4); }
+}
+ms_status norm_qkv_rope_f32(int n, int d, int heads, int, int hd, float, const float *x, const float *g, const float *W, const int *pos,
+                            const float *table, float *qkv, float *h, float *rstd, bool *done, hipStream_t) {
+    if (!(*done = every_second())) return MS_OK;
+    norm_linear(n, d, heads * hd, x, g, W, h, rstd);
+    rd(pos, (size_t)n * 4); rd(table, (size_t)hd * 4); wr(qkv, (size_t)n * heads * hd * 4);
+    return MS_OK;
+}
+ms_status norm_swiglu_f32(int n, int d, int f, float, const float *x, const float *g, const float *W, float *act, float *up, float *h,
+                          float *rstd, bool *done, hipStream_t) {
+    if (!(*done = every_second())) return MS_OK;
+    norm_linear(n, d, 2 * f, x, g, W, h, rstd);
+    wr(act, (size_t)n * f * 4); wr(up, (size_t)n * 2 * f * 4);
+    return MS_OK;
+}
+
+// ---- column reductions
+struct PartialRows { const float *p; int np, c; };
+std::vector<PartialRows> g_pending;            // written and not yet added up (the driver looks that none is left)
+static void fault(const char *what) { fprintf(stderr, "FAILED column reduction: %s\n", what); exit(1); }
+static void partial_rows(float *p, int np, int c) {
+    for (const PartialRows &q : g_pending)
+        if (q.p < p + (size_t)np * c && p < q.p + (size_t)q.np * q.c) fault("partial rows written over others that are pending");
+    for (size_t i = 0; i < (size_t)np * c; ++i) p[i] = i < (size_t)c ? 1.f : 0.f;
+    g_pending.push_back({p, np, c});
+}
+
+ms_status launch_norm_backward(int kind, int dtype, int x_fp32, int n, int d, const void *dy, const void *x, const void *g, const float *mean,
+                               const float *rstd, const void *add, void *dx, float *pg, float *pb, int grid, hipStream_t) {
+    ++g_calls["norm_backward"];
+    const size_t es = es_of(dtype);
+    rd(dy, (size_t)n * d * es); rd(x, (size_t)n * d * (x_fp32 ? 4 : es)); rd(g, d * es); rd(rstd, (size_t)n * 4);
+    rd(add, (size_t)n * d * es);
+    if (kind == 1) rd(mean, (size_t)n * 4);
+    wr(dx, (size_t)n * d * es);
+    partial_rows(pg, grid, d);
+    if (kind == 1) partial_rows(pb, grid, d);
+    return MS_OK;
+}
+
+ms_status launch_column_sums(int dtype, const ColSums &m, int n, int, int rows, hipStream_t) {
+    for (int k = 0; k < m.count; ++k) {
+        ++g_calls["colsum"];
+        rd(m.x[k], (size_t)n * m.c[k] * es_of(dtype));
+        partial_rows(m.part[k], rows, m.c[k]);
+    }
+    return MS_OK;
+}
+
+ms_status launch_reduce_partials(const ReduceJobs &jobs, int blocks, hipStream_t) {
+    ++g_calls["reduce_partials"];
+    int at = 0;
+    for (int k = 0; k < jobs.count; ++k) {
+        const ColReduce &j = jobs.job[k];
+        if (jobs.first[k] != at) fault("first block of a job");
+        at += (j.c + 31) / 32;
+        size_t i = 0;
+        while (i < g_pending.size() && (g_pending[i].p != j.part || g_pending[i].np != j.np || g_pending[i].c != j.c)) ++i;
+        if (i == g_pending.size()) fault("a job without its partial rows");
+        g_pending.erase(g_pending.begin() + i);
+        for (int q = 0; q < k; ++q)
+            if (jobs.job[q].out < j.out + j.c && j.out < jobs.job[q].out + jobs.job[q].c) fault("two jobs of one launch add to the same output");
+        for (int p = 0; p < j.np; ++p)
+            for (int c = 0; c < j.c; ++c) j.out[c] += j.part[(size_t)p * j.c + c];
+    }
+    if (at != blocks) fault("number of blocks");
+    return MS_OK;
+}
+
 ms_status launch_fill_f32(float *p, long n, float, hipStream_t) { ++g_calls["fill"]; wr(p, (size_t)n * 4); return MS_OK; }
 ms_status launch_convert_bf16_to_f32(const void *src, float *dst, long n, hipStream_t) {
     ++g_calls["convert"];
@@ -178,7 +241,6 @@ ms_status launch_convert_bf16_to_f32(const void *src, float *dst, long n, hipStr
     return MS_OK;
 }
 
-ms_status validate_kd(const ms_kd_config *kd, int n_tokens);
 ms_status kd_forward_backward(const ms_kd_config *kd, int n, const void *h_t, const void *h_s, float *loss, float *kl, void *d_h_s,
                               void *d_w_s, void *ws, size_t ws_bytes, hipStream_t) {
     ++g_calls["kd"];
