@@ -69,6 +69,8 @@ def test_swiglu_derivative_in_the_epilogue(tile, n, out, f):
         _run(dy, W, act, da, False, dW1)
     finally:
         B.k_gemm_config(0, -1)
+    if tile:                                                        # a pass of its own, and da stored, only where the products stay apart
+        assert torch.isnan(one["da"]).all() if out % 64 == 0 else torch.equal(one["da"], da)
     two = torch.empty(n, 2 * f, device="cuda", dtype=torch.bfloat16)
     B._check(B.lib().ms_k_act_backward(0, 1, n, f, B._p(da), B._p(up), B._p(two), B._stream()))
     assert torch.equal(one["dup"], two)                             # the same roundings of the same da
