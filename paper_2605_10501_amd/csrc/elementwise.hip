@@ -742,26 +742,24 @@ ms_status launch_convert_from_f32(int dtype, const float *src, void *dst, long n
 // ------------------------------------------------------------------ AdamW (the student's parameter update)
 // Five streams (four in, three or four out, all fp32, plus the weights): HBM-bound.  A state that cannot stay in the caches
 // from one step to the next (ms_adamw_streams) is accessed non-temporally, two groups of 4 elements per thread in flight
-// (eight 16-byte loads before the first use) and 512 threads (110.6 M parameters, alone in turn: 625 us with 256 threads, 615; 1024
-// threads with one group 645, a contiguous chunk per workgroup 674-703); a smaller one by the default policy, one group per thread.  The weights are
+// (eight 16-byte loads before the first use); a smaller one by the default policy, one group per thread.  The weights are
 // what the next forward pass reads and keep the default policy.
 namespace {
 template <class T, int U, bool STREAM>
-__global__ __launch_bounds__(STREAM ? 512 : 256) void adamw_kernel(long n4, float *__restrict__ grad, float *__restrict__ master,
+__global__ __launch_bounds__(256) void adamw_kernel(long n4, float *__restrict__ grad, float *__restrict__ master,
                                                      float *__restrict__ m, float *__restrict__ v, T *__restrict__ w,
                                                      float lr, float b1, float b2, float eps, float decay, float gscale,
                                                      float inv_c1, float inv_c2, int zero_grad) {
-    constexpr int NT = STREAM ? 512 : 256;
     f32x4 g[U], ww[U], mm[U], vv[U];
     auto get = [](const float *p, long i) { return STREAM ? __builtin_nontemporal_load((const f32x4 *)p + i) : ((const f32x4 *)p)[i]; };
     auto put = [](const f32x4 &x, float *p, long i) {
         if constexpr (STREAM) __builtin_nontemporal_store(x, (f32x4 *)p + i);
         else ((f32x4 *)p)[i] = x;
     };
-    const long i0 = (long)blockIdx.x * (NT * U) + threadIdx.x;
+    const long i0 = (long)blockIdx.x * (256 * U) + threadIdx.x;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const long i = i0 + u * NT;
+        const long i = i0 + u * 256;
         if (i >= n4) break;
         g[u] = get(grad, i);
         ww[u] = get(master, i);
@@ -770,7 +768,7 @@ __global__ __launch_bounds__(STREAM ? 512 : 256) void adamw_kernel(long n4, floa
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const long i = i0 + u * NT;
+        const long i = i0 + u * 256;
         if (i >= n4) return;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -814,11 +812,11 @@ extern "C" ms_status ms_adamw_step(const ms_adamw_config *cfg, int32_t dtype, in
     const float decay = 1.f - cfg->lr * cfg->weight_decay;
     const long n4 = n / 4;
     const bool stream_state = ms_adamw_streams(n);
-    const unsigned grid = (unsigned)((n4 + (stream_state ? 1023 : 255)) / (stream_state ? 1024 : 256));
+    const unsigned grid = (unsigned)((n4 + (stream_state ? 511 : 255)) / (stream_state ? 512 : 256));
     hipStream_t s = (hipStream_t)stream;
     ProfScope ps(11, (double)n * (4 * 7 + (weight ? (dtype == MS_BF16 ? 2 : 4) : 0) + (cfg->zero_grad ? 4 : 0)), s);
 #define GO(T, U, STREAM)                                                                                                      \
-    adamw_kernel<T, U, STREAM><<<grid, STREAM ? 512 : 256, 0, s>>>(n4, grad, master, m, v, (T *)weight, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, \
+    adamw_kernel<T, U, STREAM><<<grid, 256, 0, s>>>(n4, grad, master, m, v, (T *)weight, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, \
                                                     decay, cfg->grad_scale, inv_c1, inv_c2, cfg->zero_grad)
     if (dtype == MS_BF16) { if (stream_state) GO(bf16_t, 2, true); else GO(bf16_t, 1, false); }
     else { if (stream_state) GO(float, 2, true); else GO(float, 1, false); }
