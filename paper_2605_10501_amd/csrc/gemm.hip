@@ -1161,28 +1161,31 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // A chunk's student logits with a KD epilogue (ps, EPI) and another chunk's teacher logits (pt) in one grid.  The student's
 // epilogue reads the stored teacher logits, 256 KB per 256 x 256 tile; in a launch of its own all CUs come to it together
-// and wait for HBM with idle matrix cores.  Here the two kinds of tiles take turns, a round of the chip each (kTwoRun): their
+// and wait for HBM with idle matrix cores.  Here the two kinds of tiles take turns, a round of the chip each (`run`; the last rounds
+// of both together), the kind with the longer workgroups first (`first`, 1: student): their
 // times differ, so that one kind's epilogues come to run beside the other's main loops, and one last round is left instead of
-// two (see ms_choose_two for what it gains).
+// two (see ms_choose_two for what it gains).  The order is the one that ms_choose_two reckons with.  With runs of 256 also where a round is
+// 512 workgroups, part of the longer ones waited for the shorter (64 x 128 tiles, 300 tokens, H = 4096 / 1536, chunks of 8192, loss
+// only, V = 49152: 416 us, two launches 339).  In runs of 8 or 64 the two products' operand panels compete for the L2s from the start
+// (256 x 256 tiles, 8192 tokens, V = 151936: 33.6 .. 34.0 ms; apart 32.98, in runs of 256 32.75).
 struct TwoSlot { int student, index; };
-__device__ __forceinline__ TwoSlot two_slot(int b, int nt, int ns) {
-    constexpr int run = kTwoRun;
+__device__ __forceinline__ TwoSlot two_slot(int b, int nt, int ns, int run, int first) {
     const int both = (nt < ns ? nt : ns) / run * run;
-    if (b < 2 * both) return {(b / run) & 1, b / (2 * run) * run + b % run};
-    const int r = b - 2 * both;
-    return r < nt - both ? TwoSlot{0, both + r} : TwoSlot{1, both + r - (nt - both)};
+    if (b < 2 * both) return {((b / run) & 1) ^ first, b / (2 * run) * run + b % run};
+    const int r = b - 2 * both, more = (first ? ns : nt) - both;
+    return r < more ? TwoSlot{first, both + r} : TwoSlot{first ^ 1, both + r - more};
 }
 template <int EPI>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_pp_two_kernel(GemmParams pt, GemmParams ps, int nt, int ns) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_pp_two_kernel(GemmParams pt, GemmParams ps, int nt, int ns, int run, int first) {
     MS_PP_LDS;
-    const TwoSlot t = two_slot(blockIdx.x, nt, ns);
+    const TwoSlot t = two_slot(blockIdx.x, nt, ns, run, first);
     if (t.student) gemm_pp_body<EPI>(ps, lds, t.index, ns, 0);
     else gemm_pp_body<EPI_NONE>(pt, lds, t.index, nt, 0);
 }
 template <int BM, int BN, int WM, int WN, int NST, int EPI>
-__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI, NST)))) void gemm_bf16_two_kernel(GemmParams pt, GemmParams ps, int nt, int ns) {
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(fast_waves_per_simd(BM, WM * WN, EPI, NST)))) void gemm_bf16_two_kernel(GemmParams pt, GemmParams ps, int nt, int ns, int run, int first) {
     MS_FAST_LDS(BM, BN, NST);
-    const TwoSlot t = two_slot(blockIdx.x, nt, ns);
+    const TwoSlot t = two_slot(blockIdx.x, nt, ns, run, first);
     if (t.student) gemm_fast_body<BM, BN, WM, WN, false, false, EPI, true, NST>(ps, lds, t.index, ns, 0);
     else gemm_fast_body<BM, BN, WM, WN, false, false, EPI_NONE, true, NST>(pt, lds, t.index, nt, 0);
 }
@@ -1367,12 +1370,12 @@ template __global__ void gemm_bf16_pp_kernel<EPI_KD_STATS>(GemmParams);
 MS_INST_RINGS(128, 128, 4, 2, 4); MS_INST_RINGS(128, 256, 2, 4, 3); MS_INST_RINGS(64, 128, 2, 2, 3); MS_INST_RINGS(64, 64, 2, 1, 4);
 #undef MS_INST_RINGS
 #define MS_INST_TWO(EPI)                                                                                              \
-    template __global__ void gemm_bf16_pp_two_kernel<EPI>(GemmParams, GemmParams, int, int);                          \
-    template __global__ void gemm_bf16_two_kernel<128, 128, 2, 2, 2, EPI>(GemmParams, GemmParams, int, int);          \
-    template __global__ void gemm_bf16_two_kernel<128, 128, 4, 2, 4, EPI>(GemmParams, GemmParams, int, int);          \
-    template __global__ void gemm_bf16_two_kernel<128, 256, 2, 4, 3, EPI>(GemmParams, GemmParams, int, int);          \
-    template __global__ void gemm_bf16_two_kernel<64, 128, 2, 2, 3, EPI>(GemmParams, GemmParams, int, int);           \
-    template __global__ void gemm_bf16_two_kernel<64, 64, 2, 1, 4, EPI>(GemmParams, GemmParams, int, int)
+    template __global__ void gemm_bf16_pp_two_kernel<EPI>(GemmParams, GemmParams, int, int, int, int);                          \
+    template __global__ void gemm_bf16_two_kernel<128, 128, 2, 2, 2, EPI>(GemmParams, GemmParams, int, int, int, int);          \
+    template __global__ void gemm_bf16_two_kernel<128, 128, 4, 2, 4, EPI>(GemmParams, GemmParams, int, int, int, int);          \
+    template __global__ void gemm_bf16_two_kernel<128, 256, 2, 4, 3, EPI>(GemmParams, GemmParams, int, int, int, int);          \
+    template __global__ void gemm_bf16_two_kernel<64, 128, 2, 2, 3, EPI>(GemmParams, GemmParams, int, int, int, int);           \
+    template __global__ void gemm_bf16_two_kernel<64, 64, 2, 1, 4, EPI>(GemmParams, GemmParams, int, int, int, int)
 MS_INST_TWO(EPI_KD_DZ); MS_INST_TWO(EPI_KD_STATS);
 #undef MS_INST_TWO
 #define MS_INST_PAIR(BM, BN, WM, WN, NST)                                                                                    \
@@ -1761,17 +1764,17 @@ ms_status gemm_kd_epilogue(int mode, int M, int N, int K, const void *A, long ld
     return launch_bf16_fast<EPI_KD_STATS>(p, tile, 0, 0, 1, 2.0 * M * N * K, s);
 }
 
-template <int EPI> static void launch_two(int tile, GemmParams &pt, GemmParams &ps, hipStream_t s) {
+template <int EPI> static void launch_two(int tile, int first, GemmParams &pt, GemmParams &ps, hipStream_t s) {
     const MsTile &t = kTiles[tile];
     pt.tiles_m = ps.tiles_m = ms_cdiv(ps.M, t.bm);
     pt.tiles_n = ms_cdiv(pt.N, t.bn);
     ps.tiles_n = ms_cdiv(ps.N, t.bn);
-    const int nt = pt.tiles_m * pt.tiles_n, ns = ps.tiles_m * ps.tiles_n;
+    const int nt = pt.tiles_m * pt.tiles_n, ns = ps.tiles_m * ps.tiles_n, run = 256 * t.per_cu;
     if (tile == T256) {
-        gemm_bf16_pp_two_kernel<EPI><<<nt + ns, 512, 0, s>>>(pt, ps, nt, ns);
+        gemm_bf16_pp_two_kernel<EPI><<<nt + ns, 512, 0, s>>>(pt, ps, nt, ns, run, first);
         return;
     }
-#define GO(BM, BN, WM, WN, NST) gemm_bf16_two_kernel<BM, BN, WM, WN, NST, EPI><<<nt + ns, 64 * WM * WN, 0, s>>>(pt, ps, nt, ns)
+#define GO(BM, BN, WM, WN, NST) gemm_bf16_two_kernel<BM, BN, WM, WN, NST, EPI><<<nt + ns, 64 * WM * WN, 0, s>>>(pt, ps, nt, ns, run, first)
     switch (tile) {
         case R128: GO(128, 128, 4, 2, 4); break;
         case R128x256: GO(128, 256, 2, 4, 3); break;
@@ -1788,12 +1791,13 @@ ms_status gemm_kd_and_teacher(int mode, int M, int N, int K, const void *A, cons
     MS_TRY(prepare_kd(mode, M, N, K, A, K, B, K, zt, ld, stats, part, nparts, inv_t, coef, dz, ld, 0, &ps));
     Bf16Gemm t;
     MS_TRY(prepare_bf16(0, 0, M, Nt, Kt, 1.f, At, Kt, Bt, Kt, next_zt, ld, 1, 0, nullptr, nullptr, 0, 0, &t));
-    const int tile = t.fast && use_mfma16() ? ms_choose_two(M, N, ps.k_tiles_per_split, Nt, t.kt, forced_tile()) : -1;
+    int first = 0;
+    const int tile = t.fast && use_mfma16() ? ms_choose_two(M, N, ps.k_tiles_per_split, Nt, t.kt, forced_tile(), &first) : -1;
     if (tile >= 0 && ms_launch_fits(ms_tiles(kTiles[tile], M, N) + ms_tiles(kTiles[tile], M, Nt), 512)) {
         set_splits(t, 1);
         ProfScope prof(0, 2.0 * M * ((double)N * K + (double)Nt * Kt), s);
-        if (mode == EPI_KD_DZ) launch_two<EPI_KD_DZ>(tile, t.p, ps, s);
-        else launch_two<EPI_KD_STATS>(tile, t.p, ps, s);
+        if (mode == EPI_KD_DZ) launch_two<EPI_KD_DZ>(tile, first, t.p, ps, s);
+        else launch_two<EPI_KD_STATS>(tile, first, t.p, ps, s);
         MS_LAUNCH_CHECK();
         return MS_OK;
     }

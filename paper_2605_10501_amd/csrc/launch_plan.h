@@ -193,25 +193,29 @@ inline MsPair ms_choose_pair(long n, long out, long in, double dx_bytes, int for
 }
 
 // The tile for a chunk's student logits [M, N] with a KD epilogue (kt K tiles) and another chunk's teacher logits [M, Nt] (ktt K tiles)
-// as one grid, or -1 for one launch each.  kTiles' times, with 0.87 for 256 x 256, which is the ping-pong kernel here (the fit
-// is to the two-stage one): that picks the best tile in 27 of 28 heads.  Whole heads, loss and gradients, over 1 .. 6000 tokens, V =
-// 32000 / 151936, H = 4096 .. 1024, chunks of 4096 / 8192: 1.16 times as fast as apart in the mean where the grids are small, even
-// where each fills the chip several times, and none more than 1 % slower with a margin of 2 % (us: 1024 tokens, V = 32000 726 ->
-// 663; 200 tokens, V = 151936 3326 -> 2867; 2500 tokens 13359 -> 11882; without the margin 1500 tokens 7576 -> 7727).
-constexpr double kPpFactor = 0.87, kTwoMargin = 0.02;
-inline int ms_choose_two(long M, long N, int kt, long Nt, int ktt, int forced) {
-    int best = -1;
+// as one grid, or -1 for one launch each; student_first: the student's workgroups are the longer ones and come first.  kTiles'
+// times, with 0.87 for 256 x 256, which is the ping-pong kernel here (the fit is to the two-stage one), and 1.2 for 64 x 128, two of
+// which share a CU: their estimate for such a grid is right, while those of the others, which decide against it, are
+// 8-17 % too long.  Without the 1.2 they took grids of 640 workgroups, a round and a quarter, and lost to two launches of 128 x 128
+// (H = 4096 / 2048, chunks of 8192, 257 .. 320 tokens, loss only, V = 40960: 290 tokens 8 % over two launches; with it 128 x 128 shared,
+// 3 % under).  Whole heads of 16 .. 2600 tokens, H = 4096 / 2048, 4096 / 1536, 2048 / 1024, 1024 / 2048, chunks of 4096 / 8192, loss and
+// gradients or loss only (384 of them): 0.89 of the time of two launches in the mean, the best tile 0.88; 4 by 1-3 % slower
+// than two launches (800 tokens of H = 1024 / 2048 2.8 %, 900 of 4096 / 2048 1.3 %).  At several rounds of the chip the two are even.
+constexpr double kPpFactor = 0.87, kShared64x128 = 1.2, kTwoMargin = 0.02;
+inline int ms_choose_two(long M, long N, int kt, long Nt, int ktt, int forced, int *student_first = nullptr) {
+    int best = -1, first = 0;
     double us = 1e30;
     for (int i = 0; i < kNumTiles; ++i) {
         if (!ms_tile_allowed(i, forced, true)) continue;
         const MsTile &t = kTiles[i];
         const MsTileTimes &c = t.lin;
         const long ns = ms_tiles(t, M, N), nt = ms_tiles(t, M, Nt), slots = 256L * t.per_cu;
-        const double u = ms_ktile_us(c.us_per_ktile, t.per_cu, ns + nt), area = t.bm * t.bn / 65536.0, pp = i == T256 ? kPpFactor : 1.0;
-        const double dt = pp * (ktt * u + c.us_round + c.us_out * 4 * area), ds = pp * (kt * u + c.us_round + c.us_out * kKdEpilogueBytes * area);
+        const double u = ms_ktile_us(c.us_per_ktile, t.per_cu, ns + nt), area = t.bm * t.bn / 65536.0, f = i == T256 ? kPpFactor : i == R64x128 ? kShared64x128 : 1.0;
+        const double dt = f * (ktt * u + c.us_round + c.us_out * 4 * area), ds = f * (kt * u + c.us_round + c.us_out * kKdEpilogueBytes * area);
         const double est = c.us_call + (dt > ds ? ms_two_kinds(slots, nt, dt, ns, ds) : ms_two_kinds(slots, ns, ds, nt, dt));
-        if (est < us) { us = est; best = i; }
+        if (est < us) { us = est; best = i; first = ds > dt; }
     }
+    if (student_first) *student_first = first;
     if (forced > 0) return best;
     auto apart = [&](long n, int k, double bytes) {
         const int i = ms_choose_tile(M, n, k, bytes, 0, true);
@@ -219,9 +223,6 @@ inline int ms_choose_two(long M, long N, int kt, long Nt, int ktt, int forced) {
     };
     return us < (1 - kTwoMargin) * (apart(N, kt, kKdEpilogueBytes) + apart(Nt, ktt, 4)) ? best : -1;
 }
-// Workgroups of one kind before the other has its turn: a round of the chip.  In runs of 8 or 64 the two products' operand panels
-// compete for the L2s from the start (8192 tokens, V = 151936: 33.6 .. 34.0 ms; apart 32.98, in runs of 256 32.75).
-constexpr int kTwoRun = 256;
 
 // ------------------------------------------------------------------ bf16 attention
 // Workgroups of a (heads, sequences, tile levels) grid; the mapping is described at attn_slot (attention_mfma.hip).

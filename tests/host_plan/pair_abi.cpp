@@ -14,3 +14,8 @@ extern "C" int two_choose(long m, long n, int kt, long nt, int ktt, int forced) 
     const int i = ms_choose_two(m, n, kt, nt, ktt, forced);
     return i < 0 ? -1 : kTiles[i].code;
 }
+extern "C" int two_student_first(long m, long n, int kt, long nt, int ktt) {
+    int first = -1;
+    ms_choose_two(m, n, kt, nt, ktt, 0, &first);
+    return first;
+}

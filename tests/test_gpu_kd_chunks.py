@@ -17,8 +17,9 @@ def test_chunk_counts_and_widths(dtype, ht, hs, vocab, chunk):
 
 
 # bf16 heads whose student and teacher products share launches: every tile, ragged rows and columns, chunks of unequal width, a
-# round of tiles of one kind and more (kinds take turns in runs of 256 workgroups)
-@pytest.mark.parametrize("n,vocab,chunk,ht,hs", [(45, 648, 128, 128, 64), (300, 1000, 264, 64, 192), (130, 3 * 8192 + 520, 8192, 64, 64), (2100, 6 * 2048, 2048, 64, 64)])
+# round of tiles of one kind and more (kinds take turns in runs of 256 or 512 workgroups), the longer ones first: teacher or student
+@pytest.mark.parametrize("n,vocab,chunk,ht,hs", [(45, 648, 128, 128, 64), (300, 1000, 264, 64, 192), (130, 3 * 8192 + 520, 8192, 64, 64), (2100, 6 * 2048, 2048, 64, 64),
+                                                 (2100, 3 * 2048, 2048, 64, 192)])
 @pytest.mark.parametrize("tile", [0, 256, 128, 128128, 128256, 64128, 64064])
 def test_shared_launches_on_every_tile(tile, n, vocab, chunk, ht, hs):
     g = torch.Generator(device="cuda").manual_seed(n)

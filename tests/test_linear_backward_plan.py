@@ -63,3 +63,15 @@ def test_student_and_teacher_logits_share_small_grids(plan):
     assert all(f(m, 8192, 16, 8192, 32) > 0 for m in (1, 64, 300, 1024))
     assert f(1500, 8192, 32, 8192, 64) == -1                       # 192 tiles of 256 x 256 each: two launches were faster
     assert all(f(300, 4096, 16, 1000, 32, code) == code for code in (256, 128, 128128, 128256, 64128, 64064))
+
+
+def test_grids_a_little_over_a_round_do_not_take_64x128(plan):
+    """257 .. 320 tokens and a chunk of 8192: 640 workgroups of 64 x 128 on 512 places, up to 22 % slower than the two launches that they took
+    the place of; 128 x 128 is faster than both."""
+    f = lambda m, kt, ktt: plan.two_choose(C.c_long(m), C.c_long(8192), kt, C.c_long(8192), ktt, 0)
+    assert all(f(m, kt, ktt) in (-1, 128128, 128256) for m in (257, 290, 320) for kt, ktt in ((24, 64), (32, 64), (16, 32)))
+
+
+def test_the_longer_kind_comes_first(plan):
+    f = lambda kt, ktt: plan.two_student_first(C.c_long(300), C.c_long(8192), kt, C.c_long(8192), ktt)
+    assert f(16, 32) == 0 and f(32, 16) == 1
