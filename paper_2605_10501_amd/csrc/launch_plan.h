@@ -42,7 +42,8 @@ constexpr bool ms_f32_attention_tiles(int hd, long n, long n_seqs, long max_seql
 //   element, for 256 x 256 elements;  us_call: once.
 // `lin` (K-contiguous A) is fitted to what decides, the times of a shape's better tiles relative to each other, over 1278
 // shapes (M = 128 .. 46000, N = 512 .. 22016, K = 512 .. 17920, K-contiguous and K-major B, bf16 / fp32 outputs, fp32
-// residual, SwiGLU and KD epilogues; half of them choose as well for the other half).  `wgrad` (both operands K-major, +=
+// residual, SwiGLU and KD epilogues; half of them choose as well for the other half).  Its 256 x 256 row is the two-stage kernel, which
+// K-major B runs; K-contiguous products run the ping-pong kernel in that tile, which is up to 25 % faster.  `wgrad` (both operands K-major, +=
 // into fp32) is a fit to such products of 300 .. 32768 tokens, in which the output has terms of its own.
 struct MsTileTimes { double us_per_ktile[4], us_round, us_out, us_call; };
 struct MsTile {
@@ -86,8 +87,11 @@ inline bool ms_tile_allowed(int i, int forced, bool mfma16) {
 // The tile with the least estimated time, if that is clearly less than the time of the two-stage tile by occupancy.  Ties do
 // not decide: without a margin, and with times that did not know the output, 128 x 256 displaced 256 x 256 and 128 x 128 on
 // estimates 0.2-6 % apart and lost up to 18 % (2494 x 8192 x 1024 with fp32 output: 60.9 us instead of 51.3; 6500 x 8192 x
-// 4096: 386.9 instead of 358.5).  Over the sweep the choice is 1.23 times as fast as the two-stage tile in the mean, never
-// more than 4.5 % slower (3 shapes of 1278 by more than 2.5 %), and 0.4 % from the best tile.
+// 4096: 386.9 instead of 358.5).  Over the sweep the choice was 1.23 times as fast as the two-stage tile in the mean, never
+// more than 4.5 % slower (3 shapes of 1278 by more than 2.5 %), and 0.4 % from the best tile; 256 x 256 was the two-stage kernel there
+// for all operands.  With the ping-pong kernel the choice is the same, and 256 x 256 is now and then the better one: of 150 K-contiguous products
+// (18 widths of 1024 .. 11008, 256 .. 32768 rows, bf16 output, operands out of the caches) 142 are within 2 % of the best tile, five 2-6 %
+// behind, three 20 %, all of these one round of 256 x 256 (us: 1332 x 6144 x 4096 95, best 79; 1537 x 5120 x 5120 119, best 98).
 // Every tile adds up K in the same order (one accumulator per element, ascending K), so the choice does not change
 // results: the rows of a short micro-batch come out as they do in a long one.
 constexpr double kTileMargin = 0.03;
@@ -133,7 +137,9 @@ inline MsSplit ms_choose_split(long M, long N, int kt, int forced, bool mfma16) 
 // us_per_ktile), each with a part per round, us_out as in MsTileTimes; us_c: the weight gradient's read and write of C, in
 // 1e-6 us per element (with splits atomics, as in ms_choose_split).  The best tile of a pair is 1.17 times as fast as two
 // launches in the mean, the chosen one 1.15 times (two tiles' estimates may be close); pairs that are not estimated 3 % faster
-// than two launches stay apart.  One of the 324 loses more than 1 % then (777 tokens, 1536 x 8960: 66 us apart, 72 together).
+// than two launches stay apart.  On 22 layers x 39 other token counts (64 .. 46173; 766 pairs) a layer's two products then take 0.85 of the time
+// of two launches in the mean; 12 pairs lose more than 1 %, six of them 4-9 %: 600 .. 870 tokens with in >= 5120 (us, apart, together:
+// 612 tokens, 1280 x 5120 32.9, 35.7; 861 tokens, 1536 x 8960 64.7, 68.1).  No margin tells those from pairs that gain.
 // E.g. us, apart -> together: 2053 tokens, 5632 x 1024 87 -> 64; 1031 tokens, 1280 x 5120 50 -> 43; 32768 tokens, 1536 x 1536
 // 285 -> 274; a KD chunk of 1024 tokens, 8192 x 1024 84 -> 67; 4096 tokens, 5632 x 1024 111, together 114: stays apart.
 struct MsPairTimes { double d[4], us_round, us_out, us_call, w[4], us_round_w, us_c; };

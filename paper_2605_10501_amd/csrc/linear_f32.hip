@@ -9,8 +9,10 @@
 //     way through K, so it adds up their squares itself; the workgroups of the first columns also write the normed rows and rstd where
 //     a backward pass will read them.
 // One MI355X: c1 distillation step on 293 tokens, with the other launches saved in the same manner, 237 -> 200 us; one layer's forward
-// pass (d 256) at 293 tokens 49.5 -> 38.4, at 8192 268 -> 253.  Up to d = 512: a wider layer is no longer bound by launches, and the
-// squares and gains cost it 1-2 % (d 1024, 2048 tokens, forward 785 -> 791 us).
+// pass (d 256) at 293 tokens 49.5 -> 38.4, at 8192 268 -> 253.  Up to d = 512: wider layers of a few thousand tokens are no longer bound by
+// launches, and the squares and gains cost them up to 1.5 %.  Forward us, separate -> here, at 64 / 1000 / 12000 tokens: d 128 45 -> 32,
+// 53 -> 43, 182 -> 173; d 384 52 -> 43, 110 -> 102, 821 -> 813; d 512 54 -> 45, 136 -> 128, 1288 -> 1277; d 640 63 -> 53, 212 -> 206,
+// 1990 -> 2002; d 1024 85 -> 75, 414 -> 413, 4534 -> 4601.
 #include "common.h"
 #include "launch.h"
 #include "launch_plan.h"

@@ -170,8 +170,9 @@ struct Exec {
         return gemm(0, 0, m.n, out, in, x, in, W, in, y, out, res != nullptr, false, bias, res, out);
     }
     // The biases' column sums: all four of a layer in one launch at its end, when the four output gradients are still there, up
-    // to 8192 tokens (encoder layer, 1031 tokens: 37 launches -> 23, 441 -> 417 us); above, each behind the products that read
-    // its matrix, while a part of that is in the Infinity Cache (46173 tokens: 177 us against 203).
+    // to 8192 tokens (encoder layer d 1280, each behind its products -> at the end: 64 tokens 215 -> 206 us, 1031 393 -> 383, 2048 553 ->
+    // 546; even from 3000 to 10000); above, each behind the products that read its matrix, while a part of that is in the Infinity Cache
+    // (at the end 0.3-0.6 % slower from 12000 tokens on; 46173 tokens: the sums 177 us against 203).
     bool sums_at_end() const { return m.n <= 8192; }
     // dx[n, in] = dy[n, out] W[out, in];  dW[out, in] += dy[n, out]^T x[n, in];  db[out] += colsum(dy)
     ms_status linear_backward(const void *dy, int out, const void *W, int in, const void *x, void *dx, void *dW, void *db) {
